@@ -195,3 +195,26 @@ def tolerance(case):
     if op == "cholesky":              # likewise: 8e-7 in L, 1.4e-5 in its rounding at n = 4096, growing with n
         return {"rel": 1e-4}
     return {"rel": 7e-3}              # weights rounded to bfloat16: 1.4e-3 .. 1.8e-3
+
+
+# ------------------------------------------------------------------------------------------------ 64-bit results
+def exact(case, seed):
+    """What run() returns, from the definition in 64 bits.  The rounding of X and L to bfloat16 that trsm and cholesky also
+    return is compared with the unrounded result; above the diagonal that copy of L is its mirror image."""
+    op = case["op"]
+    state = prepare(case, seed)
+    if op == "matmul":
+        A, B = state[1], state[2]
+        if A.dim() == 2:
+            return torch.matmul(A.double(), B.double())
+        return torch.stack([torch.matmul(a.double(), b.double()) for a, b in zip(A, B)])
+    if op == "trsm":
+        X = torch.linalg.solve_triangular(state[1].double(), state[2].double(), upper=False)
+        return X, X
+    if op == "cholesky":
+        L = torch.linalg.cholesky(state[1].double())
+        return L, L + L.tril(-1).t()
+    out = []
+    for q, k, v in zip(*(t.double() for t in state[1:])):
+        out.append(torch.matmul(torch.softmax(torch.matmul(q, k.t()) / math.sqrt(case["d"]), -1), v))
+    return torch.stack(out)
