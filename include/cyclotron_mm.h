@@ -61,7 +61,8 @@
  * M*K, K*N, M*N and the batched spans below 2^46) is accepted.  The fast paths need
  * 16-byte aligned base pointers, batch strides and rows of A and B (K and N
  * multiples of 8 for bfloat16, of 16 for int8) but no particular multiples
- * otherwise; anything else runs on a slower shape-agnostic kernel.
+ * otherwise; anything else runs on a shape-agnostic kernel, at about half their
+ * rate.
  *
  * Kernel families and when the dispatcher picks them:
  *   narrow   N <= 16, many rows: A streamed once from memory, B resident.
@@ -71,7 +72,8 @@
  *            space; k-slices on different workgroups leave partial sums in the
  *            workspace and a second kernel adds them in ascending slice order.
  *   mfma256 / mfma128  everything else with aligned rows.
- *   generic  the rest.
+ *   generic  the rest: rows at any address, on the matrix cores when K and N are at
+ *            least 16 bytes long, off them otherwise (and when forced).
  */
 #ifndef CYCLOTRON_MM_H
 #define CYCLOTRON_MM_H
@@ -147,7 +149,7 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C,
  *     while the call is in flight.
  * Xh: device, written, n x nrhs bfloat16 row-major: X rounded to bfloat16, the values the GEMMs consumed.
  * nb: tile size, 1 <= nb <= 128.  The MFMA kernels serve the GEMMs when n, nrhs and nb are multiples of 8
- *     and the pointers are 16-byte aligned; otherwise a slower shape-agnostic kernel does.
+ *     and the pointers are 16-byte aligned; otherwise the shape-agnostic kernels do.
  * stream: hipStream_t or NULL.  The call enqueues a sequence of kernels on it and returns.  With nb == 64,
  *     nrhs a multiple of 8 below 2^24, n a multiple of 8 below 2^26 and 16-byte aligned L, X, Xh it keeps the inverses of the diagonal
  *     tiles (16 KiB per 64 rows) and a second copy of the tiles of L next to the diagonal in the order the
@@ -184,7 +186,7 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
  * Lh: device, written, n x n bfloat16 row-major: L rounded to bfloat16, the values the SYRKs and GEMMs consumed,
  *     with both triangles filled: Lh[r][c] = Lh[c][r] = bf16(L[max(r,c)][min(r,c)]).
  * nb: tile size, 1 <= nb <= 64.  The MFMA kernels serve the updates when n and nb are multiples of 8 and the
- *     pointers are 16-byte aligned; otherwise a slower shape-agnostic kernel does.
+ *     pointers are 16-byte aligned; otherwise the shape-agnostic kernels do.
  * stream: hipStream_t or NULL.  The call enqueues a sequence of kernels on it and returns.  With nb == 64 and
  *     n >= 128 it keeps the inverses of the diagonal tiles (16 KiB per 64 rows) and a copy of one diagonal tile (16 KiB)
  *     in the workspace that the library holds per device and stream (allocated or grown on the call that first needs it); otherwise it allocates no

@@ -26,14 +26,14 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
     return a < b + (uintptr_t)qbytes && b < a + (uintptr_t)pbytes;
 }
 
-enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
+enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
 
 const char *kernel_label(Kernel k)
 {
     switch (k) {
         case K_NONE: return "none";
         case K_ZERO: return "zero";
-        case K_GENERIC: return "generic";
+        case K_GENERIC: case K_UNEVEN: return "generic";   // one family: any alignment, on the matrix cores or (forced, tiny extents) off them
         case K_MFMA256: return "mfma256";
         case K_MFMA128: return "mfma128";
         case K_MFMA256X32: return "mfma256x32";
@@ -121,7 +121,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     const int tile = cyc::choose_mfma_tile(*p);
     if (tile == 256) { *k = K_MFMA256; return CYC_OK; }
     if (tile == 128) { *k = K_MFMA128; return CYC_OK; }
-    *k = K_GENERIC;
+    *k = cyc::supports_uneven(*p) ? K_UNEVEN : K_GENERIC;
     return CYC_OK;
 }
 
@@ -132,6 +132,7 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
         case K_NONE: return CYC_OK;
         case K_ZERO: e = cyc::launch_zero(p, s); break;
         case K_GENERIC: e = cyc::launch_generic(p, s); break;
+        case K_UNEVEN: e = cyc::launch_uneven(p, s); break;
         case K_MFMA256: e = cyc::launch_mfma(p, 256, 16, s); break;
         case K_MFMA128: e = cyc::launch_mfma(p, 128, 16, s); break;
         case K_MFMA256X32: e = cyc::launch_mfma(p, 256, 32, s); break;

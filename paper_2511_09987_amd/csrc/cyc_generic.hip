@@ -1,8 +1,9 @@
 // cyc_generic.hip -- shape-agnostic kernel of the weight-stationary recurrence
 // (paper, "Space-time Mappings of Dataflow Recurrences"): every C_ij is the chain
 // acc <- acc + A_ik * B_kj run in ascending k from 0, exactly as the cell row
-// (i,0..K-1) produces it for time step j.  Used for ragged extents, unaligned
-// pointers and tiny problems; the fast paths live in cyc_mfma.hip / cyc_narrow.hip.
+// (i,0..K-1) produces it for time step j.  Used for rows of less
+// than 16 bytes and when forced; every other shape runs on the matrix cores (cyc_uneven.hip for rows
+// at any address, cyc_mfma.hip / cyc_narrow.hip / cyc_narrowm.hip for aligned ones).
 #include "cyc_internal.h"
 
 namespace cyc {

@@ -42,6 +42,11 @@ inline int64_t row_stride_c(const Problem &p) { return p.ldc ? p.ldc : p.N; }
 
 // any shape, any alignment; one thread per 4x4 block of C, k ascending
 hipError_t launch_generic(const Problem &p, hipStream_t s);
+// MFMA tiled GEMM for rows at any byte address (see cyc_uneven.hip); requires supports_uneven(p)
+bool supports_uneven(const Problem &p);
+hipError_t launch_uneven(const Problem &p, hipStream_t s);
+// what no aligned kernel takes
+inline hipError_t launch_any_alignment(const Problem &p, hipStream_t s) { return supports_uneven(p) ? launch_uneven(p, s) : launch_generic(p, s); }
 // fill C with the chain's initial value (K == 0)
 hipError_t launch_zero(const Problem &p, hipStream_t s);
 // MFMA tiled GEMM; requires supports_mfma(p, tile)
