@@ -217,6 +217,19 @@ int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t
 int cyc_recurrence_attention(const void *Q, const void *K, const void *V, void *O,
                              int64_t batch, int64_t N, int64_t M, int64_t d, void *stream);
 
+/* The same for callers that bring memory.  Few queries against many keys leave most of the chip idle unless the keys of
+ * a batch element are spread over several workgroups too, whose running maxima, sums and outputs then have to be
+ * joined: cyc_recurrence_attention_split keeps them in `workspace` (device, 16-byte aligned, nothing in it needs to be
+ * cleared, free again when the call's work on `stream` is done) and joins them in ascending order of the keys with a
+ * second kernel.  cyc_attention_workspace says how many bytes such a call wants (0: it would not split; host only,
+ * also 0 for arguments that the call refuses).  With less, or with workspace NULL, the keys are not split, as in
+ * cyc_recurrence_attention.  The result is the same on every call with the same arguments; how the keys are split depends
+ * on batch, N, M and d, and with it the last bits of O.  Errors: those of cyc_recurrence_attention; CYC_ERR_SHAPE
+ * also for a misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
+int64_t cyc_attention_workspace(int64_t batch, int64_t N, int64_t M, int64_t d);
+int cyc_recurrence_attention_split(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,
+                                   int64_t d, void *workspace, int64_t workspace_bytes, void *stream);
+
 /* Human-readable name of a cyc_status (static storage, never NULL). */
 const char *cyc_status_string(int status);
 

@@ -38,6 +38,10 @@ def _load() -> ctypes.CDLL:
     lib.cyc_recurrence_cholesky.restype = cint
     lib.cyc_recurrence_attention.argtypes = [ptr, ptr, ptr, ptr, i64, i64, i64, i64, ptr]
     lib.cyc_recurrence_attention.restype = cint
+    lib.cyc_recurrence_attention_split.argtypes = [ptr, ptr, ptr, ptr, i64, i64, i64, i64, ptr, i64, ptr]
+    lib.cyc_recurrence_attention_split.restype = cint
+    lib.cyc_attention_workspace.argtypes = [i64, i64, i64, i64]
+    lib.cyc_attention_workspace.restype = i64
     lib.cyc_status_string.argtypes = [cint]
     lib.cyc_status_string.restype = ctypes.c_char_p
     lib.cyc_version.argtypes = []
@@ -109,6 +113,17 @@ def cyc_recurrence_trsm(L: int, B: int, X: int, Xh: int, n: int, nrhs: int, nb: 
 def cyc_recurrence_attention(Q: int, K: int, V: int, O: int, batch: int, N: int, M: int, d: int, stream: int = 0) -> int:
     """Raw call: device addresses as ints, returns the cyc_status."""
     return int(_lib().cyc_recurrence_attention(Q, K, V, O, batch, N, M, d, stream))
+
+
+def cyc_attention_workspace(batch: int, N: int, M: int, d: int) -> int:
+    """Bytes of workspace that cyc_recurrence_attention_split wants for these extents."""
+    return int(_lib().cyc_attention_workspace(batch, N, M, d))
+
+
+def cyc_recurrence_attention_split(Q: int, K: int, V: int, O: int, batch: int, N: int, M: int, d: int, workspace: int,
+                                   workspace_bytes: int, stream: int = 0) -> int:
+    """Raw call: device addresses as ints, returns the cyc_status."""
+    return int(_lib().cyc_recurrence_attention_split(Q, K, V, O, batch, N, M, d, workspace, workspace_bytes, stream))
 
 
 def cyc_kernel_name(A: int, B: int, C: int, batch: int, M: int, K: int, N: int,
@@ -269,7 +284,19 @@ def recurrence_attention(Q, K, V, out=None, stream=None):
     elif tuple(out.shape) != tuple(Q.shape) or out.dtype != torch.float32 or not out.is_contiguous() or out.device != Q.device:
         raise ValueError("out has the wrong shape, dtype, layout or device")
     s = (stream if stream is not None else torch.cuda.current_stream(Q.device)).cuda_stream
-    st = cyc_recurrence_attention(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), batch, N, M, d, s)
+    # The library splits no key list below 512.  The workspace comes from the allocator's pool of the stream that the call
+    # runs on, and goes back to it: whoever gets it next is ordered after this call.
+    wanted, work = cyc_attention_workspace(batch, N, M, d) if M >= 512 else 0, None
+    if wanted and stream is None:
+        work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
+    elif wanted and isinstance(stream, torch.cuda.Stream) and stream.device == Q.device:
+        with torch.cuda.stream(stream):
+            work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
+    if work is None:
+        st = cyc_recurrence_attention(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), batch, N, M, d, s)
+    else:
+        st = cyc_recurrence_attention_split(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), batch, N, M, d, work.data_ptr(),
+                                            wanted, s)
     if st != CYC_OK:
         raise CycError(st)
     return out

@@ -258,8 +258,22 @@ int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t
     return cyc::launch_chol(A, L, Lh, n, nb, workspace, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
 }
 
+int64_t cyc_attention_workspace(int64_t batch, int64_t N, int64_t M, int64_t d)
+{
+    int64_t nq, nk;
+    if (batch < 1 || batch > 65535 || N < 1 || M < 1 || !cyc::supports_attention(N, M, d)) return 0;
+    if (!mul_ok(N, d, &nq) || !mul_ok(M, d, &nk) || !mul_ok(batch, nq, &nq) || !mul_ok(batch, nk, &nk)) return 0;
+    return cyc::attention_workspace_bytes(batch, N, M, d);
+}
+
 int cyc_recurrence_attention(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,
                              int64_t d, void *stream)
+{
+    return cyc_recurrence_attention_split(Q, K, V, O, batch, N, M, d, nullptr, 0, stream);
+}
+
+int cyc_recurrence_attention_split(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,
+                                   int64_t d, void *workspace, int64_t workspace_bytes, void *stream)
 {
     if (batch < 0 || N < 0 || M < 0 || d < 0) return CYC_ERR_SHAPE;
     if (batch == 0 || N == 0) return CYC_OK;
@@ -269,7 +283,13 @@ int cyc_recurrence_attention(const void *Q, const void *K, const void *V, void *
     if (!Q || !K || !V || !O) return CYC_ERR_NULL;
     if (((uintptr_t)Q | (uintptr_t)K | (uintptr_t)V | (uintptr_t)O) & 15) return CYC_ERR_SHAPE;
     if (overlaps(O, nq * 4, Q, nq * 2) || overlaps(O, nq * 4, K, nk * 2) || overlaps(O, nq * 4, V, nk * 2)) return CYC_ERR_ALIAS;
-    return cyc::launch_attention(Q, K, V, O, batch, N, M, d, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
+    if (!workspace || workspace_bytes < 0) workspace_bytes = 0;
+    if ((uintptr_t)workspace & 15) return CYC_ERR_SHAPE;
+    if (overlaps(workspace, workspace_bytes, Q, nq * 2) || overlaps(workspace, workspace_bytes, K, nk * 2) ||
+        overlaps(workspace, workspace_bytes, V, nk * 2) || overlaps(workspace, workspace_bytes, O, nq * 4))
+        return CYC_ERR_ALIAS;
+    return cyc::launch_attention(Q, K, V, O, batch, N, M, d, workspace, workspace_bytes, (hipStream_t)stream) == hipSuccess ? CYC_OK
+                                                                                                                        : CYC_ERR_LAUNCH;
 }
 
 const char *cyc_kernel_name(const void *A, const void *B, const void *C, int64_t batch, int64_t M, int64_t K,

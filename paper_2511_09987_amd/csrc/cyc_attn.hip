@@ -7,7 +7,9 @@
 // and O_i. = o_i / l_i at the end.  The paper maps it with the query tile stationary on a processing
 // element and K, V streaming past; so here: a wave holds 32 queries as MFMA operand registers for the
 // whole kernel, a workgroup of eight waves (256 queries, two waves per SIMD) streams tiles of 64 or 128 keys
-// of K and V through LDS.
+// of K and V through LDS.  Where that leaves compute units idle, workgroups are smaller and the keys are cut into runs
+// that different workgroups take (choose_mapping below); one query per head against 4000 keys, 64 heads, is then bound by
+// the reads of K and V (5.2 TB/s).
 //
 // Both products are computed transposed, which removes every shuffle between them:
 //   S^T = K_tile Q^T   (A operand: 16 keys x 32 d from LDS; B operand: the stationary Q, whose row-major
@@ -65,7 +67,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int QB = 2;                    // 16-query blocks per wave
 constexpr int QW = QB * 16;              // queries per wave
-constexpr int NWAVE = 8;                 // waves per workgroup
 
 // 64 lanes x 16 bytes from global memory (wave-uniform base + per-lane offset) into LDS at lds_addr + lane*16
 __device__ __forceinline__ void copy16(const char *base, uint32_t lane_off, uint32_t lds_addr)
@@ -101,11 +102,15 @@ template <int OFF> __device__ __forceinline__ void lds_read_tr64(i32x2 &dst, uin
 }
 template <int PENDING> __device__ __forceinline__ void lds_wait2(i32x2 &x, i32x2 &y) { asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(x), "+v"(y) : "n"(PENDING)); }
 
-// D: head dimension; KT: keys per tile (a multiple of 32)
-template <int D, int KT>
-__global__ __launch_bounds__(NWAVE * 64) void attn_kernel(const char *__restrict__ Q, const char *__restrict__ K,
-                                                          const char *__restrict__ V, float *__restrict__ O, int N,
-                                                          int M, int nqb, float scale_log2e)
+// D: head dimension; KT: keys per tile (a multiple of 32); NWAVE: waves per workgroup (32 queries each).
+// SPLIT: the keys of a batch element are cut into `splits` runs of `run` keys (whole tiles; the last run ends at M), and a
+// workgroup takes one of them.  It leaves the running output unnormalised in part, batch x splits x N x D, and the
+// reference and sum of every query in refs, batch x splits x N x 2; attn_join_kernel joins the runs.
+template <int D, int KT, int NWAVE, bool SPLIT>
+__global__ __launch_bounds__(NWAVE * 64, NWAVE >= 4 ? 2 : 1) void attn_kernel(const char *__restrict__ Q, const char *__restrict__ K,
+                                                             const char *__restrict__ V, float *__restrict__ O, int N,
+                                                             int M, int nqb, float scale_log2e, int splits, int run,
+                                                             float *__restrict__ part, float *__restrict__ refs)
 {
     constexpr int KB = KT / 16;           // 16-key blocks per tile
     constexpr int ROW = D * 2;            // bytes per row of Q, K, V
@@ -131,12 +136,22 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_kernel(const char *__restrict
     // XCD x takes a contiguous range of (batch element, query block) pairs, in the order it receives them.
     const int total = gridDim.x, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int logical = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : (total & 7)) + slot;
-    const int64_t bz = logical / nqb;
-    const int bx = logical - (int)bz * nqb;
+    const int64_t by = logical / nqb;                   // batch element, or (batch element, run)
+    const int bx = logical - (int)by * nqb;
+    const int64_t bz = SPLIT ? by / splits : by;
     Q += bz * (int64_t)N * ROW;
     K += bz * (int64_t)M * ROW;
     V += bz * (int64_t)M * ROW;
-    O += bz * (int64_t)N * D;
+    if (SPLIT) {
+        const int first = (int)(by - bz * splits) * run;
+        K += (int64_t)first * ROW;
+        V += (int64_t)first * ROW;
+        M = M - first < run ? M - first : run;
+        O = part + by * (int64_t)N * D;
+        refs += by * (int64_t)N * 2;
+    } else {
+        O += bz * (int64_t)N * D;
+    }
     const int q0 = bx * (NWAVE * QW) + w * QW;          // first query of this wave
 
     // ---- the stationary operand: Q of this wave's queries, for the whole kernel.  B operand of
@@ -152,26 +167,32 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_kernel(const char *__restrict
     }
 
     // ---- copies of a tile of K or of V into a stage.  A copy moves RPC rows (1 KiB); copy x of wave w takes the rows
-    // x*NWAVE*RPC + w*RPC .. of the tile, so that a lane's offset within its copy (swizzle included: the row
-    // number changes by a multiple of 16 with x) is the same for every x and every full tile.  Keys past M (last
-    // tile only) re-read key M-1 and are masked below.
+    // x*NWAVE*RPC + w*RPC .. of the tile.  The swizzles repeat every 16 rows, that is every PERIOD copies, and a lane's
+    // offset within copy x (from that copy's first byte) with them.  Keys past M (last tile only) re-read key M-1 and are
+    // masked below.
+    constexpr int PERIOD = NWAVE * RPC >= 16 ? 1 : 16 / (NWAVE * RPC);
+    static_assert(NWAVE * RPC * PERIOD % 16 == 0 && COPIES % PERIOD == 0, "copies must come in whole periods of the swizzle");
     const int row0 = w * RPC + l / CPR;                             // this lane's row within copy 0
-    const uint32_t voffK = (uint32_t)row0 * ROW + (((l % CPR) ^ swzK(row0)) << 4);
-    const uint32_t voffV = (uint32_t)row0 * ROW + (((l % CPR) ^ swzV(row0)) << 4);
+    uint32_t voffK[PERIOD], voffV[PERIOD];
+#pragma unroll
+    for (int x = 0; x < PERIOD; ++x) {
+        voffK[x] = (uint32_t)row0 * ROW + (((l % CPR) ^ swzK(x * (NWAVE * RPC) + row0)) << 4);
+        voffV[x] = (uint32_t)row0 * ROW + (((l % CPR) ^ swzV(x * (NWAVE * RPC) + row0)) << 4);
+    }
     const int ntiles = (M + KT - 1) / KT;
-    auto issue = [&](const char *src, uint32_t voff, int tile, int stage_index) __attribute__((always_inline)) {
+    auto issue = [&](const char *src, const uint32_t(&voff)[PERIOD], int tile, int stage_index) __attribute__((always_inline)) {
         const char *base = src + (int64_t)tile * TILE_BYTES;
         const uint32_t dst = lds_base + stage_index * TILE_BYTES + w * 1024;
         if ((tile + 1) * KT <= M) {
 #pragma unroll
-            for (int x = 0; x < COPIES; ++x) copy16(base + x * (NWAVE * 1024), voff, dst + x * (NWAVE * 1024));
+            for (int x = 0; x < COPIES; ++x) copy16(base + x * (NWAVE * 1024), voff[x % PERIOD], dst + x * (NWAVE * 1024));
         } else {
             const int last = M - 1 - tile * KT;                   // last valid row of the tile
 #pragma unroll
             for (int x = 0; x < COPIES; ++x) {
                 const int r = x * (NWAVE * RPC) + row0;
                 // offsets are unsigned: row min(r, last) counted from the tile's first row, this lane's chunk
-                copy16(base, (uint32_t)(r <= last ? r : last) * ROW + (voff - (uint32_t)row0 * ROW), dst + x * (NWAVE * 1024));
+                copy16(base, (uint32_t)(r <= last ? r : last) * ROW + (voff[x % PERIOD] - (uint32_t)row0 * ROW), dst + x * (NWAVE * 1024));
             }
         }
     };
@@ -348,7 +369,9 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_kernel(const char *__restrict
         stats(sc);
 #pragma unroll
         for (int jq = 0; jq < QB; ++jq) {
-            const float mh = __builtin_fmaxf(m2[jq], tile_max[jq]);
+            float mh = __builtin_fmaxf(m2[jq], tile_max[jq]);
+            // a run in which every score is -inf weighs nothing beside the others (NaN scores still give NaN weights)
+            if (SPLIT) mh = __builtin_fmaxf(mh, -3.0e38f);
             const float keep = __builtin_amdgcn_exp2f(m2[jq] - mh);       // exp(m - mh); 0 on the first tile
             m2[jq] = mh;
             acc_l[jq] *= keep;
@@ -407,7 +430,13 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_kernel(const char *__restrict
     for (int jq = 0; jq < QB; ++jq) {
         const float tot = acc_l[jq][0];                 // every lane of the query holds the whole sum
         const int qi = q0 + jq * 16 + lq;
-        if (qi < N) {
+        if (SPLIT) {
+            if (qi < N) {
+#pragma unroll
+                for (int id = 0; id < DT; ++id) *(f32x4 *)(O + (int64_t)qi * D + id * 16 + 4 * g) = acc_o[id][jq];
+                if (g == 0) *(f32x2 *)(refs + (int64_t)qi * 2) = (f32x2){m2[jq], tot};
+            }
+        } else if (qi < N) {
 #pragma unroll
             for (int id = 0; id < DT; ++id) {
                 const f32x4 o = acc_o[id][jq];
@@ -415,6 +444,34 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_kernel(const char *__restrict
             }
         }
     }
+}
+
+// O_i. = sum_r exp(m_r - m) o_r / sum_r exp(m_r - m) l_r over the runs r of keys, m the largest m_r, in ascending order of r.
+// One thread per four d of a query; bound by a launch and the reads of part.
+template <int D>
+__global__ __launch_bounds__(256) void attn_join_kernel(const float *__restrict__ part, const float *__restrict__ refs,
+                                                        float *__restrict__ O, int64_t rows, int N, int splits)
+{
+    const int64_t row = (int64_t)blockIdx.x * (1024 / D) + threadIdx.x / (D / 4);   // (batch element, query)
+    const int c = threadIdx.x % (D / 4) * 4;
+    if (row >= rows) return;
+    const int64_t bz = row / N, qi = row - bz * N;
+    const float *p = part + (bz * splits * N + qi) * D + c, *ref = refs + (bz * splits * N + qi) * 2;
+    const int64_t step = (int64_t)N;
+    float m = ref[0];
+    for (int r = 1; r < splits; ++r) m = __builtin_fmaxf(m, ref[r * step * 2]);
+    f32x4 o = {0, 0, 0, 0};
+    float tot = 0;
+#pragma unroll 4
+    for (int r = 0; r < splits; ++r) {
+        const f32x2 mt = *(const f32x2 *)(ref + r * step * 2);
+        const float keep = __builtin_amdgcn_exp2f(mt[0] - m);
+        tot = __builtin_fmaf(keep, mt[1], tot);
+        const f32x4 v = *(const f32x4 *)(p + r * step * D);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(keep, v[i], o[i]);
+    }
+    *(f32x4 *)(O + row * D + c) = (f32x4){o[0] / tot, o[1] / tot, o[2] / tot, o[3] / tot};
 }
 
 }  // namespace
@@ -425,22 +482,106 @@ bool supports_attention(int64_t N, int64_t M, int64_t d)
     return (d == 64 || d == 128) && N >= 1 && M >= 1 && N < (1 << 30) && M * d * 2 < ((int64_t)1 << 32);
 }
 
+namespace {
+
+struct Mapping {
+    int nwave;                            // waves per workgroup
+    int splits, run;                      // runs of keys, keys per run
+};
+
+int64_t part_bytes(int64_t batch, int64_t N, int64_t d, int64_t splits) { return batch * splits * N * (d + 2) * 4; }
+
+// How many waves a workgroup has and into how many runs the keys are cut, by a cost in nanoseconds: rounds of workgroups on
+// the 256 compute units (two workgroups of up to four waves on each, one of eight), the time of a tile of keys with one
+// and with two workgroups on a compute unit, and for more than one run the second launch, the runs it walks and the partial
+// outputs, written and read at 3 TB/s.  Measured (microseconds; batch, N, M, d; waves / runs):
+//   64, 1, 4000, 128       1/1: 81   1/4: 27   1/8: 25   1/16: 28     (before: 8/1 at 104)
+//   1, 128, 4096, 128      4/1: 68   4/8: 19   2/16: 15   1/32: 18
+//   2, 500, 4096, 128      8/1: 102  4/1: 68   4/8: 20   2/16: 19
+//   1, 4096, 4096, 128     8/1: 101  4/1: 68   4/8: 30   8/16: 33
+//   8, 512, 2048, 64       8/1: 39   4/1: 29   2/4: 15   1/4: 15
+//   16, 1024, 1024, 128    8/1: 33   4/1: 23   2/1: 25   4/2: 29
+//   40, 2000, 2000, 128    8/1: 118  4/1: 96   2/1: 128  4/2: 118
+// A query's result does not depend on the waves per workgroup, only on the runs.  Below 512 keys there is nothing to gain
+// from runs, and partial outputs end at 64 MiB.
+Mapping choose_mapping(int64_t batch, int64_t N, int64_t M, int64_t d, int64_t workspace_bytes)
+{
+    constexpr int64_t one128[4] = {1280, 1180, 1050, 1850}, two128[4] = {1550, 1650, 1870, 0};
+    constexpr int64_t one64[4] = {1550, 1400, 1550, 2200}, two64[4] = {1700, 1800, 2500, 0};
+    const int64_t kt = d == 128 ? 64 : 128, ntiles = (M + kt - 1) / kt;
+    const int64_t *one = d == 128 ? one128 : one64, *two = d == 128 ? two128 : two64;
+    Mapping best = {8, 1, (int)(ntiles * kt)};
+    int64_t best_cost = INT64_MAX;
+    for (int64_t want = 1; want == 1 || (M >= 512 && want * 2 <= ntiles && want <= 256); want *= 2) {
+        const int64_t tiles = (ntiles + want - 1) / want, splits = (ntiles + tiles - 1) / tiles, part = part_bytes(batch, N, d, splits);
+        if (splits > 1 && (part > workspace_bytes || part > (64 << 20))) break;
+        for (int i = 3; i >= 0; --i) {                   // (eight waves first: the fewest reads of K and V among equals)
+            const int64_t groups = (N + 32 * (1 << i) - 1) / (32 * (1 << i)) * batch * splits;
+            int64_t cost;
+            if (i == 3) {
+                cost = (groups + 255) / 256 * one[i] * tiles;
+            } else {
+                const int64_t full = groups / 512, rest = groups % 512;
+                cost = (full * two[i] + (rest == 0 ? 0 : rest <= 256 ? one[i] : two[i])) * tiles;
+            }
+            if (splits > 1) cost += 3300 + 150 * splits + part * 2 / 3000;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = {1 << i, (int)splits, (int)(tiles * kt)};
+            }
+        }
+    }
+    return best;
+}
+
+template <int D, int KT, int NWAVE>
+hipError_t launch_mapping(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,
+                          const Mapping &m, float *part, hipStream_t s)
+{
+    const float scale_log2e = (float)(1.4426950408889634 / __builtin_sqrt((double)D));
+    const int64_t nqb = (N + NWAVE * QW - 1) / (NWAVE * QW);  // query blocks per batch element
+    if (nqb * batch * m.splits >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(nqb * batch * m.splits)), block(NWAVE * 64);
+    const char *q = (const char *)Q, *k = (const char *)K, *v = (const char *)V;
+    if (m.splits == 1)
+        return launch_kernel(attn_kernel<D, KT, NWAVE, false>, grid, block, s, q, k, v, (float *)O, (int)N, (int)M, (int)nqb, scale_log2e,
+                             1, m.run, (float *)nullptr, (float *)nullptr);
+    float *refs = part + batch * m.splits * N * D;
+    const hipError_t e = launch_kernel(attn_kernel<D, KT, NWAVE, true>, grid, block, s, q, k, v, (float *)O, (int)N, (int)M, (int)nqb,
+                                       scale_log2e, m.splits, m.run, part, refs);
+    if (e != hipSuccess) return e;
+    const int64_t rows = batch * N, per = 1024 / D;
+    return launch_kernel(attn_join_kernel<D>, dim3((unsigned)((rows + per - 1) / per)), dim3(256), s, (const float *)part, (const float *)refs,
+                         (float *)O, rows, (int)N, m.splits);
+}
+
+template <int D, int KT>
+hipError_t launch_head(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M, const Mapping &m,
+                       float *part, hipStream_t s)
+{
+    switch (m.nwave) {
+        case 1: return launch_mapping<D, KT, 1>(Q, K, V, O, batch, N, M, m, part, s);
+        case 2: return launch_mapping<D, KT, 2>(Q, K, V, O, batch, N, M, m, part, s);
+        case 4: return launch_mapping<D, KT, 4>(Q, K, V, O, batch, N, M, m, part, s);
+    }
+    return launch_mapping<D, KT, 8>(Q, K, V, O, batch, N, M, m, part, s);
+}
+
+}  // namespace
+
+int64_t attention_workspace_bytes(int64_t batch, int64_t N, int64_t M, int64_t d)
+{
+    const Mapping m = choose_mapping(batch, N, M, d, (int64_t)1 << 62);
+    return m.splits > 1 ? part_bytes(batch, N, d, m.splits) : 0;
+}
+
 hipError_t launch_attention(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,
-                            int64_t d, hipStream_t s)
+                            int64_t d, void *workspace, int64_t workspace_bytes, hipStream_t s)
 {
     if (!supports_attention(N, M, d) || batch < 1 || batch > 65535) return hipErrorInvalidValue;
-    const float scale_log2e = (float)(1.4426950408889634 / __builtin_sqrt((double)d));
-    const int64_t nqb = (N + NWAVE * QW - 1) / (NWAVE * QW);  // query blocks per batch element
-    if (nqb * batch >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(nqb * batch));
-    hipError_t launch_err = hipSuccess;
-    if (d == 128)
-        launch_err = launch_kernel(attn_kernel<128, 64>, grid, dim3(NWAVE * 64), s, (const char *)Q, (const char *)K,
-                           (const char *)V, (float *)O, (int)N, (int)M, (int)nqb, scale_log2e);
-    else
-        launch_err = launch_kernel(attn_kernel<64, 128>, grid, dim3(NWAVE * 64), s, (const char *)Q, (const char *)K,
-                           (const char *)V, (float *)O, (int)N, (int)M, (int)nqb, scale_log2e);
-    return launch_err;
+    const Mapping m = choose_mapping(batch, N, M, d, workspace ? workspace_bytes : 0);
+    return d == 128 ? launch_head<128, 64>(Q, K, V, O, batch, N, M, m, (float *)workspace, s)
+                    : launch_head<64, 128>(Q, K, V, O, batch, N, M, m, (float *)workspace, s);
 }
 
 }  // namespace cyc

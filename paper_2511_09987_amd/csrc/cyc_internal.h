@@ -101,8 +101,10 @@ int64_t chol_workspace_bytes(int64_t n, int64_t nb);
 hipError_t launch_chol(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, hipStream_t s);
 // FlashAttention-2 tile recurrence (see cyc_attn.hip); requires supports_attention(N, M, d)
 bool supports_attention(int64_t N, int64_t M, int64_t d);
+// workspace: attention_workspace_bytes() bytes of device memory, 16-byte aligned, or less or nullptr: the keys are not split
+int64_t attention_workspace_bytes(int64_t batch, int64_t N, int64_t M, int64_t d);
 hipError_t launch_attention(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,
-                            int64_t d, hipStream_t s);
+                            int64_t d, void *workspace, int64_t workspace_bytes, hipStream_t s);
 // HBM-bound streaming kernel for N <= 16; requires supports_narrow(p)
 bool supports_narrow(const Problem &p);
 bool prefers_narrow(const Problem &p);   // supported and expected to beat the GEMM kernels

@@ -181,3 +181,68 @@ def test_full_size_head_dimension_64(lib, attn):
         check(O[b][rows], ref, f64(V[b]))
     assert bool((O <= V.float().amax(dim=1, keepdim=True) + 1e-2).all())
     assert bool((O >= V.float().amin(dim=1, keepdim=True) - 1e-2).all())
+
+
+# every number of waves per workgroup, one run and several of them (the last one ragged), both head dimensions; the first
+# two have no more queries than one wave takes
+SPLIT_SHAPES = [(64, 1, 4000, 128), (3, 16, 2049, 64), (1, 33, 513, 128), (2, 65, 1023, 64), (1, 128, 4096, 128), (2, 500, 2500, 128),
+                (16, 130, 300, 64), (6, 1000, 520, 64)]
+
+
+@pytest.mark.parametrize("batch,N,M,d", SPLIT_SHAPES)
+def test_keys_in_runs(lib, attn, batch, N, M, d):
+    Q = ws_inputs.normal_bf16((batch, N, d), 1.5, 40 + N, 0, DEV)
+    K = ws_inputs.normal_bf16((batch, M, d), 1.5, 40 + N, 1, DEV)
+    V = ws_inputs.normal_bf16((batch, M, d), 1.0, 40 + N, 2, DEV)
+    O = lib.recurrence_attention(Q, K, V)
+    assert torch.equal(O, lib.recurrence_attention(Q, K, V))
+    whole = torch.empty_like(O)                                 # without memory for the runs
+    assert lib.cyc_recurrence_attention(Q.data_ptr(), K.data_ptr(), V.data_ptr(), whole.data_ptr(), batch, N, M, d,
+                                        torch.cuda.current_stream().cuda_stream) == 0
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    elsewhere = lib.recurrence_attention(Q, K, V, out=torch.empty_like(O), stream=side)
+    side.synchronize()
+    assert torch.equal(O, elsewhere)
+    for b in {0, batch - 1}:
+        ref = attn.attention(f64(Q[b]), f64(K[b]), f64(V[b]))
+        check(O[b], ref, f64(V[b]))
+        check(whole[b], ref, f64(V[b]))
+
+
+def test_runs_without_weight_and_runs_with_nan(lib):
+    """Scores of -inf in whole runs weigh nothing; a NaN or infinite score spoils its query."""
+    M, d = 4096, 128
+    Q = torch.zeros((2, d), dtype=torch.bfloat16, device=DEV)
+    Q[:, 0] = 1.0
+    Q[1, 1] = 1.0
+    K = torch.zeros((M, d), dtype=torch.bfloat16, device=DEV)
+    K[1024:, 0] = float("-inf")
+    V = ws_inputs.small_int_bf16((M, d), 8, 5, 2, DEV)
+    assert lib.cyc_attention_workspace(1, 2, M, d) > 0
+    O = lib.recurrence_attention(Q, K, V)
+    mean = (V[:1024].double().sum(dim=0) / 1024).float()
+    assert torch.allclose(O, mean.expand(2, d), rtol=1e-6, atol=1e-6)
+    for bad in (float("nan"), float("inf")):
+        Kb = K.clone()
+        Kb[3000, 0], Kb[3000, 1] = 0.0, bad
+        Ob = lib.recurrence_attention(Q, Kb, V)
+        assert bool(Ob[1].isnan().all())
+
+
+def test_runs_in_a_captured_graph(lib):
+    batch, N, M, d = 4, 3, 3000, 128
+    make = lambda seed: [ws_inputs.normal_bf16((batch, n, d), 1.0, seed, i, DEV) for i, n in enumerate((N, M, M))]
+    state = make(50)
+    lib.recurrence_attention(*state)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        O = lib.recurrence_attention(*state)
+    for seed in (51, 52, 53):
+        fresh = make(seed)
+        for t, f in zip(state, fresh):
+            t.copy_(f)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(O, lib.recurrence_attention(*fresh))
