@@ -71,7 +71,8 @@
  *   mfmak    unbatched, at most 64 output blocks of 128 x 128, K >= 4096: k in
  *            space; k-slices on different workgroups leave partial sums in the
  *            workspace and a second kernel adds them in ascending slice order.
- *   mfma256 / mfma128  everything else with aligned rows.
+ *   mfma256 / mfma128  everything else with aligned rows (mfma128: blocks of 128 x 128 or, where those are few, of
+ *            64 x 64 or 32 x 32).
  *   generic  the rest: rows at any address, on the matrix cores when K and N are at
  *            least 16 bytes long, off them otherwise (and when forced).
  */

@@ -26,7 +26,7 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
     return a < b + (uintptr_t)qbytes && b < a + (uintptr_t)pbytes;
 }
 
-enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
+enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_SMALL, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
 
 const char *kernel_label(Kernel k)
 {
@@ -35,7 +35,7 @@ const char *kernel_label(Kernel k)
         case K_ZERO: return "zero";
         case K_GENERIC: case K_UNEVEN: return "generic";   // one family: any alignment, on the matrix cores or (forced, tiny extents) off them
         case K_MFMA256: return "mfma256";
-        case K_MFMA128: return "mfma128";
+        case K_MFMA128: case K_SMALL: return "mfma128";
         case K_MFMA256X32: return "mfma256x32";
         case K_MFMA128X32: return "mfma128x32";
         case K_MFMAK: return "mfmak";
@@ -119,6 +119,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     if (force == K_NONE && cyc::choose_ksplit(*p, &ktile) > 1) { *k = K_MFMAK; return CYC_OK; }
     // MFMA kernels for everything with 16-byte aligned rows except slivers
     const int tile = cyc::choose_mfma_tile(*p);
+    if (force == K_NONE && tile == 128 && cyc::choose_small_block(*p)) { *k = K_SMALL; return CYC_OK; }
     if (tile == 256) { *k = K_MFMA256; return CYC_OK; }
     if (tile == 128) { *k = K_MFMA128; return CYC_OK; }
     *k = cyc::supports_uneven(*p) ? K_UNEVEN : K_GENERIC;
@@ -135,6 +136,7 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
         case K_UNEVEN: e = cyc::launch_uneven(p, s); break;
         case K_MFMA256: e = cyc::launch_mfma(p, 256, 16, s); break;
         case K_MFMA128: e = cyc::launch_mfma(p, 128, 16, s); break;
+        case K_SMALL: e = cyc::launch_small(p, cyc::choose_small_block(p), s); break;
         case K_MFMA256X32: e = cyc::launch_mfma(p, 256, 32, s); break;
         case K_MFMA128X32: e = cyc::launch_mfma(p, 128, 32, s); break;
         case K_MFMAK: {

@@ -1219,8 +1219,7 @@ hipError_t launch_chol(const void *A_, void *L_, void *Lh_, int64_t n, int64_t n
         p.N = ncols;
         p.strideA = p.strideB = p.strideC = 0;
         p.i8 = false;
-        const int tile = choose_mfma_tile(p);
-        return tile ? launch_mfma(p, tile, 16, on) : launch_any_alignment(p, on);
+        return launch_product(p, on);
     };
     bool diag_done = false;           // the diagonal tile of this panel was factored by the rows kernel of the panel before
     int64_t prepared_from = -1;       // >= 0: the launch before took the k range [k0, prepared_from) out of this launch's first workgroup's tiles

@@ -47,6 +47,12 @@ bool supports_uneven(const Problem &p);
 hipError_t launch_uneven(const Problem &p, hipStream_t s);
 // what no aligned kernel takes
 inline hipError_t launch_any_alignment(const Problem &p, hipStream_t s) { return supports_uneven(p) ? launch_uneven(p, s) : launch_generic(p, s); }
+// edge (64 or 32) of the small blocks of cyc_uneven.hip that beat blocks of 128 on this problem with aligned rows, 0 if
+// none does
+int choose_small_block(const Problem &p);
+hipError_t launch_small(const Problem &p, int block, hipStream_t s);
+// the updates of the triangular solve and of the Cholesky factorisation: one launch with the blocks that suit the problem
+hipError_t launch_product(const Problem &p, hipStream_t s);
 // fill C with the chain's initial value (K == 0)
 hipError_t launch_zero(const Problem &p, hipStream_t s);
 // MFMA tiled GEMM; requires supports_mfma(p, tile)

@@ -1171,8 +1171,7 @@ hipError_t update(const Solve &v, int64_t r0, int64_t mid, int64_t r1)
     p.N = v.nrhs;
     p.strideA = p.strideB = p.strideC = 0;
     p.i8 = false;
-    const int tile = choose_mfma_tile(p);
-    return tile ? launch_mfma(p, tile, 16, v.s) : launch_any_alignment(p, v.s);
+    return launch_product(p, v.s);
 }
 
 // the four-wave panel kernel can be used: whole 16-byte pieces of the rows of X and Xh

@@ -345,4 +345,37 @@ hipError_t launch_uneven(const Problem &p, hipStream_t s)
     return p.i8 ? launch_dtype<true>(p, s) : launch_dtype<false>(p, s);
 }
 
+// Products with aligned rows and few blocks of 128 x 128 leave most of the chip idle: blocks of 64 x 64, or of 32 x 32 with
+// eight teams along k, are then the faster ones although they stage through registers.  Costs in units of 10 ns per launch,
+// fitted to (bf16, microseconds, 128 / 64 / 32 wide blocks; i8 has twice the k per k-tile and fits the same):
+//   64 x 64 x 64 5.5 / 3.9 / 4.0        128 x 1024 x 128 8.8 / 7.5 / 4.5    512^3 6.4 / 5.8 / 4.7      384 x 2048 x 384 14.4 / 11.7 / 6.3
+//   768^3 9.1 / 7.1 / 9.6               1024^3 9.5 / 8.5 / 12.4             1536^3 16.3 / 21.4 / 35    200 x 2048 x 4096 17.8 / 12.3 / 18.1
+//   16 x (64 x 2048 x 64) 17 / 11 / 6   2 x (33 x 4096 x 4096) 34 / 28 / 20
+int choose_small_block(const Problem &p)
+{
+    if (p.M < 16 || p.N < 16 || !supports_uneven(p)) return 0;
+    auto blocks = [&](int64_t b) { return ((p.M + b - 1) / b) * ((p.N + b - 1) / b) * p.batch; };
+    const int64_t bke = p.i8 ? 128 : 64, kt = (p.K + bke - 1) / bke, n128 = blocks(128);
+    if (n128 > 256) return 0;
+    const int64_t c128 = 340 + 45 * kt, c64 = 330 + 25 * kt * ((blocks(64) + 255) / 256);
+    const int64_t c32 = 330 + ((blocks(32) + 255) / 256) * (30 + 65 * ((kt + 7) / 8));
+    if (std::min(c64, c32) >= c128) return 0;
+    return c32 <= c64 ? 32 : 64;
+}
+
+hipError_t launch_small(const Problem &p, int block, hipStream_t s)
+{
+    if (!supports_uneven(p)) return hipErrorInvalidValue;
+    if (block == 64) return p.i8 ? launch_shape<Shape<true, 2, 2, 2, 2, 1>>(p, s) : launch_shape<Shape<false, 2, 2, 2, 2, 1>>(p, s);
+    return p.i8 ? launch_shape<Shape<true, 2, 2, 1, 1, 8>>(p, s) : launch_shape<Shape<false, 2, 2, 1, 1, 8>>(p, s);
+}
+
+hipError_t launch_product(const Problem &p, hipStream_t s)
+{
+    const int tile = choose_mfma_tile(p);
+    if (tile == 128)
+        if (const int block = choose_small_block(p)) return launch_small(p, block, s);
+    return tile ? launch_mfma(p, tile, 16, s) : launch_any_alignment(p, s);
+}
+
 }  // namespace cyc
