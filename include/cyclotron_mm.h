@@ -32,9 +32,12 @@
  *     (see below): one workspace of
  *     device memory per (device, stream), allocated with hipMalloc at the
  *     first such call on that stream and replaced by a larger one (hipFree +
- *     hipMalloc, which waits for the device) when a later call needs more.
- *     A call that cannot get it returns CYC_ERR_WORKSPACE.  No other entry
- *     point allocates device memory;
+ *     hipMalloc, which waits for the device; a buffer that a stream capture
+ *     has seen is kept) when a later call needs more.  A call holds a lock
+ *     from getting it to its last launch.  A solve or factorisation that cannot
+ *     get it, also because a capture forbids the allocation, returns
+ *     CYC_ERR_WORKSPACE; a product takes a kernel that needs none.  No other
+ *     entry point allocates device memory;
  *   - for cyc_recurrence_cholesky with n > 16 nb: one extra stream and a few
  *     events per device (see there); callers that use it are serialised on
  *     the host by a lock for the duration of the enqueueing.
@@ -67,7 +70,7 @@
  * Kernel families and when the dispatcher picks them:
  *   narrow   N <= 16, many rows: A streamed once from memory, B resident.
  *   narrowm  M <= 32, B of at least a mebibyte: B streamed once, the rows of
- *            A pass over it ((j,k) in space).
+ *            A pass over it ((j,k) in space).  (Long k and few columns: mfmak.)
  *   mfmak    unbatched, at most 64 output blocks of 128 x 128, K >= 4096: k in
  *            space; k-slices on different workgroups leave partial sums in the
  *            workspace and a second kernel adds them in ascending slice order.

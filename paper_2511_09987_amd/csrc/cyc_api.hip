@@ -26,7 +26,7 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
     return a < b + (uintptr_t)qbytes && b < a + (uintptr_t)pbytes;
 }
 
-enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_SMALL, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
+enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_SMALL, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM, K_NARROWM_BLOCKS };
 
 const char *kernel_label(Kernel k)
 {
@@ -40,7 +40,7 @@ const char *kernel_label(Kernel k)
         case K_MFMA128X32: return "mfma128x32";
         case K_MFMAK: return "mfmak";
         case K_NARROW: return "narrow";
-        case K_NARROWM: return "narrowm";
+        case K_NARROWM: case K_NARROWM_BLOCKS: return "narrowm";
     }
     return "none";
 }
@@ -114,7 +114,17 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         default: break;
     }
     if (cyc::prefers_narrow(*p)) { *k = K_NARROW; return CYC_OK; }
-    if (cyc::prefers_narrowm(*p)) { *k = K_NARROWM; return CYC_OK; }
+    if (cyc::prefers_narrowm(*p)) {
+        // Its workgroups each stream 1024 columns, or 128 of them in eight k-slices: up to 512 blocks of 32 columns, with eight
+        // teams along k and one to two of them on a compute unit, keep more of the chip reading (bf16, 16 rows, microseconds there /
+        // in blocks: 8192 x 1024 52 / 12, 8192 x 8192 55 / 26, 4 x 2048 x 4096 18 / 16; but 4 x 2048 x 8192 25 / 25, i8 14 / 19),
+        // and past 128 k-tiles k goes to space across workgroups as well (32 x 17280 x 784 144 / 39, k in space 17).
+        const int64_t blocks = p->batch * ((p->N + 31) / 32), kt = p->K * es / 128;
+        if (force == K_NONE && kt > 128 && p->N <= 4096 && cyc::choose_ksplit(*p, &ktile) > 1) *k = K_MFMAK;
+        else if (force == K_NONE && blocks <= 512 && cyc::supports_uneven(*p)) *k = K_NARROWM_BLOCKS;
+        else *k = K_NARROWM;
+        return CYC_OK;
+    }
     // few output blocks, long k: k goes to space (see choose_ksplit)
     if (force == K_NONE && cyc::choose_ksplit(*p, &ktile) > 1) { *k = K_MFMAK; return CYC_OK; }
     // MFMA kernels for everything with 16-byte aligned rows except slivers
@@ -141,12 +151,14 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
         case K_MFMA128X32: e = cyc::launch_mfma(p, 128, 32, s); break;
         case K_MFMAK: {
             int tile = 0;
-            const int ks = cyc::choose_ksplit(p, &tile);
-            e = cyc::launch_mfma_ksplit(p, ks, tile, workspace, s);
+            int64_t length = 0;
+            const int ks = cyc::choose_ksplit(p, &tile, &length);
+            e = cyc::launch_mfma_ksplit(p, ks, tile, length, workspace, s);
             break;
         }
         case K_NARROW: e = cyc::launch_narrow(p, s); break;
         case K_NARROWM: e = cyc::launch_narrowm(p, s); break;
+        case K_NARROWM_BLOCKS: e = cyc::launch_small(p, 32, s); break;
     }
     return e == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
 }
@@ -159,6 +171,7 @@ constexpr int64_t kBatchPerLaunch = 65535;
 int run(const cyc::Problem &p, Kernel k, hipStream_t s, bool fixed_workspace = false)
 {
     void *workspace = nullptr;
+    cyc::WorkspaceHold hold;
     if (k == K_MFMAK) {
         // everything that can fail before the first launch is settled before it
         int tile = 0;
@@ -169,9 +182,13 @@ int run(const cyc::Problem &p, Kernel k, hipStream_t s, bool fixed_workspace = f
             workspace = cyc::static_workspace(&have);
             if (need > have) return CYC_ERR_WORKSPACE;
         } else {
-            workspace = cyc::cached_workspace(s, need);
+            workspace = hold.acquire(s, need);
+            if (!workspace) {                   // no memory, or none to be had under capture: one workgroup per block instead
+                const int t = cyc::choose_mfma_tile(p);
+                k = cyc::prefers_narrowm(p) ? K_NARROWM : t == 256 ? K_MFMA256 : t == 128 ? K_MFMA128 : cyc::supports_uneven(p) ? K_UNEVEN : K_GENERIC;
+            }
         }
-        if (!workspace) return CYC_ERR_WORKSPACE;
+        if (!workspace && k == K_MFMAK) return CYC_ERR_WORKSPACE;
     }
     if (p.batch <= kBatchPerLaunch) return run_chunk(p, k, workspace, s);
     const int64_t es = p.i8 ? 1 : 2;
@@ -233,10 +250,11 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh, int64_t
         overlaps(Xh, nr * 2, B, nr * 4) || overlaps(X, nr * 4, Xh, nr * 2))
         return CYC_ERR_ALIAS;
     // the inverses of the diagonal tiles live in the per-stream workspace; it is acquired before the first launch
+    cyc::WorkspaceHold hold;
     void *workspace = nullptr;
     const int64_t need = cyc::trsm_workspace_bytes(L, X, Xh, n, nrhs, nb);
     if (need > 0) {
-        workspace = cyc::cached_workspace((hipStream_t)stream, need);
+        workspace = hold.acquire((hipStream_t)stream, need);
         if (!workspace) return CYC_ERR_WORKSPACE;
     }
     return cyc::launch_trsm(L, B, X, Xh, n, nrhs, nb, workspace, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
@@ -251,10 +269,11 @@ int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t
     if (!A || !L || !Lh) return CYC_ERR_NULL;
     if (((uintptr_t)A | (uintptr_t)L) & 3 || ((uintptr_t)Lh & 1)) return CYC_ERR_SHAPE;
     if (overlaps(L, nn * 4, A, nn * 4) || overlaps(Lh, nn * 2, A, nn * 4) || overlaps(L, nn * 4, Lh, nn * 2)) return CYC_ERR_ALIAS;
+    cyc::WorkspaceHold hold;
     void *workspace = nullptr;
     const int64_t need = cyc::chol_workspace_bytes(n, nb);
     if (need > 0) {
-        workspace = cyc::cached_workspace((hipStream_t)stream, need);
+        workspace = hold.acquire((hipStream_t)stream, need);
         if (!workspace) return CYC_ERR_WORKSPACE;
     }
     return cyc::launch_chol(A, L, Lh, n, nb, workspace, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;

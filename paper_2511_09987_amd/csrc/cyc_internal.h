@@ -34,6 +34,7 @@ struct Problem {
     int64_t ldb = 0;                     // row stride of B in elements, 0 = N
     int64_t ldc = 0;                     // row stride of C (and of Cin) in elements, 0 = N
     const void *Cin = nullptr;           // when set, C <- Cin - A*B instead of C <- A*B (same layout as C; may be C)
+    int64_t k_total = 0;                 // k-slices only: the k extent of the whole problem, where the last slice ends
     bool kslices = false;                // the batch elements are k-slices of one problem (windows allowed with batch > 1)
 };
 inline int64_t row_stride_a(const Problem &p) { return p.lda ? p.lda : p.K; }
@@ -60,17 +61,30 @@ bool supports_mfma(const Problem &p, int tile);
 hipError_t launch_mfma(const Problem &p, int tile, int mt, hipStream_t s);   // mt: MFMA tile width, 16 or 32
 // block edge (256 or 128) of the MFMA kernel that suits the problem best, 0 if neither supports it
 int choose_mfma_tile(const Problem &p);
-// k in space: number of k-slices (a power of two, 1 = do not split) for problems with few output blocks and a
-// long k extent.  One workgroup per (output block, k-slice) writes its partial product to slice `b` of a workspace
+// k in space: number of k-slices (1 = do not split; all of *length but the last, which may be shorter) for problems with few
+// output blocks and a long k extent.  One workgroup per (output block, k-slice) writes its partial product to slice `b` of a workspace
 // of ksplit x M x N accumulator elements; a second kernel adds the slices in ascending order into C.
-int choose_ksplit(const Problem &p, int *tile);   // *tile: block edge to use, 128 or 256
+int choose_ksplit(const Problem &p, int *tile, int64_t *length);   // *tile: block edge to use, 128 or 256
+int choose_ksplit(const Problem &p, int *tile);
 inline int64_t ksplit_workspace_bytes(const Problem &p, int ksplit) { return (int64_t)ksplit * p.M * p.N * 4; }
-hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, void *workspace, hipStream_t s);
-// Device memory for the partial products.  cached_workspace: one buffer per (device, stream), allocated with hipMalloc
-// on first use, grown when a call needs more, kept until the process ends; nullptr when the allocation fails.
+hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, int64_t length, void *workspace, hipStream_t s);
+// Device memory for partial products, inverses and padded copies.  WorkspaceHold::acquire: one buffer per (device, stream),
+// allocated with hipMalloc on first use, grown when a call needs more, kept until the process ends; nullptr when the
+// allocation fails, or would be needed while the stream is being captured.  The buffer is the holder's until the object
+// goes out of scope: it stays alive until everything that uses it is enqueued.
 // static_workspace: the library's fixed array in device memory (one per device, *bytes = its size), shared by every
 // caller on that device; allocates nothing; nullptr when its address cannot be obtained.
-void *cached_workspace(hipStream_t s, int64_t bytes);
+class WorkspaceHold {
+public:
+    WorkspaceHold() = default;
+    WorkspaceHold(const WorkspaceHold &) = delete;
+    WorkspaceHold &operator=(const WorkspaceHold &) = delete;
+    void *acquire(hipStream_t s, int64_t bytes);
+    ~WorkspaceHold();
+
+private:
+    bool held_ = false;
+};
 void *static_workspace(int64_t *bytes);
 // lower-triangular forward solve L X = B in tiles of nb rows (see cyc_tri.hip); arguments validated by the caller
 // A second stream per device for work that may run beside what a call enqueues on the caller's stream (forked from

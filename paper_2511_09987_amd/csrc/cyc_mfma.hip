@@ -146,12 +146,14 @@ __device__ __forceinline__ void tile_fence()
 // and are not stored; in the last k-tile, chunks at or past K are not copied but written as zeros.
 // EPI: what the epilogue does with the accumulators: EPI_STORE C <- A*B; EPI_MINUS C <- Cin - A*B (Cin may be C).
 // A template parameter, so that each form is straight-line code.
-enum { EPI_STORE = 0, EPI_MINUS = 1 };
+// EPI_SLICE: EPI_STORE where the batch elements are k-slices of one problem; K is their length, k_total the problem's, and
+// the last slice ends there.
+enum { EPI_STORE = 0, EPI_MINUS = 1, EPI_SLICE = 2 };
 template <class C, bool RAGGED, int EPI>
 __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__ A, const char *__restrict__ B,
                                                         char *__restrict__ Cout, int M, int K, int N, int64_t sA,
                                                         int64_t sB, int64_t sC, int tiles_m, int tiles_n, int lda,
-                                                        int ldb, int ldc, const char *Cin)
+                                                        int ldb, int ldc, const char *Cin, int k_total)
 {
     constexpr int ES = C::ES, RB = C::RB, TM = C::TM, TN = C::TN;
     __shared__ __attribute__((aligned(1024))) char lds_raw[C::LDS_BYTES];
@@ -184,6 +186,7 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
     const int tm_blk = group * GM + in_group % rows_here, tn_blk = in_group / rows_here;
     const int m0 = tm_blk * C::BM, n0 = tn_blk * C::BN;
 
+    if (EPI == EPI_SLICE) K = k_total - bz * K < K ? k_total - bz * K : K;
     A += (int64_t)bz * sA * ES;
     B += (int64_t)bz * sB * ES;
     Cout += (int64_t)bz * sC * 4;
@@ -457,25 +460,28 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
 template <class C, int EPI>
 hipError_t launch_epi(const Problem &p, hipStream_t s)
 {
-    const bool ragged = p.M % C::BM || p.N % C::BN || p.K % C::BKE;
+    const bool ragged = p.M % C::BM || p.N % C::BN || p.K % C::BKE || p.k_total % C::BKE;
     const int tiles_m = (int)((p.M + C::BM - 1) / C::BM), tiles_n = (int)((p.N + C::BN - 1) / C::BN);
     dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)p.batch);
     hipError_t launch_err = hipSuccess;
     if (ragged)
         launch_err = launch_kernel(ws_mfma_kernel<C, true, EPI>, grid, dim3(C::NT), s, (const char *)p.A, (const char *)p.B,
                            (char *)p.C, (int)p.M, (int)p.K, (int)p.N, p.strideA, p.strideB, p.strideC, tiles_m, tiles_n,
-                           (int)row_stride_a(p), (int)row_stride_b(p), (int)row_stride_c(p), (const char *)p.Cin);
+                           (int)row_stride_a(p), (int)row_stride_b(p), (int)row_stride_c(p), (const char *)p.Cin, (int)p.k_total);
     else
         launch_err = launch_kernel(ws_mfma_kernel<C, false, EPI>, grid, dim3(C::NT), s, (const char *)p.A, (const char *)p.B,
                            (char *)p.C, (int)p.M, (int)p.K, (int)p.N, p.strideA, p.strideB, p.strideC, tiles_m, tiles_n,
-                           (int)row_stride_a(p), (int)row_stride_b(p), (int)row_stride_c(p), (const char *)p.Cin);
+                           (int)row_stride_a(p), (int)row_stride_b(p), (int)row_stride_c(p), (const char *)p.Cin, (int)p.k_total);
     return launch_err;
 }
 
-// EXTRA: also build the EPI_MINUS form (only the 16-wide MFMA shape, which is all its callers use)
+// EXTRA: also build the EPI_MINUS and EPI_SLICE forms (only the 16-wide MFMA shape, which is all their callers use)
 template <class C, bool EXTRA>
 hipError_t launch_cfg(const Problem &p, hipStream_t s)
 {
+    if constexpr (EXTRA) {
+        if (p.k_total) return launch_epi<C, EPI_SLICE>(p, s);
+    }
     if (!p.Cin) return launch_epi<C, EPI_STORE>(p, s);
     if constexpr (EXTRA) return launch_epi<C, EPI_MINUS>(p, s);
     return hipErrorInvalidValue;
@@ -539,11 +545,19 @@ int choose_mfma_tile(const Problem &p)
 // result is the same bits on every call).
 int choose_ksplit(const Problem &p, int *tile)
 {
+    int64_t length;
+    return choose_ksplit(p, tile, &length);
+}
+
+int choose_ksplit(const Problem &p, int *tile, int64_t *length)
+{
     *tile = 128;
+    *length = p.K;
     if (p.batch != 1 || p.lda || p.ldb || p.ldc || p.Cin || p.kslices || !supports_mfma(p, 128)) return 1;
     const int64_t b128 = ((p.M + 127) / 128) * ((p.N + 127) / 128), b256 = ((p.M + 255) / 256) * ((p.N + 255) / 256);
     const int64_t bke = p.i8 ? 128 : 64;
     if (b128 > 64 || p.K < 4096) return 1;
+    // equal slices, a power of two of them
     auto slices = [&](int64_t blocks, int64_t slots) {
         const int64_t want = std::min<int64_t>(slots / blocks, p.K / (8 * bke));   // at least eight k-tiles per slice
         int ks = 1;
@@ -553,23 +567,38 @@ int choose_ksplit(const Problem &p, int *tile)
     // 256 x 256 blocks (one per CU) re-read A and B half as often as 128 x 128 blocks (two per CU) but cost more to
     // start and to finish: take them when they compute little padding, still fill the chip and keep long slices
     const int ks256 = supports_mfma(p, 256) ? slices(b256, 256) : 1;
-    const bool big = b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096;
-    const int ks = big ? ks256 : slices(b128, 256);
-    *tile = big ? 256 : 128;
+    if (b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096) {
+        *tile = 256;
+        *length = p.K / ks256;
+        return ks256;
+    }
+    int ks = slices(b128, 256);
+    *length = p.K / ks;
+    // K need not be a multiple of anything: where the equal slices are less than 3/4 as many as the chip has room for, as many
+    // slices as there is room for, of whole k-tiles, the last one with what remains (40 x 17280 x 784 bf16: 110 us in two slices' stead, 14)
+    const int64_t nkt = (p.K + bke - 1) / bke, want = std::min<int64_t>(256 / b128, nkt / 8);
+    if (ks * 4 < want * 3) {
+        const int64_t per = (nkt + want - 1) / want;
+        ks = (int)((nkt + per - 1) / per);
+        *length = per * bke;
+    }
     return ks;
 }
 
-hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, void *workspace, hipStream_t s)
+hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, int64_t length, void *workspace, hipStream_t s)
 {
-    if (ksplit < 2 || ksplit > 256 || p.batch != 1 || p.K % ksplit || !workspace || (p.M * p.N) % 4) return hipErrorInvalidValue;
+    if (ksplit < 2 || ksplit > 256 || p.batch != 1 || length < 1 || (ksplit - 1) * length >= p.K || ksplit * length < p.K || !workspace ||
+        (p.M * p.N) % 4)
+        return hipErrorInvalidValue;
     Problem q = p;
     q.batch = ksplit;                    // the batch index of the kernel serves as the slice index
     q.kslices = true;
-    q.K = p.K / ksplit;
+    q.K = length;
+    q.k_total = p.K;
     q.lda = p.K;
     q.ldb = p.N;
     q.ldc = p.N;
-    q.strideA = q.K;                     // slice b starts at column b * K/ksplit of A ...
+    q.strideA = q.K;                     // slice b starts at column b * length of A ...
     q.strideB = q.K * p.N;               // ... and at that row of B ...
     q.C = workspace;
     q.strideC = p.M * p.N;               // ... and leaves its partial product in slice b of the workspace

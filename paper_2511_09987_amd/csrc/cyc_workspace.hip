@@ -1,13 +1,13 @@
 // cyc_workspace.hip -- device memory for the partial products of the k-in-space matmul and for the inverses of the triangular solve (see cyc_internal.h).
 //
-// Two sources.  cached_workspace(): one hipMalloc'd buffer per (device, stream), so that calls on different
-// streams never share one; grown when a call needs more, never shrunk, kept until the process ends.
+// Two sources.  WorkspaceHold: one hipMalloc'd buffer per (device, stream), so that calls on different streams never share
+// one; grown when a call needs more, never shrunk, kept until the process ends.  The object keeps a lock while it lives, so
+// that of two threads that call on one stream each has all its launches in the stream before the other's begin.
 // static_workspace(): a fixed array in the library's own device image, for callers that must not allocate.
 #include "cyc_internal.h"
 
 #include <map>
 #include <mutex>
-#include <utility>
 
 namespace cyc {
 namespace {
@@ -23,7 +23,12 @@ static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 struct PerDevice {
     bool tried = false;
     void *scratch_ptr = nullptr;                        // this device's address of `scratch`
-    std::map<hipStream_t, std::pair<void *, int64_t>> cache;   // stream -> (buffer, bytes)
+    struct Buffer {
+        void *ptr = nullptr;
+        int64_t bytes = 0;
+        bool captured = false;                          // some graph holds its address
+    };
+    std::map<hipStream_t, Buffer> cache;
 };
 PerDevice g_dev[MAX_DEVICES];
 std::mutex g_mutex;
@@ -52,21 +57,36 @@ void *static_workspace(int64_t *bytes)
     return d->scratch_ptr;
 }
 
-void *cached_workspace(hipStream_t s, int64_t bytes)
+void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
 {
-    std::lock_guard<std::mutex> hold(g_mutex);
+    if (!held_) {
+        g_mutex.lock();
+        held_ = true;
+    }
     PerDevice *d = current_device();
     if (!d || bytes <= 0) return nullptr;
     auto &slot = d->cache[s];
-    if (slot.second >= bytes) return slot.first;
-    // hipFree waits for the device, so nothing enqueued earlier still uses the old buffer when it goes
-    if (slot.first) (void)hipFree(slot.first);
-    slot = {nullptr, 0};
-    void *p = nullptr;
-    const int64_t want = (bytes + ((int64_t)1 << 20) - 1) >> 20 << 20;
-    if (hipMalloc(&p, (size_t)want) != hipSuccess) return nullptr;
-    slot = {p, want};
-    return p;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+    if (slot.bytes < bytes) {
+        if (capturing) return nullptr;                  // an allocation would end the capture
+        // hipFree waits for the device, so nothing enqueued earlier still uses the old buffer when it goes; a graph that was
+        // captured with it may be launched at any time, so that buffer stays
+        if (slot.ptr && !slot.captured) (void)hipFree(slot.ptr);
+        slot = {};
+        void *p = nullptr;
+        const int64_t want = (bytes + ((int64_t)1 << 20) - 1) >> 20 << 20;
+        if (hipMalloc(&p, (size_t)want) != hipSuccess) return nullptr;
+        slot.ptr = p;
+        slot.bytes = want;
+    }
+    slot.captured = slot.captured || capturing;
+    return slot.ptr;
+}
+
+WorkspaceHold::~WorkspaceHold()
+{
+    if (held_) g_mutex.unlock();
 }
 
 }  // namespace cyc

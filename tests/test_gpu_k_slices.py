@@ -1,0 +1,66 @@
+"""k in space over any number of k-slices, the last of them shorter, and few rows of A over a B of few columns."""
+import pytest
+import torch
+
+from datagen import ws_inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def operands(dtype, batch, M, K, N):
+    if dtype == torch.int8:
+        return [ws_inputs.uniform_int((batch,) + s, 127, M + K, i, DEV) for i, s in enumerate(((M, K), (K, N)))]
+    return [ws_inputs.normal_bf16((batch,) + s, 1.0, M + K, i, DEV) for i, s in enumerate(((M, K), (K, N)))]
+
+
+# (batch, M, K, N): as many slices as fit; k-tiles that do not divide among them; a last k-tile of one 16-byte chunk; ragged
+# blocks; then few rows (blocks of 32 columns, one and two to a compute unit; k in space; M below a block of MFMA rows)
+SHAPES = [(1, 40, 17280, 784), (1, 130, 8640, 272), (1, 128, 4112, 128), (1, 300, 9232, 144), (1, 64, 65600, 64), (1, 18, 17280, 784),
+          (1, 1, 17280, 256), (1, 20, 4000, 1008), (1, 16, 8192, 1024), (4, 32, 1040, 4096), (3, 5, 2048, 528), (1, 32, 2048, 8192)]
+
+
+@pytest.mark.parametrize("dtype", (torch.bfloat16, torch.int8))
+@pytest.mark.parametrize("batch,M,K,N", SHAPES)
+def test_products(dtype, batch, M, K, N):
+    import paper_2511_09987_amd as lib
+    A, B = operands(dtype, batch, M, K, N)
+    if batch == 1:
+        A, B = A[0], B[0]
+    C = lib.recurrence_matmul(A, B)
+    assert torch.equal(C.view(torch.int32), lib.recurrence_matmul(A, B).view(torch.int32))
+    for a, b, c in zip(A.view(batch, M, K), B.view(batch, K, N), C.view(batch, M, N)):
+        ref = torch.matmul(a.double(), b.double())
+        if dtype == torch.int8:
+            assert torch.equal(c.double(), ref)
+        else:                                                   # K roundings of 2^-24 of the sum of magnitudes at the most
+            assert bool(((c.double() - ref).abs() <= K * 2.0 ** -24 * torch.matmul(a.double().abs(), b.double().abs())).all())
+
+
+def test_first_call_on_a_stream_under_capture():
+    """No memory can be allocated while a stream is captured: the product runs without k-slices, and a graph keeps a buffer that
+    it was captured with although a later call needs a larger one."""
+    import paper_2511_09987_amd as lib
+    A, B = (t[0] for t in operands(torch.int8, 1, 64, 16384, 64))
+    A2, B2 = (t[0] for t in operands(torch.int8, 1, 500, 32768, 496))
+    want = torch.matmul(A.double(), B.double())
+    stream = torch.cuda.Stream()
+    cold, warm = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(cold, stream=stream):
+        C1 = lib.recurrence_matmul(A, B)
+    with torch.cuda.stream(stream):
+        lib.recurrence_matmul(A, B)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(warm, stream=stream):
+        C2 = lib.recurrence_matmul(A, B)
+    with torch.cuda.stream(stream):
+        C3 = lib.recurrence_matmul(A2, B2)                      # more slices of more elements
+    for _ in range(3):
+        C1.zero_()
+        C2.zero_()
+        cold.replay()
+        warm.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C1.double(), want) and torch.equal(C2.double(), want)
+    assert torch.equal(C3.double(), torch.matmul(A2.double(), B2.double()))
