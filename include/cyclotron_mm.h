@@ -153,12 +153,14 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C,
  *     while the call is in flight.
  * Xh: device, written, n x nrhs bfloat16 row-major: X rounded to bfloat16, the values the GEMMs consumed.
  * nb: tile size, 1 <= nb <= 128.  The MFMA kernels serve the GEMMs when n, nrhs and nb are multiples of 8
- *     and the pointers are 16-byte aligned; otherwise the shape-agnostic kernels do.
+ *     and the pointers are 16-byte aligned; otherwise kernels for any alignment do.
  * stream: hipStream_t or NULL.  The call enqueues a sequence of kernels on it and returns.  With nb == 64,
  *     nrhs a multiple of 8 below 2^24, n a multiple of 8 below 2^26 and 16-byte aligned L, X, Xh it keeps the inverses of the diagonal
  *     tiles (16 KiB per 64 rows) and a second copy of the tiles of L next to the diagonal in the order the
  *     kernels read them (56 KiB per 64 rows) in the workspace that the library holds per device and stream (allocated or
- *     grown on the call that first needs it, as for cyc_recurrence_matmul); otherwise it allocates nothing.
+ *     grown on the call that first needs it, as for cyc_recurrence_matmul).  With nb == 64, n >= 512 and any other nrhs, n
+ *     or alignment it solves a copy in that workspace, padded to multiples of 8, where the copy takes at most 256 MiB and
+ *     the workspace can be had (not under a capture that finds none).  Otherwise it allocates nothing.
  *     n == 0 or nrhs == 0: CYC_OK, nothing done.  A zero on the diagonal
  *     gives infinities or NaNs as IEEE division does, not an error.  Inside the kernels, waves hand solved rows
  *     to one another through LDS with bounded waits; a wait that ever ran out would leave NaN in X and Xh (in
@@ -193,8 +195,9 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
  *     pointers are 16-byte aligned; otherwise the shape-agnostic kernels do.
  * stream: hipStream_t or NULL.  The call enqueues a sequence of kernels on it and returns.  With nb == 64 and
  *     n >= 128 it keeps the inverses of the diagonal tiles (16 KiB per 64 rows) and a copy of one diagonal tile (16 KiB)
- *     in the workspace that the library holds per device and stream (allocated or grown on the call that first needs it); otherwise it allocates no
- *     device memory.  For n > 16 nb part of the work is enqueued on a second stream that the library creates per device
+ *     in the workspace that the library holds per device and stream (allocated or grown on the call that first needs it); with
+ *     nb == 64, n > 128 and n no multiple of 8 or pointers that are not 16-byte aligned it factors a padded copy there, where
+ *     the copy takes at most 256 MiB and the workspace can be had.  Otherwise it allocates no device memory.  For n > 16 nb part of the work is enqueued on a second stream that the library creates per device
  *     on first use (default priority, kept until the process ends) and that is forked from and joined back into
  *     `stream` with events inside the call: all of the call's work is ordered after what was on `stream` before
  *     and before what is enqueued on it afterwards; calls that use the second stream are serialised on the host

@@ -251,6 +251,9 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh, int64_t
         return CYC_ERR_ALIAS;
     // the inverses of the diagonal tiles live in the per-stream workspace; it is acquired before the first launch
     cyc::WorkspaceHold hold;
+    if (const int64_t padded = cyc::trsm_padded_bytes(L, X, Xh, n, nrhs, nb))
+        if (void *w = hold.acquire((hipStream_t)stream, padded))
+            return cyc::launch_trsm_padded(L, B, X, Xh, n, nrhs, nb, w, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
     void *workspace = nullptr;
     const int64_t need = cyc::trsm_workspace_bytes(L, X, Xh, n, nrhs, nb);
     if (need > 0) {
@@ -270,6 +273,9 @@ int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t
     if (((uintptr_t)A | (uintptr_t)L) & 3 || ((uintptr_t)Lh & 1)) return CYC_ERR_SHAPE;
     if (overlaps(L, nn * 4, A, nn * 4) || overlaps(Lh, nn * 2, A, nn * 4) || overlaps(L, nn * 4, Lh, nn * 2)) return CYC_ERR_ALIAS;
     cyc::WorkspaceHold hold;
+    if (const int64_t padded = cyc::chol_padded_bytes(A, L, Lh, n, nb))
+        if (void *w = hold.acquire((hipStream_t)stream, padded))
+            return cyc::launch_chol_padded(A, L, Lh, n, nb, w, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
     void *workspace = nullptr;
     const int64_t need = cyc::chol_workspace_bytes(n, nb);
     if (need > 0) {

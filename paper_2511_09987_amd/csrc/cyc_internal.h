@@ -115,6 +115,13 @@ int wait_limit();
 int64_t trsm_workspace_bytes(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb);
 hipError_t launch_trsm(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb, void *workspace,
                        hipStream_t s);
+// Problems whose rows are not 16-byte aligned miss the kernels that work through inverses of the diagonal tiles.  They are
+// solved in copies with rows (and, for the triangle, columns) filled up to a multiple of 8 by those of the identity.
+// *_padded_bytes: device memory for the copies and for the solve itself, 0 where the direct way is taken.
+int64_t trsm_padded_bytes(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb);
+hipError_t launch_trsm_padded(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb, void *workspace, hipStream_t s);
+int64_t chol_padded_bytes(const void *A, void *L, void *Lh, int64_t n, int64_t nb);
+hipError_t launch_chol_padded(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, hipStream_t s);
 // tiled Cholesky factorisation A = L L^T in tiles of nb (see cyc_chol.hip); arguments validated by the caller
 // workspace: chol_workspace_bytes() bytes of device memory (inverses of the diagonal tiles), or nullptr: no inverses
 int64_t chol_workspace_bytes(int64_t n, int64_t nb);
