@@ -26,7 +26,7 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
     return a < b + (uintptr_t)qbytes && b < a + (uintptr_t)pbytes;
 }
 
-enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_SMALL, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM, K_NARROWM_BLOCKS };
+enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_SMALL, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROW_BLOCKS, K_NARROWM, K_NARROWM_BLOCKS };
 
 const char *kernel_label(Kernel k)
 {
@@ -39,7 +39,7 @@ const char *kernel_label(Kernel k)
         case K_MFMA256X32: return "mfma256x32";
         case K_MFMA128X32: return "mfma128x32";
         case K_MFMAK: return "mfmak";
-        case K_NARROW: return "narrow";
+        case K_NARROW: case K_NARROW_BLOCKS: return "narrow";
         case K_NARROWM: case K_NARROWM_BLOCKS: return "narrowm";
     }
     return "none";
@@ -113,15 +113,23 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         case K_MFMAK: if (cyc::choose_ksplit(*p, &ktile) > 1) { *k = force; return CYC_OK; } break;
         default: break;
     }
-    if (cyc::prefers_narrow(*p)) { *k = K_NARROW; return CYC_OK; }
+    if (cyc::prefers_narrow(*p)) {
+        // Its workgroups keep all of B in registers, which they fill before they stream: up to 512 blocks of 32 rows with eight
+        // teams along k are done before that has paid (bf16, microseconds there / in blocks: 4096 x 2048 x 8 18.8 / 9.3,
+        // 4100 x 1024 x 3 15.1 / 9.6, 4 x 4096 x 3000 x 16 23.9 / 21.6, i8 2 x 8192 x 8192 x 16 26.0 / 25.5); with more blocks (i8
+        // 8 x 4096 x 4096 x 1 33.6 / 36.0) and past 128 MiB of A (2 x 8192 x 8192 x 16 48.7 / 49.7) it streams better
+        const int64_t blocks = p->batch * ((p->M + 31) / 32), bytes = p->batch * mk * es;
+        *k = force == K_NONE && blocks <= 512 && bytes <= (128 << 20) && cyc::supports_uneven(*p) ? K_NARROW_BLOCKS : K_NARROW;
+        return CYC_OK;
+    }
     if (cyc::prefers_narrowm(*p)) {
-        // Its workgroups each stream 1024 columns, or 128 of them in eight k-slices: up to 512 blocks of 32 columns, with eight
-        // teams along k and one to two of them on a compute unit, keep more of the chip reading (bf16, 16 rows, microseconds there /
-        // in blocks: 8192 x 1024 52 / 12, 8192 x 8192 55 / 26, 4 x 2048 x 4096 18 / 16; but 4 x 2048 x 8192 25 / 25, i8 14 / 19),
-        // and past 128 k-tiles k goes to space across workgroups as well (32 x 17280 x 784 144 / 39, k in space 17).
+        // Its workgroups each stream 1024 columns, or 128 of them in eight k-slices: up to 256 blocks of 32 columns, with eight
+        // teams along k and one of them on a compute unit, keep more of the chip reading (bf16, microseconds there / in blocks:
+        // 16 x 8192 x 8192 54 / 37, 20 x 4000 x 1000 32 / 12; with 512, 4 x (16 x 4096 x 4096) 32 / 37), and past 128 k-tiles k
+        // goes to space across workgroups as well (32 x 17280 x 784 144 / 39, k in space 17).
         const int64_t blocks = p->batch * ((p->N + 31) / 32), kt = p->K * es / 128;
         if (force == K_NONE && kt > 128 && p->N <= 4096 && cyc::choose_ksplit(*p, &ktile) > 1) *k = K_MFMAK;
-        else if (force == K_NONE && blocks <= 512 && cyc::supports_uneven(*p)) *k = K_NARROWM_BLOCKS;
+        else if (force == K_NONE && blocks <= 256 && cyc::supports_uneven(*p)) *k = K_NARROWM_BLOCKS;
         else *k = K_NARROWM;
         return CYC_OK;
     }
@@ -157,6 +165,7 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
             break;
         }
         case K_NARROW: e = cyc::launch_narrow(p, s); break;
+        case K_NARROW_BLOCKS: e = cyc::launch_small(p, 32, s); break;
         case K_NARROWM: e = cyc::launch_narrowm(p, s); break;
         case K_NARROWM_BLOCKS: e = cyc::launch_small(p, 32, s); break;
     }
