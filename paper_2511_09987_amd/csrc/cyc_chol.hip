@@ -1219,7 +1219,10 @@ hipError_t launch_chol(const void *A_, void *L_, void *Lh_, int64_t n, int64_t n
         p.N = ncols;
         p.strideA = p.strideB = p.strideC = 0;
         p.i8 = false;
-        return launch_product(p, on);
+        // (a product beside the tile kernels, on the side stream, keeps to blocks of 128 and as few compute units: spread over all
+        // of them in small blocks it was done sooner and held up the chain, 2461 against 2384 us at n = 8192)
+        const int tile = on != s ? choose_mfma_tile(p) : 0;
+        return tile ? launch_mfma(p, tile, 16, on) : launch_product(p, on);
     };
     bool diag_done = false;           // the diagonal tile of this panel was factored by the rows kernel of the panel before
     int64_t prepared_from = -1;       // >= 0: the launch before took the k range [k0, prepared_from) out of this launch's first workgroup's tiles
