@@ -1,6 +1,7 @@
 // cyc_uneven.hip -- the weight-stationary recurrence on the matrix cores for operands whose rows start at any byte:
 // odd extents, windows at odd columns, unaligned pointers (what cyc_mfma.hip, whose copies go straight from global
-// memory to LDS in aligned 16-byte pieces, does not take).
+// memory to LDS in aligned 16-byte pieces, does not take).  Its small blocks also serve aligned operands (choose_small_block
+// below, and the rules for few rows and few columns in cyc_api.hip).
 //
 // Same mapping and same byte geometry as cyc_mfma.hip: a k-tile is 128 bytes of a row of A (64 bf16 or 128 int8),
 // cut into eight 16-byte chunks; the partial sums are the MFMA accumulators.  What differs is the way into LDS: a chunk
@@ -10,7 +11,7 @@
 // What bounds it: the address unit.  A wave-wide load of 64 chunks at 2-byte addresses occupies it for about 34 cycles
 // (4-byte addresses 26, the aligned copies of cyc_mfma.hip 16), and a k-tile of a 96 x 128 block, 384 cycles of
 // MFMAs, takes 28 of them; fetching two k-tiles ahead instead of one, or placing the writes elsewhere among the MFMAs, changed
-// nothing (112 - 116 us at 3001 x 2999 x 3003 bf16).  That size took 1352 us on the vector ALU and takes 112 (480 TFLOP/s);
+// nothing (112 - 116 us at 3001 x 2999 x 3003 bf16).  That size took 1352 us on the vector ALU and takes 94 (576 TFLOP/s);
 // int8 69; 74 x 787 x 27 took 104 us and takes 9, which is a launch.
 //
 // No load leaves the operands.  Rows past M re-read row M-1 and chunks wholly past N the last chunk that has a
