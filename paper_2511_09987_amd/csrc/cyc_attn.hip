@@ -167,37 +167,31 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE >= 4 ? 2 : 1) void attn_kernel(co
     }
 
     // ---- copies of a tile of K or of V into a stage.  A copy moves RPC rows (1 KiB); copy x of wave w takes the rows
-    // x*NWAVE*RPC + w*RPC .. of the tile.  The swizzles repeat every 16 rows, that is every PERIOD copies, and a lane's
-    // offset within copy x (from that copy's first byte) with them.  Keys past M (last tile only) re-read key M-1 and are
-    // masked below.
-    constexpr int PERIOD = NWAVE * RPC >= 16 ? 1 : 16 / (NWAVE * RPC);
-    static_assert(NWAVE * RPC * PERIOD % 16 == 0 && COPIES % PERIOD == 0, "copies must come in whole periods of the swizzle");
+    // x*NWAVE*RPC + w*RPC .. of the tile.  The swizzles repeat every 16 rows and are linear in the bits of the row, so a lane's
+    // offset within copy x (from that copy's first byte) is the one within copy 0, its chunk bits flipped by a constant that
+    // is 0 where NWAVE*RPC is a multiple of 16.  Keys past M (last tile only) re-read key M-1 and are masked below.
     const int row0 = w * RPC + l / CPR;                             // this lane's row within copy 0
-    uint32_t voffK[PERIOD], voffV[PERIOD];
-#pragma unroll
-    for (int x = 0; x < PERIOD; ++x) {
-        voffK[x] = (uint32_t)row0 * ROW + (((l % CPR) ^ swzK(x * (NWAVE * RPC) + row0)) << 4);
-        voffV[x] = (uint32_t)row0 * ROW + (((l % CPR) ^ swzV(x * (NWAVE * RPC) + row0)) << 4);
-    }
+    const uint32_t voffK = (uint32_t)row0 * ROW + (((l % CPR) ^ swzK(row0)) << 4);
+    const uint32_t voffV = (uint32_t)row0 * ROW + (((l % CPR) ^ swzV(row0)) << 4);
     const int ntiles = (M + KT - 1) / KT;
-    auto issue = [&](const char *src, const uint32_t(&voff)[PERIOD], int tile, int stage_index) __attribute__((always_inline)) {
+    auto issue = [&](const char *src, uint32_t voff, auto swz, int tile, int stage_index) __attribute__((always_inline)) {
         const char *base = src + (int64_t)tile * TILE_BYTES;
         const uint32_t dst = lds_base + stage_index * TILE_BYTES + w * 1024;
         if ((tile + 1) * KT <= M) {
 #pragma unroll
-            for (int x = 0; x < COPIES; ++x) copy16(base + x * (NWAVE * 1024), voff[x % PERIOD], dst + x * (NWAVE * 1024));
+            for (int x = 0; x < COPIES; ++x) copy16(base + x * (NWAVE * 1024), voff ^ (uint32_t)(swz(x * (NWAVE * RPC)) << 4), dst + x * (NWAVE * 1024));
         } else {
             const int last = M - 1 - tile * KT;                   // last valid row of the tile
 #pragma unroll
             for (int x = 0; x < COPIES; ++x) {
                 const int r = x * (NWAVE * RPC) + row0;
                 // offsets are unsigned: row min(r, last) counted from the tile's first row, this lane's chunk
-                copy16(base, (uint32_t)(r <= last ? r : last) * ROW + (voff[x % PERIOD] - (uint32_t)row0 * ROW), dst + x * (NWAVE * 1024));
+                copy16(base, (uint32_t)(r <= last ? r : last) * ROW + ((voff ^ (uint32_t)(swz(r - row0) << 4)) - (uint32_t)row0 * ROW), dst + x * (NWAVE * 1024));
             }
         }
     };
-    auto issue_K = [&](int tile) __attribute__((always_inline)) { issue(K, voffK, tile, tile & 1); };
-    auto issue_V = [&](int tile) __attribute__((always_inline)) { issue(V, voffV, tile, 2 + (tile & 1)); };
+    auto issue_K = [&](int tile) __attribute__((always_inline)) { issue(K, voffK, swzK, tile, tile & 1); };
+    auto issue_V = [&](int tile) __attribute__((always_inline)) { issue(V, voffV, swzV, tile, 2 + (tile & 1)); };
 
     // ---- running state of this lane's queries (one per 16-query block jq): maximum in the log2 domain, this lane's
     // share of the sum, and O^T accumulators [d tile][query tile]
