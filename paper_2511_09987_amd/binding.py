@@ -295,13 +295,17 @@ def recurrence_attention(Q, K, V, out=None, stream=None):
         raise ValueError("out has the wrong shape, dtype, layout or device")
     s = _stream_handle(Q, stream)
     # The library splits no key list below 512.  The workspace comes from the allocator's pool of the stream that the call
-    # runs on, and goes back to it: whoever gets it next is ordered after this call.
+    # runs on, and goes back to it: whoever gets it next is ordered after this call.  Without it the call is only slower.
     wanted, work = cyc_attention_workspace(batch, N, M, d) if M >= 512 else 0, None
-    if wanted and stream is None:
-        work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
-    elif wanted and isinstance(stream, torch.cuda.Stream) and stream.device == Q.device:
-        with torch.cuda.stream(stream):
-            work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
+    if wanted:
+        try:
+            if stream is None:
+                work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
+            elif isinstance(stream, torch.cuda.Stream) and stream.device == Q.device:
+                with torch.cuda.stream(stream):
+                    work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
+        except torch.OutOfMemoryError:
+            pass
     if work is None:
         st = cyc_recurrence_attention(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), batch, N, M, d, s)
     else:
