@@ -210,6 +210,23 @@ def test_keys_in_runs(lib, attn, batch, N, M, d):
         check(whole[b], ref, f64(V[b]))
 
 
+@pytest.mark.parametrize("batch,N,M,d", [(64, 1, 4000, 128), (3, 33, 2049, 64), (1, 300, 4096, 128), (5, 16, 700, 64)])
+def test_runs_round_their_weights_as_the_whole_list_does(lib, batch, N, M, d):
+    """All runs start from the reference of the list's first tile, so splitting changes the order of the fp32 sums and nothing
+    else: M/32 instructions of at most 32 additions each and a join, every addition within 2^-24 of the sum of magnitudes."""
+    Q, K, V = (ws_inputs.normal_bf16((batch, n, d), 1.0, 60 + N, i, DEV) for i, n in enumerate((N, M, M)))
+    assert lib.cyc_attention_workspace(batch, N, M, d) > 0
+    O = lib.recurrence_attention(Q, K, V)
+
+    def unsplit(values):
+        out = torch.empty_like(O)
+        assert lib.cyc_recurrence_attention(Q.data_ptr(), K.data_ptr(), values.data_ptr(), out.data_ptr(), batch, N, M, d,
+                                            torch.cuda.current_stream().cuda_stream) == 0
+        return out
+    bound = 2.0 * (M / 32 + 64) * 2.0 ** -24 * unsplit(V.abs()).double()
+    assert bool(((O.double() - unsplit(V).double()).abs() <= bound).all())
+
+
 def test_runs_without_weight_and_runs_with_nan(lib):
     """Scores of -inf in whole runs weigh nothing; a NaN or infinite score spoils its query."""
     M, d = 4096, 128
