@@ -231,7 +231,8 @@ int cyc_recurrence_attention(const void *Q, const void *K, const void *V, void *
  * second kernel.  cyc_attention_workspace says how many bytes such a call wants (0: it would not split; host only,
  * also 0 for arguments that the call refuses).  With less, or with workspace NULL, the keys are not split, as in
  * cyc_recurrence_attention.  The result is the same on every call with the same arguments; how the keys are split depends
- * on batch, N, M and d, and with it the last bits of O.  Errors: those of cyc_recurrence_attention; CYC_ERR_SHAPE
+ * on batch, N, M and d alone, and with it the last bits of O: all runs take their weights against the reference of the first
+ * tile of keys, as the unsplit list does, and the order of the fp32 sums differs.  Errors: those of cyc_recurrence_attention; CYC_ERR_SHAPE
  * also for a misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
 int64_t cyc_attention_workspace(int64_t batch, int64_t N, int64_t M, int64_t d);
 int cyc_recurrence_attention_split(const void *Q, const void *K, const void *V, void *O, int64_t batch, int64_t N, int64_t M,

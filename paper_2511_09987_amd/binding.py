@@ -295,7 +295,8 @@ def recurrence_attention(Q, K, V, out=None, stream=None):
         raise ValueError("out has the wrong shape, dtype, layout or device")
     s = _stream_handle(Q, stream)
     # The library splits no key list below 512.  The workspace comes from the allocator's pool of the stream that the call
-    # runs on, and goes back to it: whoever gets it next is ordered after this call.  Without it the call is only slower.
+    # runs on, and goes back to it: whoever gets it next is ordered after this call.  Where there is
+    # none to be had the keys are not split, which is slower and adds the fp32 sums in another order.
     wanted, work = cyc_attention_workspace(batch, N, M, d) if M >= 512 else 0, None
     if wanted:
         try:

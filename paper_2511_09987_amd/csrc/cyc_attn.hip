@@ -518,7 +518,7 @@ int64_t part_bytes(int64_t batch, int64_t N, int64_t d, int64_t splits) { return
 //   40, 2000, 2000, 128    8/1: 118  4/1: 96   2/1: 128  4/2: 118
 // A query's result does not depend on the waves per workgroup, only on the runs.  Below 512 keys there is nothing to gain
 // from runs, and partial outputs end at 64 MiB.
-Mapping choose_mapping(int64_t batch, int64_t N, int64_t M, int64_t d, int64_t workspace_bytes)
+Mapping choose_mapping(int64_t batch, int64_t N, int64_t M, int64_t d, bool runs)
 {
     constexpr int64_t one128[4] = {1280, 1180, 1050, 1850}, two128[4] = {1550, 1650, 1870, 0};
     constexpr int64_t one64[4] = {1550, 1400, 1550, 2200}, two64[4] = {1700, 1800, 2500, 0};
@@ -526,9 +526,9 @@ Mapping choose_mapping(int64_t batch, int64_t N, int64_t M, int64_t d, int64_t w
     const int64_t *one = d == 128 ? one128 : one64, *two = d == 128 ? two128 : two64;
     Mapping best = {8, 1, (int)(ntiles * kt)};
     int64_t best_cost = INT64_MAX;
-    for (int64_t want = 1; want == 1 || (M >= 512 && want * 2 <= ntiles && want <= 256); want *= 2) {
+    for (int64_t want = 1; want == 1 || (runs && M >= 512 && want * 2 <= ntiles && want <= 256); want *= 2) {
         const int64_t tiles = (ntiles + want - 1) / want, splits = (ntiles + tiles - 1) / tiles, part = part_bytes(batch, N, d, splits);
-        if (splits > 1 && (part > workspace_bytes || part > (64 << 20))) break;
+        if (splits > 1 && part > (64 << 20)) break;
         for (int i = 3; i >= 0; --i) {                   // (eight waves first: the fewest reads of K and V among equals)
             const int64_t groups = (N + 32 * (1 << i) - 1) / (32 * (1 << i)) * batch * splits;
             int64_t cost;
@@ -585,7 +585,7 @@ hipError_t launch_head(const void *Q, const void *K, const void *V, void *O, int
 
 int64_t attention_workspace_bytes(int64_t batch, int64_t N, int64_t M, int64_t d)
 {
-    const Mapping m = choose_mapping(batch, N, M, d, (int64_t)1 << 62);
+    const Mapping m = choose_mapping(batch, N, M, d, true);
     return m.splits > 1 ? part_bytes(batch, N, d, m.splits) : 0;
 }
 
@@ -593,7 +593,9 @@ hipError_t launch_attention(const void *Q, const void *K, const void *V, void *O
                             int64_t d, void *workspace, int64_t workspace_bytes, hipStream_t s)
 {
     if (!supports_attention(N, M, d) || batch < 1 || batch > 65535) return hipErrorInvalidValue;
-    const Mapping m = choose_mapping(batch, N, M, d, workspace ? workspace_bytes : 0);
+    // two outcomes only: the runs that the extents ask for, or none where the memory for those is not there
+    const int64_t wanted = attention_workspace_bytes(batch, N, M, d);
+    const Mapping m = choose_mapping(batch, N, M, d, wanted > 0 && workspace && workspace_bytes >= wanted);
     return d == 128 ? launch_head<128, 64>(Q, K, V, O, batch, N, M, m, (float *)workspace, s)
                     : launch_head<64, 128>(Q, K, V, O, batch, N, M, m, (float *)workspace, s);
 }

@@ -227,6 +227,26 @@ def test_runs_round_their_weights_as_the_whole_list_does(lib, batch, N, M, d):
     assert bool(((O.double() - unsplit(V).double()).abs() <= bound).all())
 
 
+def test_a_workspace_too_small_for_the_runs_is_none(lib):
+    """The bits depend on whether the memory for the runs is there, not on how much of it; nothing past the workspace is touched."""
+    batch, N, M, d = 64, 1, 4000, 128
+    Q, K, V = (ws_inputs.normal_bf16((batch, n, d), 1.0, 70, i, DEV) for i, n in enumerate((N, M, M)))
+    wanted = lib.cyc_attention_workspace(batch, N, M, d)
+    around = torch.empty(wanted + 4096, dtype=torch.uint8, device=DEV)
+
+    def run(size):
+        around.fill_(77)
+        out = torch.empty((batch, N, d), device=DEV)
+        assert lib.cyc_recurrence_attention_split(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), batch, N, M, d, around.data_ptr(),
+                                                  size, torch.cuda.current_stream().cuda_stream) == 0
+        assert bool((around[size:] == 77).all())
+        return out
+    split, whole = run(wanted), run(0)
+    assert torch.equal(split, lib.recurrence_attention(Q, K, V)) and not torch.equal(split, whole)
+    for size in (wanted - 1, wanted // 2, wanted // 4, 16):
+        assert torch.equal(run(size), whole)
+
+
 def test_runs_without_weight_and_runs_with_nan(lib):
     """Scores of -inf in whole runs weigh nothing; a NaN or infinite score spoils its query."""
     M, d = 4096, 128
