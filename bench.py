@@ -123,8 +123,8 @@ def make_step(lib, torch, kind, w, sets):
             cshape = (w.batch, w.M, w.N) if w.batch > 1 else (w.M, w.N)
             data.append((A, B, torch.empty(cshape, dtype=torch.int32 if w.dtype == "i8" else torch.float32, device=DEV)))
         A, B, C = data[0]
-        info["kernel"] = lib.cyc_kernel_name(A.data_ptr(), B.data_ptr(), C.data_ptr(), w.batch, w.M, w.K, w.N,
-                                             w.M * w.K, w.K * w.N, w.M * w.N, dt)
+        info["kernel"] = lib.cyc_kernel_variant(A.data_ptr(), B.data_ptr(), C.data_ptr(), w.batch, w.M, w.K, w.N,
+                                                w.M * w.K, w.K * w.N, w.M * w.N, dt)
 
         def call(a, b, c):
             return lib.cyc_recurrence_matmul_batched(a.data_ptr(), b.data_ptr(), c.data_ptr(), w.batch, w.M, w.K, w.N,

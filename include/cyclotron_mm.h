@@ -68,16 +68,18 @@
  * rate.
  *
  * Kernel families and when the dispatcher picks them:
- *   narrow   N <= 16, many rows: A streamed once from memory, B resident.
+ *   narrow   N <= 16, many rows: A streamed once from memory, B resident; up to 512 blocks of 32 rows in those blocks.
  *   narrowm  M <= 32, B of at least a mebibyte: B streamed once, the rows of
- *            A pass over it ((j,k) in space).  (Long k and few columns: mfmak.)
+ *            A pass over it ((j,k) in space); few column blocks and long k in blocks of 32 x 32.  (Long k and few
+ *            columns: mfmak.)
  *   mfmak    unbatched, at most 64 output blocks of 128 x 128, K >= 4096: k in
  *            space; k-slices on different workgroups leave partial sums in the
  *            workspace and a second kernel adds them in ascending slice order.
  *   mfma256 / mfma128  everything else with aligned rows (mfma128: blocks of 128 x 128 or, where those are few, of
  *            64 x 64 or 32 x 32).
- *   generic  the rest: rows at any address, on the matrix cores when K and N are at
- *            least 16 bytes long, off them otherwise (and when forced).
+ *   generic  the rest: rows at any address, on the matrix cores (blocks of 256 x 128, 96 x 128, 64 x 64 or 32 x 32)
+ *            when K and N are at least 16 bytes long, or K is a multiple of 16 bytes and longer than 128; off them
+ *            otherwise, with more than 65535 batch elements, and when forced.
  */
 #ifndef CYCLOTRON_MM_H
 #define CYCLOTRON_MM_H
@@ -244,15 +246,22 @@ const char *cyc_status_string(int status);
 /* Library version: major*10000 + minor*100 + patch. */
 int cyc_version(void);
 
-/* Name of the kernel family the dispatcher would pick for this problem
- * ("mfma256", "mfma128", "mfmak", "narrow", "narrowm", "generic", "zero", "none", or the forced one); static storage.
+/* Name of the kernel family whose part of the dispatch this problem falls into
+ * ("mfma256", "mfma128", "mfmak", "narrow", "narrowm", "generic", "zero", "none", or the forced kernel); static storage.
  * Host only; enqueues nothing.  Pointers are only inspected for alignment. */
 const char *cyc_kernel_name(const void *A, const void *B, const void *C,
                             int64_t batch, int64_t M, int64_t K, int64_t N,
                             int64_t strideA, int64_t strideB, int64_t strideC, int dtype);
 
-/* Testing and benchmarking aid: from now on, in every thread, use the named kernel family (generic | mfma256 |
- * mfma128 | mfma256x32 | mfma128x32 | mfmak | narrow | narrowm) wherever it supports the problem; NULL or "" gives the
+/* The same for the kernel that runs: in the families mfma128, narrow, narrowm and generic that may be one with blocks of
+ * 256 x 128, 96 x 128, 64 x 64 or 32 x 32 that takes rows at any address ("uneven256", "uneven96", "uneven64",
+ * "uneven32").  Forcing the name that this returns gives the bits that the dispatcher's own choice gives. */
+const char *cyc_kernel_variant(const void *A, const void *B, const void *C,
+                               int64_t batch, int64_t M, int64_t K, int64_t N,
+                               int64_t strideA, int64_t strideB, int64_t strideC, int dtype);
+
+/* Testing and benchmarking aid: from now on, in every thread, use the named kernel (generic | uneven256 | uneven96 |
+ * uneven64 | uneven32 | mfma256 | mfma128 | mfma256x32 | mfma128x32 | mfmak | narrow | narrowm) wherever it supports the problem; NULL or "" gives the
  * choice back to the dispatcher.  The x32 kernels use the 32x32 MFMA shape instead of the 16x16 one; the dispatcher
  * never picks them by itself.  The environment variable CYC_FORCE_KERNEL, read once when the library first chooses
  * a kernel, supplies the initial value.  Returns CYC_ERR_SHAPE for an unknown name. */

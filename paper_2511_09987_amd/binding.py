@@ -48,6 +48,8 @@ def _load() -> ctypes.CDLL:
     lib.cyc_version.restype = cint
     lib.cyc_kernel_name.argtypes = [ptr, ptr, ptr, i64, i64, i64, i64, i64, i64, i64, cint]
     lib.cyc_kernel_name.restype = ctypes.c_char_p
+    lib.cyc_kernel_variant.argtypes = lib.cyc_kernel_name.argtypes
+    lib.cyc_kernel_variant.restype = ctypes.c_char_p
     lib.cyc_force_kernel.argtypes = [ctypes.c_char_p]
     lib.cyc_force_kernel.restype = cint
     lib.cyc_diag_mfma_ceiling.argtypes = [cint, cint, i64, ptr, ctypes.POINTER(ctypes.c_double), ptr]
@@ -141,8 +143,14 @@ def cyc_kernel_name(A: int, B: int, C: int, batch: int, M: int, K: int, N: int,
     return _lib().cyc_kernel_name(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype).decode()
 
 
+def cyc_kernel_variant(A: int, B: int, C: int, batch: int, M: int, K: int, N: int,
+                       strideA: int, strideB: int, strideC: int, dtype: int) -> str:
+    """The kernel that runs, where cyc_kernel_name says whose part of the dispatch the problem falls into."""
+    return _lib().cyc_kernel_variant(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype).decode()
+
+
 def cyc_force_kernel(name) -> int:
-    """Force a kernel family by name (None or "": back to the dispatcher); returns the cyc_status."""
+    """Force a kernel by name (None or "": back to the dispatcher); returns the cyc_status."""
     return int(_lib().cyc_force_kernel((name or "").encode()))
 
 

@@ -26,31 +26,38 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
     return a < b + (uintptr_t)qbytes && b < a + (uintptr_t)pbytes;
 }
 
-enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN, K_MFMA256, K_MFMA128, K_SMALL, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROW_BLOCKS, K_NARROWM, K_NARROWM_BLOCKS };
+enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
 
 const char *kernel_label(Kernel k)
 {
     switch (k) {
         case K_NONE: return "none";
         case K_ZERO: return "zero";
-        case K_GENERIC: case K_UNEVEN: return "generic";   // one family: any alignment, on the matrix cores or (forced, tiny extents) off them
+        case K_GENERIC: return "generic";
+        case K_UNEVEN256: return "uneven256";
+        case K_UNEVEN96: return "uneven96";
+        case K_UNEVEN64: return "uneven64";
+        case K_UNEVEN32: return "uneven32";
         case K_MFMA256: return "mfma256";
-        case K_MFMA128: case K_SMALL: return "mfma128";
+        case K_MFMA128: return "mfma128";
         case K_MFMA256X32: return "mfma256x32";
         case K_MFMA128X32: return "mfma128x32";
         case K_MFMAK: return "mfmak";
-        case K_NARROW: case K_NARROW_BLOCKS: return "narrow";
-        case K_NARROWM: case K_NARROWM_BLOCKS: return "narrowm";
+        case K_NARROW: return "narrow";
+        case K_NARROWM: return "narrowm";
     }
     return "none";
 }
+
+Kernel uneven_kernel(int block) { return block == 256 ? K_UNEVEN256 : block == 96 ? K_UNEVEN96 : block == 64 ? K_UNEVEN64 : K_UNEVEN32; }
+int uneven_block(Kernel k) { return k == K_UNEVEN256 ? 256 : k == K_UNEVEN96 ? 96 : k == K_UNEVEN64 ? 64 : 32; }
 
 // The kernel forced by cyc_force_kernel(), or by the environment variable CYC_FORCE_KERNEL, which is read once
 // (at the first call that gets as far as choosing a kernel) as the initial value.  K_NONE: the dispatcher decides.
 Kernel kernel_by_name(const char *name)
 {
     if (!name) return K_NONE;
-    for (Kernel k : {K_GENERIC, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM})
+    for (Kernel k : {K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM})
         if (!std::strcmp(name, kernel_label(k))) return k;
     return K_NONE;
 }
@@ -66,11 +73,12 @@ std::atomic<int> &wait_limit_value()
     return v;
 }
 
-// Validates and fills `p`.  Returns CYC_OK with *k == K_NONE when there is nothing to do.
+// Validates and fills `p`.  Returns CYC_OK with *k == K_NONE when there is nothing to do.  *family: the kernel whose part of
+// the dispatch the problem falls into; *k: the kernel that runs (blocks of cyc_uneven.hip stand in for several families).
 int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, int64_t K, int64_t N,
-         int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k)
+         int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k, Kernel *family)
 {
-    *k = K_NONE;
+    *k = *family = K_NONE;
     if (dtype != CYC_BF16_F32 && dtype != CYC_I8_I32) return CYC_ERR_DTYPE;
     if (batch < 0 || M < 0 || K < 0 || N < 0 || strideA < 0 || strideB < 0 || strideC < 0) return CYC_ERR_SHAPE;
     int64_t mk, kn, mn;
@@ -98,19 +106,21 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     p->strideA = strideA; p->strideB = strideB; p->strideC = strideC;
     p->i8 = i8;
 
-    if (K == 0) { *k = K_ZERO; return CYC_OK; }
+    auto take = [&](Kernel f, Kernel kernel) { *family = f; *k = kernel; return CYC_OK; };
+    if (K == 0) return take(K_ZERO, K_ZERO);
 
     // a forced kernel overrides the heuristic when it supports the problem (testing and benchmarking aid).  The x32
     // names are the MFMA kernels built on the 32x32 instruction shape, which the dispatcher never picks by itself.
     const Kernel force = (Kernel)forced_kernel().load(std::memory_order_relaxed);
     int ktile = 0;
     switch (force) {
-        case K_GENERIC: *k = K_GENERIC; return CYC_OK;
-        case K_MFMA256: case K_MFMA256X32: if (cyc::supports_mfma(*p, 256)) { *k = force; return CYC_OK; } break;
-        case K_MFMA128: case K_MFMA128X32: if (cyc::supports_mfma(*p, 128)) { *k = force; return CYC_OK; } break;
-        case K_NARROW: if (cyc::supports_narrow(*p)) { *k = force; return CYC_OK; } break;
-        case K_NARROWM: if (cyc::supports_narrowm(*p)) { *k = force; return CYC_OK; } break;
-        case K_MFMAK: if (cyc::choose_ksplit(*p, &ktile) > 1) { *k = force; return CYC_OK; } break;
+        case K_GENERIC: return take(force, force);
+        case K_UNEVEN256: case K_UNEVEN96: case K_UNEVEN64: case K_UNEVEN32: if (cyc::supports_uneven(*p)) return take(force, force); break;
+        case K_MFMA256: case K_MFMA256X32: if (cyc::supports_mfma(*p, 256)) return take(force, force); break;
+        case K_MFMA128: case K_MFMA128X32: if (cyc::supports_mfma(*p, 128)) return take(force, force); break;
+        case K_NARROW: if (cyc::supports_narrow(*p)) return take(force, force); break;
+        case K_NARROWM: if (cyc::supports_narrowm(*p)) return take(force, force); break;
+        case K_MFMAK: if (cyc::choose_ksplit(*p, &ktile) > 1) return take(force, force); break;
         default: break;
     }
     if (cyc::prefers_narrow(*p)) {
@@ -119,8 +129,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         // 4100 x 1024 x 3 15.1 / 9.6, 4 x 4096 x 3000 x 16 23.9 / 21.6, i8 2 x 8192 x 8192 x 16 26.0 / 25.5); with more blocks (i8
         // 8 x 4096 x 4096 x 1 33.6 / 36.0) and past 128 MiB of A (2 x 8192 x 8192 x 16 48.7 / 49.7) it streams better
         const int64_t blocks = p->batch * ((p->M + 31) / 32), bytes = p->batch * mk * es;
-        *k = force == K_NONE && blocks <= 512 && bytes <= (128 << 20) && cyc::supports_uneven(*p) ? K_NARROW_BLOCKS : K_NARROW;
-        return CYC_OK;
+        return take(K_NARROW, force == K_NONE && blocks <= 512 && bytes <= (128 << 20) && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROW);
     }
     if (cyc::prefers_narrowm(*p)) {
         // Its workgroups each stream 1024 columns, or 128 of them in eight k-slices: up to 256 blocks of 32 columns, with eight
@@ -128,20 +137,19 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         // 16 x 8192 x 8192 54 / 37, 20 x 4000 x 1000 32 / 12; with 512, 4 x (16 x 4096 x 4096) 32 / 37), and past 128 k-tiles k
         // goes to space across workgroups as well (32 x 17280 x 784 144 / 39, k in space 17).
         const int64_t blocks = p->batch * ((p->N + 31) / 32), kt = p->K * es / 128;
-        if (force == K_NONE && kt > 128 && p->N <= 4096 && cyc::choose_ksplit(*p, &ktile) > 1) *k = K_MFMAK;
-        else if (force == K_NONE && blocks <= 256 && cyc::supports_uneven(*p)) *k = K_NARROWM_BLOCKS;
-        else *k = K_NARROWM;
-        return CYC_OK;
+        if (force == K_NONE && kt > 128 && p->N <= 4096 && cyc::choose_ksplit(*p, &ktile) > 1) return take(K_MFMAK, K_MFMAK);
+        return take(K_NARROWM, force == K_NONE && blocks <= 256 && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROWM);
     }
     // few output blocks, long k: k goes to space (see choose_ksplit)
-    if (force == K_NONE && cyc::choose_ksplit(*p, &ktile) > 1) { *k = K_MFMAK; return CYC_OK; }
+    if (force == K_NONE && cyc::choose_ksplit(*p, &ktile) > 1) return take(K_MFMAK, K_MFMAK);
     // MFMA kernels for everything with 16-byte aligned rows except slivers
     const int tile = cyc::choose_mfma_tile(*p);
-    if (force == K_NONE && tile == 128 && cyc::choose_small_block(*p)) { *k = K_SMALL; return CYC_OK; }
-    if (tile == 256) { *k = K_MFMA256; return CYC_OK; }
-    if (tile == 128) { *k = K_MFMA128; return CYC_OK; }
-    *k = cyc::supports_uneven(*p) ? K_UNEVEN : K_GENERIC;
-    return CYC_OK;
+    if (tile == 256) return take(K_MFMA256, K_MFMA256);
+    if (tile == 128) {
+        const int block = force == K_NONE ? cyc::choose_small_block(*p) : 0;
+        return take(K_MFMA128, block ? uneven_kernel(block) : K_MFMA128);
+    }
+    return take(K_GENERIC, cyc::supports_uneven(*p) ? uneven_kernel(cyc::choose_uneven_block(*p)) : K_GENERIC);
 }
 
 int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
@@ -151,10 +159,9 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
         case K_NONE: return CYC_OK;
         case K_ZERO: e = cyc::launch_zero(p, s); break;
         case K_GENERIC: e = cyc::launch_generic(p, s); break;
-        case K_UNEVEN: e = cyc::launch_uneven(p, s); break;
+        case K_UNEVEN256: case K_UNEVEN96: case K_UNEVEN64: case K_UNEVEN32: e = cyc::launch_uneven(p, uneven_block(k), s); break;
         case K_MFMA256: e = cyc::launch_mfma(p, 256, 16, s); break;
         case K_MFMA128: e = cyc::launch_mfma(p, 128, 16, s); break;
-        case K_SMALL: e = cyc::launch_small(p, cyc::choose_small_block(p), s); break;
         case K_MFMA256X32: e = cyc::launch_mfma(p, 256, 32, s); break;
         case K_MFMA128X32: e = cyc::launch_mfma(p, 128, 32, s); break;
         case K_MFMAK: {
@@ -165,9 +172,7 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
             break;
         }
         case K_NARROW: e = cyc::launch_narrow(p, s); break;
-        case K_NARROW_BLOCKS: e = cyc::launch_small(p, 32, s); break;
         case K_NARROWM: e = cyc::launch_narrowm(p, s); break;
-        case K_NARROWM_BLOCKS: e = cyc::launch_small(p, 32, s); break;
     }
     return e == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
 }
@@ -194,7 +199,7 @@ int run(const cyc::Problem &p, Kernel k, hipStream_t s, bool fixed_workspace = f
             workspace = hold.acquire(s, need);
             if (!workspace) {                   // no memory, or none to be had under capture: one workgroup per block instead
                 const int t = cyc::choose_mfma_tile(p);
-                k = cyc::prefers_narrowm(p) ? K_NARROWM : t == 256 ? K_MFMA256 : t == 128 ? K_MFMA128 : cyc::supports_uneven(p) ? K_UNEVEN : K_GENERIC;
+                k = cyc::prefers_narrowm(p) ? K_NARROWM : t == 256 ? K_MFMA256 : t == 128 ? K_MFMA128 : cyc::supports_uneven(p) ? uneven_kernel(cyc::choose_uneven_block(p)) : K_GENERIC;
             }
         }
         if (!workspace && k == K_MFMAK) return CYC_ERR_WORKSPACE;
@@ -225,8 +230,8 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C, int64_t
                                   void *stream)
 {
     cyc::Problem p;
-    Kernel k;
-    int st = plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k);
+    Kernel k, family;
+    int st = plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family);
     if (st != CYC_OK || k == K_NONE) return st;      // an error, or nothing to do (p is then not filled in)
     return run(p, k, (hipStream_t)stream);
 }
@@ -241,8 +246,8 @@ int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C, int64_t
                                   void *stream)
 {
     cyc::Problem p;
-    Kernel k;
-    int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k);
+    Kernel k, family;
+    int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family);
     if (st != CYC_OK || k == K_NONE) return st;
     return run(p, k, (hipStream_t)stream, true);
 }
@@ -332,8 +337,17 @@ const char *cyc_kernel_name(const void *A, const void *B, const void *C, int64_t
                             int64_t N, int64_t strideA, int64_t strideB, int64_t strideC, int dtype)
 {
     cyc::Problem p;
-    Kernel k;
-    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k) != CYC_OK) return "none";
+    Kernel k, family;
+    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family) != CYC_OK) return "none";
+    return kernel_label(family);
+}
+
+const char *cyc_kernel_variant(const void *A, const void *B, const void *C, int64_t batch, int64_t M, int64_t K,
+                               int64_t N, int64_t strideA, int64_t strideB, int64_t strideC, int dtype)
+{
+    cyc::Problem p;
+    Kernel k, family;
+    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family) != CYC_OK) return "none";
     return kernel_label(k);
 }
 

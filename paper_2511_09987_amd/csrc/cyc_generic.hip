@@ -2,8 +2,9 @@
 // (paper, "Space-time Mappings of Dataflow Recurrences"): every C_ij is the chain
 // acc <- acc + A_ik * B_kj run in ascending k from 0, exactly as the cell row
 // (i,0..K-1) produces it for time step j.  Used for rows of less
-// than 16 bytes and when forced; every other shape runs on the matrix cores (cyc_uneven.hip for rows
-// at any address, cyc_mfma.hip / cyc_narrow.hip / cyc_narrowm.hip for aligned ones).
+// than 16 bytes (see supports_uneven), for more than 65535 batch elements that no aligned kernel takes, and when forced; every
+// other shape runs on the matrix cores (cyc_uneven.hip for rows at any address, cyc_mfma.hip / cyc_narrow.hip /
+// cyc_narrowm.hip for aligned ones).
 #include "cyc_internal.h"
 
 namespace cyc {

@@ -45,13 +45,13 @@ inline int64_t row_stride_c(const Problem &p) { return p.ldc ? p.ldc : p.N; }
 hipError_t launch_generic(const Problem &p, hipStream_t s);
 // MFMA tiled GEMM for rows at any byte address (see cyc_uneven.hip); requires supports_uneven(p)
 bool supports_uneven(const Problem &p);
-hipError_t launch_uneven(const Problem &p, hipStream_t s);
+int choose_uneven_block(const Problem &p);   // the block (256, 96, 64 or 32 rows) that suits the problem best
+hipError_t launch_uneven(const Problem &p, int block, hipStream_t s);
 // what no aligned kernel takes
-inline hipError_t launch_any_alignment(const Problem &p, hipStream_t s) { return supports_uneven(p) ? launch_uneven(p, s) : launch_generic(p, s); }
+inline hipError_t launch_any_alignment(const Problem &p, hipStream_t s) { return supports_uneven(p) ? launch_uneven(p, choose_uneven_block(p), s) : launch_generic(p, s); }
 // edge (64 or 32) of the small blocks of cyc_uneven.hip that beat blocks of 128 on this problem with aligned rows, 0 if
 // none does
 int choose_small_block(const Problem &p);
-hipError_t launch_small(const Problem &p, int block, hipStream_t s);
 // the updates of the triangular solve and of the Cholesky factorisation: one launch with the blocks that suit the problem
 hipError_t launch_product(const Problem &p, hipStream_t s);
 // fill C with the chain's initial value (K == 0)

@@ -315,18 +315,15 @@ template <class S> hipError_t launch_shape(const Problem &p, hipStream_t s)
                          row_stride_a(p), row_stride_b(p), row_stride_c(p), (const char *)p.Cin);
 }
 
-template <bool I8> hipError_t launch_dtype(const Problem &p, hipStream_t s)
+template <bool I8> hipError_t launch_dtype(const Problem &p, int block, hipStream_t s)
 {
-    // What the rule below weighs, in time per k-tile and round of one workgroup on each of the 256 compute units (10 ns,
-    // bf16, fitted to products of 17 .. 4095 rows and columns; int8 scales all of them by 1.25).  A block of 256 x 128 moves
-    // least per product, smaller ones leave less of the chip idle; at 2047^3 / 1501 x 3001 x 1403 / 1001^3 / 17 x 4001 x 1001 the
-    // four take 47 / 61 / 25 / -, 49 / 41 / 17 / 41, 58 / 51 / 10 / 21 and - / - / 16 / 10 us.
-    auto rounds = [&](int64_t bm, int64_t bn) { return (((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * p.batch + 255) / 256; };
-    const int64_t c256 = 140 * rounds(256, 128), c96 = 78 * rounds(96, 128), c64 = 34 * rounds(64, 64), c32 = 15 * rounds(32, 32);
-    if (c256 <= c96 && c256 <= c64 && c256 <= c32) return launch_shape<Shape<I8, 4, 4, 4, 2, 1>>(p, s);
-    if (c96 <= c64 && c96 <= c32) return launch_shape<Shape<I8, 3, 4, 2, 2, 1>>(p, s);
-    if (c64 <= c32) return launch_shape<Shape<I8, 2, 2, 2, 2, 1>>(p, s);
-    return launch_shape<Shape<I8, 2, 2, 1, 1, 8>>(p, s);
+    switch (block) {
+        case 256: return launch_shape<Shape<I8, 4, 4, 4, 2, 1>>(p, s);
+        case 96: return launch_shape<Shape<I8, 3, 4, 2, 2, 1>>(p, s);
+        case 64: return launch_shape<Shape<I8, 2, 2, 2, 2, 1>>(p, s);
+        case 32: return launch_shape<Shape<I8, 2, 2, 1, 1, 8>>(p, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -348,10 +345,23 @@ bool supports_uneven(const Problem &p)
     return lda * es * 256 + 256 < ((int64_t)1 << 32) && ldb * es * 128 + 256 < ((int64_t)1 << 32);
 }
 
-hipError_t launch_uneven(const Problem &p, hipStream_t s)
+// What the rule weighs, in time per k-tile and round of one workgroup on each of the 256 compute units (10 ns,
+// bf16, fitted to products of 17 .. 4095 rows and columns; int8 scales all of them by 1.25).  A block of 256 x 128 moves
+// least per product, smaller ones leave less of the chip idle; at 2047^3 / 1501 x 3001 x 1403 / 1001^3 / 17 x 4001 x 1001 the
+// four take 47 / 61 / 25 / -, 49 / 41 / 17 / 41, 58 / 51 / 10 / 21 and - / - / 16 / 10 us.
+int choose_uneven_block(const Problem &p)
+{
+    auto rounds = [&](int64_t bm, int64_t bn) { return (((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * p.batch + 255) / 256; };
+    const int64_t c256 = 140 * rounds(256, 128), c96 = 78 * rounds(96, 128), c64 = 34 * rounds(64, 64), c32 = 15 * rounds(32, 32);
+    if (c256 <= c96 && c256 <= c64 && c256 <= c32) return 256;
+    if (c96 <= c64 && c96 <= c32) return 96;
+    return c64 <= c32 ? 64 : 32;
+}
+
+hipError_t launch_uneven(const Problem &p, int block, hipStream_t s)
 {
     if (!supports_uneven(p)) return hipErrorInvalidValue;
-    return p.i8 ? launch_dtype<true>(p, s) : launch_dtype<false>(p, s);
+    return p.i8 ? launch_dtype<true>(p, block, s) : launch_dtype<false>(p, block, s);
 }
 
 // Products with aligned rows and few blocks of 128 x 128 leave most of the chip idle: blocks of 64 x 64, or of 32 x 32 with
@@ -372,18 +382,11 @@ int choose_small_block(const Problem &p)
     return c32 <= c64 ? 32 : 64;
 }
 
-hipError_t launch_small(const Problem &p, int block, hipStream_t s)
-{
-    if (!supports_uneven(p)) return hipErrorInvalidValue;
-    if (block == 64) return p.i8 ? launch_shape<Shape<true, 2, 2, 2, 2, 1>>(p, s) : launch_shape<Shape<false, 2, 2, 2, 2, 1>>(p, s);
-    return p.i8 ? launch_shape<Shape<true, 2, 2, 1, 1, 8>>(p, s) : launch_shape<Shape<false, 2, 2, 1, 1, 8>>(p, s);
-}
-
 hipError_t launch_product(const Problem &p, hipStream_t s)
 {
     const int tile = choose_mfma_tile(p);
     if (tile == 128)
-        if (const int block = choose_small_block(p)) return launch_small(p, block, s);
+        if (const int block = choose_small_block(p)) return launch_uneven(p, block, s);
     return tile ? launch_mfma(p, tile, 16, s) : launch_any_alignment(p, s);
 }
 

@@ -90,6 +90,28 @@ def test_dispatch_table(pkg):
     assert k(A, B, C, 1, 0, 8, 512, 0, 0, 0, 0) == "none"
 
 
+def test_variants_name_the_kernel_that_runs(pkg):
+    """A family's name says whose part of the dispatch a problem falls into; where blocks that take any alignment stand in for
+    that family's kernel, the variant says which, and its name can be forced."""
+    name, variant = pkg.cyc_kernel_name, pkg.cyc_kernel_variant
+    A, B, C = 1 << 32, 2 << 32, 3 << 32
+    blocks = ("uneven256", "uneven96", "uneven64", "uneven32")
+    for args, family in (((1, 512, 512, 512, 0, 0, 0, 0), "mfma128"), ((1, 1000, 1000, 1000, 0, 0, 0, 1), "generic"),
+                         ((1, 2047, 2047, 2047, 0, 0, 0, 0), "generic"), ((1, 4096, 2048, 8, 0, 0, 0, 0), "narrow"),
+                         ((1, 20, 4000, 1000, 0, 0, 0, 0), "narrowm")):
+        assert name(A, B, C, *args) == family and variant(A, B, C, *args) in blocks, args
+    for args, kernel in (((1, 8192, 8192, 8192, 0, 0, 0, 0), "mfma256"), ((1, 17, 33, 5, 0, 0, 0, 0), "generic"), ((70000, 9, 9, 9, 81, 81, 81, 0), "generic"),
+                         ((32, 8192, 8192, 16, 8192 * 8192, 8192 * 16, 8192 * 16, 0), "narrow"), ((1, 512, 16384, 512, 0, 0, 0, 0), "mfmak")):
+        assert name(A, B, C, *args) == variant(A, B, C, *args) == kernel, args
+    try:
+        for block in blocks:
+            assert pkg.cyc_force_kernel(block) == 0
+            assert variant(A, B, C, 1, 512, 512, 512, 0, 0, 0, 0) == name(A + 1, B, C, 1, 999, 999, 999, 0, 0, 0, 1) == block
+            assert variant(A, B, C, 1, 17, 33, 5, 0, 0, 0, 0) == "generic"      # rows below 16 bytes: the dispatcher decides
+    finally:
+        assert pkg.cyc_force_kernel(None) == 0
+
+
 def test_forced_kernel_is_a_setting_of_the_library(pkg):
     """cyc_force_kernel overrides the dispatcher where the named kernel supports the problem, and gives the choice back."""
     k = pkg.cyc_kernel_name

@@ -215,17 +215,17 @@ def test_narrow_kernel(lib, oracle, mode):
 
 @pytest.mark.parametrize("mode", ("i8", "bf16"))
 def test_narrow_all_ones_and_dispatch(lib, mode):
-    """The batched narrow workload picks the streaming kernel by itself; all-ones gives K."""
+    """The batched narrow workload picks the streaming kernel by itself, and blocks of 32 rows where there are few; all-ones
+    gives K."""
     tdt = torch.int8 if mode == "i8" else torch.bfloat16
-    batch, M, K, N = 2, 4096, 8192, 16
-    A = torch.ones((batch, M, K), dtype=tdt, device=DEV)
-    B = torch.ones((batch, K, N), dtype=tdt, device=DEV)
-    C = torch.empty((batch, M, N), dtype=torch.int32 if mode == "i8" else torch.float32, device=DEV)
-    name = lib.cyc_kernel_name(A.data_ptr(), B.data_ptr(), C.data_ptr(), batch, M, K, N, M * K, K * N, M * N,
-                               lib.CYC_I8_I32 if mode == "i8" else lib.CYC_BF16_F32)
-    assert name == "narrow"
-    lib.recurrence_matmul(A, B, out=C)
-    assert bool((C == K).all())
+    for batch, M, K, N, kernel in ((8, 4096, 4096, 16, "narrow"), (2, 4096, 8192, 16, "uneven32")):
+        A = torch.ones((batch, M, K), dtype=tdt, device=DEV)
+        B = torch.ones((batch, K, N), dtype=tdt, device=DEV)
+        C = torch.empty((batch, M, N), dtype=torch.int32 if mode == "i8" else torch.float32, device=DEV)
+        args = (A.data_ptr(), B.data_ptr(), C.data_ptr(), batch, M, K, N, M * K, K * N, M * N, lib.CYC_I8_I32 if mode == "i8" else lib.CYC_BF16_F32)
+        assert lib.cyc_kernel_name(*args) == "narrow" and lib.cyc_kernel_variant(*args) == kernel
+        lib.recurrence_matmul(A, B, out=C)
+        assert bool((C == K).all())
 
 
 # ------------------------------------------------------------ a seeded sweep of shapes

@@ -18,6 +18,7 @@ DEV = "cuda:0"
 # 256 x 128), with k extents around one 16-byte chunk, one k-tile (64 bf16, 128 int8) and one round of eight k-tiles
 EXTENTS = [(1, 16), (33, 17), (31, 65), (64, 33), (1001, 1003), (961, 1025), (1501, 1403), (1345, 1409), (2047, 2049), (1793, 1921)]
 KS = [16, 17, 63, 65, 127, 129, 193]
+BLOCKS = ("uneven256", "uneven96", "uneven64", "uneven32")
 
 
 @pytest.fixture(scope="module")
@@ -38,7 +39,8 @@ def product(lib, mode, A, B, M, K, N, offset):
     keepB, pb = embedded(B, offset, mode)
     C = torch.full((M * N + 32,), -7, dtype=torch.int32 if mode == "i8" else torch.float32, device=DEV)
     dt = lib.CYC_I8_I32 if mode == "i8" else lib.CYC_BF16_F32
-    assert lib.cyc_kernel_name(pa, pb, C.data_ptr(), 1, M, K, N, 0, 0, 0, dt) == "generic"
+    assert lib.cyc_kernel_name(pa, pb, C.data_ptr(), 1, M, K, N, 0, 0, 0, dt) in ("generic",) + BLOCKS
+    assert lib.cyc_kernel_variant(pa, pb, C.data_ptr(), 1, M, K, N, 0, 0, 0, dt) in BLOCKS, "not on the matrix cores"
     assert lib.cyc_recurrence_matmul(pa, pb, C.data_ptr(), M, K, N, dt, torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert torch.all(C[M * N:] == -7)
@@ -57,6 +59,37 @@ def test_any_alignment(lib, oracle, mode, M, N):
             Ah, Bh = torch_bf16_to_bits(A), torch_bf16_to_bits(B)
         C = product(lib, mode, A, B, M, K, N, 1 + n % 3)
         assert np.array_equal(C, oracle.ws_rowchain(Ah, Bh, mode)), (M, K, N)
+
+
+@pytest.mark.parametrize("mode", ("i8", "bf16"))
+@pytest.mark.parametrize("block", BLOCKS)
+def test_every_block_at_its_edges(lib, oracle, mode, block):
+    """Each block shape whatever the dispatcher would choose: one short of, at and one past a block and a pair of blocks."""
+    rows = int(block[6:])
+    cols = {256: 128, 96: 128, 64: 64, 32: 32}[rows]
+    assert lib.cyc_force_kernel(block) == 0
+    try:
+        for n, (M, N, K) in enumerate([(rows - 1, cols + 1, 65), (rows, cols, 128), (rows + 1, cols - 1, 17), (2 * rows + 1, 2 * cols + 1, 129),
+                                       (1, 16, 193), (3 * rows, cols + 3, 1025)]):
+            make = (lambda s, t: ws_inputs.uniform_int(s, 127, 60 + n, t, DEV)) if mode == "i8" else (lambda s, t: ws_inputs.small_int_bf16(s, 8, 60 + n, t, DEV))
+            A, B = make((M, K), 0), make((K, N), 1)
+            h = [t.cpu().numpy() if mode == "i8" else torch_bf16_to_bits(t) for t in (A, B)]
+            assert np.array_equal(product(lib, mode, A, B, M, K, N, n % 4), oracle.ws_rowchain(h[0], h[1], mode)), (M, K, N)
+    finally:
+        assert lib.cyc_force_kernel(None) == 0
+
+
+@pytest.mark.parametrize("shape", [(1, 512, 512, 512), (1, 201, 203, 205), (1, 1500, 999, 1403), (2, 4096, 1024, 7), (1, 20, 4000, 1000), (3, 300, 520, 200)])
+def test_forcing_the_variant_gives_the_same_bits(lib, shape):
+    batch, M, K, N = shape
+    A, B = ws_inputs.normal_bf16((batch, M, K), 1.0, 91, 0, DEV), ws_inputs.normal_bf16((batch, K, N), 1.0, 91, 1, DEV)
+    own = lib.recurrence_matmul(A, B)
+    variant = lib.cyc_kernel_variant(A.data_ptr(), B.data_ptr(), own.data_ptr(), batch, M, K, N, M * K, K * N, M * N, lib.CYC_BF16_F32)
+    assert lib.cyc_force_kernel(variant) == 0
+    try:
+        assert torch.equal(lib.recurrence_matmul(A, B).view(torch.int32), own.view(torch.int32)), variant
+    finally:
+        assert lib.cyc_force_kernel(None) == 0
 
 
 @pytest.mark.parametrize("M,K,N", [(74, 787, 27), (999, 515, 1001), (1501, 131, 1403), (2047, 67, 2049)])
