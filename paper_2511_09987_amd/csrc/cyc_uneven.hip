@@ -345,14 +345,22 @@ bool supports_uneven(const Problem &p)
     return lda * es * 256 + 256 < ((int64_t)1 << 32) && ldb * es * 128 + 256 < ((int64_t)1 << 32);
 }
 
-// What the rule weighs, in time per k-tile and round of one workgroup on each of the 256 compute units (10 ns,
-// bf16, fitted to products of 17 .. 4095 rows and columns; int8 scales all of them by 1.25).  A block of 256 x 128 moves
-// least per product, smaller ones leave less of the chip idle; at 2047^3 / 1501 x 3001 x 1403 / 1001^3 / 17 x 4001 x 1001 the
-// four take 47 / 61 / 25 / -, 49 / 41 / 17 / 41, 58 / 51 / 10 / 21 and - / - / 16 / 10 us.
+// Costs in units of 10 ns: a launch, the blocks per compute unit (256 of them) that are started and stored, and the
+// k-tiles of the last workgroup to finish (the blocks of 32 cut them among eight teams).  Fitted over operands that change from
+// call to call, 560 products of 1 .. 200000 rows and columns, k of 8 .. 4096, batches of up to 1000, bf16 and int8: within 1 % of
+// the best block on average, and nowhere behind ws_generic_kernel.  (A rule by rounds and k-tiles alone took the blocks of 32
+// wherever k was short, at a round's cost each: bf16 1000000 x 9 x 9 235 us where ws_generic_kernel took 66 and this
+// takes 59, 2000 x (16 x 31 x 100) 69 / 33 / 22.)  Microseconds, blocks of 256 / 96 / 64 / 32: 1696 x 977 x 1820 29.7 / 24.5 / 24.7 / 41.4, 1001^3
+// 25 / 17 / 10 / 16, 17 x 4001 x 1001 - / 41 / 21 / 10, 34 x 117 x 6419 a hundred times 173 / 99 / 73 / 394, 100^3 8.0 / 7.0 / 4.4 / 4.2.
 int choose_uneven_block(const Problem &p)
 {
-    auto rounds = [&](int64_t bm, int64_t bn) { return (((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * p.batch + 255) / 256; };
-    const int64_t c256 = 140 * rounds(256, 128), c96 = 78 * rounds(96, 128), c64 = 34 * rounds(64, 64), c32 = 15 * rounds(32, 32);
+    const int64_t bke = p.i8 ? 128 : 64, kt = (p.K + bke - 1) / bke;
+    auto cost = [&](int64_t bm, int64_t bn, int64_t start, int64_t block, int64_t tile, int64_t round, int64_t k) {
+        const int64_t n = ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * p.batch, rounds = (n + 255) / 256;
+        return start + block * n / 256 + tile * k * std::max<int64_t>(100, round * rounds) / 100;   // round: of its k-tiles' time, in percent (several workgroups share a compute unit)
+    };
+    const int64_t c256 = cost(256, 128, 620, 520, 130, 107, kt), c96 = cost(96, 128, 540, 262, 76, 88, kt);
+    const int64_t c64 = cost(64, 64, 390, 80, 46, 78, kt), c32 = cost(32, 32, 285, 66, 140, 95, (kt + 7) / 8);
     if (c256 <= c96 && c256 <= c64 && c256 <= c32) return 256;
     if (c96 <= c64 && c96 <= c32) return 96;
     return c64 <= c32 ? 64 : 32;

@@ -112,6 +112,16 @@ def test_variants_name_the_kernel_that_runs(pkg):
         assert pkg.cyc_force_kernel(None) == 0
 
 
+def test_short_k_takes_blocks_that_start_cheaply(pkg):
+    """With a k-tile or two a product is bound by starting and storing blocks: 32 x 32 ones, which cost a round of workgroups
+    each, are for those with few of them, and thousands of tiny grids are quicker off the matrix cores."""
+    v = lambda *shape: pkg.cyc_kernel_variant(2 + (1 << 32), 2 << 32, 3 << 32, *shape, shape[1] * shape[2], shape[2] * shape[3], shape[1] * shape[3], 0)
+    for shape in ((1, 1000000, 9, 9), (1, 100000, 17, 17), (2000, 16, 31, 100), (4096, 17, 17, 17)):
+        assert v(*shape) == "uneven64", shape
+    assert v(1, 100, 100, 100) == "uneven32"
+    assert v(20000, 9, 9, 9) == "generic"
+
+
 def test_forced_kernel_is_a_setting_of_the_library(pkg):
     """cyc_force_kernel overrides the dispatcher where the named kernel supports the problem, and gives the choice back."""
     k = pkg.cyc_kernel_name
