@@ -122,6 +122,14 @@ def test_short_k_takes_blocks_that_start_cheaply(pkg):
     assert v(20000, 9, 9, 9) == "generic"
 
 
+def test_whole_blocks_of_128_with_short_k_keep_their_kernel(pkg):
+    v = lambda dtype, *shape: pkg.cyc_kernel_variant(1 << 32, 2 << 32, 3 << 32, *shape, shape[1] * shape[2], shape[2] * shape[3], shape[1] * shape[3], dtype)
+    for dtype, shape in ((0, (64, 128, 128, 128)), (1, (100, 128, 128, 128)), (0, (30, 256, 384, 128)), (1, (1, 256, 128, 3456))):
+        assert v(dtype, *shape) == "mfma128", shape
+    for dtype, shape in ((0, (1, 128, 2048, 768)), (0, (1, 512, 512, 512)), (0, (30, 128, 16, 256)), (1, (1, 64, 64, 64))):
+        assert v(dtype, *shape).startswith("uneven"), shape
+
+
 def test_forced_kernel_is_a_setting_of_the_library(pkg):
     """cyc_force_kernel overrides the dispatcher where the named kernel supports the problem, and gives the choice back."""
     k = pkg.cyc_kernel_name
