@@ -132,13 +132,10 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         return take(K_NARROW, force == K_NONE && blocks <= 512 && bytes <= (128 << 20) && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROW);
     }
     if (cyc::prefers_narrowm(*p)) {
-        // Its workgroups each stream 1024 columns, or 128 of them in eight k-slices: up to 256 blocks of 32 columns, with eight
-        // teams along k and one of them on a compute unit, keep more of the chip reading (bf16, microseconds there / in blocks:
-        // 16 x 8192 x 8192 54 / 37, 20 x 4000 x 1000 32 / 12; with 512, 4 x (16 x 4096 x 4096) 32 / 37), and past 128 k-tiles k
-        // goes to space across workgroups as well (32 x 17280 x 784 144 / 39, k in space 17).
-        const int64_t blocks = p->batch * ((p->N + 31) / 32), kt = p->K * es / 128;
+        // past 128 k-tiles k goes to space across workgroups (bf16 32 x 17280 x 784 144 us there, 39 in blocks, 17 so)
+        const int64_t kt = p->K * es / 128;
         if (force == K_NONE && kt > 128 && p->N <= 4096 && cyc::choose_ksplit(*p, &ktile) > 1) return take(K_MFMAK, K_MFMAK);
-        return take(K_NARROWM, force == K_NONE && blocks <= 256 && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROWM);
+        return take(K_NARROWM, force == K_NONE && cyc::blocks_beat_narrowm(*p) && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROWM);
     }
     // few output blocks, long k: k goes to space (see choose_ksplit)
     if (force == K_NONE && cyc::choose_ksplit(*p, &ktile) > 1) return take(K_MFMAK, K_MFMAK);

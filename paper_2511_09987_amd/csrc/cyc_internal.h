@@ -139,6 +139,7 @@ hipError_t launch_narrow(const Problem &p, hipStream_t s);
 // HBM-bound streaming kernel for M <= 32 (B streamed once, the rows of A pass over it); requires supports_narrowm(p)
 bool supports_narrowm(const Problem &p);
 bool prefers_narrowm(const Problem &p);
+bool blocks_beat_narrowm(const Problem &p);   // of a problem it would be preferred for: blocks of 32 x 32 (cyc_uneven.hip) are quicker
 hipError_t launch_narrowm(const Problem &p, hipStream_t s);
 
 }  // namespace cyc

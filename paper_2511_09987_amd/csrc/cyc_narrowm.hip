@@ -296,6 +296,25 @@ bool prefers_narrowm(const Problem &p)
     return supports_narrowm(p) && p.batch * p.K * p.N >= (1 << 20) && p.N >= 64 && p.K >= 256;
 }
 
+// With too few columns for 1024 per workgroup this kernel has one workgroup per 128 columns, eight waves that each walk an eighth of
+// k in steps of 64 bytes.  Blocks of 32 x 32 put four times as many workgroups on the chip, eight teams each; they win where
+// k is long, and where rows of B start inside a 128-byte line: the pieces of rows then straddle lines, which the non-temporal
+// loads here fetch twice.  Costs in units of 10 ns, fitted over 200 products of 1 .. 32 rows whose operands change from call to
+// call: at most 3 % behind the better of the two in all but three.  Microseconds, here / in blocks: on lines bf16 4 x 1536 x 2048 7.7 / 10.8, 17 x
+// 14328 x 4544 88 / 51, i8 4 x (4 x 1264 x 768) 5.1 / 8.9, 1 x 15856 x 768 23 / 34, 17 x 13360 x 5504 44 / 33; inside lines bf16 17 x 4000 x 1128 32 / 18,
+// 12 x 512 x 4168 7.1 / 7.6, i8 24 x 8192 x 1808 44 / 22, 4 x (4 x 512 x 752) 5.6 / 7.0.  Past 256 blocks they take turns on the chip:
+// 4 x (16 x 4096 x 4096) 32 / 37, i8 16 x (16 x 752 x 1280) 6.1 / 15.
+bool blocks_beat_narrowm(const Problem &p)
+{
+    const int64_t row = p.N * (p.i8 ? 1 : 2), blocks = p.batch * ((p.N + 31) / 32), columns = p.batch * ((p.N + WCOLS - 1) / WCOLS);
+    if (blocks > 256) return false;
+    const bool lines = (row % 128 == 0 && (uintptr_t)p.B % 128 == 0) || p.N <= WCOLS, two = p.M > 16;
+    const int64_t kb = p.K * (p.i8 ? 1 : 2), steps = ((kb + 63) / 64 + NWAVES - 1) / NWAVES, turns = ((kb + 127) / 128 + 7) / 8;
+    const int64_t step = lines ? (p.i8 ? (two ? 91 : 79) : (two ? 79 : 69)) : p.i8 ? (two ? 233 : 194) : (two ? 183 : 169);
+    const int64_t here = 290 + steps * step * (lines ? 64 + columns : 64 + columns / 4) / 64;
+    return 510 + turns * (p.i8 ? 175 : 133) * (512 + blocks) / 512 < here;
+}
+
 hipError_t launch_narrowm(const Problem &p, hipStream_t s)
 {
     if (!supports_narrowm(p)) return hipErrorInvalidValue;

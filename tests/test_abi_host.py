@@ -130,6 +130,15 @@ def test_whole_blocks_of_128_with_short_k_keep_their_kernel(pkg):
         assert v(dtype, *shape).startswith("uneven"), shape
 
 
+def test_few_rows_stream_unless_blocks_are_quicker(pkg):
+    v = lambda dtype, *shape: pkg.cyc_kernel_variant(1 << 32, 2 << 32, 3 << 32, *shape, shape[1] * shape[2], shape[2] * shape[3], shape[1] * shape[3], dtype)
+    for dtype, shape in ((0, (1, 1, 1024, 1024)), (0, (4, 16, 512, 512)), (0, (1, 4, 1536, 2048)), (1, (4, 20, 1024, 1024)), (1, (1, 1, 15856, 768)),
+                         (1, (16, 16, 752, 1280)), (0, (4, 16, 4096, 4096)), (0, (1, 12, 512, 4168))):
+        assert v(dtype, *shape) == "narrowm", shape
+    for dtype, shape in ((0, (1, 17, 4000, 1128)), (1, (1, 24, 8192, 1808)), (0, (1, 20, 4784, 5888)), (0, (8, 4, 14848, 256)), (1, (1, 17, 13360, 5504))):
+        assert v(dtype, *shape) == "uneven32", shape
+
+
 def test_forced_kernel_is_a_setting_of_the_library(pkg):
     """cyc_force_kernel overrides the dispatcher where the named kernel supports the problem, and gives the choice back."""
     k = pkg.cyc_kernel_name
