@@ -392,7 +392,7 @@ int choose_small_block(const Problem &p)
     if (p.M % 128 == 0 && p.N % 128 == 0 && p.K % bke == 0) {
         c128 = 350 + 47 * kt + 3 * n128 / 2;
         c64 = 390 + 38 * kt * r64 + 2 * n128;
-        c32 = 250 + r32 * (200 + 13 * kt) + 7 * std::min<int64_t>(n128, 16);
+        c32 = 250 + r32 * (200 + 13 * kt) + 4 * std::min<int64_t>(n128, 16);
     }
     if (std::min(c64, c32) >= c128) return 0;
     return c32 <= c64 ? 32 : 64;
