@@ -34,10 +34,9 @@
  *     first such call on that stream and replaced by a larger one (hipFree +
  *     hipMalloc, which waits for the device; a buffer that a stream capture
  *     has seen is kept) when a later call needs more.  A call holds a lock
- *     from getting it to its last launch.  A solve or factorisation that cannot
+ *     from getting it to its last launch.  A call that cannot
  *     get it, also because a capture forbids the allocation, returns
- *     CYC_ERR_WORKSPACE; a product takes a kernel that needs none.  No other
- *     entry point allocates device memory;
+ *     CYC_ERR_WORKSPACE.  No other entry point allocates device memory;
  *   - for cyc_recurrence_cholesky with n > 16 nb: one extra stream and a few
  *     events per device (see there); callers that use it are serialised on
  *     the host by a lock for the duration of the enqueueing.
@@ -71,10 +70,11 @@
  *   narrow   N <= 16, many rows: A streamed once from memory, B resident; up to 512 blocks of 32 rows in those blocks.
  *   narrowm  M <= 32, B of at least a mebibyte: B streamed once, the rows of
  *            A pass over it ((j,k) in space); few column blocks and long k in blocks of 32 x 32.  (Long k and few
- *            columns: mfmak.)
+ *            columns, in the caller's memory: mfmak.)
  *   mfmak    unbatched, at most 64 output blocks of 128 x 128, K >= 4096: k in
  *            space; k-slices on different workgroups leave partial sums in the
- *            workspace and a second kernel adds them in ascending slice order.
+ *            workspace and a second kernel adds them in ascending slice order.  The slices are a power of two of equal
+ *            ones; cyc_recurrence_matmul_in also takes others.
  *   mfma256 / mfma128  everything else with aligned rows (mfma128: blocks of 128 x 128 or, where those are few, of
  *            64 x 64 or 32 x 32).
  *   generic  the rest: rows at any address, on the matrix cores (blocks of 256 x 128, 96 x 128, 64 x 64 or 32 x 32)
@@ -102,7 +102,7 @@ typedef enum {
     CYC_ERR_DTYPE = 3,   /* dtype is not a cyc_dtype */
     CYC_ERR_ALIAS = 4,   /* C overlaps A or B */
     CYC_ERR_LAUNCH = 5,  /* the HIP runtime refused a launch */
-    CYC_ERR_WORKSPACE = 6 /* the workspace a call needs could not be allocated, or exceeds the fixed one */
+    CYC_ERR_WORKSPACE = 6 /* the workspace a call needs could not be allocated, exceeds the fixed one, or is the caller's to bring */
 } cyc_status;
 
 /* One grid: C (M x N) <- A (M x K) streamed against B (K x N).
@@ -124,6 +124,19 @@ int cyc_recurrence_matmul(const void *A, const void *B, void *C,
 int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C,
                                   int64_t M, int64_t K, int64_t N,
                                   int dtype, void *stream);
+
+/* The same as cyc_recurrence_matmul for callers that bring memory.  With that, products with few output blocks and long k that no
+ * power of two divides into enough equal slices, and products of few rows with very long k, have k mapped to space as well
+ * (18 x 17280 x 784 bf16: 39 us without, 16 so); and nothing is shared with other calls on the stream or with graphs captured on it.
+ * cyc_matmul_workspace says how many bytes the call wants (0: it needs none; host only, also 0 for arguments that the call
+ * refuses).  workspace: device, 16-byte aligned, not cleared, free again when the call's work on `stream` is done.  With less
+ * than that the call returns CYC_ERR_WORKSPACE and nothing is enqueued; with workspace NULL it does so where the slices are not
+ * those of cyc_recurrence_matmul or where `stream` is being captured, and is cyc_recurrence_matmul otherwise.  Which kernel runs
+ * depends on the problem alone.  Errors otherwise: those of cyc_recurrence_matmul; CYC_ERR_SHAPE also for a
+ * misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
+int64_t cyc_matmul_workspace(const void *A, const void *B, const void *C, int64_t M, int64_t K, int64_t N, int dtype);
+int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, int64_t K, int64_t N, int dtype,
+                             void *workspace, int64_t workspace_bytes, void *stream);
 
 /* `batch` independent grids, each with its own stationary A (not part of the
  * paper; the narrow-stream workload has one weight matrix per batch element).

@@ -11,6 +11,7 @@ import os
 CYC_BF16_F32 = 0
 CYC_I8_I32 = 1
 CYC_OK = 0
+CYC_ERR_WORKSPACE = 6
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libcyclotron_mm.so")
@@ -32,6 +33,10 @@ def _load() -> ctypes.CDLL:
     lib.cyc_recurrence_matmul_noalloc.restype = cint
     lib.cyc_recurrence_matmul_batched.argtypes = [ptr, ptr, ptr, i64, i64, i64, i64, i64, i64, i64, cint, ptr]
     lib.cyc_recurrence_matmul_batched.restype = cint
+    lib.cyc_recurrence_matmul_in.argtypes = [ptr, ptr, ptr, i64, i64, i64, cint, ptr, i64, ptr]
+    lib.cyc_recurrence_matmul_in.restype = cint
+    lib.cyc_matmul_workspace.argtypes = [ptr, ptr, ptr, i64, i64, i64, cint]
+    lib.cyc_matmul_workspace.restype = i64
     lib.cyc_recurrence_trsm.argtypes = [ptr, ptr, ptr, ptr, i64, i64, i64, ptr]
     lib.cyc_recurrence_trsm.restype = cint
     lib.cyc_recurrence_cholesky.argtypes = [ptr, ptr, ptr, i64, i64, ptr]
@@ -87,6 +92,21 @@ def _stream_handle(tensor, stream) -> int:
     return raw(tensor.device.index) if raw else torch.cuda.current_stream(tensor.device).cuda_stream
 
 
+def _memory(wanted: int, tensor, stream):
+    """`wanted` bytes from the allocator's pool of the stream that a call runs on, or None.  They go back to that pool when the
+    caller drops them: whoever gets them next is ordered after the call.  Under capture they belong to the graph."""
+    import torch
+    try:
+        if stream is None:
+            return torch.empty(wanted, dtype=torch.uint8, device=tensor.device)
+        if isinstance(stream, torch.cuda.Stream) and stream.device == tensor.device:
+            with torch.cuda.stream(stream):
+                return torch.empty(wanted, dtype=torch.uint8, device=tensor.device)
+    except torch.OutOfMemoryError:
+        pass
+    return None
+
+
 class CycError(RuntimeError):
     def __init__(self, status: int):
         self.status = status
@@ -115,6 +135,17 @@ def cyc_recurrence_matmul_batched(A: int, B: int, C: int, batch: int, M: int, K:
                                   strideA: int, strideB: int, strideC: int, dtype: int, stream: int = 0) -> int:
     return int(_lib().cyc_recurrence_matmul_batched(A, B, C, batch, M, K, N, strideA, strideB, strideC,
                                                   dtype, stream))
+
+
+def cyc_matmul_workspace(A: int, B: int, C: int, M: int, K: int, N: int, dtype: int) -> int:
+    """Bytes of workspace that cyc_recurrence_matmul_in wants for this problem."""
+    return int(_lib().cyc_matmul_workspace(A, B, C, M, K, N, dtype))
+
+
+def cyc_recurrence_matmul_in(A: int, B: int, C: int, M: int, K: int, N: int, dtype: int, workspace: int, workspace_bytes: int,
+                             stream: int = 0) -> int:
+    """Raw call: device addresses as ints, returns the cyc_status."""
+    return int(_lib().cyc_recurrence_matmul_in(A, B, C, M, K, N, dtype, workspace, workspace_bytes, stream))
 
 
 def cyc_recurrence_trsm(L: int, B: int, X: int, Xh: int, n: int, nrhs: int, nb: int, stream: int = 0) -> int:
@@ -185,8 +216,10 @@ def recurrence_matmul(A, B, out=None, stream=None):
     """Tensor-level convenience: C = weight-stationary recurrence of A against B.
 
     A: (M,K) or (batch,M,K); B: (K,N) or (batch,K,N); contiguous CUDA tensors, both
-    torch.bfloat16 (C float32) or both torch.int8 (C int32).  Only allocates C and
-    forwards pointers to the C ABI on the current (or given) stream.
+    torch.bfloat16 (C float32) or both torch.int8 (C int32).  Only allocates C and, where k
+    is mapped to space, memory for the partial products, and forwards pointers to the C ABI on
+    the current (or given) stream.  (Without that memory fewer slices or none are taken, and the
+    fp32 sums are added in another order.)
     """
     import torch
     if not (A.is_cuda and B.is_cuda):
@@ -208,8 +241,16 @@ def recurrence_matmul(A, B, out=None, stream=None):
     elif tuple(out.shape) != cshape or out.dtype != cdtype or not out.is_contiguous() or out.device != A.device:
         raise ValueError("out has the wrong shape, dtype, layout or device")
     s = _stream_handle(A, stream)
-    st = cyc_recurrence_matmul_batched(A.data_ptr(), B.data_ptr(), out.data_ptr(), batch, M, K, N,
-                                       M * K, K * N, M * N, dtype, s)
+    if batch == 1:
+        args = A.data_ptr(), B.data_ptr(), out.data_ptr(), M, K, N, dtype
+        st = cyc_recurrence_matmul_in(*args, 0, 0, s)
+        if st == CYC_ERR_WORKSPACE:               # k goes to space, in memory that the caller brings
+            wanted = cyc_matmul_workspace(*args)
+            work = _memory(wanted, A, stream) if wanted else None
+            st = cyc_recurrence_matmul(*args, s) if work is None else cyc_recurrence_matmul_in(*args, work.data_ptr(), wanted, s)
+    else:
+        st = cyc_recurrence_matmul_batched(A.data_ptr(), B.data_ptr(), out.data_ptr(), batch, M, K, N,
+                                           M * K, K * N, M * N, dtype, s)
     if st != CYC_OK:
         raise CycError(st)
     return out
@@ -302,19 +343,10 @@ def recurrence_attention(Q, K, V, out=None, stream=None):
     elif tuple(out.shape) != tuple(Q.shape) or out.dtype != torch.float32 or not out.is_contiguous() or out.device != Q.device:
         raise ValueError("out has the wrong shape, dtype, layout or device")
     s = _stream_handle(Q, stream)
-    # The library splits no key list below 512.  The workspace comes from the allocator's pool of the stream that the call
-    # runs on, and goes back to it: whoever gets it next is ordered after this call.  Where there is
-    # none to be had the keys are not split, which is slower and adds the fp32 sums in another order.
-    wanted, work = cyc_attention_workspace(batch, N, M, d) if M >= 512 else 0, None
-    if wanted:
-        try:
-            if stream is None:
-                work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
-            elif isinstance(stream, torch.cuda.Stream) and stream.device == Q.device:
-                with torch.cuda.stream(stream):
-                    work = torch.empty(wanted, dtype=torch.uint8, device=Q.device)
-        except torch.OutOfMemoryError:
-            pass
+    # The library splits no key list below 512.  Without memory the keys are not split, which is slower and adds the fp32 sums in
+    # another order.
+    wanted = cyc_attention_workspace(batch, N, M, d) if M >= 512 else 0
+    work = _memory(wanted, Q, stream) if wanted else None
     if work is None:
         st = cyc_recurrence_attention(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(), batch, N, M, d, s)
     else:

@@ -26,6 +26,9 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
     return a < b + (uintptr_t)qbytes && b < a + (uintptr_t)pbytes;
 }
 
+// what a caller may bring as a workspace
+bool workspace_ok(const void *workspace, int64_t bytes) { return ((uintptr_t)workspace & 15) == 0 && bytes >= 0; }
+
 enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
 
 const char *kernel_label(Kernel k)
@@ -75,8 +78,10 @@ std::atomic<int> &wait_limit_value()
 
 // Validates and fills `p`.  Returns CYC_OK with *k == K_NONE when there is nothing to do.  *family: the kernel whose part of
 // the dispatch the problem falls into; *k: the kernel that runs (blocks of cyc_uneven.hip stand in for several families).
+// split: filled in for K_MFMAK; any_slices: the caller brings memory, so that k may also be cut where the library's own
+// workspaces are not used for it (see KSplit).
 int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, int64_t K, int64_t N,
-         int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k, Kernel *family)
+         int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k, Kernel *family, cyc::KSplit *split, bool any_slices)
 {
     *k = *family = K_NONE;
     if (dtype != CYC_BF16_F32 && dtype != CYC_I8_I32) return CYC_ERR_DTYPE;
@@ -112,7 +117,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     // a forced kernel overrides the heuristic when it supports the problem (testing and benchmarking aid).  The x32
     // names are the MFMA kernels built on the 32x32 instruction shape, which the dispatcher never picks by itself.
     const Kernel force = (Kernel)forced_kernel().load(std::memory_order_relaxed);
-    int ktile = 0;
+    auto splits = [&]() { return (*split = cyc::choose_ksplit(*p, any_slices)).slices > 1; };
     switch (force) {
         case K_GENERIC: return take(force, force);
         case K_UNEVEN256: case K_UNEVEN96: case K_UNEVEN64: case K_UNEVEN32: if (cyc::supports_uneven(*p)) return take(force, force); break;
@@ -120,7 +125,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         case K_MFMA128: case K_MFMA128X32: if (cyc::supports_mfma(*p, 128)) return take(force, force); break;
         case K_NARROW: if (cyc::supports_narrow(*p)) return take(force, force); break;
         case K_NARROWM: if (cyc::supports_narrowm(*p)) return take(force, force); break;
-        case K_MFMAK: if (cyc::choose_ksplit(*p, &ktile) > 1) return take(force, force); break;
+        case K_MFMAK: if (splits()) return take(force, force); break;
         default: break;
     }
     if (cyc::prefers_narrow(*p)) {
@@ -134,11 +139,14 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     if (cyc::prefers_narrowm(*p)) {
         // past 128 k-tiles k goes to space across workgroups (bf16 32 x 17280 x 784 144 us there, 39 in blocks, 17 so)
         const int64_t kt = p->K * es / 128;
-        if (force == K_NONE && kt > 128 && p->N <= 4096 && cyc::choose_ksplit(*p, &ktile) > 1) return take(K_MFMAK, K_MFMAK);
+        if (force == K_NONE && any_slices && kt > 128 && p->N <= 4096 && splits()) {
+            split->any = true;
+            return take(K_MFMAK, K_MFMAK);
+        }
         return take(K_NARROWM, force == K_NONE && cyc::blocks_beat_narrowm(*p) && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROWM);
     }
     // few output blocks, long k: k goes to space (see choose_ksplit)
-    if (force == K_NONE && cyc::choose_ksplit(*p, &ktile) > 1) return take(K_MFMAK, K_MFMAK);
+    if (force == K_NONE && splits()) return take(K_MFMAK, K_MFMAK);
     // MFMA kernels for everything with 16-byte aligned rows except slivers
     const int tile = cyc::choose_mfma_tile(*p);
     if (tile == 256) return take(K_MFMA256, K_MFMA256);
@@ -152,7 +160,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     return take(K_GENERIC, cyc::supports_uneven(*p) && !tiny ? uneven_kernel(cyc::choose_uneven_block(*p)) : K_GENERIC);
 }
 
-int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
+int run_chunk(const cyc::Problem &p, Kernel k, const cyc::KSplit &split, void *workspace, hipStream_t s)
 {
     hipError_t e = hipSuccess;
     switch (k) {
@@ -164,13 +172,7 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
         case K_MFMA128: e = cyc::launch_mfma(p, 128, 16, s); break;
         case K_MFMA256X32: e = cyc::launch_mfma(p, 256, 32, s); break;
         case K_MFMA128X32: e = cyc::launch_mfma(p, 128, 32, s); break;
-        case K_MFMAK: {
-            int tile = 0;
-            int64_t length = 0;
-            const int ks = cyc::choose_ksplit(p, &tile, &length);
-            e = cyc::launch_mfma_ksplit(p, ks, tile, length, workspace, s);
-            break;
-        }
+        case K_MFMAK: e = cyc::launch_mfma_ksplit(p, split, workspace, s); break;
         case K_NARROW: e = cyc::launch_narrow(p, s); break;
         case K_NARROWM: e = cyc::launch_narrowm(p, s); break;
     }
@@ -181,30 +183,23 @@ int run_chunk(const cyc::Problem &p, Kernel k, void *workspace, hipStream_t s)
 // launches of the same kernel (batch elements are independent).
 constexpr int64_t kBatchPerLaunch = 65535;
 
-// fixed_workspace: take the partial products' memory from the library's fixed array instead of the per-stream cache
-int run(const cyc::Problem &p, Kernel k, hipStream_t s, bool fixed_workspace = false)
+// where the partial products of K_MFMAK go
+enum Memory { CACHED, FIXED, GIVEN };    // the per-stream workspace, the library's fixed array, the caller's
+
+int run(const cyc::Problem &p, Kernel k, const cyc::KSplit &split, hipStream_t s, Memory memory, void *given = nullptr, int64_t given_bytes = 0)
 {
     void *workspace = nullptr;
     cyc::WorkspaceHold hold;
     if (k == K_MFMAK) {
         // everything that can fail before the first launch is settled before it
-        int tile = 0;
-        const int ks = cyc::choose_ksplit(p, &tile);
-        const int64_t need = cyc::ksplit_workspace_bytes(p, ks);
-        if (fixed_workspace) {
-            int64_t have = 0;
-            workspace = cyc::static_workspace(&have);
-            if (need > have) return CYC_ERR_WORKSPACE;
-        } else {
-            workspace = hold.acquire(s, need);
-            if (!workspace) {                   // no memory, or none to be had under capture: one workgroup per block instead
-                const int t = cyc::choose_mfma_tile(p);
-                k = cyc::prefers_narrowm(p) ? K_NARROWM : t == 256 ? K_MFMA256 : t == 128 ? K_MFMA128 : cyc::supports_uneven(p) ? uneven_kernel(cyc::choose_uneven_block(p)) : K_GENERIC;
-            }
-        }
-        if (!workspace && k == K_MFMAK) return CYC_ERR_WORKSPACE;
+        const int64_t need = cyc::ksplit_workspace_bytes(p, split.slices);
+        int64_t have = 0;
+        if (memory == FIXED) workspace = cyc::static_workspace(&have);
+        else if (memory == GIVEN) workspace = given, have = given_bytes;
+        else workspace = hold.acquire(s, need), have = need;
+        if (!workspace || need > have) return CYC_ERR_WORKSPACE;
     }
-    if (p.batch <= kBatchPerLaunch) return run_chunk(p, k, workspace, s);
+    if (p.batch <= kBatchPerLaunch) return run_chunk(p, k, split, workspace, s);
     const int64_t es = p.i8 ? 1 : 2;
     for (int64_t b0 = 0; b0 < p.batch; b0 += kBatchPerLaunch) {
         cyc::Problem q = p;
@@ -212,7 +207,7 @@ int run(const cyc::Problem &p, Kernel k, hipStream_t s, bool fixed_workspace = f
         q.A = (const char *)p.A + b0 * p.strideA * es;
         q.B = (const char *)p.B + b0 * p.strideB * es;
         q.C = (char *)p.C + b0 * p.strideC * 4;
-        if (int st = run_chunk(q, k, workspace, s); st != CYC_OK) return st;
+        if (int st = run_chunk(q, k, split, workspace, s); st != CYC_OK) return st;
     }
     return CYC_OK;
 }
@@ -231,9 +226,10 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C, int64_t
 {
     cyc::Problem p;
     Kernel k, family;
-    int st = plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family);
+    cyc::KSplit split;
+    int st = plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family, &split, false);
     if (st != CYC_OK || k == K_NONE) return st;      // an error, or nothing to do (p is then not filled in)
-    return run(p, k, (hipStream_t)stream);
+    return run(p, k, split, (hipStream_t)stream, CACHED);
 }
 
 int cyc_recurrence_matmul(const void *A, const void *B, void *C, int64_t M, int64_t K, int64_t N, int dtype,
@@ -247,9 +243,40 @@ int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C, int64_t
 {
     cyc::Problem p;
     Kernel k, family;
-    int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family);
+    cyc::KSplit split;
+    int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, false);
     if (st != CYC_OK || k == K_NONE) return st;
-    return run(p, k, (hipStream_t)stream, true);
+    return run(p, k, split, (hipStream_t)stream, FIXED);
+}
+
+int64_t cyc_matmul_workspace(const void *A, const void *B, const void *C, int64_t M, int64_t K, int64_t N, int dtype)
+{
+    cyc::Problem p;
+    Kernel k, family;
+    cyc::KSplit split;
+    if (plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, true) != CYC_OK || k != K_MFMAK) return 0;
+    return cyc::ksplit_workspace_bytes(p, split.slices);
+}
+
+int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, int64_t K, int64_t N, int dtype, void *workspace,
+                             int64_t workspace_bytes, void *stream)
+{
+    cyc::Problem p;
+    Kernel k, family;
+    cyc::KSplit split;
+    int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, true);
+    if (st != CYC_OK || k == K_NONE) return st;
+    if (k != K_MFMAK) return run(p, k, split, (hipStream_t)stream, GIVEN);
+    if (!workspace) {
+        if (split.any || cyc::is_capturing((hipStream_t)stream)) return CYC_ERR_WORKSPACE;
+        return run(p, k, split, (hipStream_t)stream, CACHED);
+    }
+    const int64_t es = p.i8 ? 1 : 2;
+    if (!workspace_ok(workspace, workspace_bytes)) return CYC_ERR_SHAPE;
+    if (overlaps(workspace, workspace_bytes, A, M * K * es) || overlaps(workspace, workspace_bytes, B, K * N * es) ||
+        overlaps(workspace, workspace_bytes, C, M * N * 4))
+        return CYC_ERR_ALIAS;
+    return run(p, k, split, (hipStream_t)stream, GIVEN, workspace, workspace_bytes);
 }
 
 int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb,
@@ -338,7 +365,8 @@ const char *cyc_kernel_name(const void *A, const void *B, const void *C, int64_t
 {
     cyc::Problem p;
     Kernel k, family;
-    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family) != CYC_OK) return "none";
+    cyc::KSplit split;
+    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family, &split, false) != CYC_OK) return "none";
     return kernel_label(family);
 }
 
@@ -347,7 +375,8 @@ const char *cyc_kernel_variant(const void *A, const void *B, const void *C, int6
 {
     cyc::Problem p;
     Kernel k, family;
-    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family) != CYC_OK) return "none";
+    cyc::KSplit split;
+    if (plan(A, B, C, batch, M, K, N, strideA, strideB, strideC, dtype, &p, &k, &family, &split, false) != CYC_OK) return "none";
     return kernel_label(k);
 }
 

@@ -61,13 +61,19 @@ bool supports_mfma(const Problem &p, int tile);
 hipError_t launch_mfma(const Problem &p, int tile, int mt, hipStream_t s);   // mt: MFMA tile width, 16 or 32
 // block edge (256 or 128) of the MFMA kernel that suits the problem best, 0 if neither supports it
 int choose_mfma_tile(const Problem &p);
-// k in space: number of k-slices (1 = do not split; all of *length but the last, which may be shorter) for problems with few
-// output blocks and a long k extent.  One workgroup per (output block, k-slice) writes its partial product to slice `b` of a workspace
-// of ksplit x M x N accumulator elements; a second kernel adds the slices in ascending order into C.
-int choose_ksplit(const Problem &p, int *tile, int64_t *length);   // *tile: block edge to use, 128 or 256
-int choose_ksplit(const Problem &p, int *tile);
+// k in space, for problems with few output blocks and a long k extent: one workgroup per (output block, k-slice) writes
+// its partial product to slice `b` of a workspace of slices x M x N accumulator elements; a second kernel adds the slices in
+// ascending order into C.
+struct KSplit {
+    int slices;                          // 1: do not split
+    int tile;                            // block edge to use, 128 or 256
+    int64_t length;                      // of every slice but the last, which may be shorter
+    bool any;                            // not the power of two of equal slices that the problem gets otherwise
+};
+// any: slices of any number and length, for callers that bring the memory; otherwise a power of two of equal ones
+KSplit choose_ksplit(const Problem &p, bool any);
 inline int64_t ksplit_workspace_bytes(const Problem &p, int ksplit) { return (int64_t)ksplit * p.M * p.N * 4; }
-hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, int64_t length, void *workspace, hipStream_t s);
+hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *workspace, hipStream_t s);
 // Device memory for partial products, inverses and padded copies.  WorkspaceHold::acquire: one buffer per (device, stream),
 // allocated with hipMalloc on first use, grown when a call needs more, kept until the process ends; nullptr when the
 // allocation fails, or would be needed while the stream is being captured.  The buffer is the holder's until the object
@@ -86,6 +92,7 @@ private:
     bool held_ = false;
 };
 void *static_workspace(int64_t *bytes);
+bool is_capturing(hipStream_t s);
 // lower-triangular forward solve L X = B in tiles of nb rows (see cyc_tri.hip); arguments validated by the caller
 // A second stream per device for work that may run beside what a call enqueues on the caller's stream (forked from
 // and joined into that stream with events inside the call).  Created on first use, default priority, kept until the

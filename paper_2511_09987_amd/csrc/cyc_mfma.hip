@@ -543,20 +543,13 @@ int choose_mfma_tile(const Problem &p)
 // row and of B's block column to itself and leaves its partial sum in its slice of a workspace; the hand-over
 // along k is a second kernel that adds the slices of every element in ascending slice order (a fixed order: the
 // result is the same bits on every call).
-int choose_ksplit(const Problem &p, int *tile)
+KSplit choose_ksplit(const Problem &p, bool any)
 {
-    int64_t length;
-    return choose_ksplit(p, tile, &length);
-}
-
-int choose_ksplit(const Problem &p, int *tile, int64_t *length)
-{
-    *tile = 128;
-    *length = p.K;
-    if (p.batch != 1 || p.lda || p.ldb || p.ldc || p.Cin || p.kslices || !supports_mfma(p, 128)) return 1;
+    KSplit one{1, 128, p.K, false};
+    if (p.batch != 1 || p.lda || p.ldb || p.ldc || p.Cin || p.kslices || !supports_mfma(p, 128)) return one;
     const int64_t b128 = ((p.M + 127) / 128) * ((p.N + 127) / 128), b256 = ((p.M + 255) / 256) * ((p.N + 255) / 256);
     const int64_t bke = p.i8 ? 128 : 64;
-    if (b128 > 64 || p.K < 4096) return 1;
+    if (b128 > 64 || p.K < 4096) return one;
     // equal slices, a power of two of them
     auto slices = [&](int64_t blocks, int64_t slots) {
         const int64_t want = std::min<int64_t>(slots / blocks, p.K / (8 * bke));   // at least eight k-tiles per slice
@@ -567,26 +560,22 @@ int choose_ksplit(const Problem &p, int *tile, int64_t *length)
     // 256 x 256 blocks (one per CU) re-read A and B half as often as 128 x 128 blocks (two per CU) but cost more to
     // start and to finish: take them when they compute little padding, still fill the chip and keep long slices
     const int ks256 = supports_mfma(p, 256) ? slices(b256, 256) : 1;
-    if (b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096) {
-        *tile = 256;
-        *length = p.K / ks256;
-        return ks256;
-    }
-    int ks = slices(b128, 256);
-    *length = p.K / ks;
+    if (b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096) return {ks256, 256, p.K / ks256, false};
+    const int ks = slices(b128, 256);
     // K need not be a multiple of anything: where the equal slices are less than 3/4 as many as the chip has room for, as many
     // slices as there is room for, of whole k-tiles, the last one with what remains (40 x 17280 x 784 bf16: 110 us in two slices' stead, 14)
     const int64_t nkt = (p.K + bke - 1) / bke, want = std::min<int64_t>(256 / b128, nkt / 8);
-    if (ks * 4 < want * 3) {
+    if (any && ks * 4 < want * 3) {
         const int64_t per = (nkt + want - 1) / want;
-        ks = (int)((nkt + per - 1) / per);
-        *length = per * bke;
+        return {(int)((nkt + per - 1) / per), 128, per * bke, true};
     }
-    return ks;
+    return {ks, 128, p.K / ks, false};
 }
 
-hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, int64_t length, void *workspace, hipStream_t s)
+hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *workspace, hipStream_t s)
 {
+    const int ksplit = split.slices;
+    const int64_t length = split.length;
     if (ksplit < 2 || ksplit > 256 || p.batch != 1 || length < 1 || (ksplit - 1) * length >= p.K || ksplit * length < p.K || !workspace ||
         (p.M * p.N) % 4)
         return hipErrorInvalidValue;
@@ -602,7 +591,7 @@ hipError_t launch_mfma_ksplit(const Problem &p, int ksplit, int tile, int64_t le
     q.strideB = q.K * p.N;               // ... and at that row of B ...
     q.C = workspace;
     q.strideC = p.M * p.N;               // ... and leaves its partial product in slice b of the workspace
-    if (hipError_t e = launch_mfma(q, tile, 16, s); e != hipSuccess) return e;
+    if (hipError_t e = launch_mfma(q, split.tile, 16, s); e != hipSuccess) return e;
     const int64_t quads = p.M * p.N / 4;
     dim3 grid((unsigned)((quads + 255) / 256));
     if (p.i8) return launch_kernel(ws_join_slices_kernel<i32x4>, grid, dim3(256), s, (const i32x4 *)workspace, (i32x4 *)p.C, quads, ksplit);

@@ -57,6 +57,12 @@ void *static_workspace(int64_t *bytes)
     return d->scratch_ptr;
 }
 
+bool is_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
 {
     if (!held_) {
@@ -66,8 +72,7 @@ void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
     PerDevice *d = current_device();
     if (!d || bytes <= 0) return nullptr;
     auto &slot = d->cache[s];
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    const bool capturing = hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+    const bool capturing = is_capturing(s);
     if (slot.bytes < bytes) {
         if (capturing) return nullptr;                  // an allocation would end the capture
         // hipFree waits for the device, so nothing enqueued earlier still uses the old buffer when it goes; a graph that was

@@ -37,9 +37,58 @@ def test_products(dtype, batch, M, K, N):
             assert bool(((c.double() - ref).abs() <= K * 2.0 ** -24 * torch.matmul(a.double().abs(), b.double().abs())).all())
 
 
+@pytest.mark.parametrize("M,K,N", [(18, 17280, 784), (40, 17280, 784), (256, 8192, 256)])
+def test_captured_and_eager_calls_give_the_same_bits(M, K, N):
+    """A captured product keeps its partial sums in memory of its graph's own: on a stream without a workspace and on one that has
+    one, replayed on two streams at once and beside eager calls on the stream that it was captured on."""
+    import paper_2511_09987_amd as lib
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    sets = [[t[0] for t in operands(torch.bfloat16, 1, M, K, N + 16 * i)] for i in range(2)]
+    want = [lib.recurrence_matmul(A, B) for A, B in sets]
+    torch.cuda.synchronize()
+    graphs, outs = [], []
+    for A, B in sets:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            outs.append(lib.recurrence_matmul(A, B))
+        graphs.append(graph)
+        with torch.cuda.stream(stream):
+            lib.recurrence_matmul(A, B)
+    for _ in range(4):
+        for out in outs:
+            out.zero_()
+        torch.cuda.synchronize()
+        for graph, s in zip(graphs, (stream, other)):
+            with torch.cuda.stream(s):
+                graph.replay()
+        eager = lib.recurrence_matmul(*sets[0], stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], want[0]) and torch.equal(outs[1], want[1]) and torch.equal(eager, want[0])
+
+
+def test_a_workspace_that_the_caller_brings():
+    """Refused when it is too small, misaligned or overlaps an operand, and asked for where the slices are not the ordinary ones;
+    nothing past it is touched."""
+    import paper_2511_09987_amd as lib
+    M, K, N = 40, 17280, 784
+    A, B = (t[0] for t in operands(torch.bfloat16, 1, M, K, N))
+    C = torch.full((M, N), 5.0, device=DEV)
+    args = A.data_ptr(), B.data_ptr(), C.data_ptr(), M, K, N, lib.CYC_BF16_F32
+    wanted, stream = lib.cyc_matmul_workspace(*args), torch.cuda.current_stream().cuda_stream
+    around = torch.full((wanted + 4096,), 77, dtype=torch.uint8, device=DEV)
+    call = lambda work, size: lib.cyc_recurrence_matmul_in(*args, work, size, stream)
+    assert wanted > 0 and call(0, 0) == 6 and call(around.data_ptr(), wanted - 1) == 6
+    assert call(around.data_ptr() + 8, wanted) == 2 and call(A.data_ptr(), wanted) == 4
+    torch.cuda.synchronize()
+    assert bool((C == 5.0).all()) and bool((around == 77).all())
+    assert call(around.data_ptr(), wanted) == 0
+    assert torch.equal(C, lib.recurrence_matmul(A, B)) and bool((around[wanted:] == 77).all())
+    for shape in ((512, 512, 512), (17, 33, 5), (16, 4096, 2048)):
+        assert lib.cyc_matmul_workspace(A.data_ptr(), B.data_ptr(), C.data_ptr(), *shape, lib.CYC_BF16_F32) == 0
+
+
 def test_first_call_on_a_stream_under_capture():
-    """No memory can be allocated while a stream is captured: the product runs without k-slices, and a graph keeps a buffer that
-    it was captured with although a later call needs a larger one."""
+    """Captured products have memory of their own, whether or not the stream has a workspace, and whatever a later call needs."""
     import paper_2511_09987_amd as lib
     A, B = (t[0] for t in operands(torch.int8, 1, 64, 16384, 64))
     A2, B2 = (t[0] for t in operands(torch.int8, 1, 500, 32768, 496))

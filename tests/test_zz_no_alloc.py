@@ -49,6 +49,38 @@ def test_noalloc_matches_the_ordinary_entry_point(lib, oracle, mode):
     assert name == "mfmak", "the first two shapes are meant to run with k in space"
 
 
+@pytest.mark.parametrize("M,K,N", [(18, 17280, 784), (32, 9216, 256)])
+def test_noalloc_keeps_few_rows_off_the_shared_array(lib, M, K, N):
+    """Products of few rows need no memory here: two streams at once, and the bits of the ordinary entry point."""
+    dt = lib.CYC_BF16_F32
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    pairs = [operands("bf16", M, K, N, 8850 + i) for i in range(2)]
+    want, outs = [], [[torch.zeros((M, N), device=DEV) for _ in range(8)] for _ in range(2)]
+    for A, B in pairs:
+        ref = torch.empty((M, N), device=DEV)
+        assert lib.cyc_kernel_variant(A.data_ptr(), B.data_ptr(), ref.data_ptr(), 1, M, K, N, 0, 0, 0, dt) != "mfmak"
+        assert lib.cyc_recurrence_matmul(A.data_ptr(), B.data_ptr(), ref.data_ptr(), M, K, N, dt, torch.cuda.current_stream().cuda_stream) == 0
+        want.append(ref)
+    torch.cuda.synchronize()
+    for turn in range(8):
+        for side, (A, B), out in zip(sides, pairs, outs):
+            assert lib.cyc_recurrence_matmul_noalloc(A.data_ptr(), B.data_ptr(), out[turn].data_ptr(), M, K, N, dt, side.cuda_stream) == 0
+    torch.cuda.synchronize()
+    for ref, out in zip(want, outs):
+        for o in out:
+            assert torch.equal(o, ref)
+
+
+@pytest.mark.parametrize("M,K,N", [(700, 96000, 528), (40, 17280, 784)])
+def test_noalloc_cuts_k_as_the_ordinary_entry_point_does(lib, M, K, N):
+    A, B = operands("i8", M, K, N, 8870)
+    ref, out = (torch.zeros((M, N), dtype=torch.int32, device=DEV) for _ in range(2))
+    stream = torch.cuda.current_stream().cuda_stream
+    assert lib.cyc_recurrence_matmul(A.data_ptr(), B.data_ptr(), ref.data_ptr(), M, K, N, lib.CYC_I8_I32, stream) == 0
+    assert lib.cyc_recurrence_matmul_noalloc(A.data_ptr(), B.data_ptr(), out.data_ptr(), M, K, N, lib.CYC_I8_I32, stream) == 0
+    assert torch.equal(ref, out) and torch.equal(ref.double(), torch.matmul(A.double(), B.double()))
+
+
 def test_noalloc_refuses_what_does_not_fit(lib):
     """512 x 262144 x 512 runs as 64 k-slices of 1 MiB each: twice the fixed workspace."""
     w = ws_inputs.KSPACE_WORKLOADS["k1_bf16_tallk"]
