@@ -173,9 +173,7 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C,
  *     nrhs a multiple of 8 below 2^24, n a multiple of 8 below 2^26 and 16-byte aligned L, X, Xh it keeps the inverses of the diagonal
  *     tiles (16 KiB per 64 rows) and a second copy of the tiles of L next to the diagonal in the order the
  *     kernels read them (56 KiB per 64 rows) in the workspace that the library holds per device and stream (allocated or
- *     grown on the call that first needs it, as for cyc_recurrence_matmul).  With nb == 64, n >= 512 and any other nrhs, n
- *     or alignment it solves a copy in that workspace, padded to multiples of 8, where the copy takes at most 256 MiB and
- *     the workspace can be had (not under a capture that finds none).  Otherwise it allocates nothing.
+ *     grown on the call that first needs it, as for cyc_recurrence_matmul).  Otherwise it allocates nothing.
  *     n == 0 or nrhs == 0: CYC_OK, nothing done.  A zero on the diagonal
  *     gives infinities or NaNs as IEEE division does, not an error.  Inside the kernels, waves hand solved rows
  *     to one another through LDS with bounded waits; a wait that ever ran out would leave NaN in X and Xh (in
@@ -185,6 +183,19 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C,
  * allocated).  CYC_ERR_LAUNCH: see the top of this file. */
 int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
                         int64_t n, int64_t nrhs, int64_t nb, void *stream);
+
+/* The same for callers that bring memory.  With nb == 64, n >= 512 and an n, nrhs or pointer that the inverses above do not take
+ * (n or nrhs no multiple of 8, an address that is not 16-byte aligned) it solves a copy in `workspace` that they do take, n and nrhs rounded up
+ * to multiples of 8, as long as the copy has at most 256 MiB (1333 x 28: 466 us without, 122 so); and nothing is shared with
+ * other calls on the stream or with graphs captured on it.  cyc_trsm_workspace says how many bytes the call wants (0: none;
+ * host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not cleared, free again when the call's
+ * work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is enqueued; with
+ * workspace NULL it does so where it would solve a copy, or needs memory while `stream` is being captured, and is
+ * cyc_recurrence_trsm otherwise.  Which kernels run depends on the problem and its alignment alone.  Errors otherwise: those of
+ * cyc_recurrence_trsm; CYC_ERR_SHAPE also for a misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
+int64_t cyc_trsm_workspace(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb);
+int cyc_recurrence_trsm_in(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb,
+                           void *workspace, int64_t workspace_bytes, void *stream);
 
 /* Tiled Cholesky factorisation  A = L L^T  of a symmetric positive definite matrix, L lower triangular
  * (paper: "Representative recurrences", Cholesky; "Cholesky Recurrence", tiled form: for every panel j
@@ -210,9 +221,8 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
  *     pointers are 16-byte aligned; otherwise the shape-agnostic kernels do.
  * stream: hipStream_t or NULL.  The call enqueues a sequence of kernels on it and returns.  With nb == 64 and
  *     n >= 128 it keeps the inverses of the diagonal tiles (16 KiB per 64 rows) and a copy of one diagonal tile (16 KiB)
- *     in the workspace that the library holds per device and stream (allocated or grown on the call that first needs it); with
- *     nb == 64, n > 128 and n no multiple of 8 or pointers that are not 16-byte aligned it factors a padded copy there, where
- *     the copy takes at most 256 MiB and the workspace can be had.  Otherwise it allocates no device memory.  For n > 16 nb part of the work is enqueued on a second stream that the library creates per device
+ *     in the workspace that the library holds per device and stream (allocated or grown on the call that first needs it); otherwise it allocates no
+ *     device memory.  For n > 16 nb part of the work is enqueued on a second stream that the library creates per device
  *     on first use (default priority, kept until the process ends) and that is forked from and joined back into
  *     `stream` with events inside the call: all of the call's work is ordered after what was on `stream` before
  *     and before what is enqueued on it afterwards; calls that use the second stream are serialised on the host
@@ -223,6 +233,12 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
  * could not be allocated).  CYC_ERR_LAUNCH: see the top of
  * this file; work already on the second stream is joined back into `stream` before the call returns. */
 int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *stream);
+
+/* The same for callers that bring memory, on the terms of cyc_recurrence_trsm_in: with nb == 64, n > 128 and n no multiple of 8 or
+ * a pointer that is not 16-byte aligned it factors a padded copy in `workspace`, of at most 256 MiB (585: 371 us without, 180 so). */
+int64_t cyc_cholesky_workspace(const void *A, void *L, void *Lh, int64_t n, int64_t nb);
+int cyc_recurrence_cholesky_in(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, int64_t workspace_bytes,
+                               void *stream);
 
 /* Attention by the tile recurrence of the paper's "FlashAttention-2 Recurrence": per query a running
  * maximum, running sum and running output over tiles of keys; the result is

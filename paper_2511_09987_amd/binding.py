@@ -41,6 +41,14 @@ def _load() -> ctypes.CDLL:
     lib.cyc_recurrence_trsm.restype = cint
     lib.cyc_recurrence_cholesky.argtypes = [ptr, ptr, ptr, i64, i64, ptr]
     lib.cyc_recurrence_cholesky.restype = cint
+    lib.cyc_recurrence_trsm_in.argtypes = [ptr, ptr, ptr, ptr, i64, i64, i64, ptr, i64, ptr]
+    lib.cyc_recurrence_trsm_in.restype = cint
+    lib.cyc_trsm_workspace.argtypes = [ptr, ptr, ptr, i64, i64, i64]
+    lib.cyc_trsm_workspace.restype = i64
+    lib.cyc_recurrence_cholesky_in.argtypes = [ptr, ptr, ptr, i64, i64, ptr, i64, ptr]
+    lib.cyc_recurrence_cholesky_in.restype = cint
+    lib.cyc_cholesky_workspace.argtypes = [ptr, ptr, ptr, i64, i64]
+    lib.cyc_cholesky_workspace.restype = i64
     lib.cyc_recurrence_attention.argtypes = [ptr, ptr, ptr, ptr, i64, i64, i64, i64, ptr]
     lib.cyc_recurrence_attention.restype = cint
     lib.cyc_recurrence_attention_split.argtypes = [ptr, ptr, ptr, ptr, i64, i64, i64, i64, ptr, i64, ptr]
@@ -153,6 +161,17 @@ def cyc_recurrence_trsm(L: int, B: int, X: int, Xh: int, n: int, nrhs: int, nb: 
     return int(_lib().cyc_recurrence_trsm(L, B, X, Xh, n, nrhs, nb, stream))
 
 
+def cyc_trsm_workspace(L: int, X: int, Xh: int, n: int, nrhs: int, nb: int) -> int:
+    """Bytes of workspace that cyc_recurrence_trsm_in wants for this system."""
+    return int(_lib().cyc_trsm_workspace(L, X, Xh, n, nrhs, nb))
+
+
+def cyc_recurrence_trsm_in(L: int, B: int, X: int, Xh: int, n: int, nrhs: int, nb: int, workspace: int, workspace_bytes: int,
+                           stream: int = 0) -> int:
+    """Raw call: device addresses as ints, returns the cyc_status."""
+    return int(_lib().cyc_recurrence_trsm_in(L, B, X, Xh, n, nrhs, nb, workspace, workspace_bytes, stream))
+
+
 def cyc_recurrence_attention(Q: int, K: int, V: int, O: int, batch: int, N: int, M: int, d: int, stream: int = 0) -> int:
     """Raw call: device addresses as ints, returns the cyc_status."""
     return int(_lib().cyc_recurrence_attention(Q, K, V, O, batch, N, M, d, stream))
@@ -261,6 +280,16 @@ def cyc_recurrence_cholesky(A: int, L: int, Lh: int, n: int, nb: int, stream: in
     return int(_lib().cyc_recurrence_cholesky(A, L, Lh, n, nb, stream))
 
 
+def cyc_cholesky_workspace(A: int, L: int, Lh: int, n: int, nb: int) -> int:
+    """Bytes of workspace that cyc_recurrence_cholesky_in wants for this matrix."""
+    return int(_lib().cyc_cholesky_workspace(A, L, Lh, n, nb))
+
+
+def cyc_recurrence_cholesky_in(A: int, L: int, Lh: int, n: int, nb: int, workspace: int, workspace_bytes: int, stream: int = 0) -> int:
+    """Raw call: device addresses as ints, returns the cyc_status."""
+    return int(_lib().cyc_recurrence_cholesky_in(A, L, Lh, n, nb, workspace, workspace_bytes, stream))
+
+
 def recurrence_cholesky(A, nb: int = 64, out=None, out_bf16=None, stream=None):
     """Tensor-level convenience: (L, Lh) with A = L L^T factored tile by tile (tiles of nb).
 
@@ -282,7 +311,12 @@ def recurrence_cholesky(A, nb: int = 64, out=None, out_bf16=None, stream=None):
         if tuple(t.shape) != (n, n) or t.dtype != dt or not t.is_contiguous() or t.device != A.device:
             raise ValueError("out / out_bf16 has the wrong shape, dtype, layout or device")
     s = _stream_handle(A, stream)
-    st = cyc_recurrence_cholesky(A.data_ptr(), out.data_ptr(), out_bf16.data_ptr(), n, nb, s)
+    args = A.data_ptr(), out.data_ptr(), out_bf16.data_ptr(), n, nb
+    st = cyc_recurrence_cholesky_in(*args, 0, 0, s)
+    if st == CYC_ERR_WORKSPACE:                   # unaligned, or under capture: in memory that the caller brings
+        wanted = cyc_cholesky_workspace(*args)
+        work = _memory(wanted, A, stream) if wanted else None
+        st = cyc_recurrence_cholesky(*args, s) if work is None else cyc_recurrence_cholesky_in(*args, work.data_ptr(), wanted, s)
     if st != CYC_OK:
         raise CycError(st)
     return out, out_bf16
@@ -312,7 +346,12 @@ def recurrence_trsm(L, B, nb: int = 64, out=None, out_bf16=None, stream=None):
         if tuple(t.shape) != (n, nrhs) or t.dtype != dt or not t.is_contiguous() or t.device != L.device:
             raise ValueError("out / out_bf16 has the wrong shape, dtype, layout or device")
     s = _stream_handle(L, stream)
-    st = cyc_recurrence_trsm(L.data_ptr(), B.data_ptr(), out.data_ptr(), out_bf16.data_ptr(), n, nrhs, nb, s)
+    args = L.data_ptr(), B.data_ptr(), out.data_ptr(), out_bf16.data_ptr(), n, nrhs, nb
+    st = cyc_recurrence_trsm_in(*args, 0, 0, s)
+    if st == CYC_ERR_WORKSPACE:                   # unaligned, or under capture: in memory that the caller brings
+        wanted = cyc_trsm_workspace(args[0], *args[2:])
+        work = _memory(wanted, L, stream) if wanted else None
+        st = cyc_recurrence_trsm(*args, s) if work is None else cyc_recurrence_trsm_in(*args, work.data_ptr(), wanted, s)
     if st != CYC_OK:
         raise CycError(st)
     return out, out_bf16

@@ -212,6 +212,62 @@ int run(const cyc::Problem &p, Kernel k, const cyc::KSplit &split, hipStream_t s
     return CYC_OK;
 }
 
+// The memory of a solve or factorisation that needs `need` bytes, settled before its first launch.  in: the entry point for callers
+// that bring it; copies: it is for padded copies, for which the library has none.  CYC_OK, or the status to return.
+int memory_of(bool in, bool copies, int64_t need, void *given, int64_t given_bytes, hipStream_t s, cyc::WorkspaceHold &hold, void **workspace)
+{
+    *workspace = nullptr;
+    if (need == 0) return CYC_OK;
+    if (in && given) *workspace = given_bytes >= need ? given : nullptr;
+    else if (!in || !(copies || cyc::is_capturing(s))) *workspace = hold.acquire(s, need);
+    return *workspace ? CYC_OK : CYC_ERR_WORKSPACE;
+}
+
+int trsm(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb, void *stream, bool in, void *given,
+         int64_t given_bytes)
+{
+    if (n < 0 || nrhs < 0 || nb < 1 || nb > 128) return CYC_ERR_SHAPE;
+    int64_t nn, nr;
+    if (!mul_ok(n, n, &nn) || !mul_ok(n, nrhs, &nr)) return CYC_ERR_SHAPE;
+    if (n == 0 || nrhs == 0) return CYC_OK;
+    if (!L || !B || !X || !Xh) return CYC_ERR_NULL;
+    if (!workspace_ok(given, given_bytes)) return CYC_ERR_SHAPE;
+    if (overlaps(X, nr * 4, L, nn * 2) || overlaps(X, nr * 4, B, nr * 4) || overlaps(Xh, nr * 2, L, nn * 2) ||
+        overlaps(Xh, nr * 2, B, nr * 4) || overlaps(X, nr * 4, Xh, nr * 2))
+        return CYC_ERR_ALIAS;
+    if (overlaps(given, given_bytes, L, nn * 2) || overlaps(given, given_bytes, B, nr * 4) || overlaps(given, given_bytes, X, nr * 4) ||
+        overlaps(given, given_bytes, Xh, nr * 2))
+        return CYC_ERR_ALIAS;
+    const int64_t padded = in ? cyc::trsm_padded_bytes(L, X, Xh, n, nrhs, nb) : 0;
+    const int64_t need = padded ? padded : cyc::trsm_workspace_bytes(L, X, Xh, n, nrhs, nb);
+    cyc::WorkspaceHold hold;
+    void *workspace;
+    if (int st = memory_of(in, padded > 0, need, given, given_bytes, (hipStream_t)stream, hold, &workspace); st != CYC_OK) return st;
+    const hipError_t e = padded ? cyc::launch_trsm_padded(L, B, X, Xh, n, nrhs, nb, workspace, (hipStream_t)stream)
+                                : cyc::launch_trsm(L, B, X, Xh, n, nrhs, nb, workspace, (hipStream_t)stream);
+    return e == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
+}
+
+int cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *stream, bool in, void *given, int64_t given_bytes)
+{
+    if (n < 0 || nb < 1 || nb > 64 || n > (1 << 22)) return CYC_ERR_SHAPE;
+    int64_t nn;
+    if (!mul_ok(n, n, &nn)) return CYC_ERR_SHAPE;
+    if (n == 0) return CYC_OK;
+    if (!A || !L || !Lh) return CYC_ERR_NULL;
+    if (((uintptr_t)A | (uintptr_t)L) & 3 || ((uintptr_t)Lh & 1) || !workspace_ok(given, given_bytes)) return CYC_ERR_SHAPE;
+    if (overlaps(L, nn * 4, A, nn * 4) || overlaps(Lh, nn * 2, A, nn * 4) || overlaps(L, nn * 4, Lh, nn * 2)) return CYC_ERR_ALIAS;
+    if (overlaps(given, given_bytes, A, nn * 4) || overlaps(given, given_bytes, L, nn * 4) || overlaps(given, given_bytes, Lh, nn * 2))
+        return CYC_ERR_ALIAS;
+    const int64_t padded = in ? cyc::chol_padded_bytes(A, L, Lh, n, nb) : 0, need = padded ? padded : cyc::chol_workspace_bytes(n, nb);
+    cyc::WorkspaceHold hold;
+    void *workspace;
+    if (int st = memory_of(in, padded > 0, need, given, given_bytes, (hipStream_t)stream, hold, &workspace); st != CYC_OK) return st;
+    const hipError_t e = padded ? cyc::launch_chol_padded(A, L, Lh, n, nb, workspace, (hipStream_t)stream)
+                                : cyc::launch_chol(A, L, Lh, n, nb, workspace, (hipStream_t)stream);
+    return e == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
+}
+
 }  // namespace
 
 namespace cyc {
@@ -282,48 +338,39 @@ int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, i
 int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb,
                         void *stream)
 {
-    if (n < 0 || nrhs < 0 || nb < 1 || nb > 128) return CYC_ERR_SHAPE;
-    int64_t nn, nr;
-    if (!mul_ok(n, n, &nn) || !mul_ok(n, nrhs, &nr)) return CYC_ERR_SHAPE;
-    if (n == 0 || nrhs == 0) return CYC_OK;
-    if (!L || !B || !X || !Xh) return CYC_ERR_NULL;
-    if (overlaps(X, nr * 4, L, nn * 2) || overlaps(X, nr * 4, B, nr * 4) || overlaps(Xh, nr * 2, L, nn * 2) ||
-        overlaps(Xh, nr * 2, B, nr * 4) || overlaps(X, nr * 4, Xh, nr * 2))
-        return CYC_ERR_ALIAS;
-    // the inverses of the diagonal tiles live in the per-stream workspace; it is acquired before the first launch
-    cyc::WorkspaceHold hold;
-    if (const int64_t padded = cyc::trsm_padded_bytes(L, X, Xh, n, nrhs, nb))
-        if (void *w = hold.acquire((hipStream_t)stream, padded))
-            return cyc::launch_trsm_padded(L, B, X, Xh, n, nrhs, nb, w, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
-    void *workspace = nullptr;
-    const int64_t need = cyc::trsm_workspace_bytes(L, X, Xh, n, nrhs, nb);
-    if (need > 0) {
-        workspace = hold.acquire((hipStream_t)stream, need);
-        if (!workspace) return CYC_ERR_WORKSPACE;
-    }
-    return cyc::launch_trsm(L, B, X, Xh, n, nrhs, nb, workspace, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
+    return trsm(L, B, X, Xh, n, nrhs, nb, stream, false, nullptr, 0);
+}
+
+int64_t cyc_trsm_workspace(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb)
+{
+    int64_t t;
+    if (n < 1 || nrhs < 1 || nb < 1 || nb > 128 || !mul_ok(n, n, &t) || !mul_ok(n, nrhs, &t)) return 0;
+    const int64_t padded = cyc::trsm_padded_bytes(L, X, Xh, n, nrhs, nb);
+    return padded ? padded : cyc::trsm_workspace_bytes(L, X, Xh, n, nrhs, nb);
+}
+
+int cyc_recurrence_trsm_in(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb,
+                           void *workspace, int64_t workspace_bytes, void *stream)
+{
+    return trsm(L, B, X, Xh, n, nrhs, nb, stream, true, workspace, workspace_bytes);
 }
 
 int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *stream)
 {
-    if (n < 0 || nb < 1 || nb > 64 || n > (1 << 22)) return CYC_ERR_SHAPE;
-    int64_t nn;
-    if (!mul_ok(n, n, &nn)) return CYC_ERR_SHAPE;
-    if (n == 0) return CYC_OK;
-    if (!A || !L || !Lh) return CYC_ERR_NULL;
-    if (((uintptr_t)A | (uintptr_t)L) & 3 || ((uintptr_t)Lh & 1)) return CYC_ERR_SHAPE;
-    if (overlaps(L, nn * 4, A, nn * 4) || overlaps(Lh, nn * 2, A, nn * 4) || overlaps(L, nn * 4, Lh, nn * 2)) return CYC_ERR_ALIAS;
-    cyc::WorkspaceHold hold;
-    if (const int64_t padded = cyc::chol_padded_bytes(A, L, Lh, n, nb))
-        if (void *w = hold.acquire((hipStream_t)stream, padded))
-            return cyc::launch_chol_padded(A, L, Lh, n, nb, w, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
-    void *workspace = nullptr;
-    const int64_t need = cyc::chol_workspace_bytes(n, nb);
-    if (need > 0) {
-        workspace = hold.acquire((hipStream_t)stream, need);
-        if (!workspace) return CYC_ERR_WORKSPACE;
-    }
-    return cyc::launch_chol(A, L, Lh, n, nb, workspace, (hipStream_t)stream) == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
+    return cholesky(A, L, Lh, n, nb, stream, false, nullptr, 0);
+}
+
+int64_t cyc_cholesky_workspace(const void *A, void *L, void *Lh, int64_t n, int64_t nb)
+{
+    if (n < 1 || n > (1 << 22) || nb < 1 || nb > 64) return 0;
+    const int64_t padded = cyc::chol_padded_bytes(A, L, Lh, n, nb);
+    return padded ? padded : cyc::chol_workspace_bytes(n, nb);
+}
+
+int cyc_recurrence_cholesky_in(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, int64_t workspace_bytes,
+                               void *stream)
+{
+    return cholesky(A, L, Lh, n, nb, stream, true, workspace, workspace_bytes);
 }
 
 int64_t cyc_attention_workspace(int64_t batch, int64_t N, int64_t M, int64_t d)

@@ -74,7 +74,7 @@ struct KSplit {
 KSplit choose_ksplit(const Problem &p, bool any);
 inline int64_t ksplit_workspace_bytes(const Problem &p, int ksplit) { return (int64_t)ksplit * p.M * p.N * 4; }
 hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *workspace, hipStream_t s);
-// Device memory for partial products, inverses and padded copies.  WorkspaceHold::acquire: one buffer per (device, stream),
+// Device memory for partial products and inverses.  WorkspaceHold::acquire: one buffer per (device, stream),
 // allocated with hipMalloc on first use, grown when a call needs more, kept until the process ends; nullptr when the
 // allocation fails, or would be needed while the stream is being captured.  The buffer is the holder's until the object
 // goes out of scope: it stays alive until everything that uses it is enqueued.
@@ -124,7 +124,7 @@ hipError_t launch_trsm(const void *L, const void *B, void *X, void *Xh, int64_t 
                        hipStream_t s);
 // Problems whose rows are not 16-byte aligned miss the kernels that work through inverses of the diagonal tiles.  They are
 // solved in copies with rows (and, for the triangle, columns) filled up to a multiple of 8 by those of the identity.
-// *_padded_bytes: device memory for the copies and for the solve itself, 0 where the direct way is taken.
+// *_padded_bytes: device memory, the caller's, for the copies and for the solve itself, 0 where the direct way is taken.
 int64_t trsm_padded_bytes(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb);
 hipError_t launch_trsm_padded(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb, void *workspace, hipStream_t s);
 int64_t chol_padded_bytes(const void *A, void *L, void *Lh, int64_t n, int64_t nb);

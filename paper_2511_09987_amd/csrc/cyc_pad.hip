@@ -4,7 +4,7 @@
 // system of any other size or address is embedded in one that has them, n and nrhs rounded up to multiples of 8,
 //     [ L 0 ] [ X 0 ]   [ B 0 ]            [ A 0 ]
 //     [ 0 I ] [ 0 0 ] = [ 0 0 ]    resp.   [ 0 I ],
-// solved in the workspace and copied out.  The added rows and columns are zeros in every product, so the sums of the
+// solved in memory that the caller brings and copied out.  The added rows and columns are zeros in every product, so the sums of the
 // others are the same.  What bounds it is still the chain of tiles; the copies are two more passes over the operands in
 // three launches.  Before / now, microseconds: solve 1333 x 28 466 / 122, 1984 x 603 428 / 122 (1984 x 608, in no need of copies,
 // 107), 2047 x 4001 - / 190; Cholesky 133 91 / 49, 585 371 / 180 (584: 171), 1001 653 / -, 2047 - / 582.
@@ -13,7 +13,7 @@
 namespace cyc {
 namespace {
 
-constexpr int64_t MAX_COPY_BYTES = (int64_t)256 << 20;   // the workspace stays with the stream: no copies beyond this
+constexpr int64_t MAX_COPY_BYTES = (int64_t)256 << 20;   // what a call asks of its caller at most: no copies beyond this
 
 inline int64_t up8(int64_t x) { return (x + 7) & ~(int64_t)7; }
 inline int64_t up256(int64_t x) { return (x + 255) & ~(int64_t)255; }

@@ -67,20 +67,71 @@ def test_factorisation(n, shift):
     assert torch.equal(L, Lagain)
 
 
-def test_under_capture():
-    """On a stream without memory for the copies the calls take the direct way."""
+@pytest.mark.parametrize("n,nrhs", [(777, 13), (776, 16)])
+def test_under_capture(n, nrhs):
+    """Captured solves and factorisations, aligned and not, have memory of their graph's own and give the eager call's bits: first
+    calls on a stream, two graphs replayed on two streams at once, eager calls on the stream that they were captured on."""
+    import paper_2511_09987_amd as lib
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    sets = [(ws_inputs.tri_lower_bf16(n, 50 + i, 0, DEV), ws_inputs.normal_f32((n, nrhs), 1.0, 50 + i, 1, DEV), ws_inputs.spd_f32(n, 60 + i, 0, DEV))
+            for i in range(2)]
+    work = lambda L, B, A, **on: (*lib.recurrence_trsm(L, B, 64, **on), *lib.recurrence_cholesky(A, 64, **on))
+    want = [work(*s) for s in sets]
+    torch.cuda.synchronize()
+    graphs, outs = [], []
+    for s in sets:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            outs.append(work(*s))
+        graphs.append(graph)
+    for _ in range(3):
+        for out in outs:
+            for t in out:
+                t.zero_()
+        torch.cuda.synchronize()
+        for graph, on in zip(graphs, (stream, other)):
+            with torch.cuda.stream(on):
+                graph.replay()
+        eager = work(*sets[0], stream=stream)
+        torch.cuda.synchronize()
+        for got, ref in ((outs[0], want[0]), (outs[1], want[1]), (eager, want[0])):
+            assert all(torch.equal(g, r) for g, r in zip(got, ref))
+
+
+def test_a_workspace_that_the_caller_brings():
+    """Asked for, refused when too small, misaligned or overlapping, not written past; the plain entry points take none and give
+    the direct way's bits whatever the workspaces of the library hold."""
     import paper_2511_09987_amd as lib
     n, nrhs = 777, 13
-    L = ws_inputs.tri_lower_bf16(n, 50, 0, DEV)
-    B = ws_inputs.normal_f32((n, nrhs), 1.0, 50, 1, DEV)
-    want, _ = lib.recurrence_trsm(L, B, 64)
-    stream = torch.cuda.Stream()
-    graph = torch.cuda.CUDAGraph()
-    torch.cuda.synchronize()
-    with torch.cuda.graph(graph, stream=stream):
-        X, _ = lib.recurrence_trsm(L, B, 64)
-    for _ in range(3):
-        X.zero_()
-        graph.replay()
+    L, B, A = ws_inputs.tri_lower_bf16(n, 50, 0, DEV), ws_inputs.normal_f32((n, nrhs), 1.0, 50, 1, DEV), ws_inputs.spd_f32(n, 60, 0, DEV)
+    X, Xh = torch.zeros((n, nrhs), device=DEV), torch.zeros((n, nrhs), dtype=torch.bfloat16, device=DEV)
+    F, Fh = torch.zeros((n, n), device=DEV), torch.zeros((n, n), dtype=torch.bfloat16, device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+    trsm, chol = (L.data_ptr(), B.data_ptr(), X.data_ptr(), Xh.data_ptr(), n, nrhs, 64), (A.data_ptr(), F.data_ptr(), Fh.data_ptr(), n, 64)
+    for call, args, wanted, results, tensor_level in (
+            (lib.cyc_recurrence_trsm_in, trsm, lib.cyc_trsm_workspace(trsm[0], *trsm[2:]), (X, Xh), lambda: lib.recurrence_trsm(L, B, 64)),
+            (lib.cyc_recurrence_cholesky_in, chol, lib.cyc_cholesky_workspace(*chol), (F, Fh), lambda: lib.recurrence_cholesky(A, 64))):
+        around = torch.full((wanted + 4096,), 77, dtype=torch.uint8, device=DEV)
+        assert wanted > 0 and call(*args, 0, 0, stream) == 6 and call(*args, around.data_ptr(), wanted - 1, stream) == 6
+        assert call(*args, around.data_ptr() + 8, wanted, stream) == 2 and call(*args, args[0], wanted, stream) == 4
         torch.cuda.synchronize()
-        assert bool((X - want).abs().max() <= 2.0 ** -9 * want.abs().max())
+        assert bool((results[0] == 0).all()) and bool((around == 77).all())
+        assert call(*args, around.data_ptr(), wanted, stream) == 0
+        assert bool((around[wanted:] == 77).all()) and all(torch.equal(a, b) for a, b in zip(results, tensor_level()))
+    for call, args, result in ((lib.cyc_recurrence_trsm, trsm, X), (lib.cyc_recurrence_cholesky, chol, F)):
+        cold, warm = torch.cuda.Stream(), torch.cuda.current_stream()
+        torch.cuda.synchronize()
+        assert call(*args, cold.cuda_stream) == 0
+        cold.synchronize()
+        first = result.clone()
+        lib.recurrence_cholesky(ws_inputs.spd_f32(1024, 60, 0, DEV), 64)             # the current stream has a workspace now
+        assert call(*args, warm.cuda_stream) == 0
+        assert torch.equal(result, first)
+
+
+def test_sizes_that_need_no_copy_want_no_more_than_before():
+    import paper_2511_09987_amd as lib
+    at = 1 << 20
+    assert lib.cyc_trsm_workspace(at, at, at, 511, 8, 64) == lib.cyc_trsm_workspace(at, at, at, 1001, 8, 32) == 0
+    assert lib.cyc_trsm_workspace(at, at, at, 1024, 64, 64) == 16 * (64 * 64 * 4 + 56 * 1024 + 4)
+    assert lib.cyc_trsm_workspace(at, at, at, 8191, 8191, 64) == 0 and lib.cyc_cholesky_workspace(at, at, at, 127, 64) == 0
