@@ -174,7 +174,9 @@ int cyc_recurrence_matmul_batched(const void *A, const void *B, void *C,
  *     tiles (16 KiB per 64 rows) and a second copy of the tiles of L next to the diagonal in the order the
  *     kernels read them (56 KiB per 64 rows) in the workspace that the library holds per device and stream (allocated or
  *     grown on the call that first needs it, as for cyc_recurrence_matmul).  Otherwise it allocates nothing.
- *     n == 0 or nrhs == 0: CYC_OK, nothing done.  A zero on the diagonal
+ *     n == 0 or nrhs == 0: CYC_OK, nothing done.  An infinity or NaN in row r of B spoils rows from r on in its column, and,
+ *     where a tile goes through its inverse, the rows above r in that tile as well (cyc_recurrence_trsm_in on a copy: only from r
+ *     on).  A zero on the diagonal
  *     gives infinities or NaNs as IEEE division does, not an error.  Inside the kernels, waves hand solved rows
  *     to one another through LDS with bounded waits; a wait that ever ran out would leave NaN in X and Xh (in
  *     the last tile of the affected panel, and in every row solved after it) rather than plausible wrong values.
@@ -186,7 +188,8 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
 
 /* The same for callers that bring memory.  With nb == 64, n >= 512 and an n, nrhs or pointer that the inverses above do not take
  * (n or nrhs no multiple of 8, an address that is not 16-byte aligned) it solves a copy in `workspace` that they do take, n and nrhs rounded up
- * to multiples of 8, as long as the copy has at most 256 MiB (1333 x 28: 466 us without, 122 so); and nothing is shared with
+ * to multiples of 8, as long as the copy has at most 256 MiB (1333 x 28: 466 us without, 115 so; 5787 x 5787 1.07 ms, and past
+ * the limit 5803 x 5803 3.36 ms); and nothing is shared with
  * other calls on the stream or with graphs captured on it.  cyc_trsm_workspace says how many bytes the call wants (0: none;
  * host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not cleared, free again when the call's
  * work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is enqueued; with
@@ -235,7 +238,8 @@ int cyc_recurrence_trsm_in(const void *L, const void *B, void *X, void *Xh, int6
 int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *stream);
 
 /* The same for callers that bring memory, on the terms of cyc_recurrence_trsm_in: with nb == 64, n > 128 and n no multiple of 8 or
- * a pointer that is not 16-byte aligned it factors a padded copy in `workspace`, of at most 256 MiB (585: 371 us without, 180 so). */
+ * a pointer that is not 16-byte aligned it factors a padded copy in `workspace`, of at most 256 MiB (585: 371 us
+ * without, 182 so; past the limit 5185: 3.95 ms, where 5184 takes 1.53). */
 int64_t cyc_cholesky_workspace(const void *A, void *L, void *Lh, int64_t n, int64_t nb);
 int cyc_recurrence_cholesky_in(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, int64_t workspace_bytes,
                                void *stream);

@@ -120,8 +120,9 @@ int wait_limit();
 
 // workspace: trsm_workspace_bytes() bytes of device memory (inverses of the diagonal tiles), or nullptr: every tile by substitution
 int64_t trsm_workspace_bytes(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb);
+// guard: infinities and NaNs stay out of the rows above them in a tile, as they do without inverses
 hipError_t launch_trsm(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb, void *workspace,
-                       hipStream_t s);
+                       hipStream_t s, bool guard = false);
 // Problems whose rows are not 16-byte aligned miss the kernels that work through inverses of the diagonal tiles.  They are
 // solved in copies with rows (and, for the triangle, columns) filled up to a multiple of 8 by those of the identity.
 // *_padded_bytes: device memory, the caller's, for the copies and for the solve itself, 0 where the direct way is taken.

@@ -98,7 +98,7 @@ hipError_t launch_trsm_padded(const void *L, const void *B, void *X, void *Xh, i
     hipError_t e = launch_kernel(pad_kernel<uint16_t>, grid_of(c.n, c.n), dim3(256), s, (const uint16_t *)L, Lp, n, n, c.n, 1, (uint16_t)0x3f80);
     // (the solve reads a right-hand side before it writes that row of X, as it does with its own running right-hand sides)
     if (e == hipSuccess) e = launch_kernel(pad_kernel<float>, grid_of(c.n, c.nrhs), dim3(256), s, (const float *)B, Xp, n, nrhs, c.nrhs, 0, 0.0f);
-    if (e == hipSuccess) e = launch_trsm(Lp, Xp, Xp, Xhp, c.n, c.nrhs, nb, w + c.total, s);
+    if (e == hipSuccess) e = launch_trsm(Lp, Xp, Xp, Xhp, c.n, c.nrhs, nb, w + c.total, s, true);
     if (e == hipSuccess) e = launch_kernel(unpad_kernel, grid_of(n, nrhs), dim3(256), s, (const float *)Xp, (const uint16_t *)Xhp, (float *)X, (uint16_t *)Xh, nrhs, c.nrhs);
     return e;
 }

@@ -768,7 +768,17 @@ __global__ __launch_bounds__(64) void tri_inverse_kernel(const uint16_t *__restr
 // rows to banks of its own, which leaves the two-way conflict that 512 bytes per instruction cannot avoid.
 __device__ __forceinline__ constexpr int xb_swizzle(int k) { return ((k >> 3) & 3) << 1; }
 
-__device__ __forceinline__ void panel_by_inverses(PanelLds &lds, const uint16_t *__restrict__ L, int64_t n, const float *Rin,
+// GUARD: a product with the inverse multiplies the zeros above its diagonal with the rows below a row, so an infinity or NaN in row
+// c of R makes NaNs of rows above c, which the substitution leaves as they are.  With GUARD the columns of a tile that come out
+// with an infinity or NaN are solved again, by substitution (a column's results then depend on that column alone).  For the
+// solves that run on padded copies, which go by substitution where there is no memory for the copies; it costs them a look at
+// the results and at a flag per tile (1333 x 28 113.9 -> 114.9 us, 2047 x 4001 184 -> 187).
+struct GuardedLds : PanelLds {
+    int spoilt[32];                    // this column of the tile has an infinity or NaN
+    int any;
+};
+template <class Lds>
+__device__ __forceinline__ void panel_by_inverses(Lds &lds, const uint16_t *__restrict__ L, int64_t n, const float *Rin,
                                                   float *X, uint16_t *__restrict__ Xh, int64_t nrhs, int64_t r0, int tiles,
                                                   const float *__restrict__ Winv, int64_t c0, const char *__restrict__ packed)
 {
@@ -777,6 +787,7 @@ __device__ __forceinline__ void panel_by_inverses(PanelLds &lds, const uint16_t 
     // solve it has one column block (w % 2) and two of the four row blocks (w / 2: blocks 0 and 3, or 1 and 2, five 16 x 16
     // blocks of the triangular inverse either way).
     constexpr int NB = 64, NT = 256, NKS = 2 * PANELW - 2, NC = 2;
+    constexpr bool GUARD = std::is_same<Lds, GuardedLds>::value;
     int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, g = lane >> 4;                // (not const: see the loop over tiles)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sc = w & 1, rbA = w >> 1 ? 1 : 0, rbB = w >> 1 ? 2 : 3;                    // the solve's column block and row blocks
@@ -979,6 +990,31 @@ __device__ __forceinline__ void panel_by_inverses(PanelLds &lds, const uint16_t 
                 Xs[row][16 * sc + lq] = v;
                 lds.Xb[t * NB + row][8 * ((2 * sc + (lq >> 3)) ^ xb_swizzle(row)) + (lq & 7)] = round_bf16(v);
             }
+        if constexpr (GUARD) {
+            float zeros = 0.0f;                                        // 0 times what is finite
+#pragma unroll
+            for (int r = 0; r < 4; ++r) zeros = __builtin_fmaf(0.0f, xa[r], __builtin_fmaf(0.0f, xb[r], zeros));
+            if (__builtin_expect(zeros != 0.0f, 0)) lds.spoilt[16 * sc + lq] = lds.any = 1;
+        }
+    };
+    // the columns of tile t that are marked, by substitution from R (every row its terms in ascending order)
+    auto resolve = [&](int t, float(*Xs)[NB + 4]) __attribute__((always_inline)) {
+        if constexpr (GUARD) {
+            const int col = (int)threadIdx.x;
+            if (col < 16 * NC && lds.spoilt[col]) {
+                const uint16_t *Lt = L + (r0 + (int64_t)t * NB) * n + r0 + (int64_t)t * NB;
+#pragma unroll 1
+                for (int r = 0; r < NB; ++r, Lt += n) {
+                    float x = lds.R[r][col];
+#pragma unroll 1
+                    for (int j = 0; j < r; ++j) x = __builtin_fmaf(-widen_bf16(Lt[j]), Xs[j][col], x);
+                    x = x / widen_bf16(Lt[r]);
+                    Xs[r][col] = x;
+                    lds.Xb[t * NB + r][8 * ((col >> 3) ^ xb_swizzle(r)) + (col & 7)] = round_bf16(x);
+                }
+                lds.spoilt[col] = 0;
+            }
+        }
     };
     // Tile t of `count`.  `mine` holds its inverse and `next` the operands of tile t + 1's product; `other` takes the
     // inverse of tile t + 1 and `later` the operands of tile t + 2.  The results stay in LDS (lds.Xs for even t, lds.D,
@@ -1036,6 +1072,13 @@ __device__ __forceinline__ void panel_by_inverses(PanelLds &lds, const uint16_t 
             __builtin_amdgcn_sched_barrier(0);
         });
         __syncthreads();                                               // tile t is solved: R is free, Xs and Xb complete
+        if constexpr (GUARD) {
+            if (__builtin_expect(lds.any != 0, 0)) {                   // uniform
+                resolve(t, Xs);
+                __syncthreads();
+                if (threadIdx.x == 0) lds.any = 0;                     // (the next tile is solved behind another barrier)
+            }
+        }
         if (t + 1 < count) {
             if (dealt)
                 stage_late(t + 1, next, [&](int i) __attribute__((always_inline)) {
@@ -1053,6 +1096,9 @@ __device__ __forceinline__ void panel_by_inverses(PanelLds &lds, const uint16_t 
         }
     };
 
+    if constexpr (GUARD) {
+        if (threadIdx.x < 32) lds.spoilt[threadIdx.x] = lds.any = 0;
+    }
     request(0, op0);
     request_inverse(0, inv0);
     if (tiles > 1) request(1, op1);
@@ -1103,12 +1149,14 @@ __device__ __forceinline__ void panel_by_inverses(PanelLds &lds, const uint16_t 
 
 // The four-wave panel: through the inverses when every tile of the panel passed tri_inverse_kernel's check (Winv and ok
 // start at the panel's first tile; Winv == nullptr: no inverses were computed), by substitution otherwise.
+// Lds: GuardedLds: with the guard of panel_by_inverses.
+template <class Lds>
 __global__ __launch_bounds__(256) void tri_panelw_kernel(const uint16_t *__restrict__ L, int64_t n, const float *Rin,
                                                          float *X, uint16_t *__restrict__ Xh, int64_t nrhs, int64_t r0,
                                                          int tiles, const float *__restrict__ Winv, const int *__restrict__ ok, int limit,
                                                          const char *__restrict__ packed)
 {
-    __shared__ __attribute__((aligned(16))) PanelLds lds;
+    __shared__ __attribute__((aligned(16))) Lds lds;
     bool inverses = Winv != nullptr;
     if (inverses)
         for (int t = 0; t < tiles; ++t) inverses = inverses && ok[t] != 0;          // uniform
@@ -1132,6 +1180,7 @@ struct Solve {
     const float *Winv;      // inverses of the full diagonal tiles, tile after tile, or nullptr
     const int *ok;          // per tile: the inverse may stand in for the substitution
     const char *packed;     // the tiles next to the diagonal in operand order (see PANEL_BAND), with Winv
+    bool guard;             // see GUARD at panel_by_inverses
 };
 
 // the running right-hand side of rows that no GEMM has touched yet is still B; afterwards it lives in X
@@ -1191,7 +1240,7 @@ hipError_t panel(const Solve &v, int64_t r0, int64_t r1)
     const int tiles = (int)((r1 - r0) / 64);
     hipError_t launch_err = hipSuccess;
     if (panelw_ok(v))
-        launch_err = launch_kernel(tri_panelw_kernel, dim3(2 * grid.x), dim3(256), v.s, v.L, v.n, rhs_of(v, r0), v.X, v.Xh, v.nrhs, r0, tiles,
+        launch_err = launch_kernel(v.guard ? tri_panelw_kernel<GuardedLds> : tri_panelw_kernel<PanelLds>, dim3(2 * grid.x), dim3(256), v.s, v.L, v.n, rhs_of(v, r0), v.X, v.Xh, v.nrhs, r0, tiles,
                                    v.Winv ? v.Winv + r0 / 64 * INV_FLOATS : nullptr, v.ok ? v.ok + r0 / 64 : nullptr, wait_limit(), v.packed);
     else
         launch_err = launch_kernel(tri_panel_kernel, grid, dim3(64), v.s, v.L, v.n, rhs_of(v, r0), v.X, v.Xh, v.nrhs, r0, tiles);
@@ -1224,16 +1273,16 @@ static bool inverses_wanted(const Solve &v)
 
 int64_t trsm_workspace_bytes(const void *L, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb)
 {
-    Solve v{(const uint16_t *)L, nullptr, (float *)X, (uint16_t *)Xh, n, nrhs, nb, nullptr, nullptr, nullptr, nullptr};
+    Solve v{(const uint16_t *)L, nullptr, (float *)X, (uint16_t *)Xh, n, nrhs, nb, nullptr, nullptr, nullptr, nullptr, false};
     // per full tile: its inverse, the operand-order copy of the tiles left of it, its verdict
     return inverses_wanted(v) ? (n / 64) * (int64_t)(INV_FLOATS * sizeof(float) + PACK_BYTES_PER_TILE_ROW + sizeof(int)) : 0;
 }
 
 hipError_t launch_trsm(const void *L, const void *B, void *X, void *Xh, int64_t n, int64_t nrhs, int64_t nb, void *workspace,
-                       hipStream_t s)
+                       hipStream_t s, bool guard)
 {
     if (nb < 1 || nb > 128 || (int64_t)((nrhs + 63) / 64) > 0x3fffffff) return hipErrorInvalidValue;
-    Solve v{(const uint16_t *)L, (const float *)B, (float *)X, (uint16_t *)Xh, n, nrhs, nb, s, nullptr, nullptr, nullptr};
+    Solve v{(const uint16_t *)L, (const float *)B, (float *)X, (uint16_t *)Xh, n, nrhs, nb, s, nullptr, nullptr, nullptr, guard};
     if (workspace && inverses_wanted(v)) {
         const int64_t full = n / 64;
         float *Winv = (float *)workspace;

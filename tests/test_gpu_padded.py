@@ -67,6 +67,35 @@ def test_factorisation(n, shift):
     assert torch.equal(L, Lagain)
 
 
+@pytest.mark.parametrize("bad", (float("inf"), float("-inf"), float("nan"), 3.0e38))
+@pytest.mark.parametrize("n,nrhs", [(1333, 28), (1087, 65)])
+def test_infinities_and_nans_spoil_no_row_above_them(n, nrhs, bad):
+    """Row r of a column depends on the rows up to r: above the first bad right-hand side the solution is what it is without it (the
+    tile of the bad row by substitution instead of through the inverse, so to the bounds of test_solve there, and to the
+    bit in the tiles before and in all other columns), and from there on finite exactly where the direct way's is."""
+    import paper_2511_09987_amd as lib
+    L = ws_inputs.tri_lower_bf16(n, 50 + n, 0, DEV)
+    B = ws_inputs.normal_f32((n, nrhs), 1.0, 50 + n, 1, DEV)
+    clean, _ = lib.recurrence_trsm(L, B, 64)
+    spots = {0: 0, 3: 1, 5: 31, 7: 32, 9: 63, 11: 64 + 17, 12: 5 * 64 + 40, 17: 8 * 64, 20: 10 * 64 + 63, 25: n - 30, nrhs - 1: n - 1}
+    Bbad = B.clone()
+    for col, row in spots.items():
+        Bbad[row, col] = bad
+    X, Xh = lib.recurrence_trsm(L, Bbad, 64)
+    assert torch.equal(Xh.view(torch.int16)[X == X], X.to(torch.bfloat16).view(torch.int16)[X == X])
+    direct, direct_h = torch.empty_like(X), torch.empty_like(Xh)
+    assert lib.cyc_recurrence_trsm(L.data_ptr(), Bbad.data_ptr(), direct.data_ptr(), direct_h.data_ptr(), n, nrhs, 64,
+                                   torch.cuda.current_stream().cuda_stream) == 0
+    if bad != 3.0e38:                                          # (a large finite value overflows where its sums happen to)
+        assert torch.equal(X.isfinite(), direct.isfinite())
+    for col in range(nrhs):
+        row = spots.get(col, n)
+        tile = row // 64 * 64
+        assert torch.equal(X[:tile, col], clean[:tile, col])
+        assert bool(X[:row, col].isfinite().all())
+        assert bool((X[tile:row, col] - clean[tile:row, col]).abs().le(2.0 ** -9 * clean.abs().max()).all())
+
+
 @pytest.mark.parametrize("n,nrhs", [(777, 13), (776, 16)])
 def test_under_capture(n, nrhs):
     """Captured solves and factorisations, aligned and not, have memory of their graph's own and give the eager call's bits: first
