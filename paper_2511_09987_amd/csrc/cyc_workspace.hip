@@ -60,7 +60,9 @@ void *static_workspace(int64_t *bytes)
 bool is_capturing(hipStream_t s)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                            // (the caller is answered by what follows, not by the next launch check)
+    return false;
 }
 
 void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
@@ -81,7 +83,10 @@ void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
         slot = {};
         void *p = nullptr;
         const int64_t want = (bytes + ((int64_t)1 << 20) - 1) >> 20 << 20;
-        if (hipMalloc(&p, (size_t)want) != hipSuccess) return nullptr;
+        if (hipMalloc(&p, (size_t)want) != hipSuccess) {
+            (void)hipGetLastError();                    // (reported by the status of the call, or by nothing where it does without)
+            return nullptr;
+        }
         slot.ptr = p;
         slot.bytes = want;
     }

@@ -1,0 +1,115 @@
+"""The per-stream workspaces (cyc_workspace.hip) on the CPU: its host code compiled against a stand-in for the few HIP calls it
+makes, so that allocations can fail, streams can be captured and threads can meet without a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SOURCE = os.path.join(HERE, "..", "paper_2511_09987_amd", "csrc", "cyc_workspace.hip")
+
+STAND_IN = r'''
+#include <hip/hip_runtime.h>
+#define HIP_SYMBOL(x) (&(x))
+#define __align__(n) __attribute__((aligned(n)))
+#include SOURCE
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <set>
+#include <string>
+#include <thread>
+#include <vector>
+#include <chrono>
+
+// ---- the stand-in: memory of `room` bytes, streams 1 .. 9, the calls in the order they came
+static std::mutex mu;
+static std::map<void *, size_t> live;
+static size_t used = 0, room = (size_t)1 << 40;
+static hipError_t last = hipSuccess;
+static std::set<hipStream_t> capturing, odd;           // odd: asking whether it is captured is an error
+static thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+static std::vector<std::string> calls;
+static hipError_t done(hipError_t e) { if (e != hipSuccess) last = e; return e; }
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError() { std::lock_guard<std::mutex> g(mu); hipError_t e = last; last = hipSuccess; return e; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st)
+{
+    std::lock_guard<std::mutex> g(mu);
+    *st = capturing.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return done(odd.count(s) ? hipErrorStreamCaptureImplicit : hipSuccess);
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m) { std::swap(*m, mode); return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t bytes)
+{
+    std::lock_guard<std::mutex> g(mu);
+    calls.push_back("malloc");
+    if (!capturing.empty() && mode != hipStreamCaptureModeRelaxed) return done(hipErrorStreamCaptureUnsupported);
+    if (used + bytes > room) return done(hipErrorOutOfMemory);
+    *p = std::malloc(1);
+    live[*p] = bytes;
+    used += bytes;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    std::lock_guard<std::mutex> g(mu);
+    calls.push_back("free");
+    if (!capturing.empty()) return done(hipErrorStreamCaptureUnsupported);
+    if (!live.count(p)) { std::puts("freed what is not there"); std::exit(1); }
+    used -= live[p];
+    live.erase(p);
+    return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void **p, const void *symbol) { *p = (void *)symbol; return hipSuccess; }
+}
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); std::exit(1); } } while (0)
+static hipStream_t stream(int i) { return (hipStream_t)(uintptr_t)i; }
+static void *get(int s, int64_t bytes) { cyc::WorkspaceHold hold; return hold.acquire(stream(s), bytes); }
+constexpr int64_t MiB = 1 << 20;
+
+static void no_error_is_left()
+{
+    room = 4 * MiB;
+    CHECK(get(1, 8 * MiB) == nullptr);
+    CHECK(last == hipSuccess);
+    odd.insert(stream(2));
+    CHECK(get(2, MiB) != nullptr);
+    CHECK(last == hipSuccess);
+    CHECK(!cyc::is_capturing(stream(2)) && last == hipSuccess);
+}
+int main(int argc, char **argv)
+{
+    const std::string what = argv[1];
+    if (what == "no_error_is_left") no_error_is_left();
+    else return 2;
+    std::puts("ok");
+    return 0;
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not shutil.which("g++"):
+        pytest.skip("no g++")
+    at = tmp_path_factory.mktemp("workspace")
+    main = at / "main.cpp"
+    main.write_text(STAND_IN)
+    out = at / "workspace"
+    p = subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                        f'-DSOURCE="{os.path.abspath(SOURCE)}"', str(main), "-o", str(out)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert p.returncode == 0, p.stdout
+    return str(out)
+
+
+SCENARIOS = ["no_error_is_left"]
+
+
+@pytest.mark.parametrize("scenario", SCENARIOS)
+def test_workspace(program, scenario):
+    p = subprocess.run([program, scenario], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout
