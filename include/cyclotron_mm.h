@@ -34,7 +34,8 @@
  *     first such call on that stream and replaced by a larger one (hipFree +
  *     hipMalloc, which waits for the device; a buffer that a stream capture
  *     has seen is kept) when a later call needs more.  A call holds a lock
- *     from getting it to its last launch.  A call that cannot
+ *     of that workspace from getting it to its last launch: calls from several threads on one stream
+ *     follow one another, and no other stream waits.  A call that cannot
  *     get it, also because a capture forbids the allocation, returns
  *     CYC_ERR_WORKSPACE.  No other entry point allocates device memory;
  *   - for cyc_recurrence_cholesky with n > 16 nb: one extra stream and a few

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <tuple>
 #include <type_traits>
 #include <utility>
@@ -89,7 +90,7 @@ public:
     ~WorkspaceHold();
 
 private:
-    bool held_ = false;
+    std::mutex *held_ = nullptr;
 };
 void *static_workspace(int64_t *bytes);
 bool is_capturing(hipStream_t s);

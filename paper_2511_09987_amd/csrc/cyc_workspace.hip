@@ -1,8 +1,8 @@
 // cyc_workspace.hip -- device memory for the partial products of the k-in-space matmul and for the inverses of the triangular solve (see cyc_internal.h).
 //
 // Two sources.  WorkspaceHold: one hipMalloc'd buffer per (device, stream), so that calls on different streams never share
-// one; grown when a call needs more, never shrunk, kept until the process ends.  The object keeps a lock while it lives, so
-// that of two threads that call on one stream each has all its launches in the stream before the other's begin.
+// one; grown when a call needs more, never shrunk, kept until the process ends.  The object keeps that buffer's lock while it
+// lives, so that of two threads that call on one stream each has all its launches in the stream before the other's begin.
 // static_workspace(): a fixed array in the library's own device image, for callers that must not allocate.
 #include "cyc_internal.h"
 
@@ -24,6 +24,7 @@ struct PerDevice {
     bool tried = false;
     void *scratch_ptr = nullptr;                        // this device's address of `scratch`
     struct Buffer {
+        std::mutex lock;                                // of the call that uses it, and of the fields below
         void *ptr = nullptr;
         int64_t bytes = 0;
         bool captured = false;                          // some graph holds its address
@@ -31,7 +32,7 @@ struct PerDevice {
     std::map<hipStream_t, Buffer> cache;
 };
 PerDevice g_dev[MAX_DEVICES];
-std::mutex g_mutex;
+std::mutex g_mutex;                                     // of g_dev; held for look-ups only
 
 PerDevice *current_device()
 {
@@ -67,36 +68,41 @@ bool is_capturing(hipStream_t s)
 
 void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
 {
-    if (!held_) {
-        g_mutex.lock();
-        held_ = true;
+    if (held_ || bytes <= 0) return nullptr;            // one buffer per object
+    PerDevice::Buffer *slot = nullptr;
+    try {
+        std::lock_guard<std::mutex> lookup(g_mutex);
+        if (PerDevice *d = current_device()) slot = &d->cache[s];   // (stays where it is: nothing is ever taken out of the map)
+    } catch (...) {
     }
-    PerDevice *d = current_device();
-    if (!d || bytes <= 0) return nullptr;
-    auto &slot = d->cache[s];
+    if (!slot) return nullptr;
+    slot->lock.lock();
+    held_ = &slot->lock;
     const bool capturing = is_capturing(s);
-    if (slot.bytes < bytes) {
+    if (slot->bytes < bytes) {
         if (capturing) return nullptr;                  // an allocation would end the capture
         // hipFree waits for the device, so nothing enqueued earlier still uses the old buffer when it goes; a graph that was
         // captured with it may be launched at any time, so that buffer stays
-        if (slot.ptr && !slot.captured) (void)hipFree(slot.ptr);
-        slot = {};
+        if (slot->ptr && !slot->captured) (void)hipFree(slot->ptr);
+        slot->ptr = nullptr;
+        slot->bytes = 0;
+        slot->captured = false;
         void *p = nullptr;
         const int64_t want = (bytes + ((int64_t)1 << 20) - 1) >> 20 << 20;
         if (hipMalloc(&p, (size_t)want) != hipSuccess) {
             (void)hipGetLastError();                    // (reported by the status of the call, or by nothing where it does without)
             return nullptr;
         }
-        slot.ptr = p;
-        slot.bytes = want;
+        slot->ptr = p;
+        slot->bytes = want;
     }
-    slot.captured = slot.captured || capturing;
-    return slot.ptr;
+    slot->captured = slot->captured || capturing;
+    return slot->ptr;
 }
 
 WorkspaceHold::~WorkspaceHold()
 {
-    if (held_) g_mutex.unlock();
+    if (held_) held_->unlock();
 }
 
 }  // namespace cyc

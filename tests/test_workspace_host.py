@@ -81,10 +81,31 @@ static void no_error_is_left()
     CHECK(last == hipSuccess);
     CHECK(!cyc::is_capturing(stream(2)) && last == hipSuccess);
 }
+
+static void a_lock_per_buffer()
+{
+    cyc::WorkspaceHold mine;
+    CHECK(mine.acquire(stream(1), MiB) != nullptr);
+    // another stream's buffer and the fixed array are there meanwhile
+    std::atomic<int> others{0}, same{0};
+    std::thread other([&] { CHECK(get(2, MiB) != nullptr); int64_t n; CHECK(cyc::static_workspace(&n) != nullptr); others = 1; });
+    for (int i = 0; i < 500 && !others; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(10));
+    CHECK(others == 1);
+    other.join();
+    // this stream's is not, until its holder goes
+    std::thread waits([&] { cyc::WorkspaceHold theirs; theirs.acquire(stream(1), 2 * MiB); same = 1; });
+    std::this_thread::sleep_for(std::chrono::milliseconds(200));
+    CHECK(same == 0);
+    mine.~WorkspaceHold();
+    new (&mine) cyc::WorkspaceHold();
+    waits.join();
+    CHECK(same == 1);
+}
 int main(int argc, char **argv)
 {
     const std::string what = argv[1];
     if (what == "no_error_is_left") no_error_is_left();
+    else if (what == "a_lock_per_buffer") a_lock_per_buffer();
     else return 2;
     std::puts("ok");
     return 0;
@@ -106,7 +127,7 @@ def program(tmp_path_factory):
     return str(out)
 
 
-SCENARIOS = ["no_error_is_left"]
+SCENARIOS = ["no_error_is_left", "a_lock_per_buffer"]
 
 
 @pytest.mark.parametrize("scenario", SCENARIOS)
