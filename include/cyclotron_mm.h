@@ -31,13 +31,18 @@
  *     cyc_recurrence_trsm and cyc_recurrence_cholesky with tiles of 64 rows
  *     (see below): one workspace of
  *     device memory per (device, stream), allocated with hipMalloc at the
- *     first such call on that stream and replaced by a larger one (hipFree +
- *     hipMalloc, which waits for the device; a buffer that a stream capture
- *     has seen is kept) when a later call needs more.  A call holds a lock
- *     of that workspace from getting it to its last launch: calls from several threads on one stream
- *     follow one another, and no other stream waits.  A call that cannot
- *     get it, also because a capture forbids the allocation, returns
- *     CYC_ERR_WORKSPACE.  No other entry point allocates device memory;
+ *     first such call on that stream and replaced by a larger one (hipMalloc +
+ *     hipFree, which waits for the device) when a later call needs more.  A
+ *     call holds a lock of that workspace from getting it to its last launch:
+ *     calls from several threads on one stream follow one another, and no other
+ *     stream waits.  A call that cannot get it returns CYC_ERR_WORKSPACE.
+ *     Under stream capture the graph is given the address of the workspace that
+ *     the stream has (or gets then; nothing is freed under a capture, and a
+ *     buffer that a graph was captured with is kept until the process ends):
+ *     launches of that graph must be ordered against other graphs captured on
+ *     that stream and against calls on it that use the workspace.  The _in entry
+ *     points, which take the caller's memory, have no such limit.  No other
+ *     entry point allocates device memory;
  *   - for cyc_recurrence_cholesky with n > 16 nb: one extra stream and a few
  *     events per device (see there); callers that use it are serialised on
  *     the host by a lock for the duration of the enqueueing.

@@ -28,6 +28,7 @@ struct PerDevice {
         void *ptr = nullptr;
         int64_t bytes = 0;
         bool captured = false;                          // some graph holds its address
+        void *former = nullptr;                         // outgrown under a capture, which cannot free it
     };
     std::map<hipStream_t, Buffer> cache;
 };
@@ -58,6 +59,11 @@ void *static_workspace(int64_t *bytes)
     return d->scratch_ptr;
 }
 
+static void release(void *p)
+{
+    if (hipFree(p) != hipSuccess) (void)hipGetLastError();
+}
+
 bool is_capturing(hipStream_t s)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -80,21 +86,37 @@ void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
     held_ = &slot->lock;
     const bool capturing = is_capturing(s);
     if (slot->bytes < bytes) {
-        if (capturing) return nullptr;                  // an allocation would end the capture
-        // hipFree waits for the device, so nothing enqueued earlier still uses the old buffer when it goes; a graph that was
-        // captured with it may be launched at any time, so that buffer stays
-        if (slot->ptr && !slot->captured) (void)hipFree(slot->ptr);
-        slot->ptr = nullptr;
-        slot->bytes = 0;
-        slot->captured = false;
-        void *p = nullptr;
         const int64_t want = (bytes + ((int64_t)1 << 20) - 1) >> 20 << 20;
-        if (hipMalloc(&p, (size_t)want) != hipSuccess) {
+        void *p = nullptr;
+        // A buffer that a graph was captured with stays: the graph may be launched at any time.  Any other goes when the new one is
+        // there, or before where there is no room for both.  (hipFree waits for the device, so nothing enqueued earlier still uses
+        // it.  Under a capture it is left to a later call; the next to grow the buffer is one, as this one will be captured.)
+        const bool old = slot->ptr && !slot->captured;
+        if (capturing) {
+            // an allocation is no part of the capture: this thread says so for its duration
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+            if (hipMalloc(&p, (size_t)want) != hipSuccess) p = nullptr;
+            if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+            if (p && old) slot->former = slot->ptr;
+        } else {
+            if (slot->former) release(slot->former);
+            slot->former = nullptr;
+            if (hipMalloc(&p, (size_t)want) != hipSuccess) p = nullptr;
+            if (old) release(slot->ptr);
+            if (old && !p) {
+                slot->ptr = nullptr;
+                slot->bytes = 0;
+                if (hipMalloc(&p, (size_t)want) != hipSuccess) p = nullptr;
+            }
+        }
+        if (!p) {
             (void)hipGetLastError();                    // (reported by the status of the call, or by nothing where it does without)
             return nullptr;
         }
         slot->ptr = p;
         slot->bytes = want;
+        slot->captured = false;
     }
     slot->captured = slot->captured || capturing;
     return slot->ptr;

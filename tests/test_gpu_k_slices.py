@@ -66,6 +66,29 @@ def test_captured_and_eager_calls_give_the_same_bits(M, K, N):
         assert torch.equal(outs[0], want[0]) and torch.equal(outs[1], want[1]) and torch.equal(eager, want[0])
 
 
+@pytest.mark.parametrize("mode", ("global", "thread_local", "relaxed"))
+def test_plain_entry_points_under_capture_on_a_fresh_stream(mode):
+    """The per-stream workspace can be had under a capture of any mode; the bits are the eager call's."""
+    import paper_2511_09987_amd as lib
+    M, K, N, n, nrhs = 256, 8192, 256, 512, 64
+    A, B = (t[0] for t in operands(torch.bfloat16, 1, M, K, N))
+    L, R, S = ws_inputs.tri_lower_bf16(n, 50, 0, DEV), ws_inputs.normal_f32((n, nrhs), 1.0, 50, 1, DEV), ws_inputs.spd_f32(n, 60, 0, DEV)
+    want = (lib.recurrence_matmul(A, B), *lib.recurrence_trsm(L, R, 64), *lib.recurrence_cholesky(S, 64))
+    C, X, Xh, F, Fh = got = [torch.empty_like(t) for t in want]
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode=mode):
+        assert lib.cyc_recurrence_matmul(A.data_ptr(), B.data_ptr(), C.data_ptr(), M, K, N, lib.CYC_BF16_F32, stream.cuda_stream) == 0
+        assert lib.cyc_recurrence_trsm(L.data_ptr(), R.data_ptr(), X.data_ptr(), Xh.data_ptr(), n, nrhs, 64, stream.cuda_stream) == 0
+        assert lib.cyc_recurrence_cholesky(S.data_ptr(), F.data_ptr(), Fh.data_ptr(), n, 64, stream.cuda_stream) == 0
+    for _ in range(3):
+        for t in got:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, w) for g, w in zip(got, want))
+
+
 def test_a_workspace_that_the_caller_brings():
     """Refused when it is too small, misaligned or overlaps an operand, and asked for where the slices are not the ordinary ones;
     nothing past it is touched."""

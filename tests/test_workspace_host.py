@@ -101,11 +101,49 @@ static void a_lock_per_buffer()
     waits.join();
     CHECK(same == 1);
 }
+static size_t frees() { size_t n = 0; for (auto &c : calls) n += c == "free"; return n; }
+static void growth()
+{
+    void *first = get(1, MiB);
+    CHECK(get(1, 1) == first && get(1, MiB) == first);
+    void *second = get(1, 3 * MiB);
+    CHECK(second && live.count(second) && !live.count(first) && used == 3 * MiB);
+    CHECK(calls == (std::vector<std::string>{"malloc", "malloc", "free"}));
+    room = 5 * MiB;                                      // no room for both: the old one goes first
+    CHECK(get(1, 4 * MiB) != nullptr && used == 4 * MiB);
+    CHECK(get(1, 6 * MiB) == nullptr && used == 0);      // and none at all: refused, and the next call gets what there is
+    CHECK(get(1, MiB) != nullptr && used == MiB);
+}
+static void capture()
+{
+    // first call of a stream, whatever the capture's mode: it gets its memory, and the thread its mode back
+    capturing.insert(stream(1));
+    void *graph1 = get(1, MiB);
+    CHECK(graph1 && mode == hipStreamCaptureModeGlobal && last == hipSuccess);
+    capturing.clear();
+    // a larger call leaves the graph its buffer
+    void *eager = get(1, 2 * MiB);
+    CHECK(eager && live.count(graph1) && frees() == 0);
+    // a larger one under a capture leaves the eager buffer, which may be in use, to a later call
+    capturing.insert(stream(1));
+    void *graph2 = get(1, 3 * MiB);
+    CHECK(graph2 && live.count(eager) && frees() == 0);
+    CHECK(get(1, 4 * MiB) != nullptr && live.count(graph2));
+    capturing.clear();
+    CHECK(get(1, 5 * MiB) && !live.count(eager) && live.count(graph1) && live.count(graph2) && frees() == 1);
+    // no room under a capture: refused, nothing freed, the buffer still there for what fits
+    room = used;
+    capturing.insert(stream(1));
+    void *before = get(1, MiB);
+    CHECK(get(1, 50 * MiB) == nullptr && last == hipSuccess && get(1, MiB) == before && frees() == 1);
+}
 int main(int argc, char **argv)
 {
     const std::string what = argv[1];
     if (what == "no_error_is_left") no_error_is_left();
     else if (what == "a_lock_per_buffer") a_lock_per_buffer();
+    else if (what == "growth") growth();
+    else if (what == "capture") capture();
     else return 2;
     std::puts("ok");
     return 0;
@@ -127,7 +165,7 @@ def program(tmp_path_factory):
     return str(out)
 
 
-SCENARIOS = ["no_error_is_left", "a_lock_per_buffer"]
+SCENARIOS = ["no_error_is_left", "a_lock_per_buffer", "growth", "capture"]
 
 
 @pytest.mark.parametrize("scenario", SCENARIOS)
