@@ -76,7 +76,7 @@
  *   narrow   N <= 16, many rows: A streamed once from memory, B resident; up to 512 blocks of 32 rows in those blocks.
  *   narrowm  M <= 32, B of at least a mebibyte: B streamed once, the rows of
  *            A pass over it ((j,k) in space); few column blocks and long k in blocks of 32 x 32.  (Long k and few
- *            columns, in the caller's memory: mfmak.)
+ *            columns, in cyc_recurrence_matmul_in: mfmak.)
  *   mfmak    unbatched, at most 64 output blocks of 128 x 128, K >= 4096: k in
  *            space; k-slices on different workgroups leave partial sums in the
  *            workspace and a second kernel adds them in ascending slice order.  The slices are a power of two of equal
@@ -131,14 +131,14 @@ int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C,
                                   int64_t M, int64_t K, int64_t N,
                                   int dtype, void *stream);
 
-/* The same as cyc_recurrence_matmul for callers that bring memory.  With that, products with few output blocks and long k that no
- * power of two divides into enough equal slices, and products of few rows with very long k, have k mapped to space as well
- * (18 x 17280 x 784 bf16: 39 us without, 16 so); and nothing is shared with other calls on the stream or with graphs captured on it.
- * cyc_matmul_workspace says how many bytes the call wants (0: it needs none; host only, also 0 for arguments that the call
- * refuses).  workspace: device, 16-byte aligned, not cleared, free again when the call's work on `stream` is done.  With less
- * than that the call returns CYC_ERR_WORKSPACE and nothing is enqueued; with workspace NULL it does so where the slices are not
- * those of cyc_recurrence_matmul or where `stream` is being captured, and is cyc_recurrence_matmul otherwise.  Which kernel runs
- * depends on the problem alone.  Errors otherwise: those of cyc_recurrence_matmul; CYC_ERR_SHAPE also for a
+/* The same as cyc_recurrence_matmul where the partial sums may lie in memory of the caller's, which calls under stream capture
+ * need if their graph is to share nothing with other graphs and calls on the stream.  Products with few output blocks and long k that no
+ * power of two divides into enough equal slices, and products of few rows with very long k, also have k mapped to space here
+ * (18 x 17280 x 784 bf16: 39 us without, 16 so; at most 16 MiB of partial sums).  cyc_matmul_workspace says how many bytes the
+ * call wants (0: it needs none; host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not
+ * cleared, free again when the call's work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is
+ * enqueued.  workspace NULL: the library's per-(device, stream) workspace, or CYC_ERR_WORKSPACE if `stream` is being captured.
+ * Which kernel runs depends on the problem alone.  Errors otherwise: those of cyc_recurrence_matmul; CYC_ERR_SHAPE also for a
  * misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
 int64_t cyc_matmul_workspace(const void *A, const void *B, const void *C, int64_t M, int64_t K, int64_t N, int dtype);
 int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, int64_t K, int64_t N, int dtype,

@@ -235,10 +235,10 @@ def recurrence_matmul(A, B, out=None, stream=None):
     """Tensor-level convenience: C = weight-stationary recurrence of A against B.
 
     A: (M,K) or (batch,M,K); B: (K,N) or (batch,K,N); contiguous CUDA tensors, both
-    torch.bfloat16 (C float32) or both torch.int8 (C int32).  Only allocates C and, where k
-    is mapped to space, memory for the partial products, and forwards pointers to the C ABI on
-    the current (or given) stream.  (Without that memory fewer slices or none are taken, and the
-    fp32 sums are added in another order.)
+    torch.bfloat16 (C float32) or both torch.int8 (C int32).  Only allocates C and, under
+    stream capture, memory for the partial products of a long k, and forwards pointers to the
+    C ABI on the current (or given) stream.  (Where no memory is to be had for those, fewer
+    slices of k or none are taken, and the fp32 sums are added in another order.)
     """
     import torch
     if not (A.is_cuda and B.is_cuda):
@@ -263,7 +263,7 @@ def recurrence_matmul(A, B, out=None, stream=None):
     if batch == 1:
         args = A.data_ptr(), B.data_ptr(), out.data_ptr(), M, K, N, dtype
         st = cyc_recurrence_matmul_in(*args, 0, 0, s)
-        if st == CYC_ERR_WORKSPACE:               # k goes to space, in memory that the caller brings
+        if st == CYC_ERR_WORKSPACE:               # under capture: partial sums in memory of the graph's own
             wanted = cyc_matmul_workspace(*args)
             work = _memory(wanted, A, stream) if wanted else None
             st = cyc_recurrence_matmul(*args, s) if work is None else cyc_recurrence_matmul_in(*args, work.data_ptr(), wanted, s)

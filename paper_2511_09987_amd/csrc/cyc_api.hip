@@ -78,8 +78,8 @@ std::atomic<int> &wait_limit_value()
 
 // Validates and fills `p`.  Returns CYC_OK with *k == K_NONE when there is nothing to do.  *family: the kernel whose part of
 // the dispatch the problem falls into; *k: the kernel that runs (blocks of cyc_uneven.hip stand in for several families).
-// split: filled in for K_MFMAK; any_slices: the caller brings memory, so that k may also be cut where the library's own
-// workspaces are not used for it (see KSplit).
+// split: filled in for K_MFMAK; any_slices: k may be cut into slices of any number and length (see KSplit), which the entry points
+// without a workspace argument do not do.
 int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, int64_t K, int64_t N,
          int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k, Kernel *family, cyc::KSplit *split, bool any_slices)
 {
@@ -139,10 +139,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     if (cyc::prefers_narrowm(*p)) {
         // past 128 k-tiles k goes to space across workgroups (bf16 32 x 17280 x 784 144 us there, 39 in blocks, 17 so)
         const int64_t kt = p->K * es / 128;
-        if (force == K_NONE && any_slices && kt > 128 && p->N <= 4096 && splits()) {
-            split->any = true;
-            return take(K_MFMAK, K_MFMAK);
-        }
+        if (force == K_NONE && any_slices && kt > 128 && p->N <= 4096 && splits()) return take(K_MFMAK, K_MFMAK);
         return take(K_NARROWM, force == K_NONE && cyc::blocks_beat_narrowm(*p) && cyc::supports_uneven(*p) ? K_UNEVEN32 : K_NARROWM);
     }
     // few output blocks, long k: k goes to space (see choose_ksplit)
@@ -323,10 +320,9 @@ int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, i
     int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, true);
     if (st != CYC_OK || k == K_NONE) return st;
     if (k != K_MFMAK) return run(p, k, split, (hipStream_t)stream, GIVEN);
-    if (!workspace) {
-        if (split.any || cyc::is_capturing((hipStream_t)stream)) return CYC_ERR_WORKSPACE;
-        return run(p, k, split, (hipStream_t)stream, CACHED);
-    }
+    // (slices of any length fit 16 MiB, 256 partial blocks of 128 x 128, which a stream's workspace may well keep; under a capture it
+    // would be shared with other graphs, and asking torch for memory on every call costs 3 us of host time)
+    if (!workspace) return cyc::is_capturing((hipStream_t)stream) ? CYC_ERR_WORKSPACE : run(p, k, split, (hipStream_t)stream, CACHED);
     const int64_t es = p.i8 ? 1 : 2;
     if (!workspace_ok(workspace, workspace_bytes)) return CYC_ERR_SHAPE;
     if (overlaps(workspace, workspace_bytes, A, M * K * es) || overlaps(workspace, workspace_bytes, B, K * N * es) ||
@@ -441,7 +437,7 @@ const char *cyc_status_string(int status)
     return "unknown cyc_status";
 }
 
-int cyc_version(void) { return 200; }
+int cyc_version(void) { return 300; }
 
 int cyc_diag_set_wait_limit(int64_t polls)
 {

@@ -69,9 +69,8 @@ struct KSplit {
     int slices;                          // 1: do not split
     int tile;                            // block edge to use, 128 or 256
     int64_t length;                      // of every slice but the last, which may be shorter
-    bool any;                            // not the power of two of equal slices that the problem gets otherwise
 };
-// any: slices of any number and length, for callers that bring the memory; otherwise a power of two of equal ones
+// any: slices of any number and length; otherwise a power of two of equal ones
 KSplit choose_ksplit(const Problem &p, bool any);
 inline int64_t ksplit_workspace_bytes(const Problem &p, int ksplit) { return (int64_t)ksplit * p.M * p.N * 4; }
 hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *workspace, hipStream_t s);

@@ -545,7 +545,7 @@ int choose_mfma_tile(const Problem &p)
 // result is the same bits on every call).
 KSplit choose_ksplit(const Problem &p, bool any)
 {
-    KSplit one{1, 128, p.K, false};
+    const KSplit one{1, 128, p.K};
     if (p.batch != 1 || p.lda || p.ldb || p.ldc || p.Cin || p.kslices || !supports_mfma(p, 128)) return one;
     const int64_t b128 = ((p.M + 127) / 128) * ((p.N + 127) / 128), b256 = ((p.M + 255) / 256) * ((p.N + 255) / 256);
     const int64_t bke = p.i8 ? 128 : 64;
@@ -560,16 +560,16 @@ KSplit choose_ksplit(const Problem &p, bool any)
     // 256 x 256 blocks (one per CU) re-read A and B half as often as 128 x 128 blocks (two per CU) but cost more to
     // start and to finish: take them when they compute little padding, still fill the chip and keep long slices
     const int ks256 = supports_mfma(p, 256) ? slices(b256, 256) : 1;
-    if (b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096) return {ks256, 256, p.K / ks256, false};
+    if (b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096) return {ks256, 256, p.K / ks256};
     const int ks = slices(b128, 256);
     // K need not be a multiple of anything: where the equal slices are less than 3/4 as many as the chip has room for, as many
     // slices as there is room for, of whole k-tiles, the last one with what remains (40 x 17280 x 784 bf16: 110 us in two slices' stead, 14)
     const int64_t nkt = (p.K + bke - 1) / bke, want = std::min<int64_t>(256 / b128, nkt / 8);
     if (any && ks * 4 < want * 3) {
         const int64_t per = (nkt + want - 1) / want;
-        return {(int)((nkt + per - 1) / per), 128, per * bke, true};
+        return {(int)((nkt + per - 1) / per), 128, per * bke};
     }
-    return {ks, 128, p.K / ks, false};
+    return {ks, 128, p.K / ks};
 }
 
 hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *workspace, hipStream_t s)

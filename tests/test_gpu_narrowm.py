@@ -90,6 +90,10 @@ def test_narrowm_dispatch(lib):
     assert name(33, 2048, 2048) != "narrowm"
     assert name(16, 128, 128) != "narrowm"                  # B too small to be worth it
     assert name(8192, 8192, 16, batch=32) == "narrow"       # the mirror-image regime keeps its own kernel
+    # the kernel itself, and where blocks of 32 x 32 stand in for it
+    kernel = lambda M, K, N, batch=1: lib.cyc_kernel_variant(0x100000, 0x20000000, 0x4000000000, batch, M, K, N, M * K, K * N, M * N, lib.CYC_BF16_F32)
+    assert kernel(16, 8192, 8192, batch=32) == kernel(32, 2048, 2048) == kernel(1, 1024, 1024) == "narrowm"
+    assert kernel(16, 8192, 8192) == kernel(17, 4000, 1128) == "uneven32"
 
 
 @pytest.mark.parametrize("mode", ("i8", "bf16"))
