@@ -294,8 +294,10 @@ def recurrence_cholesky(A, nb: int = 64, out=None, out_bf16=None, stream=None):
     """Tensor-level convenience: (L, Lh) with A = L L^T factored tile by tile (tiles of nb).
 
     A: (n,n) torch.float32 contiguous CUDA tensor, symmetric positive definite (its lower triangle is what counts).
-    Allocates L (fp32, zero above the diagonal) and Lh (bf16, both triangles filled) unless given and forwards
-    pointers to the C ABI on the current (or given) stream.
+    Allocates L (fp32, zero above the diagonal) and Lh (bf16, both triangles filled) unless given, and memory for
+    the padded copy of an unaligned matrix or under stream capture, and forwards pointers to the C ABI on the
+    current (or given) stream.  (Where that memory is not to be had an unaligned matrix is factored in place, more
+    slowly and with other last bits.)
     """
     import torch
     if not A.is_cuda:
@@ -326,7 +328,9 @@ def recurrence_trsm(L, B, nb: int = 64, out=None, out_bf16=None, stream=None):
     """Tensor-level convenience: (X, Xh) with L X = B solved tile by tile (tiles of nb rows).
 
     L: (n,n) torch.bfloat16, B: (n,nrhs) torch.float32, contiguous CUDA tensors.  Allocates X (fp32)
-    and Xh (bf16) unless given and forwards pointers to the C ABI on the current (or given) stream.
+    and Xh (bf16) unless given, and memory for the padded copy of an unaligned system or under stream
+    capture, and forwards pointers to the C ABI on the current (or given) stream.  (Where that memory is
+    not to be had an unaligned system is solved in place, more slowly and with other last bits.)
     """
     import torch
     if not (L.is_cuda and B.is_cuda):
