@@ -138,7 +138,8 @@ int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C,
  * call wants (0: it needs none; host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not
  * cleared, free again when the call's work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is
  * enqueued.  workspace NULL: the library's per-(device, stream) workspace, or CYC_ERR_WORKSPACE if `stream` is being captured.
- * Which kernel runs depends on the problem alone.  Errors otherwise: those of cyc_recurrence_matmul; CYC_ERR_SHAPE also for a
+ * Which kernel runs depends on the problem alone (cyc_kernel_name and cyc_kernel_variant answer for cyc_recurrence_matmul).
+ * Errors otherwise: those of cyc_recurrence_matmul; CYC_ERR_SHAPE also for a
  * misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
 int64_t cyc_matmul_workspace(const void *A, const void *B, const void *C, int64_t M, int64_t K, int64_t N, int dtype);
 int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, int64_t K, int64_t N, int dtype,

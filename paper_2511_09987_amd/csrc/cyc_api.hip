@@ -319,12 +319,12 @@ int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, i
     cyc::KSplit split;
     int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, true);
     if (st != CYC_OK || k == K_NONE) return st;
+    if (!workspace_ok(workspace, workspace_bytes)) return CYC_ERR_SHAPE;
     if (k != K_MFMAK) return run(p, k, split, (hipStream_t)stream, GIVEN);
     // (slices of any length fit 16 MiB, 256 partial blocks of 128 x 128, which a stream's workspace may well keep; under a capture it
     // would be shared with other graphs, and asking torch for memory on every call costs 3 us of host time)
     if (!workspace) return cyc::is_capturing((hipStream_t)stream) ? CYC_ERR_WORKSPACE : run(p, k, split, (hipStream_t)stream, CACHED);
     const int64_t es = p.i8 ? 1 : 2;
-    if (!workspace_ok(workspace, workspace_bytes)) return CYC_ERR_SHAPE;
     if (overlaps(workspace, workspace_bytes, A, M * K * es) || overlaps(workspace, workspace_bytes, B, K * N * es) ||
         overlaps(workspace, workspace_bytes, C, M * N * 4))
         return CYC_ERR_ALIAS;

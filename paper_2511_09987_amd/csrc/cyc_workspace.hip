@@ -102,12 +102,14 @@ void *WorkspaceHold::acquire(hipStream_t s, int64_t bytes)
         } else {
             if (slot->former) release(slot->former);
             slot->former = nullptr;
-            if (hipMalloc(&p, (size_t)want) != hipSuccess) p = nullptr;
-            if (old) release(slot->ptr);
-            if (old && !p) {
+            const hipError_t e = hipMalloc(&p, (size_t)want);
+            if (e != hipSuccess) p = nullptr;
+            if (old && (p || e == hipErrorOutOfMemory)) {   // (other refusals, a capture elsewhere say, leave it as it is)
+                release(slot->ptr);
                 slot->ptr = nullptr;
                 slot->bytes = 0;
-                if (hipMalloc(&p, (size_t)want) != hipSuccess) p = nullptr;
+                if (!p) (void)hipGetLastError();
+                if (!p && hipMalloc(&p, (size_t)want) != hipSuccess) p = nullptr;
             }
         }
         if (!p) {

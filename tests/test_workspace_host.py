@@ -110,9 +110,14 @@ static void growth()
     CHECK(second && live.count(second) && !live.count(first) && used == 3 * MiB);
     CHECK(calls == (std::vector<std::string>{"malloc", "malloc", "free"}));
     room = 5 * MiB;                                      // no room for both: the old one goes first
-    CHECK(get(1, 4 * MiB) != nullptr && used == 4 * MiB);
+    CHECK(get(1, 4 * MiB) != nullptr && used == 4 * MiB && last == hipSuccess);
     CHECK(get(1, 6 * MiB) == nullptr && used == 0);      // and none at all: refused, and the next call gets what there is
     CHECK(get(1, MiB) != nullptr && used == MiB);
+    // refused for another reason, a capture on another stream: the buffer stays
+    capturing.insert(stream(9));
+    const size_t before = frees();
+    void *kept = get(1, MiB);
+    CHECK(get(1, 2 * MiB) == nullptr && last == hipSuccess && get(1, MiB) == kept && frees() == before);
 }
 static void capture()
 {
