@@ -230,7 +230,7 @@ int cyc_recurrence_trsm_in(const void *L, const void *B, void *X, void *Xh, int6
  * nb: tile size, 1 <= nb <= 64.  The MFMA kernels serve the updates when n and nb are multiples of 8 and the
  *     pointers are 16-byte aligned; otherwise the shape-agnostic kernels do.
  * stream: hipStream_t or NULL.  The call enqueues a sequence of kernels on it and returns.  With nb == 64 and
- *     n >= 128 it keeps the inverses of the diagonal tiles (16 KiB per 64 rows) and a copy of one diagonal tile (16 KiB)
+ *     n >= 128 it keeps the inverses of two diagonal tiles and a copy of one (16 KiB each)
  *     in the workspace that the library holds per device and stream (allocated or grown on the call that first needs it); otherwise it allocates no
  *     device memory.  For n > 16 nb part of the work is enqueued on a second stream that the library creates per device
  *     on first use (default priority, kept until the process ends) and that is forked from and joined back into
@@ -323,9 +323,9 @@ int cyc_diag_mfma_ceiling(int dtype, int mfma_shape, int64_t iters, void *sink, 
 int cyc_diag_issue_mix(int mfma_shape, int other_kind, int others_per_round, int waves_per_simd, int64_t iters, void *sink,
                        double *ops, void *stream);
 
-/* Test aid.  Inside the tile kernels of the triangular solve and of the Cholesky factorisation waves hand work to one
+/* Test aid.  Inside the tile kernels of the triangular solve waves hand work to one
  * another through counters in LDS; every such wait is bounded, 2^20 polls, and a wave whose wait runs out goes on and
- * marks the tile, which is then written as NaN (and, in the factorisation, its inverse as unusable): NaNs instead of a
+ * marks the tile, which is then written as NaN: NaNs instead of a
  * hung GPU or of plausible wrong numbers, should that code ever be broken.  This call sets the bound for the launches
  * enqueued after it (process-wide; polls: 1 .. 2^30, 0 restores the default), so that the behaviour on a run-out wait
  * can be looked at without breaking the code.  CYC_ERR_SHAPE outside that range. */

@@ -12,6 +12,14 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-i
          # keep hipcc from forming packed fp32 instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# The tile kernels of the factorisation have a compute unit to themselves (LDS), so the compiler counts on 512 registers and puts
+# the accumulators of MFMAs, whose every value they use in vector instructions, into accumulation registers and moves them over.
+FILE_FLAGS = {"cyc_chol.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+
+
+def flags(src: str):
+    return [*FLAGS, *FILE_FLAGS.get(os.path.basename(src), [])]
+
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
@@ -32,7 +40,7 @@ def check_async_reads(src: str) -> None:
     spec.loader.exec_module(checker)
     with tempfile.TemporaryDirectory() as tmp:
         asm = os.path.join(tmp, "device.s")
-        p = subprocess.run(["hipcc", *FLAGS, "-S", "--cuda-device-only", src, "-o", asm],
+        p = subprocess.run(["hipcc", *flags(src), "-S", "--cuda-device-only", src, "-o", asm],
                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         if p.returncode != 0:
             raise RuntimeError(f"hipcc -S failed on {src}:\n{p.stdout}")
@@ -50,7 +58,7 @@ def build(verbose: bool = False) -> str:
     for src in sources():
         obj = os.path.join(CSRC, os.path.basename(src)[:-4] + ".o")
         objs.append(obj)
-        procs.append((src, subprocess.Popen(["hipcc", *FLAGS, "-c", src, "-o", obj],
+        procs.append((src, subprocess.Popen(["hipcc", *flags(src), "-c", src, "-o", obj],
                                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()

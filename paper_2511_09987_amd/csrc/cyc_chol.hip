@@ -13,22 +13,16 @@
 // Lh[k0:k1, c0:c1].  Panels are taken in groups of eight (see launch_chol):
 //   1. at the first panel of a group, one launch of the GEMM kernel takes all tiles left of the group out of the
 //      group's columns: epilogue A - product into L[g0:, g0:g0+512], which holds S until solved;
-//   2. per panel, CHOL of the diagonal tile: one lane per row, columns left to right, what a lane needs of other
-//      rows read from the tile in LDS, where every lane writes its finished columns;
-//   3. per panel, TRSM of the rows below: rows do not depend on one another, so one lane per row (64 rows per
-//      workgroup) runs the off-diagonal line of the scalar recurrence against L_jj in LDS, and writes its row of
-//      L, of Lh, and the mirrored column of Lh.
-//   Both tile kernels are workgroups of four waves: all four move the tile and first take the terms of the group's
-//   own earlier panels out of it with MFMAs of their own (TileProduct), which is far cheaper than a launch of the
-//   GEMM kernel for so short a k range; the first wave then runs the recurrence.  Step 2 for panel j + 1 is done by
+//   2. per panel, CHOL of the diagonal tile in LDS (factor_tile64 in cyc_wave.h);
+//   3. per panel, TRSM of the rows below, 64 to a workgroup: rows do not depend on one another; the off-diagonal line of the
+//      scalar recurrence against L_jj in LDS (solve_rows16), written as rows of L and of Lh and as mirrored columns of Lh.
+//   Both tile kernels are workgroups of four waves, which first take the terms of the group's own earlier panels out of
+//   the tile with MFMAs of their own (TileProduct), which is far cheaper than a launch of the
+//   GEMM kernel for so short a k range; each wave then has sixteen rows of the tile.  Step 2 for panel j + 1 is done by
 //   the first workgroup of step 3 for panel j (the rows that become tile (j+1, j)), in the same launch, also across
 //   a group boundary: the chain diagonal tile - tile below it - next diagonal tile is what the whole factorisation
-//   waits for.  On that chain
-//   - the diagonal tile's recurrence is shared by two waves: the first keeps the corners (square roots, divisions)
-//     and the multiply-adds next to them, the second takes every finished block of four columns out of the columns
-//     further right on the matrix cores (trailing_update64);
-//   - the TRSM of the tile below a well-conditioned diagonal tile is a product with the diagonal tile's inverse,
-//     which a third wave computes beside the factorisation of the tile (inverse_follow64).
+//   waits for.  On that chain the TRSM of the tile below a well-conditioned diagonal tile is a product with the diagonal
+//   tile's inverse, which waves that are done with their rows compute beside the factorisation of the tile (InverseColumns).
 // Inside a tile column everything is fp32 on unrounded values, in the order of the scalar recurrence:
 // t = S_rc; t = fma(-L_rk, L_ck, t) for k ascending; then sqrt on the diagonal, IEEE division below it.  Four such steps
 // are one v_mfma_f32_16x16x4_f32: that instruction adds its products in ascending k with one rounding each.
@@ -72,20 +66,7 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t)); }
 
-// The same for the diagonal tile, where row c of L is what lane c has just computed.  The chains of block b read the
-// rows 4b .. 4b+3 of L from LDS, where every lane writes its finished columns; the step over the columns of block k4 can
-// be read once the corner of block k4 is written.
-// The first wave takes only the steps close to the diagonal itself: the tile's columns in groups of 16 (four blocks),
-// group G handed to it by a second wave (trailing_update64) with all steps up to block 4G - 2 taken out already, on
-// the matrix cores.  Of block b it runs the steps first_k(b) .. b - 1: the last one (k4 = b - 1) is requested right
-// after the corner of block b - 1, the one before it is held back to cover that request's latency, the others (at most
-// two) run beside the corner of block b - 1, one after each of its first columns; all but the last are requested when
-// that corner starts, which is after block b - 2 was written.
-constexpr int first_k(int b) { return b < 4 ? 0 : 4 * (b / 4) - 1; }
-constexpr int own_steps(int b) { return b - first_k(b); }
-constexpr int LDF = 20;        // row stride of the hand-over buffer: 16 columns, and 16 consecutive rows on distinct banks
-
-constexpr int NT = 256;        // threads of a tile kernel: four waves move tiles and multiply, the first runs the recurrence
+constexpr int NT = 256;        // threads of a tile kernel: four waves
 
 // A 64-row tile of a row-major fp32 matrix (row stride ld) into LDS, by the workgroup: rows 0..nrows-1 (rows past that
 // repeat the last one), columns 0..cols-1.  All loads of a thread are in flight together.
@@ -149,19 +130,20 @@ struct TileLoad {
 
 // The reverse for a full-width tile held in LDS: rows 0..nrows-1 to the fp32 matrix L and, rounded, to the bfloat16
 // matrix Lh (both with row stride ld), 16 bytes per thread and store.  False when shape or alignment do not allow it.
-// LOWER: the tile is a diagonal tile; L gets zeros above the diagonal (Lh gets what the tile holds there).
-template <bool LOWER, int NTH = NT>
+// LOWER: the tile is a diagonal tile; L gets zeros above the diagonal (Lh gets what the tile holds there).  PARTS: 1: L, 2: Lh,
+// 3: both; FIRST: L from that row on only.
+template <bool LOWER, int NTH = NT, int PARTS = 3, int FIRST = 0>
 __device__ __forceinline__ bool store_tile(const float (*src)[LDT], float *L, uint16_t *Lh, int64_t ld, int nrows, int cols,
                                            int tid)
 {
     if (cols != NBMAX || ld % 8 != 0 || ((uintptr_t)L & 15) != 0 || ((uintptr_t)Lh & 15) != 0) return false;
     // all LDS reads first, without conditions (rows past nrows hold copies of the last one), then the stores: a read
     // inside the row condition would be waited for on the spot, once per row group
-    constexpr int PL = NBMAX * 16 / NTH, PH = NBMAX * 8 / NTH;      // tid counts the NTH threads that take part
-    f32x4 v[PL];
+    constexpr int PL = PARTS & 1 ? (NBMAX - FIRST) * 16 / NTH : 0, PH = PARTS & 2 ? NBMAX * 8 / NTH : 0;      // tid counts the NTH threads that take part
+    f32x4 v[PL + 1];
 #pragma unroll
     for (int i = 0; i < PL; ++i) {
-        const int r = NTH / 16 * i + (tid >> 4);
+        const int r = FIRST + NTH / 16 * i + (tid >> 4);
         v[i] = *(const f32x4 *)&src[r][4 * (tid & 15)];
         if (LOWER) {
 #pragma unroll
@@ -169,7 +151,7 @@ __device__ __forceinline__ bool store_tile(const float (*src)[LDT], float *L, ui
         }
     }
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 h[PH];
+    u32x4 h[PH + 1];
 #pragma unroll
     for (int i = 0; i < PH; ++i) {
         const int r = NTH / 8 * i + (tid >> 3);
@@ -181,7 +163,7 @@ __device__ __forceinline__ bool store_tile(const float (*src)[LDT], float *L, ui
     }
 #pragma unroll
     for (int i = 0; i < PL; ++i) {
-        const int r = NTH / 16 * i + (tid >> 4);
+        const int r = FIRST + NTH / 16 * i + (tid >> 4);
         if (r < nrows) *(f32x4 *)(L + (int64_t)r * ld + 4 * (tid & 15)) = v[i];
     }
 #pragma unroll
@@ -338,373 +320,41 @@ struct TileProductT {
 
 typedef TileProductT<KMAX> TileProduct;
 
-// ---- The inverse of a diagonal tile, computed beside its factorisation.
-// L_ij = TRSM(S_ij, L_jj) for the tile right below the diagonal tile is on the path from one diagonal tile to the
-// next: 64 dependent columns.  With W = L_jj^-1 at hand it is the product S_ij W^T on the matrix cores, which has no
-// chain; and W can be had off that path: while the first wave factors the tile, the second follows it four rows
-// behind, lane j solving L_jj y = e_j by the substitution of the triangular solve (the step list of cyc_wave.h: rows
-// 4b .. 4b+3 of L_jj are final once the factorisation has finished block b, which it announces through a counter in
-// LDS).  As in the triangular solve the product stands in for the substitution only when the tile is well
-// conditioned: the follower leaves ||W||_1 ||L_jj||_1 <= 8 (and everything finite, and no wait expired) as a verdict
-// beside W.  W is stored in the order in which the product wants its operand, the one of the triangular solve's
-// inverses: entry (r, j) in piece 4 (r / 16) + j / 16 of 1 KiB, at [(r % 16) + 16 (j % 4)][(j / 4) % 4].
-constexpr int W_FLOATS = 64 * 64;
-constexpr float W_NORM_LIMIT = 8.0f;
-
-// maximum over the 64 lanes of a wave, in every lane
-__device__ __forceinline__ float wave_max64(float v)
-{
-    auto dpp = [](float x, auto ctrl) __attribute__((always_inline)) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
-    };
-    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0xB1>{}));      // quad_perm 1,0,3,2
-    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x4E>{}));      // quad_perm 2,3,0,1
-    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
-    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x140>{}));     // row_mirror: the maximum of each row of 16
-    const unsigned u = __builtin_bit_cast(unsigned, v);
-    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const unsigned a0 = a[0], a1 = a[1];
-    const unsigned m = __builtin_bit_cast(unsigned, __builtin_fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
-    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-    const unsigned b0 = b[0], b1 = b[1];
-    return __builtin_fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
-}
-
-// What the waves of a diagonal tile's factorisation pass to one another in LDS.
-constexpr int LDY = 80;        // row stride of Y: 64 columns, and four consecutive rows on disjoint banks
-struct DiagLds {
-    float F[NBMAX][LDF];       // a group of 16 columns on its way from the second wave to the first (trailing_update64)
-    float Y[16][LDY];          // the follower's rows of W of the current group of 16 (inverse_follow64)
-    int sync[3];               // blocks of four columns finished; groups handed over; a wait ran out (trailing_update64)
-};
-
-// The follower: one wave computes W = L_jj^-1 beside the factorisation, in the order in which its work becomes
-// available.  T holds S above the factorisation's progress and L below it; *ready counts the blocks of four columns the
-// factorisation has finished.  Block k brings the columns 4k .. 4k+3 of every row of L_jj: the follower then solves
-// the rows 4k .. 4k+3 of L_jj W = I (their 4 x 4 corner is complete with that block) and takes them out of all rows
-// below at once, so that after the factorisation's last block only a corner is left to do.  The running right-hand
-// side is kept in the accumulator layout of v_mfma_f32_16x16x4_f32 (the ten 16 x 16 blocks on and below the block
-// diagonal: register r of lane l is row 16 rb + 4 (l/16) + r, column 16 cb + l%16), so that taking four rows out of
-// the rows below is one MFMA per block: A operand -L_jj[16 rb + l%16][4k + l/16], straight from T; B operand
-// W[4k + l/16][16 cb + l%16], which crosses LDS (Y) from the 16 lanes per column block that have just solved it.  Y
-// also collects the 16 rows of a group, which go out to W in the operand order of the product that uses them, 1 KiB
-// pieces as 16-byte stores.  Every read of T here is of columns of block k, behind the gate of block k.
-// Reciprocals of the diagonal by estimate and one Newton step: W is only ever used as an approximation whose error the
-// check at the end bounds.
-// Not inlined, and its LDS operands passed as addresses: inside diag_rest it raised that kernel's register count from 228
-// to 369 and put the factorisation's own values into accumulation registers, 3k cycles on the path per tile.
-__device__ __attribute__((noinline)) void inverse_follow64(uint32_t T_in_lds, uint32_t Y_in_lds, uint32_t ready_in_lds, int lane, int limit,
-                                                           float *__restrict__ W, int *__restrict__ ok)
-{
-    CYC_LDS const float *const T = (CYC_LDS const float *)(uintptr_t)T_in_lds;
-    CYC_LDS float *const Y = (CYC_LDS float *)(uintptr_t)Y_in_lds;              // [16][LDY]
-    CYC_LDS int *const ready = (CYC_LDS int *)(uintptr_t)ready_in_lds;
-    // (as a pointer to global memory: through the generic pointer of a function that is not inlined the stores would be
-    // flat instructions, which count as LDS operations too and complete out of order with them, and every wait for
-    // an LDS read below would become a wait for all of them)
-    typedef __attribute__((address_space(1))) f32x4 global_f32x4;
-    global_f32x4 *const out = (global_f32x4 *)W + lane;
-    const int i = lane & 15, g = lane >> 4;
-
-    bool expired = false;
-    auto gate = [&](int b) __attribute__((always_inline)) {
-        int polls = 0;
-        while (__hip_atomic_load(ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= b) {
-            if (++polls >= limit) {
-                expired = true;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-    };
-    auto idx = [](int rb, int cb) __attribute__((always_inline)) { return rb * (rb + 1) / 2 + cb; };
-    f32x4 t[10];                                               // the running right-hand side: the identity to begin with
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int cb = 0; cb <= rb; ++cb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) t[idx(rb, cb)][r] = rb == cb && 4 * g + r == i ? 1.0f : 0.0f;
-    float colsum_L = 0.0f, colsum_W[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    unrolled<NBLK>([&](auto index) __attribute__((always_inline)) {
-        constexpr int k = decltype(index)::value, R = k / 4, gk = k % 4;
-        gate(k);
-        // the block's corner of L_jj, the lane's own column of it (for ||L_jj||_1), and the block's columns of the rows
-        // below as stationary operands
-        f32x4 qc[4];
-        float mine[4], xm[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            qc[j] = *(CYC_LDS const f32x4 *)&T[(4 * k + j) * LDT + 4 * k];
-            mine[j] = T[(4 * k + j) * LDT + lane];
-        }
-#pragma unroll
-        for (int rb = (gk == 3 ? R + 1 : R); rb < 4; ++rb) xm[rb] = -T[(16 * rb + i) * LDT + 4 * k + g];
-        float rinv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            colsum_L += 4 * k + j >= lane ? __builtin_fabsf(mine[j]) : 0.0f;
-            const float d = qc[j][j], r0 = __builtin_amdgcn_rcpf(d);
-            rinv[j] = __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);
-        }
-        // rows 4k .. 4k+3 of W: in the lanes with l/16 = k%4 the registers of row block R are exactly those rows; the
-        // other lanes compute along on rows that are not ready
-        f32x4 y[4];
-#pragma unroll
-        for (int cb = 0; cb <= R; ++cb) {
-            const f32x4 rhs = t[idx(R, cb)];
-            float xn[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float v = rhs[j];
-#pragma unroll
-                for (int e = 0; e < j; ++e) v = __builtin_fmaf(qc[j][e], xn[e], v);
-                y[cb][j] = v * rinv[j];
-                xn[j] = -y[cb][j];
-            }
-        }
-        if (g == gk) {                                         // (one branch per block; the stores differ by constants only)
-#pragma unroll
-            for (int cb = 0; cb <= R; ++cb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    colsum_W[cb] += __builtin_fabsf(y[cb][j]);
-                    Y[(4 * gk + j) * LDY + 16 * cb + i] = y[cb][j];
-                }
-        }
-        // and out of every row below (of row block R, too: its rows up to 4k+3 are not used again)
-        // (pinned here: the compiler otherwise moves all these additions, with their operands, to the end of the function,
-        // behind the factorisation's last block)
-        asm volatile("" : "+v"(colsum_L), "+v"(colsum_W[0]), "+v"(colsum_W[1]), "+v"(colsum_W[2]), "+v"(colsum_W[3]));
-        constexpr int first_rb = gk == 3 ? R + 1 : R;          // (with its last four rows a row block is finished)
-        if (first_rb < 4) {
-            float yb[4];
-#pragma unroll
-            for (int cb = 0; cb <= R; ++cb) yb[cb] = Y[(4 * gk + g) * LDY + 16 * cb + i];
-#pragma unroll
-            for (int rb = first_rb; rb < 4; ++rb)
-#pragma unroll
-                for (int cb = 0; cb <= R; ++cb) t[idx(rb, cb)] = __builtin_amdgcn_mfma_f32_16x16x4f32(xm[rb], yb[cb], t[idx(rb, cb)], 0, 0, 0);
-        }
-        if (gk == 3) {
-            // rows 16 R .. 16 R + 15 are complete: piece (R, cb) in the order in which the product wants its operand,
-            // lane l: W[16 R + l%16][16 cb + 4 q + l/16], q = 0 .. 3
-#pragma unroll
-            for (int cb = 0; cb <= R; ++cb) {
-                f32x4 piece;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) piece[q] = Y[i * LDY + 16 * cb + 4 * q + g];
-                out[(4 * R + cb) * 64] = piece;
-            }
-        }
-    });
-    // ||W||_1: the column sums lie in four parts, one per l/16: add the lanes 16, 32 and 48 apart
-    float colsum = 0.0f;
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-        const unsigned u = __builtin_bit_cast(unsigned, colsum_W[cb]);
-        const auto h = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-        const unsigned h0 = h[0], h1 = h[1];
-        const unsigned m = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1));
-        const auto f = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-        const unsigned f0 = f[0], f1 = f[1];
-        const float sum = __builtin_bit_cast(float, f0) + __builtin_bit_cast(float, f1);
-        colsum = sum > colsum || sum != sum ? sum : colsum;                    // (keeps a NaN)
-    }
-    const float a = wave_max64(colsum_L), c = wave_max64(colsum);
-    // (a NaN anywhere would be dropped by the maxima: every lane checks its own sums)
-    const bool fine = colsum_L == colsum_L && colsum == colsum && a * c <= W_NORM_LIMIT && !expired;
-    const bool all_fine = __builtin_amdgcn_ballot_w64(!fine) == 0;
-    if (lane == 0) *ok = all_fine ? 1 : 0;
-}
-
-// The second wave of the diagonal tile's factorisation.  It keeps the columns 16 .. 63 of the tile (the six 16 x 16
-// blocks on and below the block diagonal) in accumulator layout and takes block after block of finished columns out of
-// them as soon as the first wave announces it: S_rc <- fma(-L_rk, L_ck, S_rc) for the four k of a block is one
-// v_mfma_f32_16x16x4_f32 per 16 x 16 block, which adds its four products in ascending k with one rounding each, the bits of
-// the scalar chain (checked against it on 10^7 random elements per exponent range, denormal products included; the
-// parity tests on integer and real data cover it as well).  Column group G goes to the first wave, through F, when block
-// 4G - 2 is out of it; from then on that group is the first wave's.
-// sync: [0] blocks finished by the first wave, [1] groups handed over, [2] set when a bounded wait ran out.
-__device__ __attribute__((noinline)) void trailing_update64(uint32_t T_in_lds, uint32_t F_in_lds, uint32_t sync_in_lds, int lane, int limit)
-{
-    CYC_LDS const float *const T = (CYC_LDS const float *)(uintptr_t)T_in_lds;
-    CYC_LDS float *const F = (CYC_LDS float *)(uintptr_t)F_in_lds;
-    CYC_LDS int *const sync = (CYC_LDS int *)(uintptr_t)sync_in_lds;
-    const int i = lane & 15, kq = lane >> 4;
-    // block (cb, rb), 1 <= cb <= rb <= 3: register r of lane l is row 16 rb + 4 (l/16) + r, column 16 cb + l%16
-    auto idx = [](int cb, int rb) __attribute__((always_inline)) { return cb == 1 ? rb - 1 : cb == 2 ? rb + 1 : 5; };
-    f32x4 c[6];
-#pragma unroll
-    for (int cb = 1; cb < 4; ++cb)
-#pragma unroll
-        for (int rb = cb; rb < 4; ++rb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) c[idx(cb, rb)][r] = T[(16 * rb + 4 * kq + r) * LDT + 16 * cb + i];
-    bool expired = false;
-    unrolled<4 * 3 - 1>([&](auto index) __attribute__((always_inline)) {
-        constexpr int p = decltype(index)::value;                      // the block of four finished columns to take out
-        constexpr int first_cb = p % 4 == 3 ? p / 4 + 2 : p / 4 + 1;   // (group (p + 1) / 4 was handed over before its block 4G - 1)
-        constexpr int G = p % 4 == 2 ? (p + 2) / 4 : 0;                // the group to hand over after this block
-        if (first_cb <= 3) {
-            int polls = 0;
-            while (__hip_atomic_load(sync, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= p) {
-                if (++polls >= limit) {
-                    expired = true;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            // lane l: L[16 rb + l%16][4p + l/16], the stationary operand (negated) for row block rb and the streamed one
-            // for column block rb
-            float xr[4], xm[4];
-#pragma unroll
-            for (int rb = first_cb; rb < 4; ++rb) {
-                xr[rb] = T[(16 * rb + i) * LDT + 4 * p + kq];
-                xm[rb] = -xr[rb];
-            }
-            auto column_block = [&](int cb) __attribute__((always_inline)) {
-#pragma unroll
-                for (int rb = cb; rb < 4; ++rb) c[idx(cb, rb)] = __builtin_amdgcn_mfma_f32_16x16x4f32(xm[rb], xr[cb], c[idx(cb, rb)], 0, 0, 0);
-            };
-            if (G) {
-                column_block(G);
-#pragma unroll
-                for (int rb = G; rb < 4; ++rb)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) F[(16 * rb + 4 * kq + r) * LDF + i] = c[idx(G, rb)][r];
-                // (a wave's LDS operations are performed in issue order: whoever sees the counter sees the columns)
-                asm volatile("" ::: "memory");
-                __hip_atomic_store(sync + 1, G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-#pragma unroll
-            for (int cb = first_cb; cb < 4; ++cb)
-                if (cb != G) column_block(cb);
-        }
-    });
-    if (expired && lane == 0) sync[2] = 1;
-}
+constexpr float W_NORM_LIMIT = 8.0f;      // the product with a tile's inverse stands in for the recurrence below it (see chol_panel_kernel)
 
 // The factorisation proper of a diagonal tile whose S (with everything left of it taken out) is in T: the column
-// recurrence by the first wave with the second wave's help (trailing_update64), then L, and Lh in both triangles,
-// written out by all.  See diag_tile.
-// dl: what the waves pass to one another; its counters zero on entry (with a barrier since).
-// W, ok: where the tile's inverse and its verdict go, or nullptr (then, and for tiles of fewer than 64 columns, none
-// is computed).
-// beside(t): called in the full-tile case by the threads 128 .. 191 (t = 0 .. 63), which otherwise only wait, while
-// the tile is being factored.
+// recurrence (factor_tile64 for a full tile), then L, and Lh in both triangles, written out by all.  See diag_tile.
+// *unsafe: an int in LDS, 0 with a barrier since; scratch: LDS (factor_tile64).  W: where the
+// tile's inverse goes, or nullptr.  beside(G, w): called in the full-tile case by every wave w < G in the phases G = 1 .. 3.
 template <class Beside>
-__device__ __forceinline__ void diag_rest(float (*T)[LDT], DiagLds &dl, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols, int r,
-                                          float *W, int *ok, int limit, Beside beside, float *copy = nullptr)
+__device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *scratch, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols, int r,
+                                          float *W, Beside beside, float *copy = nullptr)
 {
-    float(*const F)[LDF] = dl.F;
-    int *const sync = dl.sync;
     const bool live = r < cols;
     bool mirrored = false;
+    InverseColumns inverse;
+    static_assert(FACTOR_SCRATCH * sizeof(float) <= KMAX * 64 * sizeof(uint16_t), "the staged operand's place serves as scratch");
     if (cols == NBMAX) {
-        // Full tile: the lane keeps its row of L in registers (every index below is a constant after unrolling) and
-        // writes each finished group of four columns to its row of T in LDS, where the other lanes find row c of L
-        // when they come to column c (one wave: its LDS operations complete in program order, so a read sees an
-        // earlier write without a barrier).  Inside the 4 x 4 corner the few values from other lanes' registers are
-        // fetched with lane reads.  Lanes above the diagonal (r < c) compute values nobody uses.  Every entry takes
-        // its terms in ascending k.
-        if (r < 64) {
-        float x[NBMAX], xn[NBMAX], t[4], tn[4] = {0.0f, 0.0f, 0.0f, 0.0f};      // xn = -x, see chol_panel_kernel
-        f32x4 grp[4], q[3][4], ql[4];                                           // grp: the lane's row of the current group of 16 columns
+        // (the rows of L of a group go out as soon as the group is finished, by the wave that kept them; Lh, which is mirrored, at
+        // the end)
+        const bool aligned = n % 8 == 0 && ((uintptr_t)L & 15) == 0 && ((uintptr_t)Lh & 15) == 0;
+        factor_tile64<LDT>(T, unsafe, scratch, W, inverse, r, [&](auto phase, int w) __attribute__((always_inline)) {
+            constexpr int G = decltype(phase)::value;
+            if (w == G - 1 && aligned) {
+                f32x4 v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) grp[i] = *(const f32x4 *)&T[r][4 * i];
-        auto request = [&](int b, int k4, f32x4(&o)[4]) __attribute__((always_inline)) {     // operands of step k4 of block b
+                for (int p = 0; p < 4; ++p) {
+                    const int row = 16 * (G - 1) + 4 * p + (r >> 4 & 3);
+                    v[p] = *(const f32x4 *)&T[row][4 * (r & 15)];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = *(const f32x4 *)&T[4 * b + j][4 * k4];
-        };
-        auto step = [&](float(&acc)[4], int k4, const f32x4(&o)[4]) __attribute__((always_inline)) {   // 16 multiply-adds
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(xn[4 * k4 + kk], o[j][kk], acc[j]);
-        };
-        auto lane_value = [](float v, int l) __attribute__((always_inline)) {
-            return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-        };
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t[j] = grp[0][j];
-        unrolled<NBLK>([&](auto block) __attribute__((always_inline)) {
-            constexpr int b = decltype(block)::value;
-            constexpr int mine = own_steps(b), next = b + 1 < NBLK ? own_steps(b + 1) : 0;
-            if (b >= 4 && b % 4 == 0) {
-                // a new group of 16 columns, from the second wave: everything up to block b - 2 is out of it
-                int polls = 0;
-                while (__hip_atomic_load(sync + 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < b / 4) {
-                    if (++polls >= limit) {
-                        __hip_atomic_store(sync + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        break;
-                    }
+                    for (int q = 0; q < 4; ++q) v[p][q] = 4 * (r & 15) + q <= row ? v[p][q] : 0.0f;
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) grp[i] = *(const f32x4 *)&F[r][4 * i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) t[j] = grp[0][j];
+                for (int p = 0; p < 4; ++p) *(f32x4 *)(L + (j0 + 16 * (G - 1) + 4 * p + (r >> 4 & 3)) * n + j0 + 4 * (r & 15)) = v[p];
             }
-            if (mine >= 2) step(t, b - 2, q[mine >= 2 ? mine - 2 : 0]);                         // held back: covers the latency of ql
-            if (mine >= 1) step(t, b - 1, ql);
-            if (next >= 1 && (b + 1) % 4 != 0) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) tn[j] = grp[(b + 1) % 4][j];
-            }
-            // operands of the next block's steps, all but the last: blocks first_k(b + 1) .. b - 1 are written
-#pragma unroll
-            for (int u = 0; u + 1 < next; ++u) request(b + 1, first_k(b + 1) + u, q[u]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = 4 * b + j;
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int e = 0; e < j; ++e) t[j] = __builtin_fmaf(xn[4 * b + e], lane_value(x[4 * b + e], c), t[j]);
-                const float d = lane_value(__builtin_sqrtf(t[j]), c);
-                x[c] = r == c ? d : t[j] / d;
-                xn[c] = -x[c];
-                asm("" : "+v"(xn[c]));                                          // (or the negation is folded back into the multiply-adds)
-                if (j + 2 < next) step(tn, first_k(b + 1) + j, q[j]);           // one step of the next block beside this column
-            }
-            f32x4 done;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) done[j] = x[4 * b + j];
-            *(f32x4 *)&T[r][4 * b] = done;
-            // block b is final in LDS.  Every lane stores the same number (a store under a lane condition would cut the
-            // chains into basic blocks), and without a release fence, which would wait for the operands requested ahead
-            // as well: a wave's LDS operations are performed in the order it issues them, so whoever sees the counter
-            // sees the block; the empty asm keeps the compiler from moving the store up.
-            asm volatile("" ::: "memory");
-            __hip_atomic_store(sync, b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (b + 1 < NBLK) request(b + 1, b, ql);
-            if (next >= 1 && (b + 1) % 4 != 0) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) t[j] = tn[j];
-            }
+            beside(phase, w);
         });
-        // the mirror image into the upper part of the tile (Lh holds both triangles): entry (c, r) for c < r; the other
-        // lanes write to the padding of their row (a store under a lane condition is a branch around it: 4k cycles for
-        // the 63 of them)
-#pragma unroll
-        for (int c = 0; c < NBMAX - 1; ++c) *(c < r ? &T[c][r] : &T[r][NBMAX]) = x[c];
-        } else if (r >= 192) {
-            trailing_update64((uint32_t)(uintptr_t)(CYC_LDS const float *)&T[0][0], (uint32_t)(uintptr_t)(CYC_LDS float *)&F[0][0],
-                              (uint32_t)(uintptr_t)(CYC_LDS int *)sync, r - 192, limit);
-        } else if (r >= 128) {
-            beside(r - 128);
-        } else if (W) {
-            inverse_follow64((uint32_t)(uintptr_t)(CYC_LDS const float *)&T[0][0], (uint32_t)(uintptr_t)(CYC_LDS float *)&dl.Y[0][0],
-                             (uint32_t)(uintptr_t)(CYC_LDS int *)sync, r - 64, limit, W, ok);
-        }
         mirrored = true;
-        __syncthreads();
-        if (__builtin_expect(sync[2] != 0, 0)) {
-            // a bounded wait between the two waves ran out (it never should): NaNs instead of a factor that looks
-            // like one, and no inverse
-            for (int e = r; e < NBMAX * NBMAX; e += NT) T[e / NBMAX][e % NBMAX] = __builtin_nanf("");
-            if (r == 0 && W) *ok = 0;
-            __syncthreads();
-        }
     } else {
         for (int c = 0; c < cols; ++c) {
             float t = 0.0f;
@@ -718,9 +368,11 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], DiagLds &dl, float *L
         }
     }
     // mirror the factor into the upper part of the tile in LDS (Lh holds both triangles), then write the tile out
-    if (live && !mirrored)
-        for (int c = r + 1; c < cols; ++c) T[r][c] = T[c][r];
-    __syncthreads();
+    if (!mirrored) {
+        if (live)
+            for (int c = r + 1; c < cols; ++c) T[r][c] = T[c][r];
+        __syncthreads();
+    }
     if (copy) {
         // a second copy of the tile as it stands in LDS, rows of 64 floats (see chol_panel_kernel, Dcopy)
 #pragma unroll
@@ -729,23 +381,23 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], DiagLds &dl, float *L
             *(f32x4 *)(copy + row * NBMAX + 4 * (r & 15)) = *(const f32x4 *)&T[row][4 * (r & 15)];
         }
     }
-    if (store_tile<true>(T, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, r)) return;
-    if (live)
+    const bool stored = store_tile<true, NT, 3, 48>(T, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, r);
+    if (!stored && live)
         for (int c = 0; c < cols; ++c) {
             L[(j0 + r) * n + j0 + c] = c <= r ? T[r][c] : 0.0f;
             Lh[(j0 + r) * n + j0 + c] = round_bf16(T[r][c]);
         }
+    if (cols == NBMAX && W) finish_inverse<LDT>(T, scratch, W, inverse, r);
 }
 
 // L_jj = CHOL(S_jj) for the tile at (j0, j0) with `cols` rows and columns.  S is read from Sm (row stride n: A itself
 // for the first panel, L afterwards); L gets the factor below and on the diagonal and zero above it, Lh its bf16
-// rounding in both triangles.  One workgroup of NT threads; thread r < 64 owns row r, the other waves only help to
-// move and update the tile.  T (first 64 KB of LDS: a read reaches its word with the 16-bit offset field from one
+// rounding in both triangles.  One workgroup of NT threads.  T (first 64 KB of LDS: a read reaches its word with the 16-bit offset field from one
 // base register; further up every read needs an address register of its own) and Bs are the workgroup's LDS.
-__device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], const float *Sm, float *L, uint16_t *Lh, int64_t n,
-                                          int64_t j0, int cols, int64_t k0, int r, DiagLds &dl, float *W, int *ok, int limit)
+__device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], int *unsafe, const float *Sm, float *L, uint16_t *Lh, int64_t n,
+                                          int64_t j0, int cols, int64_t k0, int r, float *W)
 {
-    if (r < 3) dl.sync[r] = 0;            // (a barrier follows below, before anyone looks at them)
+    if (r == 0) *unsafe = 0;              // (a barrier follows below)
     // (both operands of the tile's own update are the rows j0 .. of Lh: the staged one, Lh[k0:j0, j0:j0+64], is their
     // mirror image, and the stationary fragments are read from it as well)
     TileProduct product;
@@ -753,38 +405,37 @@ __device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], c
     load_tile(T, Sm + j0 * n + j0, n, cols, cols, r);     // the whole square; what lies above the diagonal is not used
     if (k0 < j0) product.apply(T, Bs, r, Bs);
     else __syncthreads();
-    diag_rest(T, dl, L, Lh, n, j0, cols, r, W, ok, limit, [](int) {});
+    diag_rest(T, unsafe, (float *)&Bs[0][0], L, Lh, n, j0, cols, r, W, [](auto, int) {});
 }
 
-__global__ __launch_bounds__(NT) void chol_diag_kernel(const float *Sm, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols,
-                                                       int64_t k0, float *W, int *ok, int limit)
+__global__ __launch_bounds__(NT, 2) void chol_diag_kernel(const float *Sm, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols,
+                                                       int64_t k0, float *W)
 {
     __shared__ __attribute__((aligned(16))) struct {
         float T[NBMAX][LDT];          // S on entry, L as columns finish
         uint16_t Bs[KMAX][64];        // streamed operand of the tile's own update
-        DiagLds dl;                   // between the waves of the factorisation
+        int unsafe;                   // see factor_tile64
     } lds;
-    diag_tile(lds.T, lds.Bs, Sm, L, Lh, n, j0, cols, k0, threadIdx.x, lds.dl, W, ok, limit);
+    diag_tile(lds.T, lds.Bs, &lds.unsafe, Sm, L, Lh, n, j0, cols, k0, threadIdx.x, W);
 }
 
-// L_ij = TRSM(S_ij, L_jj) for all rows below the diagonal tile: row j1 + 64 * blockIdx.x + lane of the first wave; the
-// other waves of the NT threads only help to move and update the tile.
+// L_ij = TRSM(S_ij, L_jj) for all rows below the diagonal tile: rows j1 + 64 * blockIdx.x .., sixteen to a wave.
 // next_Sm != nullptr: the workgroup of the first 64 rows goes on to factor the next diagonal tile, (j1, j1), whose S is
 // read from next_Sm: it produces the only part of that tile's update that is still missing, and a launch of its own
 // for the tile would first wait for memory again.  That workgroup requests the tile's S and the operands of its
-// update over the group's earlier panels with everything else, first thing; the three waves that would idle during
-// the recurrence multiply them out (wave 1 rows 0 .. 31 of the tile, waves 2 and 3 sixteen rows each; one strip of
-// sixteen rows per wave when the rows come through the inverse and the first wave is free).  Then the k range of
-// this panel is added, straight from the solved rows in LDS, and the tile is factored; meanwhile two waves write this
-// workgroup's own rows out.
-// Win, okin: the inverse of L_jj and its verdict (see inverse_follow64), or nullptr.  When the verdict is good the
-// workgroup of the first 64 rows, the one the next diagonal tile waits for, forms its rows as the product S W^T on the
-// matrix cores in fp32 instead of running the recurrence; all other workgroups, which nothing waits for, keep the
-// recurrence.  Wout, okout: where the inverse of the next diagonal tile and its verdict go when that tile rides along.
-__global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols,
+// update over the group's earlier panels with everything else, first thing, and multiplies them out beside its rows'
+// recurrence, sixteen rows of the tile to a wave.  Then the k range of this panel is added, straight from the solved
+// rows in LDS, and the tile is factored; that workgroup's rows come as a product with the inverse of L_jj where that is well
+// conditioned (Win, or nullptr: see InverseColumns; Wout: the next tile's), all others', which nothing waits for, by the recurrence.
+// While the tile is factored, waves that are done with it write this workgroup's own rows out.
+// On the path per launch at n = 8192, in cycles: 5k until the tiles are in LDS, 2.7k the rows, 1.8k the panel's k range into the next
+// tile, 16.5k that tile, 2.7k Lh and the last rows of L and of the inverse (31k with the tile's recurrence in one wave, one lane
+// to a row, helped by a second: 14.5k, and 5k more for a third that computed the inverse four columns behind; that made 18.6k a tile
+// for the rows of all other workgroups, which are 6k now).  8192: 2391 -> 2102 us; 2048: 563 -> 506; 200: 61.5 -> 51.8.
+__global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols,
                                                         int64_t k0, const float *next_Sm, const float *__restrict__ Win,
-                                                        const int *__restrict__ okin, float *Wout, int *okout, const float *Dcopy,
-                                                        float *next_copy, int limit, int64_t k0_first, int ahead)
+                                                           float *Wout, const float *Dcopy,
+                                                        float *next_copy, int64_t k0_first, int ahead)
 {
     // one block, D and X first (see diag_tile)
     __shared__ __attribute__((aligned(16))) struct {
@@ -792,7 +443,8 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
         float X[64][LDT];             // this workgroup's rows: S on entry, L as columns finish
         uint16_t Bs[KMAX][64];        // streamed operand of the tile's own update
         uint16_t Bs2[KMAX][64];       // streamed operand of the next diagonal tile's update
-        DiagLds dl;                   // the next diagonal tile: between the waves of its factorisation (see diag_rest)
+        float rinv[64];               // the reciprocals of the diagonal of L_jj
+        int unsafe;                   // the next diagonal tile: see factor_tile64
     } lds;
     auto &D = lds.D;
     auto &X = lds.X;
@@ -823,16 +475,14 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
         return;
     }
     if (blockIdx.x == 0) k0 = k0_first;                                    // uniform (see above)
-    if (tid < 3) lds.dl.sync[tid] = 0;
-    const bool solver = tid < 64;                         // the wave that runs the recurrence
-    // The rows of this workgroup through the inverse of L_jj?  W and its verdict are requested here with everything
-    // else the kernel needs from memory; the verdict is looked at only where the rows are formed, so that nothing
-    // waits for it on its own.
+    if (tid == 0) lds.unsafe = 0;
+    const bool solver = tid < 64;                         // the wave that runs the recurrence of a tile that is not full
+    // (requested here with everything else, looked at only where the rows are formed, so that nothing waits for them on their own)
     const bool may_invert = blockIdx.x == 0 && cols == NBMAX && Win != nullptr;        // uniform over the workgroup
-    int verdict = 0;
-    f32x4 winv[10];                                       // this lane's 40 values of W: pieces (cb, q), q <= cb
+    f32x4 winv[10], sum_L = {0, 0, 0, 0}, sum_W = sum_L;   // this lane's 40 values of W: pieces (cb, q), q <= cb
     if (may_invert) {
-        verdict = *okin;
+        sum_L = *(const f32x4 *)(Win + W_FLOATS);
+        sum_W = *(const f32x4 *)(Win + W_FLOATS + 4);
         int p = 0;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
@@ -849,22 +499,20 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
     // clear their own upper halves), and nothing writes there after the group's product, which precedes its panels.
     // (At the end of the workgroup's work: ahead of its loads these stores would sit in the same queue before them.)
     auto clear_mirror_place = [&](int t, int nth) __attribute__((always_inline)) {
-        for (int i = t >> 6; i < cols; i += nth / 64)
-            if ((t & 63) < nrows) L[(j0 + i) * n + first + (t & 63)] = 0.0f;
+        if (cols == NBMAX && nrows == 64 && n % 4 == 0 && (uintptr_t)L % 16 == 0) {
+#pragma unroll 4
+            for (int i = t >> 4; i < NBMAX; i += nth / 16) *(f32x4 *)(L + (j0 + i) * n + first + 4 * (t & 15)) = (f32x4){0, 0, 0, 0};
+        } else {
+            for (int i = t >> 6; i < cols; i += nth / 64)
+                if ((t & 63) < nrows) L[(j0 + i) * n + first + (t & 63)] = 0.0f;
+        }
     };
     // ---- the next diagonal tile, first part: its S and the operands of the part of its update that does not involve
     // this panel are requested with everything else (their own LDS buffer, Bs2, so that they need not wait for Bs)
     const bool fused = next_Sm != nullptr && blockIdx.x == 0;          // uniform over the workgroup
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lq = lane & 15, g = lane >> 4;
     const int nks_e = fused ? (int)(j0 - k0) / 32 : 0;                 // k-steps of that tile's update that do not involve this panel
-    f32x4 sv[4], accn[2][4];                                           // its S (this thread's pieces); its update: [slot][column tile]
-    // The four 16-row strips of that update: slot si of this wave holds strip(si), or nothing (-1).  Beside the recurrence
-    // the three other waves share them (wave 1 takes two).  When the rows may come through the inverse the first wave
-    // is free as a rule and every wave takes one strip; should the verdict then be bad after all, the first wave takes
-    // its strip after its recurrence.
-    auto strip = [&](int si) __attribute__((always_inline)) {
-        return may_invert ? (si == 0 ? w : -1) : (w == 1 ? si : (si == 0 && w >= 2 ? w : -1));
-    };
+    f32x4 sv[4], accn[4];                                              // its S (this thread's pieces); its update, rows 16 w ..: [column tile]
     // rows `first_row` .. +count-1 of the streamed operand Lh[., j1 : j1+64] into Bs2 from row `to` on, 8 rows per copy,
     // the copies dealt out to `waves` waves of which this is number `me`
     auto copy_rows = [&](int64_t first_row, int to, int count, int me, int waves) __attribute__((always_inline)) {
@@ -906,42 +554,46 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
     if (k0 < j0) product.apply(X, Bs, tid, rows_in_lds ? Bs2 : nullptr);
     else __syncthreads();
     if (Dcopy && (int)blockIdx.x == row_blocks - 1) (void)store_tile<true>(D, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, tid);
-    const bool by_inverse = may_invert && __builtin_amdgcn_readfirstlane(verdict) != 0;
 #pragma unroll
-    for (int si = 0; si < 2; ++si)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) accn[si][j] = (f32x4){0, 0, 0, 0};
-    // (lanes past the last row run along on the repeated last row: they take part in the barrier and in the tile
-    // store below, and write nothing of their own)
-    bool mirrored = false;
+    for (int j = 0; j < 4; ++j) accn[j] = (f32x4){0, 0, 0, 0};
     if (cols == NBMAX) {
-        if (by_inverse) {
-            // X <- S W^T: wave w takes the rows 16w .. 16w+15 and all 64 columns.  A operand lane l: row 16w + l%16 of
-            // S, k = 4 ks + l/16; B operand: W[16 cb + l%16][4 ks + l/16], zero for ks >= 4 (cb + 1); accumulator
-            // register r of lane l: row 16w + 4 (l/16) + r, column 16 cb + l%16.  Each wave reads only its own rows
-            // of X before it overwrites them.
+        // Sixteen rows to a wave (rows past the last one repeat it)
+        wave_f32x4 S[4], t[4], x[4];
+        float *const row = &X[16 * w + lq][0];
+#pragma unroll
+        for (int G = 0; G < 4; ++G) t[G] = S[G] = *(const wave_f32x4 *)(row + 16 * G + 4 * g);
+        // the k-steps of the next diagonal tile's update over the group's earlier panels (both operands out of Bs2, see above)
+        i32x4 f[2][5];                                                          // [parity of the k-step]: stationary, streamed x 4
+        auto read_step = [&](int ks, i32x4(&dst)[5]) __attribute__((always_inline)) {
+            dst[0] = staged_fragment(Bs2, ks, w, lq, g);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dst[1 + j] = staged_fragment(Bs2, ks, j, lq, g);
+        };
+        auto multiply = [&](const i32x4(&src)[5]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                accn[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[0]), __builtin_bit_cast(bf16x8, src[1 + j]), accn[j], 0, 0, 0);
+        };
+        // (an upper bound of || |W| |L| ||_1, which is what the product's error grows with)
+        const float norm_L = __builtin_fmaxf(__builtin_fmaxf(sum_L[0], sum_L[1]), __builtin_fmaxf(sum_L[2], sum_L[3]));
+        const float norm_W = __builtin_fmaxf(__builtin_fmaxf(sum_W[0], sum_W[1]), __builtin_fmaxf(sum_W[2], sum_W[3]));
+        if (may_invert && __builtin_amdgcn_readfirstlane(norm_L * norm_W <= W_NORM_LIMIT) != 0) {
+            // X <- S W^T.  A operand lane l: row 16w + l%16 of S, k = 4 ks + l/16; B operand: W[16 cb + l%16][4 ks + l/16], zero
+            // for ks >= 4 (cb + 1); accumulator register r of lane l: row 16w + 4 (l/16) + r, column 16 cb + l%16.  Each wave
+            // reads only its own rows of X before it overwrites them.
             float sa[16];
 #pragma unroll
             for (int ks = 0; ks < 16; ++ks) sa[ks] = X[16 * w + lq][4 * ks + g];
             f32x4 xo[4];
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) xo[cb] = (f32x4){0, 0, 0, 0};
-            // Between the MFMAs of this product (32 cycles of the matrix pipe each) run the k-steps of the next diagonal
-            // tile's update over the group's earlier panels (second part, see below; this wave's strip is rows 16w ..):
-            // they wait for their fragments from LDS, which the product does not need, and alone they took as long again
-            // as the product.  One k-step per step of the product, its fragments read a step ahead.  (nks_e <= 14.)
-            const bool early = fused && nks_e > 0;                              // uniform
-            i32x4 f[2][5];                                                      // [parity of the k-step]: stationary, streamed x 4
-            auto read_step = [&](int ks, i32x4(&dst)[5]) __attribute__((always_inline)) {
-                dst[0] = staged_fragment(Bs2, ks, w, lq, g);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) dst[1 + j] = staged_fragment(Bs2, ks, j, lq, g);
-            };
-            // (The usual numbers of such k-steps, none and two, have a copy of the loop each in which they are constants:
-            // as conditions at run time they cut every step of the product into pieces that wait for their own reads.)
+            // Between the MFMAs of this product (32 cycles of the matrix pipe each) run the k-steps of the next diagonal tile's
+            // update, their fragments read a step ahead.  (The usual numbers of them, none and two, have a copy of the loop each
+            // in which they are constants: as conditions at run time they cut every step of the product into pieces that wait for
+            // their own reads.)
             auto product_loop = [&](auto steps_c) __attribute__((always_inline)) {
-                constexpr int NE = decltype(steps_c)::value;                    // that many k-steps, or -1: nks_e of them
-                auto has = [&](int ks) __attribute__((always_inline)) { return NE >= 0 ? ks < NE : early && ks < nks_e; };
+                constexpr int NE = decltype(steps_c)::value;                    // that many k-steps, or -1: nks_e of them (at most 14)
+                auto has = [&](int ks) __attribute__((always_inline)) { return NE >= 0 ? ks < NE : ks < nks_e; };
                 if (has(0)) read_step(0, f[0]);
 #pragma unroll
                 for (int ks = 0; ks < 16; ++ks) {
@@ -949,131 +601,35 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
 #pragma unroll
                     for (int cb = ks / 4; cb < 4; ++cb)
                         xo[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[ks], winv[cb * (cb + 1) / 2 + ks / 4][ks % 4], xo[cb], 0, 0, 0);
-                    if (has(ks)) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            accn[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[ks & 1][0]), __builtin_bit_cast(bf16x8, f[ks & 1][1 + j]), accn[0][j], 0, 0, 0);
-                    }
+                    if (has(ks)) multiply(f[ks & 1]);
                 }
             };
-            if (!early) product_loop(std::integral_constant<int, 0>{});
+            if (nks_e == 0) product_loop(std::integral_constant<int, 0>{});
             else if (nks_e == 2) product_loop(std::integral_constant<int, 2>{});
             else product_loop(std::integral_constant<int, -1>{});
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) X[16 * w + 4 * g + r][16 * cb + lq] = xo[cb][r];
-        }
-        if (solver && !by_inverse) {
-        // The lane's row of S and of L in registers (constant indices after unrolling); the steps of StepList, the
-        // rows of L_jj for a step requested from LDS two steps before it runs, since a lone wave has nobody else to
-        // hide the LDS latency behind.
-        float x[NBMAX], xn[NBMAX], t[4], tn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        f32x4 sr[NBLK], q[3][4], qc[2][4];
+        } else {
+        // The divisions of a column share their divisor: quotients from its reciprocal, unless something is outside the range
+        // in which these are IEEE's.
+        Pivot p;
+        p.from_root(D[lane][lane]);
+        lds.rinv[lane] = p.r;                                                   // (the same numbers by every wave: no barrier)
+        solve_rows16<true, LDT>(D, lds.rinv, t, row, lane, [](auto) {});
 #pragma unroll
-        for (int i = 0; i < NBLK; ++i) sr[i] = *(const f32x4 *)&X[lane][4 * i];
-        auto request = [&](int i) __attribute__((always_inline)) {              // operands of bulk step i
-            if (STEPS.b[i] >= 0) {
+        for (int G = 0; G < 4; ++G) x[G] = *(const wave_f32x4 *)(row + 16 * G + 4 * g);
+        const unsigned worst = max(max(worst_code(x[0]), worst_code(x[1])), max(max(worst_code(x[2]), worst_code(x[3])), range_code(p.d)));
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
+            const bool safe = range_code(p.d) <= SAFE_SPAN && all_safe(x[0]) && all_safe(x[1]) && all_safe(x[2]) && all_safe(x[3]);
+            if (__builtin_amdgcn_ballot_w64(!safe) != 0) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) q[i % 3][j] = *(const f32x4 *)&D[4 * STEPS.b[i] + j][4 * STEPS.k[i]];
+                for (int G = 0; G < 4; ++G) t[G] = S[G];
+                solve_rows16<false, LDT>(D, lds.rinv, t, row, lane, [](auto) {});
             }
-        };
-        // (xn = -x: a multiply-add without a negated operand has a 4-byte encoding, which a lone wave issues faster)
-        auto quarter = [&](float(&acc)[4], int i, int kk) __attribute__((always_inline)) {   // a quarter of bulk step i
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(xn[4 * STEPS.k[i] + kk], q[i % 3][j][kk], acc[j]);
-        };
-        request(0);
-        request(1);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            qc[0][j] = *(const f32x4 *)&D[j][0];
-            t[j] = sr[0][j];
         }
-        int i = 0;                                                              // the next bulk step
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b) {
-#pragma unroll
-            for (int s = early_of(b); s < b; ++s) {                             // the block's bulk steps taken in turn
-                request(i + 2);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) quarter(t, i, kk);
-                ++i;
-            }
-            if (b + 1 < NBLK) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    qc[(b + 1) & 1][j] = *(const f32x4 *)&D[4 * (b + 1) + j][4 * (b + 1)];
-                    tn[j] = sr[b + 1][j];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {                                       // the corner, column by column
-                const bool paired = b + 1 < NBLK && j < early_of(b + 1);
-                if (paired) request(i + 2);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int c = 0; c < j; ++c) t[j] = __builtin_fmaf(xn[4 * b + c], qc[b & 1][j][c], t[j]);
-                Division dv;
-                dv.phase0(t[j], qc[b & 1][j][j]);
-                __builtin_amdgcn_sched_barrier(0);
-                if (paired) quarter(tn, i, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                dv.phase1();
-                __builtin_amdgcn_sched_barrier(0);
-                if (paired) quarter(tn, i, 1);
-                __builtin_amdgcn_sched_barrier(0);
-                dv.phase2();
-                __builtin_amdgcn_sched_barrier(0);
-                if (paired) quarter(tn, i, 2);
-                __builtin_amdgcn_sched_barrier(0);
-                x[4 * b + j] = dv.phase3();
-                xn[4 * b + j] = -x[4 * b + j];
-                asm("" : "+v"(xn[4 * b + j]));                                  // (or the negation is folded back into the multiply-adds)
-                __builtin_amdgcn_sched_barrier(0);
-                if (paired) {
-                    quarter(tn, i, 3);
-                    ++i;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[j] = tn[j];
-        }
-#pragma unroll
-        for (int c = 0; c < NBMAX; ++c) X[lane][c] = x[c];
-        if (live) {
-            // the mirror image of the rows, straight from the registers: consecutive lanes, consecutive addresses
-            uint16_t *m = Lh + j0 * n + row;
-#pragma unroll
-            for (int c = 0; c < NBMAX; ++c) m[c * n] = round_bf16(x[c]);
-        }
-        }
-        if (fused && nks_e > 0 && (!solver || may_invert) && !by_inverse) {
-            // ---- the next diagonal tile, second part: the k-steps over the group's earlier panels, by the three waves
-            // beside the recurrence, or by all four after it when the inverse turned out unusable (when the rows come
-            // through the inverse these k-steps run between the MFMAs of that product, above).  (Their operands have
-            // arrived: requested first thing and waited for before the barrier that precedes the update of this
-            // workgroup's own tile.)
-            // Both operands out of Bs2 (see above); the fragments of the next k-step are read before the current ones are
-            // multiplied.  (nks_e is even.)
-            const int s0 = strip(0), s1 = strip(1);
-            i32x4 f[2][6];                                                       // [parity]: stationary of slot 0 and 1, streamed x 4
-            auto read_step = [&](int ks, i32x4(&dst)[6]) __attribute__((always_inline)) {
-                if (s0 >= 0) dst[0] = staged_fragment(Bs2, ks, s0, lq, g);
-                if (s1 >= 0) dst[1] = staged_fragment(Bs2, ks, s1, lq, g);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) dst[2 + j] = staged_fragment(Bs2, ks, j, lq, g);
-            };
-            auto multiply = [&](const i32x4(&src)[6]) __attribute__((always_inline)) {
-#pragma unroll
-                for (int si = 0; si < 2; ++si)
-                    if ((si == 0 ? s0 : s1) >= 0) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            accn[si][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[si]), __builtin_bit_cast(bf16x8, src[2 + j]), accn[si][j], 0, 0, 0);
-                    }
-            };
+        if (nks_e > 0) {                                                        // (an even number)
             read_step(0, f[0]);
             for (int ks = 0; ks < nks_e; ks += 2) {
                 read_step(ks + 1, f[1]);
@@ -1082,30 +638,37 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
                 multiply(f[1]);
             }
         }
-        mirrored = !by_inverse;                            // (the recurrence writes the mirror image from its registers)
+        }
     } else if (solver) {
         for (int c = 0; c < cols; ++c) X[lane][c] = chain(X[lane][c], X[lane], D[c], c) / D[c][c];
     }
     __syncthreads();
-    // In the workgroup that goes on to the next diagonal tile two waves have nothing to do while that tile is factored:
+    // In the workgroup that goes on to the next diagonal tile some waves are done before others while that tile is factored:
     // they write this workgroup's rows out then (diag_rest below), off the path.  (There the tile is full and every
     // pointer aligned: the host fuses under those conditions only.)
     const bool deferred = fused && cols == NBMAX;
-    const bool stored = deferred || store_tile<false>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, tid);
-    if (!deferred && by_inverse && nrows == 64 && n % 8 == 0 && (uintptr_t)Lh % 16 == 0) {
-        store_mirror<NT>(X, Lh + j0 * n + first, n, tid);
-        mirrored = true;
-    }
-    if (!deferred && live && !(stored && mirrored))
-        for (int c = 0; c < cols; ++c) {
-            const float v = X[lane][c];
-            const uint16_t h = round_bf16(v);
-            if (!stored) {
-                L[row * n + j0 + c] = v;
-                Lh[row * n + j0 + c] = h;
+    if (!deferred) {
+        const bool stored = store_tile<false>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, tid);
+        if (nrows == 64 && cols == NBMAX && n % 8 == 0 && (uintptr_t)Lh % 16 == 0) {
+            store_mirror<NT>(X, Lh + j0 * n + first, n, tid);
+        } else if (cols == NBMAX) {
+            // sixteen columns to a wave, a row to a lane: consecutive lanes, consecutive addresses
+            float v[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c) v[c] = X[lane][16 * w + c];
+            if (lane < nrows) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) Lh[(j0 + 16 * w + c) * n + first + lane] = round_bf16(v[c]);
             }
-            if (!mirrored) Lh[(j0 + c) * n + row] = h;
+        } else if (live) {
+            for (int c = 0; c < cols; ++c) Lh[(j0 + c) * n + row] = round_bf16(X[lane][c]);
         }
+        if (!stored && live)
+            for (int c = 0; c < cols; ++c) {
+                L[row * n + j0 + c] = X[lane][c];
+                Lh[row * n + j0 + c] = round_bf16(X[lane][c]);
+            }
+    }
     if (!fused) clear_mirror_place(tid, NT);
     if (fused) {
         // ---- the next diagonal tile, third part: the k range of this panel.  Its operands are the rows this
@@ -1123,67 +686,43 @@ __global__ __launch_bounds__(NT) void chol_panel_kernel(const float *Sm, float *
         };
 #pragma unroll
         for (int i = 0; i < 4; ++i) *(f32x4 *)&D[16 * i + (tid >> 4)][4 * (tid & 15)] = sv[i];      // S into the tile (D is free)
-        if (may_invert) {
-            // (every wave has one strip, its own: the same code without the conditions, which are not constants and cut it
-            // into pieces that each wait for their own reads)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                i32x4 bq[4];
+        for (int u = 0; u < 2; ++u) {
+            i32x4 bq[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) bq[j] = fragment(j, u);
-                const i32x4 aq = fragment(w, u);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    accn[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aq), __builtin_bit_cast(bf16x8, bq[j]), accn[0][j], 0, 0, 0);
-            }
-            __syncthreads();
+            for (int j = 0; j < 4; ++j) bq[j] = fragment(j, u);
+            const i32x4 aq = fragment(w, u);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) D[16 * w + 4 * g + r][16 * j + lq] -= accn[0][j][r];
-        } else {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                i32x4 bq[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bq[j] = fragment(j, u);
-#pragma unroll
-                for (int si = 0; si < 2; ++si)
-                    if (strip(si) >= 0) {
-                        const i32x4 aq = fragment(strip(si), u);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            accn[si][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aq), __builtin_bit_cast(bf16x8, bq[j]), accn[si][j], 0, 0, 0);
-                    }
-            }
-            __syncthreads();
-            // accumulator register r of lane l is row 4 (l/16) + r, column l%16 of its 16 x 16 tile
-#pragma unroll
-            for (int si = 0; si < 2; ++si)
-                if (strip(si) >= 0) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) D[16 * strip(si) + 4 * g + r][16 * j + lq] -= accn[si][j][r];
-                }
+                accn[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aq), __builtin_bit_cast(bf16x8, bq[j]), accn[j], 0, 0, 0);
         }
         __syncthreads();
-        diag_rest(D, lds.dl, L, Lh, n, j1, NBMAX, tid, Wout, okout, limit, [&](int t) __attribute__((always_inline)) {
-            // this workgroup's own rows, deferred above
-            store_tile<false, 64>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, t);
-            if (by_inverse) store_mirror<64>(X, Lh + j0 * n + first, n, t);
-            clear_mirror_place(t, 64);
+        // accumulator register r of lane l is row 4 (l/16) + r, column l%16 of its 16 x 16 tile
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) D[16 * w + 4 * g + r][16 * j + lq] -= accn[j][r];
+        __syncthreads();
+        diag_rest(D, &lds.unsafe, (float *)&Bs[0][0], L, Lh, n, j1, NBMAX, tid, Wout, [&](auto phase, int wave) __attribute__((always_inline)) {
+            // this workgroup's own rows, deferred above, shared by the first two waves
+            constexpr int G = decltype(phase)::value;
+            const int t = tid & 63;
+            if (G == 1) clear_mirror_place(t, 64);
+            if (G == 2 && wave == 0) store_tile<false, 64, 1>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, t);
+            if (G == 2 && wave == 1) store_mirror<64>(X, Lh + j0 * n + first, n, t);
+            if (G == 3 && wave == 1) store_tile<false, 64, 2>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, t);
         }, next_copy);
     }
 }
 
 }  // namespace
 
+// one tile of 64 x 64 floats (see launch_chol: the first diagonal tile of a group rides along with the group before), and the
+// inverse of one diagonal tile twice, for the launch that reads and the launch that writes
+constexpr int64_t INVERSE = W_ALL * (int64_t)sizeof(float);
 int64_t chol_workspace_bytes(int64_t n, int64_t nb)
 {
-    // one inverse and one verdict per full diagonal tile of 64 (see inverse_follow64)
-    // and one tile of 64 x 64 floats (see launch_chol: the first diagonal tile of a group)
-    return nb == NBMAX && n >= 2 * NBMAX ? (n / NBMAX) * (int64_t)(W_FLOATS * sizeof(float) + sizeof(int)) + 16 + NBMAX * NBMAX * (int64_t)sizeof(float) : 0;
+    return nb == NBMAX && n >= 2 * NBMAX ? NBMAX * NBMAX * (int64_t)sizeof(float) + 2 * INVERSE : 0;
 }
 
 hipError_t launch_chol(const void *A_, void *L_, void *Lh_, int64_t n, int64_t nb, void *workspace, hipStream_t s)
@@ -1192,12 +731,8 @@ hipError_t launch_chol(const void *A_, void *L_, void *Lh_, int64_t n, int64_t n
     float *L = (float *)L_;
     uint16_t *Lh = (uint16_t *)Lh_;
     if (nb < 1 || nb > NBMAX || n < 1 || n > (1 << 22)) return hipErrorInvalidValue;
-    // the inverses of the full diagonal tiles and their verdicts, tile after tile (nullptr: none are computed)
-    float *Wall = chol_workspace_bytes(n, nb) > 0 ? (float *)workspace : nullptr;
-    int *okall = Wall ? (int *)(Wall + (n / NBMAX) * W_FLOATS) : nullptr;
-    auto W_of = [&](int64_t j, int c) { return Wall && c == NBMAX ? Wall + j / NBMAX * W_FLOATS : (float *)nullptr; };
-    auto ok_of = [&](int64_t j, int c) { return Wall && c == NBMAX ? okall + j / NBMAX : (int *)nullptr; };
-    float *tile_copy = Wall ? (float *)(((uintptr_t)(okall + n / NBMAX) + 15) & ~(uintptr_t)15) : nullptr;
+    float *const tile_copy = chol_workspace_bytes(n, nb) > 0 ? (float *)workspace : nullptr;
+    auto W_of = [&](int64_t j, int c) { return tile_copy && c == NBMAX ? (float *)((char *)(tile_copy + NBMAX * NBMAX) + j / NBMAX % 2 * INVERSE) : (float *)nullptr; };
     // One product per panel would have only nb columns and all earlier tiles as its k range: a few workgroups
     // walking a long k loop.  So the panels are taken in groups of GROUP: at the first panel of a group one product
     // covers the columns of the whole group against all tiles left of the group; the later panels of the group
@@ -1286,7 +821,7 @@ hipError_t launch_chol(const void *A_, void *L_, void *Lh_, int64_t n, int64_t n
             }
         }
         if (!diag_done) {
-            hipError_t e = launch_kernel(chol_diag_kernel, dim3(1), dim3(NT), s, Sm, L, Lh, n, j0, cols, k0, W_of(j0, cols), ok_of(j0, cols), wait_limit());
+            hipError_t e = launch_kernel(chol_diag_kernel, dim3(1), dim3(NT), s, Sm, L, Lh, n, j0, cols, k0, W_of(j0, cols));
             if (e != hipSuccess) return fail(e);
         }
         diag_done = false;
@@ -1311,8 +846,8 @@ hipError_t launch_chol(const void *A_, void *L_, void *Lh_, int64_t n, int64_t n
             const int64_t k0_first = prepared_from >= 0 ? prepared_from : k0;
             hipError_t e = launch_kernel(chol_panel_kernel, dim3((unsigned)((n - j1 + 63) / 64 + (prepare ? 2 : 0))), dim3(NT), s, Sm, L, Lh, n, j0, cols, k0,
                                fuse ? (g0 > 0 ? (const float *)L : A) : (const float *)nullptr, (const float *)W_of(j0, cols),
-                               (const int *)ok_of(j0, cols), fuse ? W_of(j1, NBMAX) : (float *)nullptr, fuse ? ok_of(j1, NBMAX) : (int *)nullptr,
-                               copied ? (const float *)tile_copy : (const float *)nullptr, fuse && next_group ? tile_copy : (float *)nullptr, wait_limit(),
+                               fuse ? W_of(j1, NBMAX) : (float *)nullptr,
+                               copied ? (const float *)tile_copy : (const float *)nullptr, fuse && next_group ? tile_copy : (float *)nullptr,
                                k0_first, prepare ? 1 : 0);
             if (e != hipSuccess) return fail(e);
             prepared_from = prepare ? j0 : -1;

@@ -115,7 +115,7 @@ private:
 };
 
 // Bound, in polls, of the waits by which waves hand work to one another inside the tile kernels of the triangular solve
-// and of the Cholesky factorisation (cyc_diag_set_wait_limit; 2^20 unless a test has set it).
+// (cyc_diag_set_wait_limit; 2^20 unless a test has set it).
 int wait_limit();
 
 // workspace: trsm_workspace_bytes() bytes of device memory (inverses of the diagonal tiles), or nullptr: every tile by substitution
@@ -131,7 +131,7 @@ hipError_t launch_trsm_padded(const void *L, const void *B, void *X, void *Xh, i
 int64_t chol_padded_bytes(const void *A, void *L, void *Lh, int64_t n, int64_t nb);
 hipError_t launch_chol_padded(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, hipStream_t s);
 // tiled Cholesky factorisation A = L L^T in tiles of nb (see cyc_chol.hip); arguments validated by the caller
-// workspace: chol_workspace_bytes() bytes of device memory (inverses of the diagonal tiles), or nullptr: no inverses
+// workspace: chol_workspace_bytes() bytes of device memory (inverses and a copy of diagonal tiles), or nullptr: no inverses
 int64_t chol_workspace_bytes(int64_t n, int64_t nb);
 hipError_t launch_chol(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, hipStream_t s);
 // FlashAttention-2 tile recurrence (see cyc_attn.hip); requires supports_attention(N, M, d)

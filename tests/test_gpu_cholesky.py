@@ -234,3 +234,38 @@ def test_rows_below_an_ill_conditioned_diagonal_tile_keep_the_chain(lib, chol):
     scale = np.abs(ref).max()
     err = np.abs(L.astype(np.float64) - ref)
     assert err.max() <= 4 * 2.0 ** -9 * scale * 64, "bound scaled by the norm of the ill-conditioned tile"
+
+
+@pytest.mark.parametrize("case", ["large", "small", "mixed", "tiny_in_tile", "tiny_below", "zeros", "ones"])
+def test_quotients_from_reciprocals_are_the_divisions(lib, chol, case):
+    """The tile kernels take roots and quotients from hardware estimates and exact remainders where everything that comes out
+    lies in [2^-50, 2^50] or is zero, and start over with IEEE root and division elsewhere: bit for bit the oracle's first
+    panel (the rows right below the diagonal tile, a product with its inverse, excepted) on either side of that line, with
+    zeros of both signs, and for a pivot whose significand is 24 ones, whose reciprocal is next to a tie."""
+    n, nb = 256, 64
+    A = ws_inputs.spd_f32(n, 17, 0, "cpu").numpy()
+    d = np.ones(n, dtype=np.float32)
+    if case in ("large", "small"):
+        d[:] = 2.0 ** (52 if case == "large" else -52)
+    elif case == "mixed":                          # L from 2^-55 to 2^50
+        d = (2.0 ** np.linspace(-50, 50, n).round()).astype(np.float32)[np.random.default_rng(3).permutation(n)]
+    A = d[:, None] * A * d[None, :]
+    if case == "tiny_in_tile":
+        A[40, :20] *= np.float32(1e-18)
+        A[:20, 40] = A[40, :20]
+    elif case == "tiny_below":
+        A[200, :64] *= np.float32(1e-18)
+        A[:64, 200] = A[200, :64]
+    elif case == "zeros":
+        A[::3, :][:, 1::3] = np.float32(-0.0)
+        A[1::3, :][:, ::3] = np.float32(-0.0)
+    elif case == "ones":
+        A[:, 0] = A[0, :] = 2.0 ** -(np.arange(n) % 12 + 6)
+        A[0, 0] = 1 - 2.0 ** -24                   # its root: 1 - 2^-24 again, 24 ones
+    A = np.ascontiguousarray(A, dtype=np.float32)
+    L, _ = run(lib, torch.from_numpy(A).to(DEV), nb)
+    Lo, _ = chol.chol_tiled(A, nb)
+    assert np.all(np.isfinite(Lo))
+    rows = np.r_[0:64, 128:n]
+    same = np.tril(np.ones((n, nb), dtype=bool))[rows]
+    assert np.array_equal(L[rows, :nb].view(np.int32)[same], Lo[rows, :nb].astype(np.float32).view(np.int32)[same])
