@@ -134,7 +134,7 @@ int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C,
 /* The same as cyc_recurrence_matmul where the partial sums may lie in memory of the caller's, which calls under stream capture
  * need if their graph is to share nothing with other graphs and calls on the stream.  Products with few output blocks and long k that no
  * power of two divides into enough equal slices, and products of few rows with very long k, also have k mapped to space here
- * (18 x 17280 x 784 bf16: 39 us without, 16 so; at most 16 MiB of partial sums).  cyc_matmul_workspace says how many bytes the
+ * (18 x 17280 x 784 bf16: 39 us without, 16 so; at most 64 MiB of partial sums).  cyc_matmul_workspace says how many bytes the
  * call wants (0: it needs none; host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not
  * cleared, free again when the call's work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is
  * enqueued.  workspace NULL: the library's per-(device, stream) workspace, or CYC_ERR_WORKSPACE if `stream` is being captured.

@@ -321,7 +321,7 @@ int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, i
     if (st != CYC_OK || k == K_NONE) return st;
     if (!workspace_ok(workspace, workspace_bytes)) return CYC_ERR_SHAPE;
     if (k != K_MFMAK) return run(p, k, split, (hipStream_t)stream, GIVEN);
-    // (slices of any length fit 16 MiB, 256 partial blocks of 128 x 128, which a stream's workspace may well keep; under a capture it
+    // (partial sums fit 64 MiB, 256 blocks of 256 x 256, which a stream's workspace may well keep; under a capture it
     // would be shared with other graphs, and asking torch for memory on every call costs 3 us of host time)
     if (!workspace) return cyc::is_capturing((hipStream_t)stream) ? CYC_ERR_WORKSPACE : run(p, k, split, (hipStream_t)stream, CACHED);
     const int64_t es = p.i8 ? 1 : 2;

@@ -170,7 +170,16 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
     // of A (the stationary operand) stay in that XCD's L2 while the columns stream by.
     int bid = blockIdx.x, bz = blockIdx.y;              // block of C and batch element (or k-slice) of this workgroup
     const int nblk = tiles_m * tiles_n;
-    if ((nblk & 7) == 0) {
+    if (EPI == EPI_SLICE && nblk == 1) {
+        bid = 0;                                         // (nothing is shared)
+    } else if (EPI == EPI_SLICE) {
+        // k-slices: the blocks of one slice share its A and B, so each XCD gets a contiguous run of (slice, block) pairs, the
+        // first (their number mod 8) XCDs one more
+        const int number = blockIdx.y * nblk + blockIdx.x, total = nblk * (int)gridDim.y, xcd = number & 7;
+        const int at = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : total & 7) + (number >> 3);
+        bz = (int)((unsigned)at / (unsigned)nblk);
+        bid = at - bz * nblk;
+    } else if ((nblk & 7) == 0) {
         bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
     } else if ((gridDim.y & 7) == 0) {
         // few blocks per batch element (or k-slice): keep the blocks of one element, which share its A and B, on one
@@ -227,11 +236,18 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
     // stage sa), otherwise a piece of the B tile (into B stage sb)
     // (`tail`: this call may be about the last k-tile; false in the bulk of the k loop, where the copy is
     // then unconditional)
-    const char *srcA = baseA + 2 * 128, *srcB = baseB + 2 * stepB;   // source of the k-tile being fetched in the loop
+    // The k-slices of a problem start about bz k-tiles into their range and come back to its beginning at the end (the last, ragged
+    // k-tile of a RAGGED problem keeps its place): slices are often a power of two apart, and workgroups that all ask for the same
+    // k-tile of theirs then meet in the same few channels of the memory (512 x 262144 x 512 bf16: 156 us, 144 so).
+    const int whole = EPI == EPI_SLICE ? (RAGGED ? last : nkt) : 0;
+    const int turn = whole > 0 ? bz & ((1 << (31 - __builtin_clz(whole))) - 1) : 0;      // (below whole; a division would cost more than it is worth)
+    auto place = [&](int t) __attribute__((always_inline)) { return EPI == EPI_SLICE && t < whole ? (t + turn < whole ? t + turn : t + turn - whole) : t; };
+    const char *srcA = baseA + (int64_t)place(2) * 128, *srcB = baseB + place(2) * stepB;   // source of the k-tile being fetched in the loop
+    int before_wrap = whole - 1 - place(2);                          // (whole > 2 in the bulk of the loop, which alone looks at it)
     auto issue_one = [&](int x, int sa, int sb, int ktile, bool tail) __attribute__((always_inline)) {
         const uint32_t dst = x < C::AI ? sa * C::A_BYTES + (w * C::AI + x) * 1024
                                        : LDS_B0 + sb * C::B_BYTES + (w * C::BI + x - C::AI) * 1024;
-        const char *src = x < C::AI ? baseA + (int64_t)ktile * 128 : baseB + (int64_t)ktile * stepB;
+        const char *src = x < C::AI ? baseA + (int64_t)place(ktile) * 128 : baseB + (int64_t)place(ktile) * stepB;
         const uint32_t off = x < C::AI ? voffA[x] : voffB[x - C::AI];
         if (RAGGED && tail && ktile == last) {
             if ((tail_ok >> x) & 1) async_copy16(src, off, lds_base + dst);
@@ -380,8 +396,8 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
         const int sa0 = kt & 1, sa1 = sa0 ^ 1;
         const int sb1 = sb0 == 2 ? 0 : sb0 + 1, sb2 = sb1 == 2 ? 0 : sb1 + 1;
         if (careful) {
-            srcA = baseA + (int64_t)tile_at(kt + 2) * 128;
-            srcB = baseB + (int64_t)tile_at(kt + 2) * stepB;
+            srcA = baseA + (int64_t)place(tile_at(kt + 2)) * 128;
+            srcB = baseB + (int64_t)place(tile_at(kt + 2)) * stepB;
         }
         const bool at_last = RAGGED && careful && kt + 2 >= last;
         half(0, sa0, sb0, 1, C::AI, C::BI, 0, sb2, at_last);
@@ -394,6 +410,11 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
         if (!careful) {
             srcA += 128;
             srcB += stepB;
+            if (EPI == EPI_SLICE && before_wrap-- == 0) {
+                srcA = baseA;
+                srcB = baseB;
+                before_wrap = whole - 1;
+            }
         }
         sb0 = sb1;
     };
@@ -561,14 +582,26 @@ KSplit choose_ksplit(const Problem &p, bool any)
     // start and to finish: take them when they compute little padding, still fill the chip and keep long slices
     const int ks256 = supports_mfma(p, 256) ? slices(b256, 256) : 1;
     if (b256 * 4 * 5 <= b128 * 6 && b256 * ks256 >= 200 && p.K / ks256 >= 4096) return {ks256, 256, p.K / ks256};
-    const int ks = slices(b128, 256);
-    // K need not be a multiple of anything: where the equal slices are less than 3/4 as many as the chip has room for, as many
-    // slices as there is room for, of whole k-tiles, the last one with what remains (40 x 17280 x 784 bf16: 110 us in two slices' stead, 14)
-    const int64_t nkt = (p.K + bke - 1) / bke, want = std::min<int64_t>(256 / b128, nkt / 8);
-    if (any && ks * 4 < want * 3) {
-        const int64_t per = (nkt + want - 1) / want;
-        return {(int)((nkt + per - 1) / per), 128, per * bke};
+    // K need not be a multiple of anything: as many slices as the chip has room for, of whole k-tiles, the last one with what
+    // remains.  Blocks of 256 x 256, one to a compute unit, from 20 k-tiles a slice on (bf16 512 x 262208 x 512 136 us, 175 in
+    // blocks of 128; 1000 x 24000 x 1000, 24 k-tiles, 60 / 70; 1024 x 16384 x 1024, 16, 48 / 41; i8 1000 x 100032 x 992 100 / 154,
+    // 768 x 50048 x 768, 14, 45 / 41); blocks of 128 x 128 two to a compute unit from 28 on (bf16 64 x 131072 x 1000 62 us, 67 with
+    // one; 768 x 30720 x 768 50 / 62; 128 x 65536 x 1024, 16 k-tiles, 43 / 39)
+    const int64_t nkt = (p.K + bke - 1) / bke;
+    auto cut = [&](int64_t n, int tile) {
+        const int64_t per = (nkt + n - 1) / n;
+        return KSplit{(int)((nkt + per - 1) / per), tile, per * bke};
+    };
+    if (any) {
+        const int64_t n256 = 256 / b256, n128 = std::min<int64_t>(512 / b128, 256);
+        if (supports_mfma(p, 256) && b256 * 4 * 5 <= b128 * 6 && n256 > 1 && nkt > 19 * n256) return cut(n256, 256);
+        if (n128 > 1 && nkt > 27 * n128) return cut(n128, 128);
     }
+    // where the equal slices are less than 3/4 as many as there is room for, slices of any number here, too (40 x 17280 x 784
+    // bf16: 110 us in two slices' stead, 14)
+    const int ks = slices(b128, 256);
+    const int64_t want = std::min<int64_t>(256 / b128, nkt / 8);
+    if (any && ks * 4 < want * 3) return cut(want, 128);
     return {ks, 128, p.K / ks};
 }
 
