@@ -617,16 +617,16 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
         Pivot p;
         p.from_root(D[lane][lane]);
         lds.rinv[lane] = p.r;                                                   // (the same numbers by every wave: no barrier)
-        solve_rows16<true, LDT>(D, lds.rinv, t, row, lane, [](auto) {});
+        solve_rows16<true, NBLK>(D, lds.rinv, t, row, lane, [](auto, float) {});
 #pragma unroll
         for (int G = 0; G < 4; ++G) x[G] = *(const wave_f32x4 *)(row + 16 * G + 4 * g);
-        const unsigned worst = max(max(worst_code(x[0]), worst_code(x[1])), max(max(worst_code(x[2]), worst_code(x[3])), range_code(p.d)));
+        const unsigned worst = max(max(worst_code(x[0]), worst_code(x[1])), max(max(worst_code(x[2]), worst_code(x[3])), p.code()));
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
-            const bool safe = range_code(p.d) <= SAFE_SPAN && all_safe(x[0]) && all_safe(x[1]) && all_safe(x[2]) && all_safe(x[3]);
+            const bool safe = p.code() <= SAFE_SPAN && all_safe(x[0]) && all_safe(x[1]) && all_safe(x[2]) && all_safe(x[3]);
             if (__builtin_amdgcn_ballot_w64(!safe) != 0) {
 #pragma unroll
                 for (int G = 0; G < 4; ++G) t[G] = S[G];
-                solve_rows16<false, LDT>(D, lds.rinv, t, row, lane, [](auto) {});
+                solve_rows16<false, NBLK>(D, lds.rinv, t, row, lane, [](auto, float) {});
             }
         }
         if (nks_e > 0) {                                                        // (an even number)

@@ -28,149 +28,156 @@ namespace {
 
 #define CYC_LDS __attribute__((address_space(3)))
 
-constexpr int SUB = 8;     // rows a lane carries at a time
-
 __device__ __forceinline__ float widen_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 // fp32 -> bfloat16 bit pattern, round to nearest, ties to even; NaN stays NaN (the hardware conversion)
 __device__ __forceinline__ uint16_t round_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 
-// SUB chains take the x of the tile's rows [0, rb): t[q] = fma(-L[rb+q][j], x_j, t[q]) for j ascending.
-// rb is a multiple of 8.  The LDS reads of eight steps are issued together and only then consumed (left to
-// itself the scheduler, under register pressure, issues them one step at a time and every step then
-// waits out the full LDS latency).  Lt[j][r] = L[r][j] (fp32), xs[j][lane] = x_j of this lane's column.
-template <int NB>
-__device__ __forceinline__ void take_earlier_rows(float (&t)[SUB], const float (*Lt)[NB], const float (*xs)[64], int rb, int lane)
+constexpr int LDD = 64 + 4;    // row stride of fp32 tiles in LDS (see solve_rows16)
+
+// One 64 x 64 block of L in fp32, row-major, into LDS by 256 threads: rows r0 .., columns j0 .. of the rows and columns below
+// `rows` and `cols`, whose rest is the identity's (DIAGONAL) or zero.  Above the diagonal of a DIAGONAL block there may be anything.
+// vec: the rows' 16-byte pieces are aligned and whole.
+template <bool DIAGONAL>
+__device__ __forceinline__ void stage_block(float (*D)[LDD], const uint16_t *__restrict__ L, int64_t n, int64_t r0, int64_t j0, int rows, bool vec, int tid)
 {
-#pragma unroll 1
-    for (int j0 = 0; j0 < rb; j0 += 8) {
-        float x[8];
-        float4 l0[8], l1[8];
+    if (vec) {
+        uint4 piece[2];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            x[u] = xs[j0 + u][lane];
-            l0[u] = *(const float4 *)&Lt[j0 + u][rb];
-            l1[u] = *(const float4 *)&Lt[j0 + u][rb + 4];
+        for (int p = 0; p < 2; ++p) {
+            const int id = tid + 256 * p, r = id >> 3, jc = id & 7;
+            piece[p] = make_uint4(0, 0, 0, 0);
+            if (r < rows && (!DIAGONAL || 8 * jc <= r)) piece[p] = *(const uint4 *)(L + (r0 + r) * n + j0 + 8 * jc);
         }
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            t[0] = __builtin_fmaf(-l0[u].x, x[u], t[0]);
-            t[1] = __builtin_fmaf(-l0[u].y, x[u], t[1]);
-            t[2] = __builtin_fmaf(-l0[u].z, x[u], t[2]);
-            t[3] = __builtin_fmaf(-l0[u].w, x[u], t[3]);
-            t[4] = __builtin_fmaf(-l1[u].x, x[u], t[4]);
-            t[5] = __builtin_fmaf(-l1[u].y, x[u], t[5]);
-            t[6] = __builtin_fmaf(-l1[u].z, x[u], t[6]);
-            t[7] = __builtin_fmaf(-l1[u].w, x[u], t[7]);
+        for (int p = 0; p < 2; ++p) {
+            const int id = tid + 256 * p, r = id >> 3, jc = id & 7;
+            const uint32_t v[4] = {piece[p].x, piece[p].y, piece[p].z, piece[p].w};
+            wave_f32x4 lo, hi;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                lo[e] = widen_bf16((uint16_t)(v[e >> 1] >> (16 * (e & 1))));
+                hi[e] = widen_bf16((uint16_t)(v[2 + (e >> 1)] >> (16 * (e & 1))));
+                if (DIAGONAL && r >= rows) {
+                    lo[e] = 8 * jc + e == r ? 1.0f : 0.0f;
+                    hi[e] = 8 * jc + 4 + e == r ? 1.0f : 0.0f;
+                }
+            }
+            *(wave_f32x4 *)&D[r][8 * jc] = lo;
+            *(wave_f32x4 *)&D[r][8 * jc + 4] = hi;
         }
-        __builtin_amdgcn_sched_barrier(0);
+    } else {
+        uint16_t v[16];
+        const int j = tid & 63;
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const int r = 4 * p + (tid >> 6);
+            v[p] = 0;
+            if (r < rows && (!DIAGONAL || j <= r)) v[p] = L[(r0 + r) * n + j0 + j];
+        }
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const int r = 4 * p + (tid >> 6);
+            D[r][j] = DIAGONAL && r >= rows && j == r ? 1.0f : widen_bf16(v[p]);
+        }
     }
 }
 
-// The SUB x SUB corner of L_II that couples the rows rb .. rb+SUB-1, fetched in one round before the chains
-// over the earlier rows run, so that no LDS read sits inside the dependent chain of the corner solve:
-// corner(p, q) = L[rb+q][rb+p] for p <= q.
-template <int NB>
-struct Corner {
-    float4 lo[SUB], hi[SUB];
-    __device__ __forceinline__ void fetch(const float (*Lt)[NB], int rb)
-    {
-#pragma unroll
-        for (int p = 0; p < SUB; ++p) {
-            lo[p] = *(const float4 *)&Lt[rb + p][rb];
-            hi[p] = *(const float4 *)&Lt[rb + p][rb + 4];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    __device__ __forceinline__ float at(int p, int q) const
-    {
-        const float4 v = q < 4 ? lo[p] : hi[p];
-        const int e = q & 3;
-        return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
-    }
-};
-
-// Diagonal space: X_I = TRSM(L_II, R_I) for one tile of `rows` <= NB rows starting at row r0, all
-// right-hand sides.  One wave per 64 columns, one lane per column: a column of X is a chain
+// Diagonal space: X_I = TRSM(L_II, R_I) for one tile of `rows` rows starting at row r0, all right-hand sides, 64 to a workgroup
+// and sixteen to a wave: a column of X is a chain
 //     t = R_r;  t = fma(-L_rj, x_j, t)  for j ascending over the tile's earlier rows;  x_r = t / L_rr
-// in fp32 on the unrounded x.  A lane works on SUB rows at a time: SUB independent chains take the
-// x of all earlier rows of the tile (kept in LDS, one column per lane), then the SUB x SUB corner is
-// solved in registers.  L_II is staged in LDS once, transposed ([j][r], fp32), so that the SUB
-// coefficients a step needs are two broadcast 16-byte reads; nothing above the diagonal is used.
-// FULL: the tile has exactly NB rows and its rows of L are 16-byte aligned (no per-row checks).
-template <int NB, bool FULL>
-__global__ __launch_bounds__(64) void tri_diag_kernel(const uint16_t *__restrict__ L, int64_t n, const float *Rin,
-                                                      float *X, uint16_t *__restrict__ Xh, int64_t nrhs, int64_t r0,
-                                                      int rows_arg, int vec_arg)
+// in fp32 on the unrounded x, which solve_rows16 runs for sixteen of them (a right-hand side is one of its rows).  Tiles of more
+// than 64 rows in two blocks: what the first takes out of the second is the same instruction on the values as they were spread.
+// BLOCKS: blocks of four rows in all, at least rows / 4.  A right-hand side in a lane of its own, eight rows at a time, took 11.8 us
+// for a tile of 64 rows, this 6.5; tiles of 128 rows 50 (with the launch), this 11 (1024 x 512 439 -> 131 us, 2048 x 256 in tiles of 32 855 -> 634).
+template <int BLOCKS>
+__global__ __launch_bounds__(256) void tri_diag_kernel(const uint16_t *__restrict__ L, int64_t n, const float *Rin,
+                                                       float *X, uint16_t *__restrict__ Xh, int64_t nrhs, int64_t r0, int rows, int vec)
 {
-    const int rows = FULL ? NB : rows_arg;
-    const bool vec = FULL || vec_arg;
-    __shared__ __attribute__((aligned(16))) float Lt[NB][NB];    // Lt[j][r] = L[r0+r][r0+j], j <= r
-    __shared__ float xs[NB][64];                                 // xs[j][lane] = x_j of this lane's column
-    const int lane = threadIdx.x;
-    const int64_t c = (int64_t)blockIdx.x * 64 + lane;
-
-    // stage L_II.  With 16-byte aligned rows each lane fetches 16-byte pieces of rows, all loads in flight
-    // together (pieces wholly above the diagonal are skipped; of a piece that straddles it only the part
-    // at or below the diagonal is used); otherwise element by element.
-    if (vec) {
-        const int cpr = rows >> 3;                               // 16-byte pieces per row of the tile
-        constexpr int PER_LANE = NB * NB / 8 / 64;
-        uint4 piece[PER_LANE];
+    constexpr int TWO = BLOCKS > NBLK ? 1 : 0, FIRST = TWO ? NBLK : BLOCKS;        // blocks of the first 64 rows
+    static_assert(BLOCKS % 4 == 0 && (!TWO || BLOCKS == 2 * NBLK), "whole groups of sixteen rows");
+    __shared__ __attribute__((aligned(16))) struct {
+        float D[1 + 2 * TWO][64][LDD];                     // the diagonal blocks first, then the one below the first
+        float Y[1 + TWO][64][LDD];                         // the solution, [right-hand side][row]
+        float rinv[1 + TWO][64];
+    } lds;
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t c0 = (int64_t)blockIdx.x * 64;
+    const int64_t mine = c0 + 16 * w + i < nrhs ? c0 + 16 * w + i : nrhs - 1;      // columns past the last one shadow it
+    wave_f32x4 S[BLOCKS / 4];
 #pragma unroll
-        for (int x = 0; x < PER_LANE; ++x) {
-            const int id = lane + 64 * x, r = id / cpr, jc = id - r * cpr;
-            piece[x] = make_uint4(0, 0, 0, 0);
-            if (r < rows && jc * 8 <= r) piece[x] = *(const uint4 *)(L + (r0 + r) * n + r0 + jc * 8);
+    for (int G = 0; G < BLOCKS / 4; ++G)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k = 16 * G + 4 * g + r;
+            S[G][r] = k < rows ? Rin[(r0 + k) * nrhs + mine] : 0.0f;
         }
-#pragma unroll
-        for (int x = 0; x < PER_LANE; ++x) {
-            const int id = lane + 64 * x, r = id / cpr, jc = id - r * cpr;
-            if (r < rows && jc * 8 <= r) {
-                const uint32_t w[4] = {piece[x].x, piece[x].y, piece[x].z, piece[x].w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int j = jc * 8 + e;
-                    if (j <= r) Lt[j][r] = widen_bf16((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
-                }
-            }
-        }
-    } else {
-        for (int r = lane; r < rows; r += 64)
-            for (int j = 0; j <= r; ++j) Lt[j][r] = widen_bf16(L[(r0 + r) * n + r0 + j]);
+    stage_block<true>(lds.D[0], L, n, r0, r0, rows < 64 ? rows : 64, vec, tid);
+    if (TWO) {
+        stage_block<true>(lds.D[TWO], L, n, r0 + 64, r0 + 64, rows - 64, vec, tid);
+        stage_block<false>(lds.D[2 * TWO], L, n, r0 + 64, r0, rows - 64, vec, tid);
     }
     __syncthreads();
-    if (c >= nrhs) return;        // lanes past the last column only helped staging L; no barrier follows
-
-    // the tile's right-hand side comes in with one round of loads, not one per SUB rows
-    const float *rp = Rin + r0 * nrhs + c;
-    float *xp = X + r0 * nrhs + c;
-    uint16_t *hp = Xh + r0 * nrhs + c;
-    // xs[r][lane] holds R_r until row r is solved and x_r from then on.  (The loop over the row groups
-    // below is deliberately not unrolled: a wave runs through this code once, so straight-line code
-    // would be fetched from memory instruction by instruction; a loop body stays in the instruction cache.)
-#pragma unroll 16
-    for (int r = 0; r < rows; ++r) xs[r][lane] = rp[r * nrhs];
-
-#pragma unroll 1
-    for (int rb = 0; rb < rows; rb += SUB) {
-        float t[SUB];
+    unsigned worst = 0;
+    bool divisors_safe = true;
 #pragma unroll
-        for (int q = 0; q < SUB; ++q) t[q] = rb + q < rows ? xs[rb + q][lane] : 0.0f;
-        Corner<NB> corner;
-        corner.fetch(Lt, rb);
-        take_earlier_rows<NB>(t, Lt, xs, rb, lane);
-        // the SUB x SUB corner
+    for (int q = 0; q <= TWO; ++q) {
+        Pivot p;
+        p.from_root(lds.D[q][lane][lane]);
+        lds.rinv[q][lane] = p.r;                           // (the same numbers by every wave: no barrier)
+        worst = max(worst, p.code());
+        divisors_safe = divisors_safe && p.code() <= SAFE_SPAN;
+    }
+    auto run = [&](auto by_pivots) __attribute__((always_inline)) {
+        constexpr bool PIVOTS = decltype(by_pivots)::value;
+        wave_f32x4 t[FIRST / 4];
+        float out[FIRST];
 #pragma unroll
-        for (int q = 0; q < SUB; ++q) {
-            if (rb + q < rows) {                                 // uniform over the wave
+        for (int G = 0; G < FIRST / 4; ++G) t[G] = S[G];
+        solve_rows16<PIVOTS, FIRST>(lds.D[0], lds.rinv[0], t, &lds.Y[0][16 * w + i][0], lane,
+                                    [&](auto block, float v) __attribute__((always_inline)) { out[decltype(block)::value] = v; });
+        if constexpr (TWO) {
+            wave_f32x4 u[4];
 #pragma unroll
-                for (int p = 0; p < q; ++p) t[q] = __builtin_fmaf(-corner.at(p, q), t[p], t[q]);
-                t[q] = t[q] / corner.at(q, q);
-                xs[rb + q][lane] = t[q];
-                xp[(rb + q) * nrhs] = t[q];
-                hp[(rb + q) * nrhs] = round_bf16(t[q]);
+            for (int H = 0; H < 4; ++H) u[H] = S[4 + H];
+#pragma unroll
+            for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+                for (int H = 0; H < 4; ++H) u[H] = __builtin_amdgcn_mfma_f32_16x16x4f32(lds.D[2][16 * H + i][4 * b + g], out[b], u[H], 0, 0, 0);
+            solve_rows16<PIVOTS, NBLK>(lds.D[1], lds.rinv[1], u, &lds.Y[1][16 * w + i][0], lane, [](auto, float) {});
+        }
+    };
+    run(std::true_type{});
+    // quotients by reciprocals are IEEE's in the safe range (see Pivot); elsewhere once more with divisions
+    wave_f32x4 x[BLOCKS / 4];
+#pragma unroll
+    for (int G = 0; G < BLOCKS / 4; ++G) {
+        x[G] = *(const wave_f32x4 *)&lds.Y[G / 4][16 * w + i][16 * (G % 4) + 4 * g];
+        worst = max(worst, worst_code(x[G]));
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
+        bool safe = divisors_safe;
+#pragma unroll
+        for (int G = 0; G < BLOCKS / 4; ++G) safe = safe && all_safe(x[G]);        // (zeros are)
+        if (__builtin_amdgcn_ballot_w64(!safe) != 0) run(std::false_type{});
+    }
+    __syncthreads();
+    // a right-hand side to a lane, sixteen rows of each 64 to a wave (fewer where the tile has fewer)
+    const int64_t c = c0 + lane;
+    if (c < nrhs) {
+        constexpr int PER = BLOCKS >= 16 ? 16 : BLOCKS;
+#pragma unroll
+        for (int q = 0; q <= TWO; ++q) {
+            float v[PER];
+#pragma unroll
+            for (int p = 0; p < PER; ++p) v[p] = lds.Y[q][lane][PER * w + p];
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int r = 64 * q + PER * w + p;
+                if (r < rows) {                            // uniform
+                    X[(r0 + r) * nrhs + c] = v[p];
+                    Xh[(r0 + r) * nrhs + c] = round_bf16(v[p]);
+                }
             }
         }
     }
@@ -679,73 +686,84 @@ constexpr int INV_FLOATS = 64 * 64;        // one inverse in the workspace, in t
 constexpr int PANEL_BAND = 7, PACK_PIECES = 8, PACK_BYTES_PER_TILE_ROW = PANEL_BAND * PACK_PIECES * 1024;
 constexpr float INV_NORM_LIMIT = 8.0f;
 
-// One wave per full diagonal tile: lane j solves L_tt y = e_j.  Entry (r, j) of the inverse is stored where the panel
+// Four waves per full diagonal tile: wave w solves L_tt y = e_j for j = 16 w .. 16 w + 15.  Entry (r, j) of the inverse is stored where the panel
 // kernel's MFMA wants it as its A operand.  Which k a slot of that MFMA stands for is free as long as both operands
 // agree; slot l/16 of k-step ks is k = 16 (ks / 4) + 4 (l / 16) + ks % 4, so that the four rows of R which a k-step
 // reads as the other operand lie four rows apart, on disjoint LDS banks.  Operand lane (r % 16) + 16 (j / 4 % 4) thus
 // holds entry (r, j) for row block rb = r / 16 and k-step ks = 4 (j / 16) + j % 4.  A tile is 16 pieces of 1 KiB, piece
 // 4 rb + ks / 4 holding the four k-steps ks / 4 * 4 .. + 3 of all 64 operand lanes ([lane][ks % 4]), so that a wave
 // fetches a piece with one fully coalesced 16-byte load per lane.
-__global__ __launch_bounds__(64) void tri_inverse_kernel(const uint16_t *__restrict__ L, int64_t n, float *__restrict__ Winv,
-                                                         int *__restrict__ ok, char *__restrict__ packed, int full)
+// It precedes the first panel.  One wave per tile, a column to a lane, took 15 us, this 7 (1000 x 136 72 -> 57 us with the short tile).
+__global__ __launch_bounds__(256) void tri_inverse_kernel(const uint16_t *__restrict__ L, int64_t n, float *__restrict__ Winv,
+                                                          int *__restrict__ ok, char *__restrict__ packed, int full)
 {
-    constexpr int NB = 64, LDD = NB + 4, cpr = NB / 8, PER_LANE = NB * NB / 8 / 64;
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= full) {
-        // the workgroups behind the `full` that invert: one piece each of the operand-order copy (see PANEL_BAND)
-        const int id = (int)blockIdx.x - full, T = id / (PANEL_BAND * PACK_PIECES), rest = id % (PANEL_BAND * PACK_PIECES);
-        const int S = T - 1 - rest / PACK_PIECES, piece = rest % PACK_PIECES, l = threadIdx.x;
+        // the workgroups behind the `full` that invert: one piece each to a wave of the operand-order copy (see PANEL_BAND)
+        const int id = 4 * ((int)blockIdx.x - full) + w, T = id / (PANEL_BAND * PACK_PIECES), rest = id % (PANEL_BAND * PACK_PIECES);
+        const int S = T - 1 - rest / PACK_PIECES, piece = rest % PACK_PIECES, l = lane;
         if (S >= 0)
             *(uint4 *)(packed + ((int64_t)id * 64 + l) * 16) =
                 *(const uint4 *)(L + ((int64_t)T * 64 + 16 * (piece >> 1) + (l & 15)) * n + (int64_t)S * 64 + 32 * (piece & 1) + 8 * (l >> 4));
         return;
     }
-    __shared__ __attribute__((aligned(16))) float D[NB][LDD];
-    __shared__ float norms[2][64];
-    const int lane = threadIdx.x;
-    const int64_t rt = (int64_t)blockIdx.x * NB;
+    static_assert(PANEL_BAND * PACK_PIECES % 4 == 0, "the pieces of a tile row fill whole workgroups");
+    __shared__ __attribute__((aligned(16))) struct {
+        float D[64][LDD], Y[64][LDD];                            // Y: [column of the inverse][row]
+        float rinv[64], norms[2][4];
+    } lds;
+    const int64_t rt = (int64_t)blockIdx.x * 64;
+    stage_block<true>(lds.D, L, n, rt, rt, 64, true, tid);
+    __syncthreads();
+    Pivot p;
+    p.from_root(lds.D[lane][lane]);
+    lds.rinv[lane] = p.r;                                        // (the same numbers by every wave: no barrier)
+    float sum_L = 0.0f, sum_W = 0.0f;                            // of column 16 w + i, this lane's rows
+    wave_f32x4 t[4];
+    auto start = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int x = 0; x < PER_LANE; ++x) {                         // the 16-byte pieces on and below the diagonal, widened
-        const int id = lane + 64 * x, r = id / cpr, jc = id % cpr;
-        if (jc * 8 <= r) {
-            const uint4 piece = *(const uint4 *)(L + (rt + r) * n + rt + jc * 8);
-            const uint32_t v[4] = {piece.x, piece.y, piece.z, piece.w};
-            f32x4 lo, hi;
+        for (int G = 0; G < 4; ++G)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                lo[e] = widen_bf16((uint16_t)(v[e >> 1] >> (16 * (e & 1))));
-                hi[e] = widen_bf16((uint16_t)(v[2 + (e >> 1)] >> (16 * (e & 1))));
-            }
-            *(f32x4 *)&D[r][jc * 8] = lo;
-            *(f32x4 *)&D[r][jc * 8 + 4] = hi;
+            for (int r = 0; r < 4; ++r) t[G][r] = 16 * G + 4 * g + r == 16 * w + i ? 1.0f : 0.0f;
+    };
+    float *const row = &lds.Y[16 * w + i][0];
+    start();
+    solve_rows16<true, NBLK>(lds.D, lds.rinv, t, row, lane, [](auto, float) {});
+    // (the rows above the diagonal come out as exact zeros; everything else has to be in the range of Pivot or zero)
+    bool safe = p.code() <= SAFE_SPAN;
+#pragma unroll
+    for (int G = 0; G < 4; ++G) safe = safe && all_safe(*(const wave_f32x4 *)(row + 16 * G + 4 * g));
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!safe) != 0, 0)) {
+        start();
+        solve_rows16<false, NBLK>(lds.D, lds.rinv, t, row, lane, [](auto, float) {});
+    }
+    float *const out = Winv + (int64_t)blockIdx.x * INV_FLOATS + w * 256 + lane * 4;
+#pragma unroll
+    for (int G = 0; G < 4; ++G) {
+        wave_f32x4 piece;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            piece[q] = lds.Y[16 * w + 4 * g + q][16 * G + i];
+            sum_W += __builtin_fabsf(row[16 * G + 4 * g + q]);
+            const int r = 16 * G + 4 * g + q;
+            sum_L += r >= 16 * w + i ? __builtin_fabsf(lds.D[r][16 * w + i]) : 0.0f;
         }
+        *(wave_f32x4 *)(out + G * 1024) = piece;
+    }
+    const float largest_L = largest_column(sum_L), largest_W = largest_column(sum_W);
+    if (lane == 0) {
+        lds.norms[0][w] = largest_L;
+        lds.norms[1][w] = largest_W;
     }
     __syncthreads();
-    float colsum_L = 0.0f;                                       // column `lane` of |L_tt|, on and below the diagonal
-    for (int i = 0; i < NB; ++i) colsum_L += i >= lane ? __builtin_fabsf(D[i][lane]) : 0.0f;
-    float x[NB], xn[NB];
+    if (tid == 0) {
+        float a = 0.0f, b = 0.0f;                                // (a NaN is an infinity here, and no product of one is below the limit)
 #pragma unroll
-    for (int r = 0; r < NB; ++r) x[r] = r == lane ? 1.0f : 0.0f;
-    float colsum_inv = 0.0f;
-    float *out = Winv + (int64_t)blockIdx.x * INV_FLOATS + (lane >> 4) * 256 + ((lane >> 2) & 3) * 64 + (lane & 3);
-    solve_tile64<LDD>(
-        D, x, xn,
-        [&](int r, float y) __attribute__((always_inline)) {
-            out[(r >> 4) * 1024 + (r & 15) * 4] = y;              // rows above the lane's own come out as exact zeros
-            colsum_inv += __builtin_fabsf(y);
-        },
-        []() __attribute__((always_inline)) {});
-    norms[0][lane] = colsum_L;
-    norms[1][lane] = colsum_inv;
-    __syncthreads();
-    if (lane == 0) {
-        float a = 0.0f, b = 0.0f;
-        bool finite = true;
-        for (int j = 0; j < 64; ++j) {
-            a = __builtin_fmaxf(a, norms[0][j]);
-            b = __builtin_fmaxf(b, norms[1][j]);
-            finite = finite && norms[0][j] == norms[0][j] && norms[1][j] == norms[1][j];   // fmax drops a NaN
+        for (int q = 0; q < 4; ++q) {
+            a = __builtin_fmaxf(a, lds.norms[0][q]);
+            b = __builtin_fmaxf(b, lds.norms[1][q]);
         }
-        ok[blockIdx.x] = finite && a * b <= INV_NORM_LIMIT ? 1 : 0;
+        ok[blockIdx.x] = a * b <= INV_NORM_LIMIT ? 1 : 0;
     }
 }
 
@@ -1194,14 +1212,8 @@ hipError_t diag(const Solve &v, int64_t r0, int64_t r1)
     // 16-byte pieces of the tile's rows can be fetched whole
     const int vec = ((uintptr_t)v.L % 16 == 0) && v.n % 8 == 0 && r0 % 8 == 0 && rows % 8 == 0;
     hipError_t launch_err = hipSuccess;
-    if (vec && rows == 64)
-        launch_err = launch_kernel(tri_diag_kernel<64, true>, grid, dim3(64), v.s, v.L, v.n, R, v.X, v.Xh, v.nrhs, r0, rows, vec);
-    else if (vec && rows == 128)
-        launch_err = launch_kernel(tri_diag_kernel<128, true>, grid, dim3(64), v.s, v.L, v.n, R, v.X, v.Xh, v.nrhs, r0, rows, vec);
-    else if (rows <= 64)
-        launch_err = launch_kernel(tri_diag_kernel<64, false>, grid, dim3(64), v.s, v.L, v.n, R, v.X, v.Xh, v.nrhs, r0, rows, vec);
-    else
-        launch_err = launch_kernel(tri_diag_kernel<128, false>, grid, dim3(64), v.s, v.L, v.n, R, v.X, v.Xh, v.nrhs, r0, rows, vec);
+    const auto kernel = rows <= 16 ? tri_diag_kernel<4> : rows <= 32 ? tri_diag_kernel<8> : rows <= 64 ? tri_diag_kernel<16> : tri_diag_kernel<32>;
+    launch_err = launch_kernel(kernel, grid, dim3(256), v.s, v.L, v.n, R, v.X, v.Xh, v.nrhs, r0, rows, vec);
     return launch_err;
 }
 
@@ -1288,7 +1300,7 @@ hipError_t launch_trsm(const void *L, const void *B, void *X, void *Xh, int64_t 
         float *Winv = (float *)workspace;
         char *packed = (char *)(Winv + full * INV_FLOATS);
         int *ok = (int *)(packed + full * PACK_BYTES_PER_TILE_ROW);
-        const hipError_t e = launch_kernel(tri_inverse_kernel, dim3((unsigned)(full + full * PANEL_BAND * PACK_PIECES)), dim3(64), s, v.L, n, Winv, ok,
+        const hipError_t e = launch_kernel(tri_inverse_kernel, dim3((unsigned)(full + full * PANEL_BAND * PACK_PIECES / 4)), dim3(256), s, v.L, n, Winv, ok,
                                            packed, (int)full);
         if (e != hipSuccess) return e;
         v.Winv = Winv;

@@ -56,12 +56,17 @@ struct Division {
     }
 };
 
+// 2 |x| as a bit pattern less that of 2^-50: unsafe above SAFE_SPAN, and for a zero, which is safe (NaN and infinity are not)
+constexpr unsigned SAFE_LOW = (127u - 50u) << 24, SAFE_SPAN = 100u << 24;
+__device__ __forceinline__ unsigned range_code(float x) { return (__builtin_bit_cast(unsigned, x) << 1) - SAFE_LOW; }
+__device__ __forceinline__ bool in_safe_range(unsigned code) { return code <= SAFE_SPAN || code == 0u - SAFE_LOW; }
+
 // Correctly rounded square root and quotients by it in fewer dependent instructions than the compiler's expansions (7 from
 // the pivot to a quotient, 27 there), for a pivot that a whole column is divided by.  Markstein's method: the hardware's
 // estimates, off by a unit in the last place at most, corrected by exact remainders, d = g + (s - g g) y / 2, and with a
 // correctly rounded reciprocal r, q = q0 - (d q0 - t) r for q0 = t r.  The remainders are exact and the results those of IEEE
 // as long as nothing over- or underflows: where every |x| that comes out, pivots included, lies in [2^-50, 2^50] or is zero
-// (in_safe_range below; zeros keep their sign); callers take the compiler's way elsewhere.
+// (in_safe_range; zeros keep their sign where the pivot is positive); callers take the compiler's way elsewhere.
 // Evidence, on the device: the root on every float in [2^-100, 2^100); the quotient on 3.4e10 random pairs, and for every
 // divisor on all numerators whose quotient lies within 15 / (2 D) units of a midpoint, D being the divisor's 24-bit
 // significand: the error before the last rounding, at most 1.5 units * 2^-23, reaches 6 / (2 D).
@@ -84,15 +89,12 @@ struct Pivot {
         const float q = t * r;
         return __builtin_fmaf(-__builtin_fmaf(d, q, -t), r, q);
     }
+    // of a divisor: below SAFE_SPAN when it is one for quotient()
+    __device__ __forceinline__ unsigned code() const { return d > 0.0f ? range_code(d) : ~0u; }
 
 private:
     __device__ __forceinline__ void refine(float estimate) { r = __builtin_fmaf(__builtin_fmaf(-d, estimate, 1.0f), estimate, estimate); }
 };
-// 2 |x| as a bit pattern less that of 2^-50: unsafe above SAFE_SPAN, and for a zero, which is safe (NaN and infinity are not)
-constexpr unsigned SAFE_LOW = (127u - 50u) << 24, SAFE_SPAN = 100u << 24;
-__device__ __forceinline__ unsigned range_code(float x) { return (__builtin_bit_cast(unsigned, x) << 1) - SAFE_LOW; }
-__device__ __forceinline__ bool in_safe_range(unsigned code) { return code <= SAFE_SPAN || code == 0u - SAFE_LOW; }
-
 // The column recurrence of a 64-wide tile as a fixed list of steps, for the kernels that run it in one wave with
 // the lane's row in registers.  The 64 columns go in 16 blocks of four.  The four chains of block b first take the
 // columns left of the block (b "bulk" steps of four k each: 16 independent multiply-adds), then the 4 x 4 corner
@@ -152,9 +154,10 @@ __device__ __forceinline__ float spread16(const wave_f32x4 &x)
 // row[c] <- the solution of X L^T = S for the wave's sixteen rows, whose S is in t (used up); row: where the lane's row i lies in
 // LDS, 64 columns and four of padding.  D: L in LDS, fp32, row-major; only what lies on and below the diagonal matters.  rinv: the
 // reciprocals of its diagonal (PIVOTS; see Pivot: the caller looks at what came out, and solves again without PIVOTS where that
-// is outside the safe range).  beside(block) is called once per block of four columns with its number, a constant.
-template <bool PIVOTS, int LDD, class Beside>
-__device__ __forceinline__ void solve_rows16(const float (*D)[LDD], const float *rinv, wave_f32x4 (&t)[4], float *row, int lane, Beside beside)
+// is outside the safe range).  each(block, out) is called once per block of four columns with its number, a constant, and minus its
+// values in operand order: lane 16 q + i has column 4 block + q of row i.  BLOCKS: so many blocks only.
+template <bool PIVOTS, int BLOCKS, int LDD, class Each>
+__device__ __forceinline__ void solve_rows16(const float (*D)[LDD], const float *rinv, wave_f32x4 (&t)[BLOCKS / 4], float *row, int lane, Each each)
 {
     const int i = lane & 15, g = lane >> 4;
     // (as many values of a corner's row as it has: what a read brings and nobody uses is given to the next read's destination, which
@@ -174,13 +177,13 @@ __device__ __forceinline__ void solve_rows16(const float (*D)[LDD], const float 
         c3[p] = *(const wave_f32x4 *)&D[4 * b + 3][4 * b];
         if (PIVOTS) ri[p] = *(const wave_f32x4 *)(rinv + 4 * b);
 #pragma unroll
-        for (int h = (b + 1) / 4; h < 4; ++h) a[p][h] = D[16 * h + i][4 * b + g];
+        for (int h = (b + 1) / 4; h < BLOCKS / 4; ++h) a[p][h] = D[16 * h + i][4 * b + g];
     };
     request(std::integral_constant<int, 0>{});
-    unrolled<NBLK>([&](auto index) __attribute__((always_inline)) {
+    unrolled<BLOCKS>([&](auto index) __attribute__((always_inline)) {
         constexpr int b = decltype(index)::value, G = b / 4, gk = b % 4, first = (b + 1) / 4;
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (b + 1 < NBLK) request(std::integral_constant<int, b + 1>{});
+        if constexpr (b + 1 < BLOCKS) request(std::integral_constant<int, b + 1>{});
         __builtin_amdgcn_sched_barrier(0);
         wave_f32x4 c = t[G], v;                                                 // (a copy: the other lanes hold other columns)
         constexpr int p = b & 1;
@@ -198,10 +201,10 @@ __device__ __forceinline__ void solve_rows16(const float (*D)[LDD], const float 
             for (int e = j + 1; e < 4; ++e) c[e] = __builtin_fmaf(-v[j], corner[e][j], c[e]);
         }
         *(wave_f32x4 *)(row + (g == gk ? 16 * G + 4 * gk : 64)) = v;            // (the other lanes': into the padding)
-        beside(index);
         const float out = -spread16<gk>(v);
+        each(index, out);
 #pragma unroll
-        for (int h = first; h < 4; ++h) t[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][h], out, t[h], 0, 0, 0);
+        for (int h = first; h < BLOCKS / 4; ++h) t[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][h], out, t[h], 0, 0, 0);
     });
 }
 // the worst of four results, and whether all of them are safe (zeros included)
@@ -209,6 +212,26 @@ __device__ __forceinline__ unsigned worst_code(const wave_f32x4 &x) { return max
 __device__ __forceinline__ bool all_safe(const wave_f32x4 &x)
 {
     return in_safe_range(range_code(x[0])) && in_safe_range(range_code(x[1])) && in_safe_range(range_code(x[2])) && in_safe_range(range_code(x[3]));
+}
+
+// The largest of sixteen column sums of which each lane 16 g + i holds the part of column i in its own rows; infinity for NaN.
+__device__ __forceinline__ float largest_column(float part)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, part);
+    const auto h = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned h0 = h[0], h1 = h[1];
+    const unsigned m = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1));
+    const auto f = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    const unsigned f0 = f[0], f1 = f[1];
+    float v = __builtin_bit_cast(float, f0) + __builtin_bit_cast(float, f1);
+    v = v == v ? v : __builtin_inff();
+    auto dpp = [](float x, auto ctrl) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0xB1>{}));       // quad_perm 1,0,3,2
+    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x4E>{}));       // quad_perm 2,3,0,1
+    v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x141>{}));      // row_half_mirror
+    return __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x140>{}));   // row_mirror
 }
 
 // W = L^-1 of a tile beside its factorisation (factor_tile64): wave w takes the columns 16 w .. 16 w + 15, sixteen right-hand
@@ -278,26 +301,7 @@ struct InverseColumns {
     }
     __device__ __forceinline__ void finish(float *__restrict__ W, int w, int lane)
     {
-        auto over_groups = [](float v) __attribute__((always_inline)) {        // the sum over the lanes 16, 32 and 48 apart
-            const unsigned u = __builtin_bit_cast(unsigned, v);
-            const auto h = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-            const unsigned h0 = h[0], h1 = h[1];
-            const unsigned m = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1));
-            const auto f = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-            const unsigned f0 = f[0], f1 = f[1];
-            const float sum = __builtin_bit_cast(float, f0) + __builtin_bit_cast(float, f1);
-            return sum == sum ? sum : __builtin_inff();
-        };
-        auto over_lanes = [](float v) __attribute__((always_inline)) {         // the maximum over sixteen lanes
-            auto dpp = [](float x, auto ctrl) __attribute__((always_inline)) {
-                return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
-            };
-            v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0xB1>{}));   // quad_perm 1,0,3,2
-            v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x4E>{}));   // quad_perm 2,3,0,1
-            v = __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x141>{}));  // row_half_mirror
-            return __builtin_fmaxf(v, dpp(v, std::integral_constant<int, 0x140>{}));   // row_mirror
-        };
-        const float largest_L = over_lanes(over_groups(sum_L)), largest_W = over_lanes(over_groups(sum_W));
+        const float largest_L = largest_column(sum_L), largest_W = largest_column(sum_W);
         if (lane == 0) {
             W[W_FLOATS + w] = largest_L;
             W[W_FLOATS + 4 + w] = largest_W;

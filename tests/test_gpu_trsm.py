@@ -216,3 +216,32 @@ def test_zero_on_the_diagonal_gives_ieee_infinities_not_an_error(lib):
     X = X.cpu().numpy()
     assert np.all(np.isfinite(X[:70])), "rows before the zero pivot are unaffected"
     assert not np.any(np.isfinite(X[70])), "the row of the zero pivot is a division by zero in every column"
+
+
+@pytest.mark.parametrize("n,nrhs,nb", [(64, 24, 64), (61, 70, 64), (32, 17, 32), (16, 64, 16), (13, 65, 16), (128, 80, 128), (100, 9, 128), (65, 64, 128)])
+@pytest.mark.parametrize("case", ["plain", "negative", "large", "small", "tiny", "zeros"])
+def test_quotients_from_reciprocals_are_the_divisions(lib, tri, n, nrhs, nb, case):
+    """One tile on one launch: the quotients come from reciprocals of the diagonal where everything that comes out lies in
+    [2^-50, 2^50] or is zero and the diagonal is positive, and from divisions elsewhere: bit for bit the oracle's chain on
+    either side of that line (but for the product with the inverse, see above, which this passes by: no 64 x 8k system)."""
+    L = ws_inputs.tri_lower_bf16(n, 90 + n, 0, DEV)
+    B = ws_inputs.normal_f32((n, nrhs), 1.0, 90 + n, 1, DEV)
+    if case == "negative":
+        L[:, ::3] *= -1
+    elif case in ("large", "small"):
+        B *= 2.0 ** (55 if case == "large" else -55)
+    elif case == "tiny":
+        L *= 2.0 ** -30
+        L[n // 2] *= 2.0 ** -30
+    elif case == "zeros":
+        B[::2, ::3] = -0.0
+        B[:, 1::3] = 0.0
+        L.tril_()[:, 1::2] *= torch.eye(n, device=DEV, dtype=L.dtype)[:, 1::2]
+    if nb == 64 and n == 64:
+        B = B[:, :nrhs - 1].contiguous()                # not a multiple of 8: by substitution
+    X, Xh = lib.recurrence_trsm(L, B, nb)
+    torch.cuda.synchronize()
+    Xo, Xho = tri.tri_tiled(torch_bf16_to_bits(L), B.cpu().numpy(), nb)
+    assert np.all(np.isfinite(Xo))
+    assert np.array_equal(X.cpu().numpy().view(np.int32), Xo.astype(np.float32).view(np.int32))
+    assert np.array_equal(torch_bf16_to_bits(Xh), Xho)
