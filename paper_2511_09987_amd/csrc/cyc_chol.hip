@@ -37,27 +37,6 @@ constexpr int LDT = NBMAX + 4; // row stride of the tiles in LDS: rows stay 16-b
                                // spread over all banks for 16-byte reads
 typedef float f32x4 __attribute__((ext_vector_type(4), may_alias));   // read from arrays written as floats
 
-// t - sum_{k<c} x[k] y[k] as the chain t = fma(-x[k], y[k], t), k ascending; x and y are 16-byte aligned rows in LDS.
-// Four terms per pair of 16-byte reads, the reads of the next four issued before the current four are used.
-__device__ __forceinline__ float chain(float t, const float *x, const float *y, int c)
-{
-    const int c4 = c & ~3;
-    if (c4) {
-        f32x4 a = *(const f32x4 *)x, b = *(const f32x4 *)y;
-        for (int k = 4; k < c4; k += 4) {
-            const f32x4 a2 = *(const f32x4 *)(x + k), b2 = *(const f32x4 *)(y + k);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) t = __builtin_fmaf(-a[q], b[q], t);
-            a = a2;
-            b = b2;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) t = __builtin_fmaf(-a[q], b[q], t);
-    }
-    for (int k = c4; k < c; ++k) t = __builtin_fmaf(-x[k], y[k], t);
-    return t;
-}
-
 // fp32 -> bfloat16 bit pattern, round to nearest, ties to even; NaN stays NaN (the hardware conversion)
 __device__ __forceinline__ uint16_t round_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 // two values rounded and packed (a in the low half) by one conversion instruction, where rounding them one by one and
@@ -69,7 +48,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) { return __built
 constexpr int NT = 256;        // threads of a tile kernel: four waves
 
 // A 64-row tile of a row-major fp32 matrix (row stride ld) into LDS, by the workgroup: rows 0..nrows-1 (rows past that
-// repeat the last one), columns 0..cols-1.  All loads of a thread are in flight together.
+// repeat the last one), columns 0..cols-1, zeros right of them.  DIAGONAL: a tile of cols x cols, padded with the identity.  (Of up to 32 or 16 columns: to 32 or 16, all that is looked at.)  All
+// loads of a thread are in flight together.
+template <bool DIAGONAL>
 __device__ __forceinline__ void load_tile(float (*dst)[LDT], const float *src, int64_t ld, int nrows, int cols, int tid)
 {
     if (cols == NBMAX && ld % 4 == 0 && ((uintptr_t)src & 15) == 0) {
@@ -83,19 +64,25 @@ __device__ __forceinline__ void load_tile(float (*dst)[LDT], const float *src, i
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) *(f32x4 *)&dst[NT / 16 * i + (tid >> 4)][4 * (tid & 15)] = v[i];
     } else {
-        for (int i0 = 0; i0 < NBMAX * cols; i0 += NT * 4) {
-            float v[4];
+        // a row to 64 lanes, or to 32 or 16 where that is all of the tile that is looked at
+        auto load = [&](auto width) __attribute__((always_inline)) {
+            constexpr int WIDTH = decltype(width)::value, PASSES = NBMAX * WIDTH / NT;
+            const int c = tid % WIDTH;
+            float v[PASSES];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = i0 + NT * q + tid, r = i / cols, c = i - r * cols;
-                v[q] = i < NBMAX * cols ? src[(int64_t)(r < nrows ? r : nrows - 1) * ld + c] : 0.0f;
+            for (int i = 0; i < PASSES; ++i) {
+                const int r = NT / WIDTH * i + tid / WIDTH;
+                v[i] = c < cols ? src[(int64_t)(r < nrows ? r : nrows - 1) * ld + c] : 0.0f;
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = i0 + NT * q + tid, r = i / cols, c = i - r * cols;
-                if (i < NBMAX * cols) dst[r][c] = v[q];
+            for (int i = 0; i < PASSES; ++i) {
+                const int r = NT / WIDTH * i + tid / WIDTH;
+                dst[r][c] = DIAGONAL && (r >= cols || c >= cols) ? (r == c ? 1.0f : 0.0f) : v[i];
             }
-        }
+        };
+        if (cols > 32) load(std::integral_constant<int, 64>{});
+        else if (cols > 16) load(std::integral_constant<int, 32>{});
+        else load(std::integral_constant<int, 16>{});
     }
 }
 
@@ -117,13 +104,14 @@ struct TileLoad {
             }
         }
     }
+    template <bool DIAGONAL = false>
     __device__ __forceinline__ void place(float (*dst)[LDT], const float *src, int64_t ld, int nrows, int cols, int tid)
     {
         if (whole) {
 #pragma unroll
             for (int i = 0; i < PASSES; ++i) *(f32x4 *)&dst[NT / 16 * i + (tid >> 4)][4 * (tid & 15)] = v[i];
         } else {
-            load_tile(dst, src, ld, nrows, cols, tid);
+            load_tile<DIAGONAL>(dst, src, ld, nrows, cols, tid);
         }
     }
 };
@@ -172,6 +160,31 @@ __device__ __forceinline__ bool store_tile(const float (*src)[LDT], float *L, ui
         if (r < nrows) *(u32x4 *)(Lh + (int64_t)r * ld + 8 * (tid & 7)) = h[i];
     }
     return true;
+}
+
+// The same for any shape and alignment, by all threads: a row to 64, 32 or 16 lanes.
+template <bool LOWER>
+__device__ __forceinline__ void store_rows(const float (*src)[LDT], float *L, uint16_t *Lh, int64_t ld, int nrows, int cols, int tid)
+{
+    auto store = [&](auto width) __attribute__((always_inline)) {
+        constexpr int WIDTH = decltype(width)::value, PASSES = NBMAX * WIDTH / NT;
+        const int c = tid % WIDTH;
+        float v[PASSES];
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) v[i] = src[NT / WIDTH * i + tid / WIDTH][c];
+        if (c >= cols) return;
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            const int r = NT / WIDTH * i + tid / WIDTH;
+            if (r < nrows) {
+                L[(int64_t)r * ld + c] = LOWER && c > r ? 0.0f : v[i];
+                Lh[(int64_t)r * ld + c] = round_bf16(v[i]);
+            }
+        }
+    };
+    if (cols > 32) store(std::integral_constant<int, 64>{});
+    else if (cols > 16) store(std::integral_constant<int, 32>{});
+    else store(std::integral_constant<int, 16>{});
 }
 
 // The mirror image of 64 finished rows (a tile in LDS) into the upper triangle of Lh, by NTH threads: thread (column c,
@@ -330,15 +343,13 @@ template <class Beside>
 __device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *scratch, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols, int r,
                                           float *W, Beside beside, float *copy = nullptr)
 {
-    const bool live = r < cols;
-    bool mirrored = false;
     InverseColumns inverse;
     static_assert(FACTOR_SCRATCH * sizeof(float) <= KMAX * 64 * sizeof(uint16_t), "the staged operand's place serves as scratch");
     if (cols == NBMAX) {
         // (the rows of L of a group go out as soon as the group is finished, by the wave that kept them; Lh, which is mirrored, at
         // the end)
         const bool aligned = n % 8 == 0 && ((uintptr_t)L & 15) == 0 && ((uintptr_t)Lh & 15) == 0;
-        factor_tile64<LDT>(T, unsafe, scratch, W, inverse, r, [&](auto phase, int w) __attribute__((always_inline)) {
+        factor_tile64<4>(T, unsafe, scratch, W, inverse, r, [&](auto phase, int w) __attribute__((always_inline)) {
             constexpr int G = decltype(phase)::value;
             if (w == G - 1 && aligned) {
                 f32x4 v[4];
@@ -354,24 +365,12 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *s
             }
             beside(phase, w);
         });
-        mirrored = true;
+    } else if (cols > 32) {
+        factor_tile64<4>(T, unsafe, scratch, (float *)nullptr, inverse, r, [](auto, int) {});
+    } else if (cols > 16) {
+        factor_tile64<2>(T, unsafe, scratch, (float *)nullptr, inverse, r, [](auto, int) {});
     } else {
-        for (int c = 0; c < cols; ++c) {
-            float t = 0.0f;
-            if (live && r >= c) {
-                t = chain(T[r][c], T[r], T[c], c);
-                if (r == c) T[c][c] = __builtin_sqrtf(t);
-            }
-            __syncthreads();
-            if (live && r > c) T[r][c] = t / T[c][c];
-            __syncthreads();
-        }
-    }
-    // mirror the factor into the upper part of the tile in LDS (Lh holds both triangles), then write the tile out
-    if (!mirrored) {
-        if (live)
-            for (int c = r + 1; c < cols; ++c) T[r][c] = T[c][r];
-        __syncthreads();
+        factor_tile64<1>(T, unsafe, scratch, (float *)nullptr, inverse, r, [](auto, int) {});
     }
     if (copy) {
         // a second copy of the tile as it stands in LDS, rows of 64 floats (see chol_panel_kernel, Dcopy)
@@ -382,11 +381,7 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *s
         }
     }
     const bool stored = store_tile<true, NT, 3, 48>(T, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, r);
-    if (!stored && live)
-        for (int c = 0; c < cols; ++c) {
-            L[(j0 + r) * n + j0 + c] = c <= r ? T[r][c] : 0.0f;
-            Lh[(j0 + r) * n + j0 + c] = round_bf16(T[r][c]);
-        }
+    if (!stored) store_rows<true>(T, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, r);
     if (cols == NBMAX && W) finish_inverse<LDT>(T, scratch, W, inverse, r);
 }
 
@@ -402,7 +397,7 @@ __device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], i
     // mirror image, and the stationary fragments are read from it as well)
     TileProduct product;
     if (k0 < j0) product.request(Bs, Lh, n, j0, cols, k0, j0, j0, r, true);     // k0 < j0 only for full tiles, see launch_chol
-    load_tile(T, Sm + j0 * n + j0, n, cols, cols, r);     // the whole square; what lies above the diagonal is not used
+    load_tile<true>(T, Sm + j0 * n + j0, n, cols, cols, r);     // the whole square; what lies above the diagonal is not used
     if (k0 < j0) product.apply(T, Bs, r, Bs);
     else __syncthreads();
     diag_rest(T, unsafe, (float *)&Bs[0][0], L, Lh, n, j0, cols, r, W, [](auto, int) {});
@@ -476,7 +471,6 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
     }
     if (blockIdx.x == 0) k0 = k0_first;                                    // uniform (see above)
     if (tid == 0) lds.unsafe = 0;
-    const bool solver = tid < 64;                         // the wave that runs the recurrence of a tile that is not full
     // (requested here with everything else, looked at only where the rows are formed, so that nothing waits for them on their own)
     const bool may_invert = blockIdx.x == 0 && cols == NBMAX && Win != nullptr;        // uniform over the workgroup
     f32x4 winv[10], sum_L = {0, 0, 0, 0}, sum_W = sum_L;   // this lane's 40 values of W: pieces (cb, q), q <= cb
@@ -489,8 +483,7 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
 #pragma unroll
             for (int q4 = 0; q4 <= cb; ++q4) winv[p++] = *(const f32x4 *)(Win + (cb * 4 + q4) * 256 + lane * 4);
     }
-    const int64_t j1 = j0 + cols, row = j1 + (int64_t)blockIdx.x * 64 + lane;
-    const bool live = solver && row < n;
+    const int64_t j1 = j0 + cols;
     const int64_t first = j1 + (int64_t)blockIdx.x * 64;
     const int nrows = (int)(n - first < 64 ? n - first : 64);
     // L is zero above the diagonal, and the products of the matrix-multiply kernel have written S there (a group's window
@@ -548,7 +541,7 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
     const int64_t ldD = Dcopy ? NBMAX : n;
     of_D.request(Dsrc, ldD, cols, cols, tid);
     of_X.request(Sm + first * n + j0, n, nrows, cols, tid);
-    of_D.place(D, Dsrc, ldD, cols, cols, tid);
+    of_D.place<true>(D, Dsrc, ldD, cols, cols, tid);
     of_X.place(X, Sm + first * n + j0, n, nrows, cols, tid);
     // (nks_e > 0 implies k0 < j0: apply waits for every copy of this wave, Bs2's included, before its barrier)
     if (k0 < j0) product.apply(X, Bs, tid, rows_in_lds ? Bs2 : nullptr);
@@ -556,7 +549,7 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
     if (Dcopy && (int)blockIdx.x == row_blocks - 1) (void)store_tile<true>(D, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, tid);
 #pragma unroll
     for (int j = 0; j < 4; ++j) accn[j] = (f32x4){0, 0, 0, 0};
-    if (cols == NBMAX) {
+    {
         // Sixteen rows to a wave (rows past the last one repeat it)
         wave_f32x4 S[4], t[4], x[4];
         float *const row = &X[16 * w + lq][0];
@@ -612,35 +605,45 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
 #pragma unroll
                 for (int r = 0; r < 4; ++r) X[16 * w + 4 * g + r][16 * cb + lq] = xo[cb][r];
         } else {
-        // The divisions of a column share their divisor: quotients from its reciprocal, unless something is outside the range
-        // in which these are IEEE's.
-        Pivot p;
-        p.from_root(D[lane][lane]);
-        lds.rinv[lane] = p.r;                                                   // (the same numbers by every wave: no barrier)
-        solve_rows16<true, NBLK>(D, lds.rinv, t, row, lane, [](auto, float) {});
+            // The divisions of a column share their divisor: quotients from its reciprocal, unless something is outside the
+            // range in which these are IEEE's.  (Columns past the last one are zeros against the identity.)
+            Pivot p;
+            p.from_root(lane < cols ? D[lane][lane] : 1.0f);
+            lds.rinv[lane] = p.r;                                               // (the same numbers by every wave: no barrier)
+            auto solve = [&](auto by_pivots) __attribute__((always_inline)) {
+                constexpr bool PIVOTS = decltype(by_pivots)::value;
+                if (cols > 32) {
+                    solve_rows16<PIVOTS, NBLK>(D, lds.rinv, t, row, lane, [](auto, float) {});
+                } else if (cols > 16) {
+                    wave_f32x4 u[2] = {t[0], t[1]};
+                    solve_rows16<PIVOTS, NBLK / 2>(D, lds.rinv, u, row, lane, [](auto, float) {});
+                } else {
+                    wave_f32x4 u[1] = {t[0]};
+                    solve_rows16<PIVOTS, NBLK / 4>(D, lds.rinv, u, row, lane, [](auto, float) {});
+                }
+            };
+            solve(std::true_type{});
 #pragma unroll
-        for (int G = 0; G < 4; ++G) x[G] = *(const wave_f32x4 *)(row + 16 * G + 4 * g);
-        const unsigned worst = max(max(worst_code(x[0]), worst_code(x[1])), max(max(worst_code(x[2]), worst_code(x[3])), p.code()));
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
-            const bool safe = p.code() <= SAFE_SPAN && all_safe(x[0]) && all_safe(x[1]) && all_safe(x[2]) && all_safe(x[3]);
-            if (__builtin_amdgcn_ballot_w64(!safe) != 0) {
+            for (int G = 0; G < 4; ++G) x[G] = 16 * G < cols ? *(const wave_f32x4 *)(row + 16 * G + 4 * g) : (wave_f32x4){1, 1, 1, 1};
+            const unsigned worst = max(max(worst_code(x[0]), worst_code(x[1])), max(max(worst_code(x[2]), worst_code(x[3])), p.code()));
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
+                const bool safe = p.code() <= SAFE_SPAN && all_safe(x[0]) && all_safe(x[1]) && all_safe(x[2]) && all_safe(x[3]);
+                if (__builtin_amdgcn_ballot_w64(!safe) != 0) {
 #pragma unroll
-                for (int G = 0; G < 4; ++G) t[G] = S[G];
-                solve_rows16<false, NBLK>(D, lds.rinv, t, row, lane, [](auto, float) {});
+                    for (int G = 0; G < 4; ++G) t[G] = S[G];
+                    solve(std::false_type{});
+                }
+            }
+            if (nks_e > 0) {                                                    // (an even number)
+                read_step(0, f[0]);
+                for (int ks = 0; ks < nks_e; ks += 2) {
+                    read_step(ks + 1, f[1]);
+                    multiply(f[0]);
+                    if (ks + 2 < nks_e) read_step(ks + 2, f[0]);
+                    multiply(f[1]);
+                }
             }
         }
-        if (nks_e > 0) {                                                        // (an even number)
-            read_step(0, f[0]);
-            for (int ks = 0; ks < nks_e; ks += 2) {
-                read_step(ks + 1, f[1]);
-                multiply(f[0]);
-                if (ks + 2 < nks_e) read_step(ks + 2, f[0]);
-                multiply(f[1]);
-            }
-        }
-        }
-    } else if (solver) {
-        for (int c = 0; c < cols; ++c) X[lane][c] = chain(X[lane][c], X[lane], D[c], c) / D[c][c];
     }
     __syncthreads();
     // In the workgroup that goes on to the next diagonal tile some waves are done before others while that tile is factored:
@@ -648,26 +651,21 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
     // pointer aligned: the host fuses under those conditions only.)
     const bool deferred = fused && cols == NBMAX;
     if (!deferred) {
-        const bool stored = store_tile<false>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, tid);
+        if (!store_tile<false>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, tid))
+            store_rows<false>(X, L + first * n + j0, Lh + first * n + j0, n, nrows, cols, tid);
         if (nrows == 64 && cols == NBMAX && n % 8 == 0 && (uintptr_t)Lh % 16 == 0) {
             store_mirror<NT>(X, Lh + j0 * n + first, n, tid);
-        } else if (cols == NBMAX) {
+        } else {
             // sixteen columns to a wave, a row to a lane: consecutive lanes, consecutive addresses
             float v[16];
 #pragma unroll
             for (int c = 0; c < 16; ++c) v[c] = X[lane][16 * w + c];
             if (lane < nrows) {
 #pragma unroll
-                for (int c = 0; c < 16; ++c) Lh[(j0 + 16 * w + c) * n + first + lane] = round_bf16(v[c]);
+                for (int c = 0; c < 16; ++c)
+                    if (16 * w + c < cols) Lh[(j0 + 16 * w + c) * n + first + lane] = round_bf16(v[c]);
             }
-        } else if (live) {
-            for (int c = 0; c < cols; ++c) Lh[(j0 + c) * n + row] = round_bf16(X[lane][c]);
         }
-        if (!stored && live)
-            for (int c = 0; c < cols; ++c) {
-                L[row * n + j0 + c] = X[lane][c];
-                Lh[row * n + j0 + c] = round_bf16(X[lane][c]);
-            }
     }
     if (!fused) clear_mirror_place(tid, NT);
     if (fused) {

@@ -319,9 +319,10 @@ struct InverseColumns {
 // (InverseColumns; W == nullptr: none is computed); what the last group of rows of that needs is left for finish_inverse().
 // beside(G, w): called in the phases G = 1 .. 3 by every wave w < G; the first G groups of columns and of rows are finished then
 // (called again where the tile is started over).  scratch: LDS, FACTOR_SCRATCH floats.
+// GROUPS: of a tile padded with the identity from column 16 GROUPS on, only so many groups of columns (and of rows).
 // A barrier must have made S visible; ends with one.  *unsafe: an int in LDS, 0 on entry.
 constexpr int FACTOR_SCRATCH = 4 * 320 + 64 * 64;
-template <int LDD, class Beside>
+template <int GROUPS, int LDD, class Beside>
 __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, float *scratch, float *W, InverseColumns &inverse, int tid, Beside beside)
 {
     float *const saved = scratch + 4 * 320;                    // S, to start from again
@@ -341,20 +342,20 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
     };
     auto factor = [&](auto by_pivots) __attribute__((always_inline)) {
         constexpr bool PIVOTS = decltype(by_pivots)::value;
-        wave_f32x4 s[4], sd[4];                                // S of the own rows and of the blocks on the diagonal, group by group
+        wave_f32x4 s[GROUPS], sd[GROUPS];                      // S of the own rows and of the blocks on the diagonal, group by group
         float mine[NBLK];                                      // the own rows of L, spread: lane 16 q + i of block b is column 4 b + q
 #pragma unroll
-        for (int G = 0; G < 4; ++G) {
+        for (int G = 0; G < GROUPS; ++G) {
             s[G] = *(const wave_f32x4 *)(row + 16 * G + 4 * g);
             sd[G] = *(const wave_f32x4 *)&T[16 * G + i][16 * G + 4 * g];
             // (kept for the second try; in registers they made the kernel spill into accumulation registers)
             if (PIVOTS) *(wave_f32x4 *)(saved + 64 * own_row + 16 * G + 4 * g) = s[G];
         }
         __syncthreads();
-        inverse.start(w, lane);
-        unrolled<4>([&](auto group) __attribute__((always_inline)) {
-            constexpr int G = decltype(group)::value, NEXT = G < 3 ? G + 1 : 3;
-            if (w >= G) {                                      // uniform over the wave
+        if (W) inverse.start(w, lane);
+        unrolled<GROUPS>([&](auto group) __attribute__((always_inline)) {
+            constexpr int G = decltype(group)::value, NEXT = G < GROUPS - 1 ? G + 1 : G;
+            if (w >= G && w < GROUPS) {                                      // uniform over the wave
                 float ahead[NBLK];                             // minus rows of group G + 1, the columns before group G
                 if constexpr (G > 0) {
                     float a[4];
@@ -366,7 +367,7 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
                         s[G] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], mine[4 * (G - 1) + q], s[G], 0, 0, 0);
                     }
                 }
-                if constexpr (G < 3) {
+                if constexpr (G < GROUPS - 1) {
 #pragma unroll
                     for (int k = 0; k < 4 * G; ++k) ahead[k] = -T[16 * (G + 1) + i][4 * k + g];
                 }
@@ -402,7 +403,7 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
                         }
                         xd[j] = qd;
                         xt[j] = own_row == 16 * G + n ? pivot : qt;
-                        if constexpr (G < 3 && n / 2 < 4 * G) {                // one of the terms of the groups before out of group G + 1
+                        if constexpr (G < GROUPS - 1 && n / 2 < 4 * G) {                // one of the terms of the groups before out of group G + 1
                             constexpr int k = n / 2;
                             if constexpr (n % 2 == 0) sd[NEXT] = __builtin_amdgcn_mfma_f32_16x16x4f32(ahead[k], -ahead[k], sd[NEXT], 0, 0, 0);
                             else s[NEXT] = __builtin_amdgcn_mfma_f32_16x16x4f32(ahead[k], mine[k], s[NEXT], 0, 0, 0);
@@ -429,7 +430,7 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
                 constexpr int before = G > 0 ? G - 1 : 0;
                 if (w == before) mirror(std::integral_constant<int, before>{});
                 if (W) inverse.template group<before>(T, scratch + 320 * w, W, w, lane);
-                beside(group, w);
+                if (w < G) beside(group, w);
             }
             __syncthreads();
         });
@@ -437,11 +438,11 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
     factor(std::true_type{});
     if (__builtin_expect(*(volatile int *)unsafe != 0, 0)) {                   // once more, as the compiler expands root and division
 #pragma unroll
-        for (int G = 0; G < 4; ++G) *(wave_f32x4 *)(row + 16 * G + 4 * g) = *(const wave_f32x4 *)(saved + 64 * own_row + 16 * G + 4 * g);
+        for (int G = 0; G < GROUPS; ++G) *(wave_f32x4 *)(row + 16 * G + 4 * g) = *(const wave_f32x4 *)(saved + 64 * own_row + 16 * G + 4 * g);
         __syncthreads();
         factor(std::false_type{});
     }
-    if (w == 0) mirror(std::integral_constant<int, 3>{});
+    if (w == 0) mirror(std::integral_constant<int, GROUPS - 1>{});
     __syncthreads();
 }
 template <int LDD>

@@ -237,12 +237,13 @@ def test_rows_below_an_ill_conditioned_diagonal_tile_keep_the_chain(lib, chol):
 
 
 @pytest.mark.parametrize("case", ["large", "small", "mixed", "tiny_in_tile", "tiny_below", "zeros", "ones"])
-def test_quotients_from_reciprocals_are_the_divisions(lib, chol, case):
+@pytest.mark.parametrize("nb", [64, 48, 32, 16, 10])
+def test_quotients_from_reciprocals_are_the_divisions(lib, chol, nb, case):
     """The tile kernels take roots and quotients from hardware estimates and exact remainders where everything that comes out
     lies in [2^-50, 2^50] or is zero, and start over with IEEE root and division elsewhere: bit for bit the oracle's first
     panel (the rows right below the diagonal tile, a product with its inverse, excepted) on either side of that line, with
     zeros of both signs, and for a pivot whose significand is 24 ones, whose reciprocal is next to a tie."""
-    n, nb = 256, 64
+    n = 256
     A = ws_inputs.spd_f32(n, 17, 0, "cpu").numpy()
     d = np.ones(n, dtype=np.float32)
     if case in ("large", "small"):
@@ -266,6 +267,6 @@ def test_quotients_from_reciprocals_are_the_divisions(lib, chol, case):
     L, _ = run(lib, torch.from_numpy(A).to(DEV), nb)
     Lo, _ = chol.chol_tiled(A, nb)
     assert np.all(np.isfinite(Lo))
-    rows = np.r_[0:64, 128:n]
+    rows = np.r_[0:64, 128:n] if nb == 64 else np.arange(n)
     same = np.tril(np.ones((n, nb), dtype=bool))[rows]
     assert np.array_equal(L[rows, :nb].view(np.int32)[same], Lo[rows, :nb].astype(np.float32).view(np.int32)[same])
