@@ -81,7 +81,8 @@
  *            space; k-slices on different workgroups leave partial sums in the
  *            workspace and a second kernel adds them in ascending slice order.  The slices are a power of two of equal
  *            ones; cyc_recurrence_matmul_in also takes others.
- *   mfma256 / mfma128  everything else with aligned rows (mfma128: blocks of 128 x 128 or, where those are few, of
+ *   mfma256 / mfma128  everything else with aligned rows (mfma256: blocks of 256 x 256 or, where those leave compute units idle, of
+ *            192 x 192 (mfma192); mfma128: blocks of 128 x 128 or, where those are few, of
  *            64 x 64 or 32 x 32).
  *   generic  the rest: rows at any address, on the matrix cores (blocks of 256 x 128, 96 x 128, 64 x 64 or 32 x 32)
  *            when K and N are at least 16 bytes long, or K is a multiple of 16 bytes and longer than 128; off them
@@ -301,7 +302,7 @@ const char *cyc_kernel_variant(const void *A, const void *B, const void *C,
                                int64_t strideA, int64_t strideB, int64_t strideC, int dtype);
 
 /* Testing and benchmarking aid: from now on, in every thread, use the named kernel (generic | uneven256 | uneven96 |
- * uneven64 | uneven32 | mfma256 | mfma128 | mfma256x32 | mfma128x32 | mfmak | narrow | narrowm) wherever it supports the problem; NULL or "" gives the
+ * uneven64 | uneven32 | mfma256 | mfma192 | mfma128 | mfma256x32 | mfma128x32 | mfmak | narrow | narrowm) wherever it supports the problem; NULL or "" gives the
  * choice back to the dispatcher.  The x32 kernels use the 32x32 MFMA shape instead of the 16x16 one; the dispatcher
  * never picks them by itself.  The environment variable CYC_FORCE_KERNEL, read once when the library first chooses
  * a kernel, supplies the initial value.  Returns CYC_ERR_SHAPE for an unknown name. */

@@ -29,7 +29,7 @@ bool overlaps(const void *p, int64_t pbytes, const void *q, int64_t qbytes)
 // what a caller may bring as a workspace
 bool workspace_ok(const void *workspace, int64_t bytes) { return ((uintptr_t)workspace & 15) == 0 && bytes >= 0; }
 
-enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
+enum Kernel { K_NONE, K_ZERO, K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA192, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM };
 
 const char *kernel_label(Kernel k)
 {
@@ -42,6 +42,7 @@ const char *kernel_label(Kernel k)
         case K_UNEVEN64: return "uneven64";
         case K_UNEVEN32: return "uneven32";
         case K_MFMA256: return "mfma256";
+        case K_MFMA192: return "mfma192";
         case K_MFMA128: return "mfma128";
         case K_MFMA256X32: return "mfma256x32";
         case K_MFMA128X32: return "mfma128x32";
@@ -60,7 +61,7 @@ int uneven_block(Kernel k) { return k == K_UNEVEN256 ? 256 : k == K_UNEVEN96 ? 9
 Kernel kernel_by_name(const char *name)
 {
     if (!name) return K_NONE;
-    for (Kernel k : {K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM})
+    for (Kernel k : {K_GENERIC, K_UNEVEN256, K_UNEVEN96, K_UNEVEN64, K_UNEVEN32, K_MFMA256, K_MFMA192, K_MFMA128, K_MFMA256X32, K_MFMA128X32, K_MFMAK, K_NARROW, K_NARROWM})
         if (!std::strcmp(name, kernel_label(k))) return k;
     return K_NONE;
 }
@@ -122,6 +123,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
         case K_GENERIC: return take(force, force);
         case K_UNEVEN256: case K_UNEVEN96: case K_UNEVEN64: case K_UNEVEN32: if (cyc::supports_uneven(*p)) return take(force, force); break;
         case K_MFMA256: case K_MFMA256X32: if (cyc::supports_mfma(*p, 256)) return take(force, force); break;
+        case K_MFMA192: if (cyc::supports_mfma(*p, 192)) return take(K_MFMA256, force); break;
         case K_MFMA128: case K_MFMA128X32: if (cyc::supports_mfma(*p, 128)) return take(force, force); break;
         case K_NARROW: if (cyc::supports_narrow(*p)) return take(force, force); break;
         case K_NARROWM: if (cyc::supports_narrowm(*p)) return take(force, force); break;
@@ -146,7 +148,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     if (force == K_NONE && splits()) return take(K_MFMAK, K_MFMAK);
     // MFMA kernels for everything with 16-byte aligned rows except slivers
     const int tile = cyc::choose_mfma_tile(*p);
-    if (tile == 256) return take(K_MFMA256, K_MFMA256);
+    if (tile >= 192) return take(K_MFMA256, tile == 192 && force == K_NONE ? K_MFMA192 : K_MFMA256);
     if (tile == 128) {
         const int block = force == K_NONE ? cyc::choose_small_block(*p) : 0;
         return take(K_MFMA128, block ? uneven_kernel(block) : K_MFMA128);
@@ -166,6 +168,7 @@ int run_chunk(const cyc::Problem &p, Kernel k, const cyc::KSplit &split, void *w
         case K_GENERIC: e = cyc::launch_generic(p, s); break;
         case K_UNEVEN256: case K_UNEVEN96: case K_UNEVEN64: case K_UNEVEN32: e = cyc::launch_uneven(p, uneven_block(k), s); break;
         case K_MFMA256: e = cyc::launch_mfma(p, 256, 16, s); break;
+        case K_MFMA192: e = cyc::launch_mfma(p, 192, 16, s); break;
         case K_MFMA128: e = cyc::launch_mfma(p, 128, 16, s); break;
         case K_MFMA256X32: e = cyc::launch_mfma(p, 256, 32, s); break;
         case K_MFMA128X32: e = cyc::launch_mfma(p, 128, 32, s); break;

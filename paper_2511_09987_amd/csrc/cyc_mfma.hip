@@ -87,7 +87,6 @@ struct Cfg {
     static constexpr int NSA = 2, NSB = 3;         // LDS stages: A is double, B triple buffered
     static constexpr int LDS_BYTES = NSA * A_BYTES + NSB * B_BYTES;
     static constexpr int CPR = RB / 16;            // 16-byte chunks per B row
-    static constexpr int RPI = 64 / CPR;           // B rows covered by one wave-wide 1 KiB load
     static constexpr int AI = BM / 8 / NW;         // 1 KiB A loads per wave per k-tile
     static constexpr int BI = B_BYTES / 1024 / NW; // 1 KiB B loads per wave per k-tile
     static constexpr int TM = BM / WM / MT, TN = BN / WN / MT;   // MFMA tiles per wave
@@ -102,6 +101,10 @@ __device__ __forceinline__ int swzA(int r) { return (r >> 1) & 7; }
 template <class C>
 __device__ __forceinline__ int swzB(int k)
 {
+    // rows of 24 or 12 chunks (blocks of 192 columns): the XOR stays within groups of eight or four.  Rows two (bf16) or four (int8)
+    // apart start at the same bank
+    if (C::CPR == 24) return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+    if (C::CPR == 12) return ((k >> 2) & 1) | (((k >> 4) & 1) << 1);
     if (C::MT == 32) {
         if (!C::I8v) return ((k & 3) << 2) | (C::CPR >= 32 ? ((k >> 3) & 1) << 4 : 0);
         return C::CPR >= 16 ? (k & 7) << 1 : ((k >> 1) & 3) << 1;
@@ -221,8 +224,9 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
     }
 #pragma unroll
     for (int t = 0; t < C::BI; ++t) {
-        int kr = (w * C::BI + t) * C::RPI + l / C::CPR;
-        int c = (l % C::CPR) ^ swzB<C>(kr);
+        const int chunk = (w * C::BI + t) * 64 + l;           // of the B tile, row after row
+        int kr = chunk / C::CPR;
+        int c = (chunk % C::CPR) ^ swzB<C>(kr);
         if (RAGGED) {
             if (last * C::BKE + kr < K) tail_ok |= 1u << (C::AI + t);
             const int cmax = (N - n0) * ES / 16 - 1;      // last 16-byte chunk of this block's columns that exists
@@ -528,7 +532,7 @@ __global__ __launch_bounds__(256) void ws_join_slices_kernel(const V *__restrict
 // base pointers and batch strides); shapes that are not multiples of the block take the RAGGED variant.
 bool supports_mfma(const Problem &p, int tile)
 {
-    if (tile != 256 && tile != 128) return false;
+    if (tile != 256 && tile != 192 && tile != 128) return false;
     const int es = p.i8 ? 1 : 2;
     if (p.K <= 0 || p.M <= 0 || p.N <= 0) return false;
     const int64_t lda = row_stride_a(p), ldb = row_stride_b(p), ldc = row_stride_c(p);
@@ -544,7 +548,7 @@ bool supports_mfma(const Problem &p, int tile)
     return true;
 }
 
-// Block size by a small cost model: a CU runs one 256x256 block or two 128x128 blocks at a time; a 128x128
+// (0, 128, 192 or 256.)  Block size by a small cost model: a CU runs one 256x256 block or two 128x128 blocks at a time; a 128x128
 // block does a quarter of the work at about 3/4 of the efficiency.  Compare the number of rounds each needs.
 int choose_mfma_tile(const Problem &p)
 {
@@ -554,7 +558,15 @@ int choose_mfma_tile(const Problem &p)
     const double cost256 = (double)((n256 + 255) / 256);
     const double cost128 = (double)((n128 + 511) / 512) * 0.675;
     const bool ok256 = supports_mfma(p, 256), ok128 = supports_mfma(p, 128);
-    if (ok256 && (!ok128 || cost256 <= cost128)) return 256;
+    if (ok256 && (!ok128 || cost256 <= cost128)) {
+        // Blocks of 192 x 192, 0.68 of the time of one of 256, where their last round is the fuller one by enough: a round of few
+        // blocks takes 0.7 of a full one, the rest as it fills up (bf16 3000 x 2992 x 3008, 256 blocks instead of 144: 66 -> 50 us,
+        // 3072 x 4096 x 3072 77 -> 60; 3500 x 3488 x 3504, 361 instead of 196, 85 / 103; 6000 x 6000 x 6000, 1024 instead of
+        // 576, level at the power limit, hence the margin).
+        auto rounds = [](int64_t blocks) { return (double)(blocks / 256) + (blocks % 256 ? 0.7 + 0.3 * (double)(blocks % 256) / 256 : 0.0); };
+        const int64_t n192 = ((p.M + 191) / 192) * ((p.N + 191) / 192) * p.batch;
+        return !p.Cin && supports_mfma(p, 192) && 0.68 * rounds(n192) < 0.93 * rounds(n256) ? 192 : 256;
+    }
     return ok128 ? 128 : 0;
 }
 
@@ -633,11 +645,13 @@ hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *works
 
 hipError_t launch_mfma(const Problem &p, int tile, int mt, hipStream_t s)
 {
-    if (!supports_mfma(p, tile) || (mt != 16 && mt != 32)) return hipErrorInvalidValue;
+    if (!supports_mfma(p, tile) || (mt != 16 && mt != 32) || (tile == 192 && mt != 16)) return hipErrorInvalidValue;
     // 4 waves of 128x128 (256-block) or 64x64 (128-block), one per SIMD; in the 256-block the accumulators
     // fill the 256 AGPRs.  Eight waves of 128x64 read 50 % more LDS per MFMA and measured slower with
     // either MFMA shape.  mt chooses the MFMA shape: 16 is what the dispatcher uses (see the comment at Acc).
     if (mt == 16) {
+        if (tile == 192)
+            return p.i8 ? launch_cfg<Cfg<true, 192, 192, 2, 2, 16>, false>(p, s) : launch_cfg<Cfg<false, 192, 192, 2, 2, 16>, false>(p, s);
         if (tile == 256)
             return p.i8 ? launch_cfg<Cfg<true, 256, 256, 2, 2, 16>, true>(p, s) : launch_cfg<Cfg<false, 256, 256, 2, 2, 16>, true>(p, s);
         return p.i8 ? launch_cfg<Cfg<true, 128, 128, 2, 2, 16>, true>(p, s) : launch_cfg<Cfg<false, 128, 128, 2, 2, 16>, true>(p, s);
