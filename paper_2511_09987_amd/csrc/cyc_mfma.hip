@@ -175,9 +175,10 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
     const int nblk = tiles_m * tiles_n;
     if (EPI == EPI_SLICE && nblk == 1) {
         bid = 0;                                         // (nothing is shared)
-    } else if (EPI == EPI_SLICE) {
+    } else if (EPI == EPI_SLICE && ((nblk & 7) != 0 || K >= 16 * C::BKE)) {
         // k-slices: the blocks of one slice share its A and B, so each XCD gets a contiguous run of (slice, block) pairs, the
-        // first (their number mod 8) XCDs one more
+        // first (their number mod 8) XCDs one more (short slices of a multiple of eight blocks have little to share and are dealt
+        // out as below: 933 x 4480 x 392 18.6 us, 19.2 so)
         const int number = blockIdx.y * nblk + blockIdx.x, total = nblk * (int)gridDim.y, xcd = number & 7;
         const int at = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : total & 7) + (number >> 3);
         bz = (int)((unsigned)at / (unsigned)nblk);
@@ -243,9 +244,10 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
     // The k-slices of a problem start about bz k-tiles into their range and come back to its beginning at the end (the last, ragged
     // k-tile of a RAGGED problem keeps its place): slices are often a power of two apart, and workgroups that all ask for the same
     // k-tile of theirs then meet in the same few channels of the memory (512 x 262144 x 512 bf16: 156 us, 144 so).
-    const int whole = EPI == EPI_SLICE ? (RAGGED ? last : nkt) : 0;
+    constexpr bool TURN = EPI == EPI_SLICE && C::BM == 256;         // (the shorter calls in blocks of 128 would pay 0.3 us for it)
+    const int whole = TURN ? (RAGGED ? last : nkt) : 0;
     const int turn = whole > 0 ? bz & ((1 << (31 - __builtin_clz(whole))) - 1) : 0;      // (below whole; a division would cost more than it is worth)
-    auto place = [&](int t) __attribute__((always_inline)) { return EPI == EPI_SLICE && t < whole ? (t + turn < whole ? t + turn : t + turn - whole) : t; };
+    auto place = [&](int t) __attribute__((always_inline)) { return TURN && t < whole ? (t + turn < whole ? t + turn : t + turn - whole) : t; };
     const char *srcA = baseA + (int64_t)place(2) * 128, *srcB = baseB + place(2) * stepB;   // source of the k-tile being fetched in the loop
     int before_wrap = whole - 1 - place(2);                          // (whole > 2 in the bulk of the loop, which alone looks at it)
     auto issue_one = [&](int x, int sa, int sb, int ktile, bool tail) __attribute__((always_inline)) {
@@ -414,7 +416,7 @@ __global__ __launch_bounds__(C::NT) void ws_mfma_kernel(const char *__restrict__
         if (!careful) {
             srcA += 128;
             srcB += stepB;
-            if (EPI == EPI_SLICE && before_wrap-- == 0) {
+            if (TURN && before_wrap-- == 0) {
                 srcA = baseA;
                 srcB = baseB;
                 before_wrap = whole - 1;
