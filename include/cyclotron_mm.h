@@ -196,8 +196,8 @@ int cyc_recurrence_trsm(const void *L, const void *B, void *X, void *Xh,
 
 /* The same for callers that bring memory.  With nb == 64, n >= 512 and an n, nrhs or pointer that the inverses above do not take
  * (n or nrhs no multiple of 8, an address that is not 16-byte aligned) it solves a copy in `workspace` that they do take, n and nrhs rounded up
- * to multiples of 8, as long as the copy has at most 256 MiB (1333 x 28: 466 us without, 115 so; 5787 x 5787 1.07 ms, and past
- * the limit 5803 x 5803 3.36 ms); and nothing is shared with
+ * to multiples of 8, as long as the copy has at most 256 MiB (1333 x 28: 270 us without, 95 so; 5787 x 5787 1.05 ms, and past
+ * the limit 5803 x 5803 2.51 ms); and nothing is shared with
  * other calls on the stream or with graphs captured on it.  cyc_trsm_workspace says how many bytes the call wants (0: none;
  * host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not cleared, free again when the call's
  * work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is enqueued; with
@@ -246,8 +246,8 @@ int cyc_recurrence_trsm_in(const void *L, const void *B, void *X, void *Xh, int6
 int cyc_recurrence_cholesky(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *stream);
 
 /* The same for callers that bring memory, on the terms of cyc_recurrence_trsm_in: with nb == 64, n > 128 and n no multiple of 8 or
- * a pointer that is not 16-byte aligned it factors a padded copy in `workspace`, of at most 256 MiB (585: 371 us
- * without, 182 so; past the limit 5185: 3.95 ms, where 5184 takes 1.53). */
+ * a pointer that is not 16-byte aligned it factors a padded copy in `workspace`, of at most 256 MiB (585: 255 us
+ * without, 157 so; past the limit 5185: 2.82 ms, where 5184 takes 1.35). */
 int64_t cyc_cholesky_workspace(const void *A, void *L, void *Lh, int64_t n, int64_t nb);
 int cyc_recurrence_cholesky_in(const void *A, void *L, void *Lh, int64_t n, int64_t nb, void *workspace, int64_t workspace_bytes,
                                void *stream);

@@ -6,8 +6,8 @@
 //     [ 0 I ] [ 0 0 ] = [ 0 0 ]    resp.   [ 0 I ],
 // solved in memory that the caller brings and copied out.  The added rows and columns are zeros in every product, so the sums of the
 // others are the same.  What bounds it is still the chain of tiles; the copies are two more passes over the operands in
-// three launches.  Tile by tile / now, microseconds: solve 1333 x 28 466 / 115, 1984 x 603 428 / 124 (1984 x 608, in no need of copies,
-// 107), 2047 x 4001 - / 187; Cholesky 133 91 / 49, 585 371 / 182 (584: 171), 1001 653 / 303, 2047 - / 582.
+// three launches.  Tile by tile / now, microseconds: solve 513 x 8 104 / 37, 1333 x 28 270 / 95, 1984 x 603
+// 429 / 116, 2047 x 4001 681 / 179; Cholesky 133 53 / 42, 585 255 / 157, 1001 443 / 252, 2047 1014 / 522.
 #include "cyc_internal.h"
 
 namespace cyc {
