@@ -137,9 +137,11 @@ int cyc_recurrence_matmul_noalloc(const void *A, const void *B, void *C,
  * power of two divides into enough equal slices, and products of few rows with very long k, also have k mapped to space here
  * (18 x 17280 x 784 bf16: 39 us without, 16 so; at most 64 MiB of partial sums).  cyc_matmul_workspace says how many bytes the
  * call wants (0: it needs none; host only, also 0 for arguments that the call refuses).  workspace: device, 16-byte aligned, not
- * cleared, free again when the call's work on `stream` is done.  With less than that the call returns CYC_ERR_WORKSPACE and nothing is
- * enqueued.  workspace NULL: the library's per-(device, stream) workspace, or CYC_ERR_WORKSPACE if `stream` is being captured.
- * Which kernel runs depends on the problem alone (cyc_kernel_name and cyc_kernel_variant answer for cyc_recurrence_matmul).
+ * cleared, free again when the call's work on `stream` is done.  With less than that the call takes fewer slices, whose fp32 sums are
+ * added in another order (unequal slices fit 16 MiB: 1000 x 24000 x 1000 bf16 70 us so, 60 with the 64 MiB that it wants), or
+ * returns CYC_ERR_WORKSPACE with nothing enqueued where those do not fit either.  workspace NULL: the library's per-(device, stream)
+ * workspace, or CYC_ERR_WORKSPACE if `stream` is being captured.
+ * Which kernel runs depends on the problem and the memory alone (cyc_kernel_name and cyc_kernel_variant answer for cyc_recurrence_matmul).
  * Errors otherwise: those of cyc_recurrence_matmul; CYC_ERR_SHAPE also for a
  * misaligned and CYC_ERR_ALIAS for an overlapping workspace. */
 int64_t cyc_matmul_workspace(const void *A, const void *B, const void *C, int64_t M, int64_t K, int64_t N, int dtype);

@@ -265,8 +265,13 @@ def recurrence_matmul(A, B, out=None, stream=None):
         st = cyc_recurrence_matmul_in(*args, 0, 0, s)
         if st == CYC_ERR_WORKSPACE:               # under capture: partial sums in memory of the graph's own
             wanted = cyc_matmul_workspace(*args)
-            work = _memory(wanted, A, stream) if wanted else None
-            st = cyc_recurrence_matmul(*args, s) if work is None else cyc_recurrence_matmul_in(*args, work.data_ptr(), wanted, s)
+            for size in (wanted, min(wanted, 16 << 20)):      # (what fewer slices need, where there is not all of it)
+                work = _memory(size, A, stream) if size else None
+                if work is not None:
+                    st = cyc_recurrence_matmul_in(*args, work.data_ptr(), size, s)
+                    break
+            if st == CYC_ERR_WORKSPACE:
+                st = cyc_recurrence_matmul(*args, s)
     else:
         st = cyc_recurrence_matmul_batched(A.data_ptr(), B.data_ptr(), out.data_ptr(), batch, M, K, N,
                                            M * K, K * N, M * N, dtype, s)

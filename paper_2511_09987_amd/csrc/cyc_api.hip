@@ -80,9 +80,11 @@ std::atomic<int> &wait_limit_value()
 // Validates and fills `p`.  Returns CYC_OK with *k == K_NONE when there is nothing to do.  *family: the kernel whose part of
 // the dispatch the problem falls into; *k: the kernel that runs (blocks of cyc_uneven.hip stand in for several families).
 // split: filled in for K_MFMAK; any_slices: k may be cut into slices of any number and length (see KSplit), which the entry points
-// without a workspace argument do not do.
+// without a workspace argument do not do; memory: what there is for them (choose_ksplit).
+constexpr int64_t UNLIMITED = INT64_MAX;
 int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, int64_t K, int64_t N,
-         int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k, Kernel *family, cyc::KSplit *split, bool any_slices)
+         int64_t strideA, int64_t strideB, int64_t strideC, int dtype, cyc::Problem *p, Kernel *k, Kernel *family, cyc::KSplit *split, bool any_slices,
+         int64_t memory = UNLIMITED)
 {
     *k = *family = K_NONE;
     if (dtype != CYC_BF16_F32 && dtype != CYC_I8_I32) return CYC_ERR_DTYPE;
@@ -118,7 +120,7 @@ int plan(const void *A, const void *B, const void *C, int64_t batch, int64_t M, 
     // a forced kernel overrides the heuristic when it supports the problem (testing and benchmarking aid).  The x32
     // names are the MFMA kernels built on the 32x32 instruction shape, which the dispatcher never picks by itself.
     const Kernel force = (Kernel)forced_kernel().load(std::memory_order_relaxed);
-    auto splits = [&]() { return (*split = cyc::choose_ksplit(*p, any_slices)).slices > 1; };
+    auto splits = [&]() { return (*split = cyc::choose_ksplit(*p, any_slices, memory)).slices > 1; };
     switch (force) {
         case K_GENERIC: return take(force, force);
         case K_UNEVEN256: case K_UNEVEN96: case K_UNEVEN64: case K_UNEVEN32: if (cyc::supports_uneven(*p)) return take(force, force); break;
@@ -320,13 +322,22 @@ int cyc_recurrence_matmul_in(const void *A, const void *B, void *C, int64_t M, i
     cyc::Problem p;
     Kernel k, family;
     cyc::KSplit split;
-    int st = plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, true);
+    auto plan_for = [&](int64_t memory) { return plan(A, B, C, 1, M, K, N, 0, 0, 0, dtype, &p, &k, &family, &split, true, memory); };
+    int st = plan_for(workspace && workspace_bytes >= 0 ? workspace_bytes : UNLIMITED);
     if (st != CYC_OK || k == K_NONE) return st;
     if (!workspace_ok(workspace, workspace_bytes)) return CYC_ERR_SHAPE;
     if (k != K_MFMAK) return run(p, k, split, (hipStream_t)stream, GIVEN);
     // (partial sums fit 64 MiB, 256 blocks of 256 x 256, which a stream's workspace may well keep; under a capture it
     // would be shared with other graphs, and asking torch for memory on every call costs 3 us of host time)
-    if (!workspace) return cyc::is_capturing((hipStream_t)stream) ? CYC_ERR_WORKSPACE : run(p, k, split, (hipStream_t)stream, CACHED);
+    if (!workspace) {
+        if (cyc::is_capturing((hipStream_t)stream)) return CYC_ERR_WORKSPACE;
+        st = run(p, k, split, (hipStream_t)stream, CACHED);
+        if (st != CYC_ERR_WORKSPACE) return st;
+        // the device has no such memory left: the slices that need least, if those are others
+        const int slices = split.slices;
+        st = plan_for(0);
+        return st == CYC_OK && k == K_MFMAK && split.slices < slices ? run(p, k, split, (hipStream_t)stream, CACHED) : CYC_ERR_WORKSPACE;
+    }
     const int64_t es = p.i8 ? 1 : 2;
     if (overlaps(workspace, workspace_bytes, A, M * K * es) || overlaps(workspace, workspace_bytes, B, K * N * es) ||
         overlaps(workspace, workspace_bytes, C, M * N * 4))

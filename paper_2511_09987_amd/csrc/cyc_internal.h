@@ -71,7 +71,9 @@ struct KSplit {
     int64_t length;                      // of every slice but the last, which may be shorter
 };
 // any: slices of any number and length; otherwise a power of two of equal ones
-KSplit choose_ksplit(const Problem &p, bool any);
+// (memory: bytes there are for the partial sums; slices that need more give way to the fewer that callers had before those came, however
+// much these need)
+KSplit choose_ksplit(const Problem &p, bool any, int64_t memory);
 inline int64_t ksplit_workspace_bytes(const Problem &p, int ksplit) { return (int64_t)ksplit * p.M * p.N * 4; }
 hipError_t launch_mfma_ksplit(const Problem &p, const KSplit &split, void *workspace, hipStream_t s);
 // Device memory for partial products and inverses.  WorkspaceHold::acquire: one buffer per (device, stream),

@@ -578,7 +578,7 @@ int choose_mfma_tile(const Problem &p)
 // row and of B's block column to itself and leaves its partial sum in its slice of a workspace; the hand-over
 // along k is a second kernel that adds the slices of every element in ascending slice order (a fixed order: the
 // result is the same bits on every call).
-KSplit choose_ksplit(const Problem &p, bool any)
+KSplit choose_ksplit(const Problem &p, bool any, int64_t memory)
 {
     const KSplit one{1, 128, p.K};
     if (p.batch != 1 || p.lda || p.ldb || p.ldc || p.Cin || p.kslices || !supports_mfma(p, 128)) return one;
@@ -608,8 +608,13 @@ KSplit choose_ksplit(const Problem &p, bool any)
     };
     if (any) {
         const int64_t n256 = 256 / b256, n128 = std::min<int64_t>(512 / b128, 256);
-        if (supports_mfma(p, 256) && b256 * 4 * 5 <= b128 * 6 && n256 > 1 && nkt > 19 * n256) return cut(n256, 256);
-        if (n128 > 1 && nkt > 27 * n128) return cut(n128, 128);
+        // (up to 64 MiB of partial sums; with less memory the slices below, which fit 16 where they are unequal)
+        auto fits = [&](const KSplit &k) { return ksplit_workspace_bytes(p, k.slices) <= memory; };
+        if (supports_mfma(p, 256) && b256 * 4 * 5 <= b128 * 6 && n256 > 1 && nkt > 19 * n256) {
+            if (const KSplit k = cut(n256, 256); fits(k)) return k;
+        } else if (n128 > 1 && nkt > 27 * n128) {
+            if (const KSplit k = cut(n128, 128); fits(k)) return k;
+        }
     }
     // where the equal slices are less than 3/4 as many as there is room for, slices of any number here, too (40 x 17280 x 784
     // bf16: 110 us in two slices' stead, 14)

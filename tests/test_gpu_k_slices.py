@@ -156,3 +156,26 @@ def test_first_call_on_a_stream_under_capture():
         torch.cuda.synchronize()
         assert torch.equal(C1.double(), want) and torch.equal(C2.double(), want)
     assert torch.equal(C3.double(), torch.matmul(A2.double(), B2.double()))
+
+
+@pytest.mark.parametrize("dtype", (torch.bfloat16, torch.int8))
+@pytest.mark.parametrize("M,K,N", [(1000, 24000, 1008), (512, 64 * 64 * 20 + 64, 512), (128, 64 * 64 * 28 - 16, 1024), (700, 96000, 528)])
+def test_a_workspace_of_16_mib_takes_the_slices_that_fit(dtype, M, K, N):
+    """Callers that bring the 16 MiB that slices of any length once needed at the most are served, by fewer of them; with no memory at
+    all the call is refused."""
+    import paper_2511_09987_amd as lib
+    K *= 2 if dtype == torch.int8 else 1
+    A, B = (t[0] for t in operands(dtype, 1, M, K, N))
+    C = torch.full((M, N), 5, dtype=torch.int32 if dtype == torch.int8 else torch.float32, device=DEV)
+    args = A.data_ptr(), B.data_ptr(), C.data_ptr(), M, K, N, lib.CYC_I8_I32 if dtype == torch.int8 else lib.CYC_BF16_F32
+    size, stream = 16 << 20, torch.cuda.current_stream().cuda_stream
+    assert lib.cyc_matmul_workspace(*args) > size
+    around = torch.full((size + 4096,), 77, dtype=torch.uint8, device=DEV)
+    assert lib.cyc_recurrence_matmul_in(*args, around.data_ptr(), 0, stream) == 6 and bool((C == 5).all())
+    assert lib.cyc_recurrence_matmul_in(*args, around.data_ptr(), size, stream) == 0
+    assert bool((around[size:] == 77).all())
+    ref = torch.matmul(A.double(), B.double())
+    if dtype == torch.int8:
+        assert torch.equal(C.double(), ref)
+    else:                                                       # K roundings of 2^-24 of the sum of magnitudes at the most
+        assert bool(((C.double() - ref).abs() <= K * 2.0 ** -24 * torch.matmul(A.double().abs(), B.double().abs())).all())
