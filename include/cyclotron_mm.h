@@ -342,6 +342,15 @@ int cyc_diag_set_wait_limit(int64_t polls);
  * tiles: 0 .. 2^24. */
 int cyc_diag_mfma_f32_tiles(const void *A, const void *B, const void *C, void *D, int64_t tiles, void *stream);
 
+/* Verification aid.  The square roots, reciprocals and quotients that the tile kernels form from hardware estimates and exact
+ * remainders, against the compiler's IEEE root and division.  what 0: the root of the float whose bits are i, for i = first ..
+ * first + count - 1 in [2^-100, 2^100) (0x0d800000 .. 0x71800000); in [1, 4) also, where its reciprocal is not the correctly rounded
+ * one (24 floats), the quotients of all 2^23 numerators' significands by that root.  what 1: for the divisors
+ * 1 + i 2^-23, i in 0 .. 2^23 - 1, the reciprocal, 16 quotients of hashed numerators, and those of the numerators whose quotient
+ * comes closest to a midpoint between two floats (all within 15 / (2 D) units of one where the 24-bit significand D is odd).
+ * *bad (device, uint64_t, 8-byte aligned) is increased by the number of results whose bits differ. */
+int cyc_diag_pivots(int what, int64_t first, int64_t count, void *bad, void *stream);
+
 /* Measurement aid: one wave that runs for `microseconds` (1 .. 2000000) and then writes to out (device, two
  * uint64_t, 8-byte aligned) the shader clock cycles and the ticks of the constant 100 MHz counter that went by.
  * Launched on a second stream beside other kernels it gives the engine clock sustained under their load:

@@ -15,6 +15,7 @@
 // two waves per SIMD: the time per round against the 256 cycles says what the other instructions cost.
 #include "../../include/cyclotron_mm.h"
 #include "cyc_internal.h"
+#include "cyc_wave.h"
 
 namespace cyc {
 namespace {
@@ -170,6 +171,56 @@ __global__ __launch_bounds__(64) void mfma_f32_tiles_kernel(const float *__restr
     }
 }
 
+// see cyc_diag_pivots
+__global__ __launch_bounds__(256) void pivots_kernel(int what, int64_t first, int64_t count, unsigned long long *__restrict__ bad)
+{
+    auto differ = [](float a, float b) { return __builtin_bit_cast(uint32_t, a) != __builtin_bit_cast(uint32_t, b) ? 1u : 0u; };
+    const int64_t end = first + count, step = (int64_t)gridDim.x * blockDim.x;
+    unsigned long long wrong = 0;
+    for (int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += step) {
+        Pivot p;
+        if (what == 0) {
+            const float s = __builtin_bit_cast(float, (uint32_t)i);
+            p.from_square(s);
+            wrong += differ(p.d, __builtin_sqrtf(s));
+            if (s >= 1.0f && s < 4.0f && differ(p.r, 1.0f / p.d))
+                for (uint32_t T = 0; T < 1u << 23; ++T) {
+                    const float t = __builtin_bit_cast(float, 0x3f800000u + T);
+                    wrong += differ(p.quotient(t), t / p.d);
+                }
+            continue;
+        }
+        const uint64_t D = (1u << 23) + (uint64_t)i;
+        const float d = (float)D * 0x1p-23f;
+        p.from_root(d);
+        wrong += differ(p.r, 1.0f / d);
+        uint32_t hash = (uint32_t)i * 2654435761u + 12345u;
+        for (int n = 0; n < 16; ++n) {
+            hash = hash * 1664525u + 1013904223u;
+            const float t = (float)((1u << 23) + (hash >> 9)) * 0x1p-23f;
+            wrong += differ(p.quotient(t), t / d);
+        }
+        // T 2^K = m D + rest with m odd and in [2^24, 2^25): T / D lies rest / (2 D) units of its last place off a midpoint.
+        // D = odd 2^e: rest = small 2^e, and m is known modulo 2^(K - e), of whose 2^e choices four are looked at
+        const int e = __builtin_ctzll(D);
+        const uint64_t odd = D >> e;
+        uint64_t inverse = odd;                                    // modulo 2^64, by Newton's iteration from 3 bits on
+        for (int n = 0; n < 5; ++n) inverse *= 2 - odd * inverse;
+        for (int K = 24; K <= 25; ++K)
+            for (int small = -15; small <= 15; small += 2)
+                for (int lift = 0; lift < (e < 2 ? 1 << e : 4); ++lift) {
+                    const int64_t rest = (int64_t)small << e;
+                    const uint64_t high = e < 2 ? lift : (hash >> (7 * lift)) & ((1u << e) - 1);
+                    const uint64_t m = (((0 - (uint64_t)small) * inverse) & ((1ull << (K - e)) - 1)) + (high << (K - e)) + (K == 24 ? 1ull << 24 : 0);
+                    const int64_t T = (int64_t)(m * D + (uint64_t)rest) >> K;
+                    if (m < (1u << 24) || T < (1 << 23) || T >= (1 << 24)) continue;
+                    const float t = (float)T * 0x1p-23f;
+                    wrong += differ(p.quotient(t), t / d);
+                }
+    }
+    if (wrong) atomicAdd(bad, wrong);
+}
+
 __global__ __launch_bounds__(64) void clock_kernel(uint64_t *out, int64_t ticks)
 {
     const uint64_t w0 = wall_clock64(), c0 = clock64();
@@ -253,6 +304,19 @@ int cyc_diag_mfma_f32_tiles(const void *A, const void *B, const void *C, void *D
     const unsigned blocks = (unsigned)(tiles < 4096 ? tiles : 4096);
     const hipError_t e = cyc::launch_kernel(cyc::mfma_f32_tiles_kernel, dim3(blocks), dim3(64), (hipStream_t)stream, (const float *)A,
                                             (const float *)B, (const float *)C, (float *)D, tiles);
+    return e == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
+}
+
+int cyc_diag_pivots(int what, int64_t first, int64_t count, void *bad, void *stream)
+{
+    const int64_t lo = what == 0 ? (127 - 100) << 23 : 0, hi = what == 0 ? (int64_t)(127 + 100) << 23 : 1 << 23;
+    if ((what != 0 && what != 1) || count < 0 || first < lo || first > hi || count > hi - first) return CYC_ERR_SHAPE;
+    if (count == 0) return CYC_OK;
+    if (!bad) return CYC_ERR_NULL;
+    if ((uintptr_t)bad & 7) return CYC_ERR_SHAPE;
+    const int64_t blocks = (count + 255) / 256;
+    const hipError_t e = cyc::launch_kernel(cyc::pivots_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), (hipStream_t)stream, what,
+                                            first, count, (unsigned long long *)bad);
     return e == hipSuccess ? CYC_OK : CYC_ERR_LAUNCH;
 }
 

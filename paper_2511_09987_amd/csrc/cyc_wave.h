@@ -67,9 +67,12 @@ __device__ __forceinline__ bool in_safe_range(unsigned code) { return code <= SA
 // correctly rounded reciprocal r, q = q0 - (d q0 - t) r for q0 = t r.  The remainders are exact and the results those of IEEE
 // as long as nothing over- or underflows: where every |x| that comes out, pivots included, lies in [2^-50, 2^50] or is zero
 // (in_safe_range; zeros keep their sign where the pivot is positive); callers take the compiler's way elsewhere.
-// Evidence, on the device: the root on every float in [2^-100, 2^100); the quotient on 3.4e10 random pairs, and for every
-// divisor on all numerators whose quotient lies within 15 / (2 D) units of a midpoint, D being the divisor's 24-bit
-// significand: the error before the last rounding, at most 1.5 units * 2^-23, reaches 6 / (2 D).
+// Evidence, on the device (cyc_diag_pivots): the root on every float in [2^-100, 2^100); for every divisor's
+// significand D, 24 bits, the reciprocal and the quotients of the numerators for which these lie within 15 / (2 D) units of a
+// midpoint (all of them for odd D): the error before the last rounding, at most 1.5 units * 2^-23, reaches 6 / (2 D).  The
+// reciprocal of a root is a unit off for 24 squares in [1, 4): there every numerator.
+// One exception that a look at the results does not show: a numerator k 2^-149 over the divisor next below 2 k gives 0 here,
+// and the smallest denormal number, 2^-149, by division.
 // (One unit is added to the estimate of 1 / sqrt(s): without it the reciprocal of a significand of 24 ones comes out as a tie.)
 struct Pivot {
     float d, r;                                               // sqrt(s), 1 / d

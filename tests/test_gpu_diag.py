@@ -118,3 +118,14 @@ def test_fp32_mfma_adds_its_four_products_like_the_scalar_chain(lib):
                         other[t, i, j] = acc
             assert (other[:2].view(np.uint32) != want[:2].view(np.uint32)).any(), name
 
+
+
+def test_roots_and_quotients_from_estimates_are_ieees(lib):
+    """Every float in [2^-100, 2^100) and every divisor's significand: no root or quotient may differ from IEEE's."""
+    bad = torch.zeros(1, dtype=torch.int64, device="cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    first, end = 27 << 23, 227 << 23
+    assert lib.cyc_diag_pivots(0, first, end - first, bad.data_ptr(), st) == 0
+    assert int(bad) == 0
+    assert lib.cyc_diag_pivots(1, 0, 1 << 23, bad.data_ptr(), st) == 0
+    assert int(bad) == 0
