@@ -337,11 +337,11 @@ constexpr float W_NORM_LIMIT = 8.0f;      // the product with a tile's inverse s
 
 // The factorisation proper of a diagonal tile whose S (with everything left of it taken out) is in T: the column
 // recurrence (factor_tile64 for a full tile), then L, and Lh in both triangles, written out by all.  See diag_tile.
-// *unsafe: an int in LDS, 0 with a barrier since; scratch: LDS (factor_tile64).  W: where the
+// unsafe: two bytes in LDS, 0 with a barrier since; scratch: LDS (factor_tile64).  W: where the
 // tile's inverse goes, or nullptr.  beside(G, w): called in the full-tile case by every wave w < G in the phases G = 1 .. 3.
 template <class Beside>
-__device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *scratch, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols, int r,
-                                          float *W, Beside beside, float *copy = nullptr)
+__device__ __forceinline__ void diag_rest(float (*T)[LDT], char *unsafe, float *scratch, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols, int r,
+                                          float *W, bool hint, Beside beside, float *copy = nullptr)
 {
     InverseColumns inverse;
     static_assert(FACTOR_SCRATCH * sizeof(float) <= KMAX * 64 * sizeof(uint16_t), "the staged operand's place serves as scratch");
@@ -349,7 +349,7 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *s
         // (the rows of L of a group go out as soon as the group is finished, by the wave that kept them; Lh, which is mirrored, at
         // the end)
         const bool aligned = n % 8 == 0 && ((uintptr_t)L & 15) == 0 && ((uintptr_t)Lh & 15) == 0;
-        factor_tile64<4>(T, unsafe, scratch, W, inverse, r, [&](auto phase, int w) __attribute__((always_inline)) {
+        hint = factor_tile64<4>(T, unsafe, scratch, W, inverse, r, hint, [&](auto phase, int w) __attribute__((always_inline)) {
             constexpr int G = decltype(phase)::value;
             if (w == G - 1 && aligned) {
                 f32x4 v[4];
@@ -366,11 +366,11 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *s
             beside(phase, w);
         });
     } else if (cols > 32) {
-        factor_tile64<4>(T, unsafe, scratch, (float *)nullptr, inverse, r, [](auto, int) {});
+        factor_tile64<4>(T, unsafe, scratch, (float *)nullptr, inverse, r, false, [](auto, int) {});
     } else if (cols > 16) {
-        factor_tile64<2>(T, unsafe, scratch, (float *)nullptr, inverse, r, [](auto, int) {});
+        factor_tile64<2>(T, unsafe, scratch, (float *)nullptr, inverse, r, false, [](auto, int) {});
     } else {
-        factor_tile64<1>(T, unsafe, scratch, (float *)nullptr, inverse, r, [](auto, int) {});
+        factor_tile64<1>(T, unsafe, scratch, (float *)nullptr, inverse, r, false, [](auto, int) {});
     }
     if (copy) {
         // a second copy of the tile as it stands in LDS, rows of 64 floats (see chol_panel_kernel, Dcopy)
@@ -382,17 +382,17 @@ __device__ __forceinline__ void diag_rest(float (*T)[LDT], int *unsafe, float *s
     }
     const bool stored = store_tile<true, NT, 3, 48>(T, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, r);
     if (!stored) store_rows<true>(T, L + j0 * n + j0, Lh + j0 * n + j0, n, cols, cols, r);
-    if (cols == NBMAX && W) finish_inverse<LDT>(T, scratch, W, inverse, r);
+    if (cols == NBMAX && W) finish_inverse<LDT>(T, scratch, W, inverse, r, hint);
 }
 
 // L_jj = CHOL(S_jj) for the tile at (j0, j0) with `cols` rows and columns.  S is read from Sm (row stride n: A itself
 // for the first panel, L afterwards); L gets the factor below and on the diagonal and zero above it, Lh its bf16
 // rounding in both triangles.  One workgroup of NT threads.  T (first 64 KB of LDS: a read reaches its word with the 16-bit offset field from one
 // base register; further up every read needs an address register of its own) and Bs are the workgroup's LDS.
-__device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], int *unsafe, const float *Sm, float *L, uint16_t *Lh, int64_t n,
+__device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], char *unsafe, const float *Sm, float *L, uint16_t *Lh, int64_t n,
                                           int64_t j0, int cols, int64_t k0, int r, float *W)
 {
-    if (r == 0) *unsafe = 0;              // (a barrier follows below)
+    if (r < 2) unsafe[r] = 0;              // (a barrier follows below)
     // (both operands of the tile's own update are the rows j0 .. of Lh: the staged one, Lh[k0:j0, j0:j0+64], is their
     // mirror image, and the stationary fragments are read from it as well)
     TileProduct product;
@@ -400,7 +400,7 @@ __device__ __forceinline__ void diag_tile(float (*T)[LDT], uint16_t (*Bs)[64], i
     load_tile<true>(T, Sm + j0 * n + j0, n, cols, cols, r);     // the whole square; what lies above the diagonal is not used
     if (k0 < j0) product.apply(T, Bs, r, Bs);
     else __syncthreads();
-    diag_rest(T, unsafe, (float *)&Bs[0][0], L, Lh, n, j0, cols, r, W, [](auto, int) {});
+    diag_rest(T, unsafe, (float *)&Bs[0][0], L, Lh, n, j0, cols, r, W, false, [](auto, int) {});
 }
 
 __global__ __launch_bounds__(NT, 2) void chol_diag_kernel(const float *Sm, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols,
@@ -409,9 +409,9 @@ __global__ __launch_bounds__(NT, 2) void chol_diag_kernel(const float *Sm, float
     __shared__ __attribute__((aligned(16))) struct {
         float T[NBMAX][LDT];          // S on entry, L as columns finish
         uint16_t Bs[KMAX][64];        // streamed operand of the tile's own update
-        int unsafe;                   // see factor_tile64
+        char unsafe[2];               // see factor_tile64
     } lds;
-    diag_tile(lds.T, lds.Bs, &lds.unsafe, Sm, L, Lh, n, j0, cols, k0, threadIdx.x, W);
+    diag_tile(lds.T, lds.Bs, lds.unsafe, Sm, L, Lh, n, j0, cols, k0, threadIdx.x, W);
 }
 
 // L_ij = TRSM(S_ij, L_jj) for all rows below the diagonal tile: rows j1 + 64 * blockIdx.x .., sixteen to a wave.
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
         uint16_t Bs[KMAX][64];        // streamed operand of the tile's own update
         uint16_t Bs2[KMAX][64];       // streamed operand of the next diagonal tile's update
         float rinv[64];               // the reciprocals of the diagonal of L_jj
-        int unsafe;                   // the next diagonal tile: see factor_tile64
+        char unsafe[2];               // the next diagonal tile: see factor_tile64
     } lds;
     auto &D = lds.D;
     auto &X = lds.X;
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
         return;
     }
     if (blockIdx.x == 0) k0 = k0_first;                                    // uniform (see above)
-    if (tid == 0) lds.unsafe = 0;
+    if (tid < 2) lds.unsafe[tid] = 0;
     // (requested here with everything else, looked at only where the rows are formed, so that nothing waits for them on their own)
     const bool may_invert = blockIdx.x == 0 && cols == NBMAX && Win != nullptr;        // uniform over the workgroup
     f32x4 winv[10], sum_L = {0, 0, 0, 0}, sum_W = sum_L;   // this lane's 40 values of W: pieces (cb, q), q <= cb
@@ -568,8 +568,12 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
                 accn[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[0]), __builtin_bit_cast(bf16x8, src[1 + j]), accn[j], 0, 0, 0);
         };
         // (an upper bound of || |W| |L| ||_1, which is what the product's error grows with)
-        const float norm_L = __builtin_fmaxf(__builtin_fmaxf(sum_L[0], sum_L[1]), __builtin_fmaxf(sum_L[2], sum_L[3]));
-        const float norm_W = __builtin_fmaxf(__builtin_fmaxf(sum_W[0], sum_W[1]), __builtin_fmaxf(sum_W[2], sum_W[3]));
+        // (the sign of the sums of |L| is a hint for the next diagonal tile, see factor_tile64)
+        auto largest = [](const f32x4 &v) __attribute__((always_inline)) {
+            return __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1])), __builtin_fmaxf(__builtin_fabsf(v[2]), __builtin_fabsf(v[3])));
+        };
+        const float norm_L = largest(sum_L);
+        const float norm_W = largest(sum_W);
         if (may_invert && __builtin_amdgcn_readfirstlane(norm_L * norm_W <= W_NORM_LIMIT) != 0) {
             // X <- S W^T.  A operand lane l: row 16w + l%16 of S, k = 4 ks + l/16; B operand: W[16 cb + l%16][4 ks + l/16], zero
             // for ks >= 4 (cb + 1); accumulator register r of lane l: row 16w + 4 (l/16) + r, column 16 cb + l%16.  Each wave
@@ -701,7 +705,9 @@ __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, floa
 #pragma unroll
             for (int r = 0; r < 4; ++r) D[16 * w + 4 * g + r][16 * j + lq] -= accn[j][r];
         __syncthreads();
-        diag_rest(D, &lds.unsafe, (float *)&Bs[0][0], L, Lh, n, j1, NBMAX, tid, Wout, [&](auto phase, int wave) __attribute__((always_inline)) {
+        // (zero where there is no inverse; one tile in eight is tried afresh)
+        const bool hint = __builtin_amdgcn_readfirstlane((int)__builtin_signbit(sum_L[0])) != 0 && (j1 / NBMAX & 7) != 0;
+        diag_rest(D, lds.unsafe, (float *)&Bs[0][0], L, Lh, n, j1, NBMAX, tid, Wout, hint, [&](auto phase, int wave) __attribute__((always_inline)) {
             // this workgroup's own rows, deferred above, shared by the first two waves
             constexpr int G = decltype(phase)::value;
             const int t = tid & 63;

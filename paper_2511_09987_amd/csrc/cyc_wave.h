@@ -1,4 +1,4 @@
-// cyc_wave.h -- small device helpers shared by the kernels that run a scalar recurrence in one wave
+// cyc_wave.h -- device helpers shared by the kernels that run the scalar recurrence of a tile, in one wave or in four
 // (the tile kernels of the triangular solve and of the Cholesky factorisation).
 #pragma once
 
@@ -302,11 +302,12 @@ struct InverseColumns {
         for (int q = 0; q < 4; ++q) piece[q] = scratch[i * 20 + 4 * q + g];
         *(wave_f32x4 *)(W + (4 * G + w) * 256 + 4 * lane) = piece;
     }
-    __device__ __forceinline__ void finish(float *__restrict__ W, int w, int lane)
+    // hint: see factor_tile64; it goes along as the sign of the sums of |L|
+    __device__ __forceinline__ void finish(float *__restrict__ W, int w, int lane, bool hint)
     {
         const float largest_L = largest_column(sum_L), largest_W = largest_column(sum_W);
         if (lane == 0) {
-            W[W_FLOATS + w] = largest_L;
+            W[W_FLOATS + w] = hint ? -largest_L : largest_L;
             W[W_FLOATS + 4 + w] = largest_W;
         }
     }
@@ -323,10 +324,17 @@ struct InverseColumns {
 // beside(G, w): called in the phases G = 1 .. 3 by every wave w < G; the first G groups of columns and of rows are finished then
 // (called again where the tile is started over).  scratch: LDS, FACTOR_SCRATCH floats.
 // GROUPS: of a tile padded with the identity from column 16 GROUPS on, only so many groups of columns (and of rows).
-// A barrier must have made S visible; ends with one.  *unsafe: an int in LDS, 0 on entry.
+// Roots and quotients come from estimates and exact remainders (Pivot).  At the end of every phase the wave looks at what came out,
+// and the tile is started over with the compiler's root and division, which takes 10 us, where something may not be IEEE's:
+// a result that is not zero and outside [2^-50, 2^50] or, as long as every pivot is at least 2^-24, outside [2^-76, 2^50] (what
+// counts is that the product of a quotient and its divisor is at least 2^-100).  hint: the tile before it was like that, begin with root and
+// division; returned: whether this one was, or began so.  A covariance whose entries fall to nothing within a tile is then
+// factored once per tile: n = 4096, entries 0.5^|i - j|, 1725 us with a second pass per tile, 1041 now; exp(-((i - j) / 3)^2 / 2), 2057 and 1634
+// (with root and division always, a row to a lane in one wave: 1151 and 1617, and 1151 in place of 1021 where all lies in the range).
+// A barrier must have made S visible; ends with one.  unsafe: two bytes in LDS, 0 on entry.
 constexpr int FACTOR_SCRATCH = 4 * 320 + 64 * 64;
 template <int GROUPS, int LDD, class Beside>
-__device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, float *scratch, float *W, InverseColumns &inverse, int tid, Beside beside)
+__device__ __forceinline__ bool factor_tile64(float (*T)[LDD], char *unsafe, float *scratch, float *W, InverseColumns &inverse, int tid, bool hint, Beside beside)
 {
     float *const saved = scratch + 4 * 320;                    // S, to start from again
     static_assert(LDD >= 68, "four columns of padding take the stores that go nowhere");
@@ -426,7 +434,18 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
 #pragma unroll
                     for (int r = 0; r < 4; ++r) seen[r] = own_row >= 16 * G + 4 * g + r ? seen[r] : 1.0f;
                     if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst_code(seen) > SAFE_SPAN) != 0, 0)) {
-                        if (!all_safe(seen)) *unsafe = 1;
+                        if (!all_safe(seen)) {
+                            // (zeros come out above every limit less one)
+                            unsigned low = ~0u, high = 0;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const unsigned twice = __builtin_bit_cast(unsigned, seen[r]) << 1;
+                                low = min(low, twice - 1);
+                                high = max(high, twice);
+                            }
+                            unsafe[0] = 1;
+                            if (low < ((127u - 76u) << 24) - 1 || high > (127u + 50u) << 24) unsafe[1] = 1;
+                        }
                     }
                 }
             } else {
@@ -438,22 +457,30 @@ __device__ __forceinline__ void factor_tile64(float (*T)[LDD], int *unsafe, floa
             __syncthreads();
         });
     };
-    factor(std::true_type{});
-    if (__builtin_expect(*(volatile int *)unsafe != 0, 0)) {                   // once more, as the compiler expands root and division
+    bool again = hint;
+    if (!again) {
+        factor(std::true_type{});
+        if (__builtin_expect(*(volatile char *)unsafe != 0, 0)) {
+            again = ((volatile char *)unsafe)[1] != 0 || __builtin_amdgcn_ballot_w64(lane < 16 * GROUPS && T[lane][lane] < 0x1p-24f) != 0;
+            __syncthreads();                                   // (every wave has looked at the pivots)
+            if (again) {
 #pragma unroll
-        for (int G = 0; G < GROUPS; ++G) *(wave_f32x4 *)(row + 16 * G + 4 * g) = *(const wave_f32x4 *)(saved + 64 * own_row + 16 * G + 4 * g);
-        __syncthreads();
-        factor(std::false_type{});
+                for (int G = 0; G < GROUPS; ++G) *(wave_f32x4 *)(row + 16 * G + 4 * g) = *(const wave_f32x4 *)(saved + 64 * own_row + 16 * G + 4 * g);
+                __syncthreads();
+            }
+        }
     }
+    if (__builtin_expect(again, 0)) factor(std::false_type{});
     if (w == 0) mirror(std::integral_constant<int, GROUPS - 1>{});
     __syncthreads();
+    return again;
 }
 template <int LDD>
-__device__ __forceinline__ void finish_inverse(const float (*T)[LDD], float *scratch, float *W, InverseColumns &inverse, int tid)
+__device__ __forceinline__ void finish_inverse(const float (*T)[LDD], float *scratch, float *W, InverseColumns &inverse, int tid, bool hint)
 {
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     inverse.group<3>(T, scratch + 320 * w, W, w, lane);
-    inverse.finish(W, w, lane);
+    inverse.finish(W, w, lane, hint);
 }
 
 }  // namespace cyc

@@ -270,3 +270,84 @@ def test_quotients_from_reciprocals_are_the_divisions(lib, chol, nb, case):
     rows = np.r_[0:64, 128:n] if nb == 64 else np.arange(n)
     same = np.tril(np.ones((n, nb), dtype=bool))[rows]
     assert np.array_equal(L[rows, :nb].view(np.int32)[same], Lo[rows, :nb].astype(np.float32).view(np.int32)[same])
+
+
+def covariance(n, kind):
+    """Covariances of equally spaced points, whose entries fall off within a tile: to 2^-63, 2^-126 (no denormal numbers) and
+    through the denormal numbers to zero."""
+    lag = np.abs(np.subtract.outer(np.arange(n), np.arange(n))).astype(np.float64)
+    A = {"half": 0.5 ** lag, "quarter": 0.25 ** lag, "gauss": np.exp(-(lag / 2) ** 2 / 2) + 0.5 * (lag == 0)}[kind]
+    return A.astype(np.float32)
+
+
+def diagonal_tile(kind, n, seed):
+    A = ws_inputs.spd_f32(n, seed, 0, "cpu").numpy()
+    if kind in ("half", "quarter", "gauss"):
+        return covariance(n, kind)
+    if kind == "quarter_small":
+        return covariance(n, "quarter") * np.float32(2.0 ** -20)
+    if kind in ("large", "small"):
+        return A * np.float32(2.0 ** (104 if kind == "large" else -80))
+    if kind == "indefinite":
+        A[n - 3, n - 3] = -1.0
+    return A
+
+
+@pytest.mark.parametrize("rest", [64, 40, 24, 9])
+@pytest.mark.parametrize("first", ["plain", "half", "gauss"])
+def test_every_diagonal_tile_is_the_oracles(lib, chol, first, rest):
+    """Diagonal tiles with nothing beside them, through three groups of panels: each is bit for bit the oracle's, whether its roots
+    and quotients came from estimates, from a second pass with root and division, or from these at once because the tile before it
+    needed that, up to a negative pivot in the last tile (full, or padded to 64, 32 or 16 columns), which makes the columns from there on
+    NaN."""
+    kinds = [first, "plain", "gauss", "gauss", "plain", "half", "quarter", "plain", "large", "large", "small", "quarter_small", "half", "plain",
+             "quarter", "gauss", "half", "gauss", "plain", "indefinite"]
+    n = 64 * (len(kinds) - 1) + rest
+    A = np.zeros((n, n), dtype=np.float32)
+    for t, kind in enumerate(kinds):
+        s = slice(64 * t, min(64 * t + 64, n))
+        A[s, s] = diagonal_tile(kind, s.stop - s.start, 500 + t)
+    L, Lh = run(lib, torch.from_numpy(A).to(DEV), 64)
+    for t, kind in enumerate(kinds):
+        s = slice(64 * t, min(64 * t + 64, n))
+        Lo, Lho = chol.chol_tiled(np.ascontiguousarray(A[s, s]), 64)
+        assert np.isfinite(Lo).all() == (kind != "indefinite")
+        low = np.tril_indices(s.stop - s.start)
+        assert np.array_equal(L[s, s][low], Lo.astype(np.float32)[low], equal_nan=True), (t, kind)
+        assert np.array_equal(Lh[s, s][low], bits_to_f64(Lho)[low], equal_nan=True), (t, kind)
+        assert not np.any(np.triu(L[s, s], 1))
+        L[s, s] = 0
+    assert not np.any(L[:-rest]) and not np.any(L[-rest:, :-rest])
+
+
+@pytest.mark.parametrize("n", [256, 1096, 1280])
+@pytest.mark.parametrize("k", [-36, -30, -22, 40, 50, 55])
+def test_a_power_of_four_gives_the_scaled_factor(lib, n, k):
+    """4^k A has the factor 2^k L in every bit, as nothing over- or underflows: rows, mirrored rows, inverses and all that is written
+    beside a diagonal tile come out the same when the tile is started over and when it takes root and division from the start."""
+    A = ws_inputs.spd_f32(n, 300 + n, 0, DEV)
+    L, Lh = run(lib, A, 64)
+    Ls, Lhs = run(lib, A * 4.0 ** k, 64)
+    assert np.array_equal(Ls, L * np.float32(2.0 ** k)) and np.array_equal(Lhs, Lh * 2.0 ** k)
+    check_structure(Ls, Lhs)
+
+
+@pytest.mark.parametrize("kind", ["half", "quarter", "gauss"])
+def test_entries_that_fall_to_nothing_do_not_double_the_time(lib, kind):
+    """The tile everything waits for is not factored twice where its entries span many powers of two: 1.02 times the time of a matrix
+    whose entries do not as long as they stay above 2^-76, 1.3 times below (1.7 and more when each tile was)."""
+    n = 4096
+    plain, other = ws_inputs.spd_f32(n, 7, 0, DEV), torch.from_numpy(covariance(n, kind)).to(DEV)
+    L, Lh = torch.empty_like(plain), torch.empty((n, n), dtype=torch.bfloat16, device=DEV)
+
+    def time(A):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(4):
+            lib.recurrence_cholesky(A, out=L, out_bf16=Lh)
+        end.record()
+        end.synchronize()
+        return begin.elapsed_time(end)
+    time(plain), time(other)
+    pairs = [(time(plain), time(other)) for _ in range(9)]
+    assert sorted(b / a for a, b in pairs)[4] < (1.25 if kind == "half" else 1.5)
