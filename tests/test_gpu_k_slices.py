@@ -40,15 +40,15 @@ def test_products(dtype, batch, M, K, N):
 # slices in blocks of 256 x 256 (more than 19 k-tiles each, unequal, whole and ragged blocks, a ragged last k-tile) and in twice
 # as many blocks of 128 x 128 (more than 27), on either side of both lines; slices start at different k-tiles of their range
 @pytest.mark.parametrize("dtype", (torch.bfloat16, torch.int8))
-@pytest.mark.parametrize("M,tiles,N", [(512, 64 * 19, 512), (512, 64 * 19 + 1, 512), (1000, 16 * 23 + 5, 1008), (64, 64 * 27, 1008), (64, 64 * 28 - 3, 1008),
-                                       (128, 256 * 27 + 3, 128), (130, 6 * 27 + 128, 784)])
-def test_long_slices(dtype, M, tiles, N):
+@pytest.mark.parametrize("M,tiles,N,slices", [(512, 64 * 19, 512, 32), (512, 64 * 19 + 1, 512, 61), (1000, 16 * 23 + 5, 1008, 16), (64, 64 * 27, 1008, 32),
+                                              (64, 64 * 28 - 3, 1008, 64), (128, 256 * 27 + 3, 128, 247), (130, 6 * 27 + 128, 784, 18)])
+def test_long_slices(dtype, M, tiles, N, slices):
     import paper_2511_09987_amd as lib
     bke = 128 if dtype == torch.int8 else 64
     for K in (tiles * bke, tiles * bke - 16):
         A, B = (t[0] for t in operands(dtype, 1, M, K, N))
         C = lib.recurrence_matmul(A, B)
-        assert lib.cyc_matmul_workspace(A.data_ptr(), B.data_ptr(), C.data_ptr(), M, K, N, lib.CYC_I8_I32 if dtype == torch.int8 else lib.CYC_BF16_F32) > 0
+        assert lib.cyc_matmul_workspace(A.data_ptr(), B.data_ptr(), C.data_ptr(), M, K, N, lib.CYC_I8_I32 if dtype == torch.int8 else lib.CYC_BF16_F32) == 4 * slices * M * N, K
         assert torch.equal(C.view(torch.int32), lib.recurrence_matmul(A, B).view(torch.int32))
         ref = torch.matmul(A.double(), B.double())
         if dtype == torch.int8:

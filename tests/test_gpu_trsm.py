@@ -218,12 +218,12 @@ def test_zero_on_the_diagonal_gives_ieee_infinities_not_an_error(lib):
     assert not np.any(np.isfinite(X[70])), "the row of the zero pivot is a division by zero in every column"
 
 
-@pytest.mark.parametrize("n,nrhs,nb", [(64, 24, 64), (61, 70, 64), (32, 17, 32), (16, 64, 16), (13, 65, 16), (128, 80, 128), (100, 9, 128), (65, 64, 128)])
+@pytest.mark.parametrize("n,nrhs,nb", [(62, 23, 64), (61, 70, 64), (32, 17, 32), (16, 64, 16), (13, 65, 16), (128, 80, 128), (100, 9, 128), (65, 64, 128)])
 @pytest.mark.parametrize("case", ["plain", "negative", "large", "small", "tiny", "zeros"])
 def test_quotients_from_reciprocals_are_the_divisions(lib, tri, n, nrhs, nb, case):
     """One tile on one launch: the quotients come from reciprocals of the diagonal where everything that comes out lies in
     [2^-50, 2^50] or is zero and the diagonal is positive, and from divisions elsewhere: bit for bit the oracle's chain on
-    either side of that line (but for the product with the inverse, see above, which this passes by: no 64 x 8k system)."""
+    either side of that line (full tiles of 64 aligned rows have a kernel of their own, without reciprocals: see the next test)."""
     L = ws_inputs.tri_lower_bf16(n, 90 + n, 0, DEV)
     B = ws_inputs.normal_f32((n, nrhs), 1.0, 90 + n, 1, DEV)
     if case == "negative":
@@ -237,11 +237,53 @@ def test_quotients_from_reciprocals_are_the_divisions(lib, tri, n, nrhs, nb, cas
         B[::2, ::3] = -0.0
         B[:, 1::3] = 0.0
         L.tril_()[:, 1::2] *= torch.eye(n, device=DEV, dtype=L.dtype)[:, 1::2]
-    if nb == 64 and n == 64:
-        B = B[:, :nrhs - 1].contiguous()                # not a multiple of 8: by substitution
     X, Xh = lib.recurrence_trsm(L, B, nb)
     torch.cuda.synchronize()
     Xo, Xho = tri.tri_tiled(torch_bf16_to_bits(L), B.cpu().numpy(), nb)
     assert np.all(np.isfinite(Xo))
     assert np.array_equal(X.cpu().numpy().view(np.int32), Xo.astype(np.float32).view(np.int32))
     assert np.array_equal(torch_bf16_to_bits(Xh), Xho)
+
+
+@pytest.mark.parametrize("case", ["plain", "negative", "large", "small", "tiny", "zeros"])
+def test_quotients_in_a_full_tile_at_an_unaligned_address(lib, tri, case):
+    """The same for a tile of 64 rows: at an address that is no multiple of 16 bytes, through the entry point that makes no copy."""
+    n, nrhs = 64, 24
+    L = ws_inputs.tri_lower_bf16(n, 190, 0, DEV)
+    B = ws_inputs.normal_f32((n, nrhs), 1.0, 190, 1, DEV)
+    if case == "negative":
+        L[:, ::3] *= -1
+    elif case in ("large", "small"):
+        B *= 2.0 ** (55 if case == "large" else -55)
+    elif case == "tiny":
+        L *= 2.0 ** -30
+        L[n // 2] *= 2.0 ** -30
+    elif case == "zeros":
+        B[::2, ::3] = -0.0
+        B[:, 1::3] = 0.0
+    at = torch.empty(n * n + 8, dtype=torch.bfloat16, device=DEV)[1:1 + n * n].view(n, n)
+    at.copy_(L)
+    assert at.data_ptr() % 16 == 2
+    X, Xh = torch.empty_like(B), torch.empty((n, nrhs), dtype=torch.bfloat16, device=DEV)
+    assert lib.cyc_recurrence_trsm(at.data_ptr(), B.data_ptr(), X.data_ptr(), Xh.data_ptr(), n, nrhs, 64, torch.cuda.current_stream().cuda_stream) == 0
+    Xo, Xho = tri.tri_tiled(torch_bf16_to_bits(L), B.cpu().numpy(), 64)
+    assert np.array_equal(X.cpu().numpy().view(np.int32), Xo.astype(np.float32).view(np.int32))
+    assert np.array_equal(torch_bf16_to_bits(Xh), Xho)
+
+
+@pytest.mark.parametrize("n,nrhs", [(512, 64), (1024, 136)])
+def test_the_inverse_by_divisions_is_the_one_by_reciprocals(lib, n, nrhs):
+    """A negative diagonal entry sends the inverse of its tile to the pass with divisions, which has to be the same inverse up to
+    signs, and used: every second column of L and row of X negated leaves the other rows of X as they were, in every bit."""
+    L = ws_inputs.tri_lower_bf16(n, 191, 0, DEV)
+    B = ws_inputs.normal_f32((n, nrhs), 1.0, 191, 1, DEV)
+    X, Xh = lib.recurrence_trsm(L, B, 64)
+    signs = torch.ones(n, device=DEV)
+    signs[::2] = -1
+    Xs, Xhs = lib.recurrence_trsm(L * signs.to(L.dtype)[None, :], B, 64)
+    assert torch.equal(Xs, X * signs[:, None]) and torch.equal(Xhs.float(), Xh.float() * signs[:, None])
+    # (the product with the inverse, not the chain: that differs from it in last bits)
+    bad = L.clone()
+    bad[:64, :64] = torch.tril(torch.ones((64, 64), dtype=L.dtype, device=DEV))
+    Xb, _ = lib.recurrence_trsm(bad, torch.cat((bad[:64, :64].float() @ X[:64], B[64:])).contiguous(), 64)
+    assert bool(torch.isfinite(Xb).all()) and not torch.equal(Xb[64:128], X[64:128])
