@@ -119,14 +119,14 @@ __global__ __launch_bounds__(256) void tri_diag_kernel(const uint16_t *__restric
     }
     __syncthreads();
     unsigned worst = 0;
-    bool divisors_safe = true;
+    bool divisors_safe = true, divisors_large = true;
 #pragma unroll
     for (int q = 0; q <= TWO; ++q) {
         Pivot p;
         p.from_root(lds.D[q][lane][lane]);
         lds.rinv[q][lane] = p.r;                           // (the same numbers by every wave: no barrier)
-        worst = max(worst, p.code());
         divisors_safe = divisors_safe && p.code() <= SAFE_SPAN;
+        divisors_large = divisors_large && lower_limit(p.code()) != 0;
     }
     auto run = [&](auto by_pivots) __attribute__((always_inline)) {
         constexpr bool PIVOTS = decltype(by_pivots)::value;
@@ -147,20 +147,26 @@ __global__ __launch_bounds__(256) void tri_diag_kernel(const uint16_t *__restric
             solve_rows16<PIVOTS, NBLK>(lds.D[1], lds.rinv[1], u, &lds.Y[1][16 * w + i][0], lane, [](auto, float) {});
         }
     };
-    run(std::true_type{});
-    // quotients by reciprocals are IEEE's in the safe range (see Pivot); elsewhere once more with divisions
-    wave_f32x4 x[BLOCKS / 4];
+    // quotients by reciprocals are IEEE's in the safe range (see Pivot); elsewhere divisions: at once where a divisor is outside it (a
+    // negative one is), once more where a result turns out to be (sixteen tiles of 64 rows: 204 us, 219 by divisions, 258 by both)
+    bool divide = __builtin_amdgcn_ballot_w64(!divisors_safe) != 0;
+    if (__builtin_expect(!divide, 1)) {
+        run(std::true_type{});
+        wave_f32x4 x[BLOCKS / 4];
 #pragma unroll
-    for (int G = 0; G < BLOCKS / 4; ++G) {
-        x[G] = *(const wave_f32x4 *)&lds.Y[G / 4][16 * w + i][16 * (G % 4) + 4 * g];
-        worst = max(worst, worst_code(x[G]));
-    }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
-        bool safe = divisors_safe;
+        for (int G = 0; G < BLOCKS / 4; ++G) {
+            x[G] = *(const wave_f32x4 *)&lds.Y[G / 4][16 * w + i][16 * (G % 4) + 4 * g];
+            worst = max(worst, worst_code(x[G]));
+        }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > SAFE_SPAN) != 0, 0)) {
+            const unsigned lower = __builtin_amdgcn_ballot_w64(!divisors_large) == 0 ? lower_limit(~0u) : 0;
+            bool safe = true;
 #pragma unroll
-        for (int G = 0; G < BLOCKS / 4; ++G) safe = safe && all_safe(x[G]);        // (zeros are)
-        if (__builtin_amdgcn_ballot_w64(!safe) != 0) run(std::false_type{});
+            for (int G = 0; G < BLOCKS / 4; ++G) safe = safe && all_safe(x[G], lower);        // (zeros are)
+            divide = __builtin_amdgcn_ballot_w64(!safe) != 0;
+        }
     }
+    if (__builtin_expect(divide, 0)) run(std::false_type{});
     __syncthreads();
     // a right-hand side to a lane, sixteen rows of each 64 to a wave (fewer where the tile has fewer)
     const int64_t c = c0 + lane;
@@ -727,13 +733,18 @@ __global__ __launch_bounds__(256) void tri_inverse_kernel(const uint16_t *__rest
             for (int r = 0; r < 4; ++r) t[G][r] = 16 * G + 4 * g + r == 16 * w + i ? 1.0f : 0.0f;
     };
     float *const row = &lds.Y[16 * w + i][0];
-    start();
-    solve_rows16<true, NBLK>(lds.D, lds.rinv, t, row, lane, [](auto, float) {});
-    // (the rows above the diagonal come out as exact zeros; everything else has to be in the range of Pivot or zero)
-    bool safe = p.code() <= SAFE_SPAN;
+    // (the rows above the diagonal come out as exact zeros; everything else has to be in the range of Pivot or zero: see tri_diag_kernel)
+    bool divide = __builtin_amdgcn_ballot_w64(p.code() > SAFE_SPAN) != 0;
+    if (__builtin_expect(!divide, 1)) {
+        start();
+        solve_rows16<true, NBLK>(lds.D, lds.rinv, t, row, lane, [](auto, float) {});
+        const unsigned lower = __builtin_amdgcn_ballot_w64(lower_limit(p.code()) == 0) == 0 ? lower_limit(~0u) : 0;
+        bool safe = true;
 #pragma unroll
-    for (int G = 0; G < 4; ++G) safe = safe && all_safe(*(const wave_f32x4 *)(row + 16 * G + 4 * g));
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!safe) != 0, 0)) {
+        for (int G = 0; G < 4; ++G) safe = safe && all_safe(*(const wave_f32x4 *)(row + 16 * G + 4 * g), lower);
+        divide = __builtin_amdgcn_ballot_w64(!safe) != 0;
+    }
+    if (__builtin_expect(divide, 0)) {
         start();
         solve_rows16<false, NBLK>(lds.D, lds.rinv, t, row, lane, [](auto, float) {});
     }

@@ -59,13 +59,16 @@ struct Division {
 // 2 |x| as a bit pattern less that of 2^-50: unsafe above SAFE_SPAN, and for a zero, which is safe (NaN and infinity are not)
 constexpr unsigned SAFE_LOW = (127u - 50u) << 24, SAFE_SPAN = 100u << 24;
 __device__ __forceinline__ unsigned range_code(float x) { return (__builtin_bit_cast(unsigned, x) << 1) - SAFE_LOW; }
-__device__ __forceinline__ bool in_safe_range(unsigned code) { return code <= SAFE_SPAN || code == 0u - SAFE_LOW; }
+__device__ __forceinline__ bool in_safe_range(unsigned code, unsigned lower) { return code + lower <= SAFE_SPAN + lower || code == 0u - SAFE_LOW; }
+// What counts is that a quotient times its divisor is at least 2^-100: with divisors of at least 2^-24 (code: see Pivot) results
+// down to 2^-76 are safe, too.  (lower, above: 0 or this)
+__device__ __forceinline__ unsigned lower_limit(unsigned code) { return code >= 26u << 24 ? 26u << 24 : 0u; }
 
 // Correctly rounded square root and quotients by it in fewer dependent instructions than the compiler's expansions (7 from
 // the pivot to a quotient, 27 there), for a pivot that a whole column is divided by.  Markstein's method: the hardware's
 // estimates, off by a unit in the last place at most, corrected by exact remainders, d = g + (s - g g) y / 2, and with a
 // correctly rounded reciprocal r, q = q0 - (d q0 - t) r for q0 = t r.  The remainders are exact and the results those of IEEE
-// as long as nothing over- or underflows: where every |x| that comes out, pivots included, lies in [2^-50, 2^50] or is zero
+// as long as nothing over- or underflows: where every |x| that comes out, pivots included, lies in [2^-50, 2^50] or is zero, or see lower_limit
 // (in_safe_range; zeros keep their sign where the pivot is positive); callers take the compiler's way elsewhere.
 // Evidence, on the device (cyc_diag_pivots): the root on every float in [2^-100, 2^100); for every divisor's
 // significand D, 24 bits, the reciprocal and the quotients of the numerators for which these lie within 15 / (2 D) units of a
@@ -212,9 +215,10 @@ __device__ __forceinline__ void solve_rows16(const float (*D)[LDD], const float 
 }
 // the worst of four results, and whether all of them are safe (zeros included)
 __device__ __forceinline__ unsigned worst_code(const wave_f32x4 &x) { return max(max(range_code(x[0]), range_code(x[1])), max(range_code(x[2]), range_code(x[3]))); }
-__device__ __forceinline__ bool all_safe(const wave_f32x4 &x)
+__device__ __forceinline__ bool all_safe(const wave_f32x4 &x, unsigned lower = 0)
 {
-    return in_safe_range(range_code(x[0])) && in_safe_range(range_code(x[1])) && in_safe_range(range_code(x[2])) && in_safe_range(range_code(x[3]));
+    return in_safe_range(range_code(x[0]), lower) && in_safe_range(range_code(x[1]), lower) && in_safe_range(range_code(x[2]), lower) &&
+           in_safe_range(range_code(x[3]), lower);
 }
 
 // The largest of sixteen column sums of which each lane 16 g + i holds the part of column i in its own rows; infinity for NaN.

@@ -287,3 +287,50 @@ def test_the_inverse_by_divisions_is_the_one_by_reciprocals(lib, n, nrhs):
     bad[:64, :64] = torch.tril(torch.ones((64, 64), dtype=L.dtype, device=DEV))
     Xb, _ = lib.recurrence_trsm(bad, torch.cat((bad[:64, :64].float() @ X[:64], B[64:])).contiguous(), 64)
     assert bool(torch.isfinite(Xb).all()) and not torch.equal(Xb[64:128], X[64:128])
+
+
+@pytest.mark.parametrize("n,nb", [(64, 64), (61, 64), (30, 32), (16, 16), (128, 128)])
+@pytest.mark.parametrize("divisor,result", [(0, -70), (0, -90), (0, -115), (-23, -74), (-26, -60), (-45, -55), (30, -60)])
+def test_small_results_are_the_divisions(lib, tri, n, nb, divisor, result):
+    """Results below 2^-50 with a diagonal above and below 2^-24 (powers of two: divisor, result), either side of the lines between
+    quotients from reciprocals and divisions: bit for bit the oracle's chain.  At an unaligned address, without a copy."""
+    nrhs = 40
+    L = ws_inputs.tri_lower_bf16(n, 290 + n, 0, DEV) * 2.0 ** divisor
+    B = ws_inputs.normal_f32((n, nrhs), 1.0, 290 + n, 1, DEV)
+    B = torch.where(torch.arange(nrhs, device=DEV)[None, :] % 2 == 0, B, B * 2.0 ** 10) * 2.0 ** (divisor + result)
+    at = torch.empty(n * n + 8, dtype=torch.bfloat16, device=DEV)[1:1 + n * n].view(n, n)
+    at.copy_(L)
+    X, Xh = torch.empty_like(B), torch.empty((n, nrhs), dtype=torch.bfloat16, device=DEV)
+    assert lib.cyc_recurrence_trsm(at.data_ptr(), B.data_ptr(), X.data_ptr(), Xh.data_ptr(), n, nrhs, nb, torch.cuda.current_stream().cuda_stream) == 0
+    Xo, Xho = tri.tri_tiled(torch_bf16_to_bits(at), B.cpu().numpy(), nb)
+    assert np.array_equal(X.cpu().numpy().view(np.int32), Xo.astype(np.float32).view(np.int32))
+    assert np.array_equal(torch_bf16_to_bits(Xh), Xho)
+
+
+@pytest.mark.parametrize("case", ["negative", "small"])
+def test_signs_and_small_results_do_not_double_the_time(lib, case):
+    """A diagonal with negative entries goes to divisions without a pass of quotients before them, and results down to 2^-76 to one
+    pass of quotients alone: sixteen tiles one after the other, at an unaligned address and without a copy.  1.07 and 1.03 times the time
+    of the plain system, 1.29 and 1.26 with two passes."""
+    n, nrhs = 1024, 24
+    L = ws_inputs.tri_lower_bf16(n, 390, 0, DEV)
+    B = ws_inputs.normal_f32((n, nrhs), 1.0, 390, 1, DEV)
+    signs = torch.where(torch.arange(n, device=DEV) % 3 == 0, -1.0, 1.0).to(L.dtype)
+    plain, other = (torch.empty(n * n + 8, dtype=torch.bfloat16, device=DEV)[1:1 + n * n].view(n, n) for _ in range(2))
+    plain.copy_(L)
+    other.copy_(L * signs[None, :] if case == "negative" else L)
+    Bo = B * 2.0 ** -58 if case == "small" else B
+    X, Xh = torch.empty_like(B), torch.empty((n, nrhs), dtype=torch.bfloat16, device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def time(L, B):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(20):
+            assert lib.cyc_recurrence_trsm(L.data_ptr(), B.data_ptr(), X.data_ptr(), Xh.data_ptr(), n, nrhs, 64, stream) == 0
+        end.record()
+        end.synchronize()
+        return begin.elapsed_time(end)
+    time(plain, B), time(other, Bo)
+    pairs = [(time(plain, B), time(other, Bo)) for _ in range(9)]
+    assert sorted(b / a for a, b in pairs)[4] < 1.18
