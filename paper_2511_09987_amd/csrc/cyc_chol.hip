@@ -426,7 +426,7 @@ __global__ __launch_bounds__(NT, 2) void chol_diag_kernel(const float *Sm, float
 // On the path per launch at n = 8192, in cycles: 5k until the tiles are in LDS, 2.7k the rows, 1.8k the panel's k range into the next
 // tile, 16.5k that tile, 2.7k Lh and the last rows of L and of the inverse (31k with the tile's recurrence in one wave, one lane
 // to a row, helped by a second: 14.5k, and 5k more for a third that computed the inverse four columns behind; that made 18.6k a tile
-// for the rows of all other workgroups, which are 6k now).  8192: 2388 -> 2083 us; 2048: 563 -> 506; 200: 61.5 -> 51.8.
+// for the rows of all other workgroups, which are 6k now).  8192: 2388 -> 2083 us, and 2115 with the hint and limits of factor_tile64; 2048: 563 -> 506; 200: 61.5 -> 51.8.
 __global__ __launch_bounds__(NT, 2) void chol_panel_kernel(const float *Sm, float *L, uint16_t *Lh, int64_t n, int64_t j0, int cols,
                                                         int64_t k0, const float *next_Sm, const float *__restrict__ Win,
                                                            float *Wout, const float *Dcopy,
